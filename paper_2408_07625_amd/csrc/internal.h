@@ -171,6 +171,187 @@ __host__ __device__ __forceinline__ uint64_t spin_split(uint64_t x) {
     return x;
 }
 
+// ---------------------------------------------------------------------------
+// Spin-string join (join.hip).  A key is its spin-up string (even qubits) and
+// its spin-down string (odd qubits), each compressed to one integer; an XY
+// mask has the same two parts.
+// ---------------------------------------------------------------------------
+template <int W>
+using JoinStr = std::conditional_t<W == 1, uint32_t, uint64_t>;
+
+template <int W>
+__host__ __device__ __forceinline__ void spin_strings(const uint64_t* k, JoinStr<W>& a, JoinStr<W>& b) {
+    const uint64_t s = spin_split(k[0]);
+    if constexpr (W == 1) {
+        a = static_cast<uint32_t>(s);
+        b = static_cast<uint32_t>(s >> 32);
+    } else {
+        const uint64_t t = spin_split(k[1]);
+        a = (s & 0xFFFFFFFFull) | (t << 32);
+        b = (s >> 32) | (t & 0xFFFFFFFF00000000ull);
+    }
+}
+
+// Table position of a string (multiplicative hashing, 2^bits slots).
+__host__ __device__ __forceinline__ uint32_t join_hash(uint32_t k, int bits) { return (k * 0x9E3779B1u) >> (32 - bits); }
+__host__ __device__ __forceinline__ uint32_t join_hash(uint64_t k, int bits) {
+    return static_cast<uint32_t>((k * 0x9E3779B97F4A7C15ull) >> (64 - bits));
+}
+
+__host__ __device__ __forceinline__ uint32_t join_low(uint32_t d) { return static_cast<uint32_t>(__builtin_ctz(d)); }
+__host__ __device__ __forceinline__ uint32_t join_low(uint64_t d) { return static_cast<uint32_t>(__builtin_ctzll(d)); }
+__host__ __device__ __forceinline__ uint32_t join_high(uint32_t d) { return 31u - static_cast<uint32_t>(__builtin_clz(d)); }
+__host__ __device__ __forceinline__ uint32_t join_high(uint64_t d) { return 63u - static_cast<uint32_t>(__builtin_clzll(d)); }
+__host__ __device__ __forceinline__ uint32_t join_count(uint32_t d) { return static_cast<uint32_t>(__builtin_popcount(d)); }
+__host__ __device__ __forceinline__ uint32_t join_count(uint64_t d) { return static_cast<uint32_t>(__builtin_popcountll(d)); }
+
+// Number of a string with two bits set: its rank among them.
+template <class ST>
+__host__ __device__ __forceinline__ uint32_t join_pair_id(ST d) {
+    const uint32_t j = join_high(d);
+    return j * (j - 1u) / 2u + join_low(d);
+}
+// Number of a string with no, two or four of its n bits set: 0, then the
+// pairs, then the fours by their rank C(l3,4) + C(l2,3) + C(l1,2) + l0 (the
+// products divided by 6 stay under 2^24, where float is exact).
+template <class ST>
+__host__ __device__ __forceinline__ uint32_t join_even_id(ST d, uint32_t n) {
+    const uint32_t c = join_count(d);
+    if (c == 0u) return 0u;
+    if (c == 2u) return 1u + join_pair_id(d);
+    const ST d1 = d & (d - 1);
+    const uint32_t l0 = join_low(d), l1 = join_low(d1), l3 = join_high(d);
+    const uint32_t l2 = join_high(static_cast<ST>(d1 & (d1 - 1)) ^ (static_cast<ST>(1) << l3));
+    const float c3 = static_cast<float>(l2 * (l2 - 1u) * (l2 - 2u)) * (1.0f / 6.0f);
+    const float c4 = static_cast<float>((l3 * (l3 - 1u) / 2u) * ((l3 - 2u) * (l3 - 3u) / 2u)) * (1.0f / 6.0f);
+    return 1u + n * (n - 1u) / 2u + l0 + l1 * (l1 - 1u) / 2u + static_cast<uint32_t>(c3 + 0.5f) +
+           static_cast<uint32_t>(c4 + 0.5f);
+}
+inline int64_t join_even_count(int64_t n) {
+    return 1 + n * (n - 1) / 2 + n * (n - 1) * (n - 2) * (n - 3) / 24;
+}
+
+// The three parities of a one-spin mask w (at most four bits l0 < l1 < ...):
+// of its two lowest bits, of all, of l1 and l2.
+template <class ST>
+__host__ __device__ __forceinline__ void join_parity_masks(ST w, ST& p1, ST& p3) {
+    const ST w1 = w & (w - 1);        // without l0
+    const ST w2 = w1 & (w1 - 1);      // without l0, l1
+    const ST w3 = w2 & (w2 - 1);
+    p1 = w ^ w2;
+    p3 = w1 ^ w3;
+}
+
+constexpr uint32_t kJoinNone = 0xFFFFFFFFu;   // id of an empty slot
+constexpr uint32_t kJoinFull = 0x80000000u;   // base flag: masks of one spin, ids by table
+
+struct JoinMask {
+    uint32_t base;   // place of the other spin's id 0 (kJoinFull: the one-spin masks)
+    uint32_t span;   // popcounts of the other spin's parts: largest less smallest
+};
+// How the matrix element of a place is evaluated.  With m = x ^ x' and the
+// ket x', a term of YZ mask yz adds h' (-1)^|ket & yz|; its bits outside m
+// are z, those inside y.
+//   kJoinSign    all terms share z and the dependence on ket & m goes through
+//                three parities idx: H = (-1)^|ket & z| T[idx]
+//   kJoinLinear  the z differ from one mask in at most one bit each and y is 0
+//                or m: H = (-1)^|ket & z| sum over the nibbles of the ket's
+//                strings of a 16-entry table of parity |ket & m|
+//   kJoinRun     any other run: summed term by term
+enum JoinKind : uint32_t { kJoinEmpty = 0, kJoinSign = 1, kJoinLinear = 2, kJoinRunKind = 3 };
+constexpr int kJoinIdx = 8;          // values of idx
+constexpr uint32_t kJoinMain = 3;    // both parities odd: a pair of equal electron numbers
+// A place's z by strings and T[kJoinMain]; places of another kind, and those
+// whose T is to be read by idx, hold a NaN there: kind in the low bits of the
+// high word, linear table in the low word.
+template <int W>
+struct alignas(W == 1 ? 16 : 32) JoinPlace {
+    JoinStr<W> za, zb;
+    uint32_t lo, hi;
+};
+constexpr uint32_t kJoinTag = 0x7FF80000u;
+// Term run of a place: first term, lengths of its real and imaginary parts
+// (16 bits each).
+struct JoinRun {
+    uint32_t begin;
+    uint32_t lens;
+};
+template <int W>
+struct JoinSlot {
+    JoinStr<W> key;
+    JoinStr<W> id;   // kJoinNone: empty
+};
+// Samples of one string: positions [start, start + len) of the sorted order
+// (len 0: empty slot).
+struct JoinBucket {
+    uint64_t key;
+    uint32_t start;
+    uint32_t len;
+};
+// Which strings are heavy (device words).
+struct JoinHeavy {
+    uint32_t min;       // smallest heavy bucket (kJoinNone: none is)
+    uint32_t n[2];      // heavy spin-up / spin-down strings
+    uint32_t taken[2];  // ids given out
+    uint32_t bits[2];   // their tables' sizes
+    uint32_t hist[2][26];   // buckets of at least 16 by floor(log2(size))
+};
+constexpr uint32_t kJoinCore = 1u << 16;       // cells of the heavy-heavy table
+constexpr int kJoinHeavyBits = 14;             // a quarter of these slots may be taken
+constexpr uint32_t kJoinHeavySlots = 1u << kJoinHeavyBits;
+// The masks (a, b) of H, spin-up part a and spin-down part b, in three
+// sections of places: (0, b) by the table b_own; (a, b) with both parts, at
+// base(a) + id(b); (a, 0) with a != 0 by the table a_own.
+struct JoinHamDev {
+    bool ok = false;
+    int n_a = 0;                       // alist: 0 (if a mask has it), then the a that occur with some b != 0
+    const void* alist = nullptr;       // JoinStr<W>[n_a]
+    const JoinMask* amask = nullptr;
+    int n_b = 0;                       // blist: the b that occur with some a != 0
+    const void* blist = nullptr;       // JoinStr<W>[n_b]
+    const JoinMask* bmask = nullptr;   // base: place of id(a) 0
+    // ids by position: join_pair_id of a two-spin mask's parts (place = base
+    // of id(a) 0 + id(a) stride + id(b)), join_even_id of a one-spin mask
+    bool direct = false;
+    int string_bits = 0;
+    uint32_t stride = 0;
+    const void* b_cross = nullptr;     // JoinSlot<W> tables: id(b) where not direct
+    const void* b_own = nullptr;
+    const void* a_own = nullptr;
+    int b_cross_bits = 0, b_own_bits = 0, a_own_bits = 0;
+    const void* place = nullptr;       // JoinPlace<W>[places]
+    const double* sign = nullptr;      // T [kJoinIdx][places]
+    const double* linear = nullptr;    // [tables][2][spin-up, spin-down][nibbles][16]
+    const JoinRun* runs = nullptr;     // [places]
+    const int32_t* gids = nullptr;     // [places] group
+    uint32_t places = 0;
+    int nibbles = 0;                   // of one string
+    uint32_t a_base = 0, a_pmin = 0, a_span = 0;   // the section (a, 0): first place, popcounts
+    bool has_a_own = false;
+};
+// U in its two sorted orders (positions [0, M): by spin-up string; [M, 2M):
+// by spin-down string), each stable in the caller's order.
+struct JoinDev {
+    int64_t M = 0;
+    const int32_t* perm = nullptr;     // [2M] sample of a position
+    const void* group = nullptr;       // JoinStr<W>[2M] sorted string
+    const void* scan = nullptr;        // JoinStr<W>[2M] the other string
+    double2* vec = nullptr;            // [2M] amplitudes (FP64 pairs or float4 bits)
+    const JoinBucket* slots = nullptr; // [2][2^bits]
+    int bits = 0;
+    const uint64_t* keys = nullptr;    // [M][W] caller order
+    // Strings of at least heavy->min samples are heavy.  A pair that changes
+    // both spins is found from its column's spin-up bucket where that is
+    // light, else from its spin-down bucket where that is light, else in the
+    // table of the samples whose two strings are heavy.
+    const JoinHeavy* heavy = nullptr;
+    const void* heavy_slots = nullptr;    // JoinSlot<W>[2][kJoinHeavySlots] string -> id
+    const uint32_t* core = nullptr;       // [heavy spin-up][heavy spin-down] position + 1 (0: none)
+    const void* cross = nullptr;          // JoinStr<W>[M] scan strings of the spin-down order, no
+                                          // column with a light spin-up string passing any test
+    const uint32_t* prep_err = nullptr;
+};
+
 template <int TK>
 __host__ __device__ __forceinline__ typename TabT<TK>::hash salted(const Table& T, uint64_t h) {
     return static_cast<typename TabT<TK>::hash>(h ^ T.salt);
@@ -644,6 +825,51 @@ struct SortScratch {
     int64_t* hist_off;
     int64_t* scan;
 };
+// Spin-string join (join.hip).  Eligible keys: the strings plus one order
+// bit must fit a 64-bit sort key.
+constexpr int kJoinMaxQubits = 126;
+inline int join_string_bits(int n_qubits) { return (n_qubits + 1) / 2; }
+// Whether a Hamiltonian's masks allow the heavy / light split: ids by
+// position, and spare bits in a string that lift a column over every popcount
+// a cross pair may have.
+inline bool join_splits(int n_qubits, const JoinHamDev& H, uint32_t cross_span) {
+    const int sb = join_string_bits(n_qubits);
+    return H.direct && (sb <= 32 ? 32 : 64) - sb > static_cast<int>(cross_span) + 1;
+}
+inline int join_bucket_bits(int64_t M) {   // bucket table of one order: load at most 1/2
+    int b = 4;
+    while ((int64_t(1) << b) < 2 * M) ++b;
+    return b;
+}
+// Buffers of the index (sizes in elements).
+struct JoinBuild {
+    const uint64_t* keys;      // U
+    int64_t M;
+    int n_qubits;
+    bool split;                // heavy / light split on
+    uint64_t *key, *key2;      // [2M] sort scratch
+    uint32_t *val, *val2;
+    uint32_t* hist;            // radix scratch for 2M
+    int64_t *hist_off, *hist_scan;
+    int32_t* perm;             // [2M]
+    void *group, *scan;        // JoinStr<W>[2M]
+    void* cross;               // JoinStr<W>[M]
+    JoinBucket* slots;         // [2][2^bits]
+    int bits;
+    JoinHeavy* heavy;
+    void* heavy_slots;         // JoinSlot<W>[2][kJoinHeavySlots]
+    uint32_t* core;            // [kJoinCore]
+};
+hipError_t launch_join_index(int W, const JoinBuild& B, hipStream_t st);
+// Row sums into partial[chunk][M]: chunk 0 the spin-down order (own buckets,
+// then the light buckets of blist), chunk 1 the heavy-heavy table, chunks 2 ..
+// P.chunks - 1 the masks of alist, P.per_chunk each.
+hipError_t launch_join_pairs(bool adjoint, int precision, const HamDev& H, const JoinHamDev& JH, const JoinDev& J,
+                             const Plan& P, const double2* vec, const float4* vecf, void* partial, hipStream_t st);
+hipError_t launch_join_count(const HamDev& H, const JoinHamDev& JH, const JoinDev& J, const Plan& P, int32_t* counts,
+                             hipStream_t st);
+hipError_t launch_join_fill(const HamDev& H, const JoinHamDev& JH, const JoinDev& J, const Plan& P, int jbits,
+                            const int64_t* offsets, uint64_t* pkey, uint32_t* pval, hipStream_t st);
 hipError_t launch_sort_keys(int W, int n_bits, const uint64_t* keys, int64_t n, const SortScratch& S,
                             uint64_t* sorted, int32_t* perm, hipStream_t st);
 hipError_t launch_trie_build(int W, const uint64_t* keys, int64_t n_total, int64_t per, TNode* nodes,

@@ -1,0 +1,307 @@
+// Host side of the spin-string join (join.hip): the Hamiltonian's XY masks by
+// their spin-up and spin-down parts.
+#pragma once
+
+#include "ham.h"
+#include "host.h"
+#include "internal.h"
+
+#include <algorithm>
+#include <cmath>
+#include <cstdint>
+#include <cstring>
+#include <vector>
+
+namespace eloc {
+
+template <int W>
+struct HostJoin {
+    using ST = JoinStr<W>;
+    bool ok = false;
+    std::vector<ST> alist, blist;
+    std::vector<JoinMask> amask, bmask;
+    bool direct = false;
+    uint32_t stride = 0;
+    std::vector<JoinSlot<W>> b_cross, b_own, a_own;   // spin part -> id
+    // by place
+    std::vector<JoinPlace<W>> place;
+    std::vector<double> sign;         // [kJoinIdx][places]
+    std::vector<double> linear;       // [tables][2][2 nibbles][16]
+    std::vector<JoinRun> runs;
+    std::vector<int32_t> gids;
+    int nibbles = 0;
+    uint32_t a_base = 0;              // places of the masks (a, 0)
+    uint32_t a_pmin = 0, a_span = 0;  // their smallest popcount, largest less smallest
+    uint32_t cross_span = 0;          // largest popcount of a part of a two-spin mask
+};
+
+// Slots of a table of n spin parts (load at most 1/4).
+inline uint64_t join_capacity(size_t n) { return pow2_at_least(4 * std::max<uint64_t>(n, 2)); }
+
+template <int W>
+inline void join_insert(std::vector<JoinSlot<W>>& t, JoinStr<W> key, uint32_t id) {
+    const int bits = bits_for(t.size() - 1);
+    size_t s = join_hash(key, bits);
+    while (t[s].id != kJoinNone) s = (s + 1) & (t.size() - 1);
+    t[s].key = key;
+    t[s].id = id;
+}
+
+// T[idx] of a group whose terms share z; false where the dependence on ket & m
+// does not go through idx.  mixed: y is a union of the spin-up and the
+// spin-down part, whose parities idx holds; else y is an even subset of at most
+// four bits, and idx holds the parities of join_parity_masks and of all.
+template <int W>
+inline bool join_signs(const HostHam<W>& hh, const GroupRec<W>& gr, JoinStr<W> a, JoinStr<W> b, bool mixed,
+                       double (&T)[kJoinIdx]) {
+    using ST = JoinStr<W>;
+    const ST w = a | b;
+    if (!mixed && join_count(w) > 4) return false;
+    ST ket[kJoinIdx];   // ket bits of every idx: l1 clear, the rest follows
+    if (!mixed) {
+        ST bit[4], v = w;
+        for (int i = 0; i < 4; ++i) {
+            bit[i] = v & (~v + 1);
+            v &= v - 1;
+        }
+        for (uint32_t i = 0; i < kJoinIdx; ++i) {
+            ST k = 0;
+            if (i & 1u) k |= bit[0];
+            if (i & 4u) k |= bit[2];
+            if ((join_count(k) & 1u) != ((i >> 1) & 1u)) k |= bit[3];
+            ket[i] = k;
+        }
+    }
+    double c[4] = {0.0, 0.0, 0.0, 0.0};   // mixed: by (y has the spin-up part, the spin-down part)
+    for (double& t : T) t = 0.0;
+    for (int t = gr.begin; t < gr.end; ++t) {
+        const TermRec<W>& tr = hh.terms[static_cast<size_t>(t)];
+        uint64_t y[W];
+        for (int q = 0; q < W; ++q) y[q] = tr.yz[q] & gr.xy[q];
+        ST ya, yb;
+        spin_strings<W>(y, ya, yb);
+        if (mixed) {
+            if ((ya != 0 && ya != a) || (yb != 0 && yb != b)) return false;
+            c[(ya != 0 ? 1 : 0) + (yb != 0 ? 2 : 0)] += tr.h;
+        } else {
+            const ST yy = ya | yb;
+            if (join_count(yy) & 1u) return false;
+            for (size_t i = 0; i < kJoinIdx; ++i) T[i] += (join_count(static_cast<ST>(ket[i] & yy)) & 1u) ? -tr.h : tr.h;
+        }
+    }
+    for (size_t i = 0; i < kJoinIdx; ++i) {
+        if (mixed) {
+            const double pa = (i & 1u) ? -1.0 : 1.0, pb = (i & 2u) ? -1.0 : 1.0;
+            T[i] = (c[0] + pa * c[1]) + pb * (c[2] + pa * c[3]);
+        }
+        if (!std::isfinite(T[i])) return false;
+    }
+    return true;
+}
+
+template <int W>
+inline JoinPlace<W> join_tag(JoinKind kind, uint32_t number = 0) {
+    return JoinPlace<W>{0, 0, number, kJoinTag | static_cast<uint32_t>(kind)};
+}
+inline JoinKind join_kind_of(uint32_t hi) {
+    return (hi & kJoinTag) == kJoinTag ? static_cast<JoinKind>(hi & 7u) : kJoinSign;
+}
+
+// One place's evaluation; appends a linear table where it needs one.
+template <int W>
+void join_place(const HostHam<W>& hh, const GroupRec<W>& gr, size_t place, bool mixed, HostJoin<W>& out) {
+    using ST = JoinStr<W>;
+    const size_t P = out.place.size();
+    JoinPlace<W>& pl = out.place[place];
+    pl = join_tag<W>(kJoinRunKind);
+    if (gr.end != gr.mid) return;
+    ST a, b;
+    spin_strings<W>(gr.xy, a, b);
+    // the bits outside the mask: one z for all terms, or a majority z and
+    // one further bit
+    uint64_t z[W];
+    const int n = gr.end - gr.begin;
+    bool one = true;
+    for (int w = 0; w < W; ++w) {
+        z[w] = hh.terms[static_cast<size_t>(gr.begin)].yz[w] & ~gr.xy[w];
+        for (int t = gr.begin + 1; t < gr.end; ++t)
+            one = one && ((hh.terms[static_cast<size_t>(t)].yz[w] & ~gr.xy[w]) == z[w]);
+    }
+    if (one) {
+        double T[kJoinIdx];
+        if (!join_signs<W>(hh, gr, a, b, mixed, T)) return;
+        pl = join_tag<W>(kJoinSign);
+        spin_strings<W>(z, pl.za, pl.zb);
+        for (size_t i = 0; i < kJoinIdx; ++i) out.sign[i * P + place] = T[i];
+        if (mixed) {
+            uint64_t bits;
+            std::memcpy(&bits, &T[kJoinMain], sizeof(bits));
+            pl.lo = static_cast<uint32_t>(bits);
+            pl.hi = static_cast<uint32_t>(bits >> 32);
+        }
+        return;
+    }
+    if (n < 8 || (a == 0 && b == 0)) return;
+    {   // a bit of the majority z is the majority of the bits
+        int c[64 * W] = {};
+        for (int t = gr.begin; t < gr.end; ++t)
+            for (int w = 0; w < W; ++w)
+                for (uint64_t v = hh.terms[static_cast<size_t>(t)].yz[w] & ~gr.xy[w]; v; v &= v - 1)
+                    ++c[64 * w + __builtin_ctzll(v)];
+        for (int w = 0; w < W; ++w) {
+            z[w] = 0;
+            for (int q = 0; q < 64; ++q)
+                if (2 * c[64 * w + q] > n) z[w] |= 1ull << q;
+        }
+    }
+    const size_t half = static_cast<size_t>(out.nibbles) * 16, per = 2 * half;
+    std::vector<double> tab(2 * per, 0.0);
+    for (int t = gr.begin; t < gr.end; ++t) {
+        const TermRec<W>& tr = hh.terms[static_cast<size_t>(t)];
+        int bit = -1, extra = 0;
+        bool none = true, all = true;
+        for (int w = 0; w < W; ++w) {
+            const uint64_t e = (tr.yz[w] & ~gr.xy[w]) ^ z[w], y = tr.yz[w] & gr.xy[w];
+            extra += __builtin_popcountll(e);
+            if (e) bit = 64 * w + __builtin_ctzll(e);
+            none = none && y == 0;
+            all = all && y == gr.xy[w];
+        }
+        if (extra > 1 || !(none || all)) return;
+        const int q = bit < 0 ? 0 : bit / 2;   // bit of the string
+        for (int par = 0; par < 2; ++par) {
+            const double h = (all && par) ? -tr.h : tr.h;
+            double* F = tab.data() + static_cast<size_t>(par) * per + (bit >= 0 && (bit & 1) ? half : 0) +
+                        static_cast<size_t>(q / 4) * 16;
+            for (int v = 0; v < 16; ++v) F[v] += (bit >= 0 && ((v >> (q % 4)) & 1)) ? -h : h;
+        }
+    }
+    const size_t number = out.linear.size() / (2 * per);
+    if (number >= (size_t(1) << 16)) return;
+    out.linear.insert(out.linear.end(), tab.begin(), tab.end());
+    pl = join_tag<W>(kJoinLinear, static_cast<uint32_t>(number));
+    spin_strings<W>(z, pl.za, pl.zb);
+}
+
+// ok stays false where the masks do not factor well: more places than four
+// times the groups, or over an eighth of the groups summed term by term.
+template <int W>
+void build_host_join(const HostHam<W>& hh, int n_qubits, HostJoin<W>& out) {
+    using ST = JoinStr<W>;
+    const int64_t G = hh.G;
+    if (hh.maxpart >= kNarrowMaxPart) return;   // a run's part lengths travel in 16 bits
+    // distinct parts: of the two-spin masks, and of the one-spin masks
+    const auto number = [](XYMap& map, std::vector<ST>& vals, ST v) {
+        const uint64_t k = v;
+        const int64_t i = map.find_or_insert(&k, static_cast<int64_t>(vals.size()));
+        if (i == static_cast<int64_t>(vals.size())) vals.push_back(v);
+        return i;
+    };
+    std::vector<ST> as(static_cast<size_t>(G)), bs(static_cast<size_t>(G));
+    XYMap amap(1), bmap(1), aomap(1), bomap(1);
+    std::vector<ST> avals, bvals, aown, bown;
+    std::vector<int32_t> bid(static_cast<size_t>(G));
+    bool zero = false, pairs = true;   // pairs: every mask has ids by position
+    for (int64_t g = 0; g < G; ++g) {
+        ST a, b;
+        spin_strings<W>(&hh.gkeys[static_cast<size_t>(g * W)], a, b);
+        as[static_cast<size_t>(g)] = a;
+        bs[static_cast<size_t>(g)] = b;
+        int64_t id;
+        const uint32_t pa = join_count(a), pb = join_count(b);
+        if (a == 0 || b == 0) {
+            zero = zero || a == 0;
+            id = a == 0 ? number(bomap, bown, b) : number(aomap, aown, a);
+            pairs = pairs && (pa + pb) % 2 == 0 && pa + pb <= 4;
+        } else {
+            (void)number(amap, avals, a);
+            id = number(bmap, bvals, b);
+            pairs = pairs && pa == 2 && pb == 2;
+            out.cross_span = std::max(out.cross_span, std::max(pa, pb));
+        }
+        bid[static_cast<size_t>(g)] = static_cast<int32_t>(id);
+    }
+    out.alist.assign(avals.begin(), avals.end());
+    std::sort(out.alist.begin(), out.alist.end());
+    out.blist.assign(bvals.begin(), bvals.end());
+    std::sort(out.blist.begin(), out.blist.end());
+    if (zero) out.alist.insert(out.alist.begin(), ST(0));
+    const int64_t na = static_cast<int64_t>(out.alist.size());
+    const int sb = join_string_bits(n_qubits);
+    const int64_t n_pairs = static_cast<int64_t>(sb) * (sb - 1) / 2, n_even = join_even_count(sb);
+    // ids by position unless that leaves too many places empty
+    const auto size = [&](bool direct) {
+        if (direct) return 2 * n_even + n_pairs * n_pairs;
+        return static_cast<int64_t>(bown.size() + aown.size()) + static_cast<int64_t>(avals.size() * bvals.size());
+    };
+    out.direct = pairs && size(true) <= 4 * G + 4096;
+    const int64_t places = size(out.direct);
+    if (na < 1 || places > 4 * G + 4096 || places >= (int64_t(1) << 25)) return;
+    out.stride = static_cast<uint32_t>(out.direct ? n_pairs : static_cast<int64_t>(bvals.size()));
+    const uint32_t cross = static_cast<uint32_t>(out.direct ? n_even : static_cast<int64_t>(bown.size()));
+    out.a_base = static_cast<uint32_t>(places - (out.direct ? n_even : static_cast<int64_t>(aown.size())));
+    const auto a_index = [&](ST a) {   // of a two-spin mask's spin-up part
+        return static_cast<uint32_t>(std::lower_bound(out.alist.begin(), out.alist.end(), a) - out.alist.begin());
+    };
+    const auto a_base_of = [&](ST a) {
+        const uint32_t i = out.direct ? join_pair_id(a) : a_index(a) - (zero ? 1u : 0u);
+        return cross + i * out.stride;
+    };
+    out.amask.resize(static_cast<size_t>(na));
+    for (int64_t k = 0; k < na; ++k) {
+        const ST a = out.alist[static_cast<size_t>(k)];
+        out.amask[static_cast<size_t>(k)] = JoinMask{a == 0 ? kJoinFull : a_base_of(a), 0u};
+    }
+    out.bmask.resize(out.blist.size());
+    for (size_t k = 0; k < out.blist.size(); ++k)
+        out.bmask[k] = JoinMask{out.direct ? cross + join_pair_id(out.blist[k]) : 0u, out.cross_span - 1u};
+    out.nibbles = (sb + 3) / 4;
+    out.runs.assign(static_cast<size_t>(places), JoinRun{0, 0});
+    out.gids.assign(static_cast<size_t>(places), -1);
+    out.place.assign(static_cast<size_t>(places), join_tag<W>(kJoinEmpty));
+    out.sign.assign(static_cast<size_t>(places) * kJoinIdx, 0.0);
+    int64_t by_run = 0;
+    uint32_t pmin = ~0u, pmax = 0;
+    for (int64_t g = 0; g < G; ++g) {
+        const ST a = as[static_cast<size_t>(g)], b = bs[static_cast<size_t>(g)];
+        size_t place = static_cast<size_t>(bid[static_cast<size_t>(g)]);
+        if (a == 0) {
+            JoinMask& m = out.amask[0];
+            m.span = std::max(m.span, join_count(b));
+            if (out.direct) place = join_even_id(b, static_cast<uint32_t>(sb));
+        } else if (b == 0) {
+            if (out.direct) place = join_even_id(a, static_cast<uint32_t>(sb));
+            place += out.a_base;
+            pmin = std::min(pmin, join_count(a));
+            pmax = std::max(pmax, join_count(a));
+        } else {
+            JoinMask& m = out.amask[out.direct ? 0 : a_index(a)];
+            if (!out.direct) m.span = std::max<uint32_t>(m.span, join_count(b) - 1u);
+            place = a_base_of(a) + (out.direct ? join_pair_id(b) : place);
+        }
+        const GroupRec<W>& gr = hh.groups[static_cast<size_t>(g)];
+        out.runs[place] = JoinRun{static_cast<uint32_t>(gr.begin),
+                                  static_cast<uint32_t>(gr.mid - gr.begin) |
+                                      (static_cast<uint32_t>(gr.end - gr.mid) << 16)};
+        out.gids[place] = static_cast<int32_t>(g);
+        join_place<W>(hh, gr, place, a != 0 && b != 0, out);
+        by_run += join_kind_of(out.place[place].hi) == kJoinRunKind;
+    }
+    if (8 * by_run > G) return;
+    if (out.direct)
+        for (int64_t k = zero ? 1 : 0; k < na; ++k) out.amask[static_cast<size_t>(k)].span = 1u;
+    if (!aown.empty()) {
+        out.a_pmin = pmin;
+        out.a_span = pmax - pmin;
+    }
+    const auto table = [](std::vector<JoinSlot<W>>& t, const std::vector<ST>& vals) {
+        t.assign(join_capacity(vals.size()), JoinSlot<W>{0, kJoinNone});
+        for (size_t i = 0; i < vals.size(); ++i) join_insert<W>(t, vals[i], static_cast<uint32_t>(i));
+    };
+    table(out.b_cross, bvals);
+    table(out.b_own, bown);
+    table(out.a_own, aown);
+    out.ok = true;
+}
+
+}  // namespace eloc
