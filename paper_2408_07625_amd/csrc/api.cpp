@@ -616,6 +616,7 @@ int ingest(eloc_ctx c, int n_qubits, int64_t n_terms, const double* coeff, const
         JH.runs = c->jh_runs.as<JoinRun>();
         JH.gids = c->jh_gids.as<int32_t>();
         JH.places = static_cast<uint32_t>(hj.place.size());
+        JH.cross = hj.cross;
         JH.nibbles = hj.nibbles;
         JH.a_base = hj.a_base;
         JH.a_pmin = hj.a_pmin;
@@ -1600,6 +1601,13 @@ int eloc_find_pairs(eloc_ctx c, int variant, int64_t capacity, int32_t* i_dev, i
     const int end_bit = 2 * jbits;
     ELOC_HIP(c, c->pkey.ensure(sizeof(uint64_t) * total));
     ELOC_HIP(c, c->pval.ensure(sizeof(uint32_t) * total));
+    if (M <= kRowSortMax) {
+        ELOC_HIP(c, fill_pairs(c, variant, P, jbits));
+        ELOC_HIP(c, launch_rows_sorted(c->offsets.as<int64_t>(), M, P.chunks, jbits, c->pkey.as<uint64_t>(),
+                                       c->pval.as<uint32_t>(), i_dev, j_dev, g_dev, c->stream));
+        ELOC_HIP(c, hipStreamSynchronize(c->stream));
+        return ELOC_OK;
+    }
     ELOC_HIP(c, c->pkey2.ensure(sizeof(uint64_t) * total));
     ELOC_HIP(c, c->pval2.ensure(sizeof(uint32_t) * total));
     ELOC_HIP(c, fill_pairs(c, variant, P, jbits));
@@ -1638,10 +1646,14 @@ int eloc_pair_elements(eloc_ctx c, int64_t n, const int32_t* i_dev, const int32_
         ELOC_HIP(c, c->pe_grp.ensure(sizeof(int32_t) * n));
         ELOC_HIP(c, c->scan_scratch.ensure(sizeof(int64_t) * scan_scratch_len(n)));
     }
-    ELOC_HIP(c, launch_pair_elements(c->H, c->S, n, i_dev, j_dev, reinterpret_cast<double2*>(h_dev),
-                                     phases ? c->pe_cnt.as<int32_t>() : nullptr,
-                                     phases ? c->pe_grp.as<int32_t>() : nullptr, c->err_run.as<uint32_t>(),
-                                     c->stream));
+    int32_t* cnt = phases ? c->pe_cnt.as<int32_t>() : nullptr;
+    int32_t* grp = phases ? c->pe_grp.as<int32_t>() : nullptr;
+    if (c->JH.ok && c->JH.direct)
+        ELOC_HIP(c, launch_join_elements(c->H, c->JH, c->S, n, i_dev, j_dev, reinterpret_cast<double2*>(h_dev), cnt, grp,
+                                         c->err_run.as<uint32_t>(), c->stream));
+    else
+        ELOC_HIP(c, launch_pair_elements(c->H, c->S, n, i_dev, j_dev, reinterpret_cast<double2*>(h_dev), cnt, grp,
+                                         c->err_run.as<uint32_t>(), c->stream));
     if (phases) {
         ELOC_HIP(c, launch_scan_i32(c->pe_cnt.as<int32_t>(), n, term_offsets_dev, c->scan_scratch.as<int64_t>(),
                                     c->stream));
@@ -1712,7 +1724,11 @@ int eloc_store_pairs(eloc_ctx c, int variant, size_t budget_bytes, int64_t* n_pa
     ELOC_HIP(c, c->st_rowptr.ensure(sizeof(int64_t) * (M + 1)));
     if (total > 0) {
         ELOC_HIP(c, fill_pairs(c, variant, P, jbits));
-        ELOC_HIP(c, launch_pairs_to_csr(c->H, c->S, total, c->pkey.as<uint64_t>(), c->pval.as<uint32_t>(), jbits,
+        if (c->JH.ok && c->JH.direct)
+            ELOC_HIP(c, launch_join_to_csr(c->H, c->JH, c->S, total, c->pkey.as<uint64_t>(), jbits,
+                                           c->st_col.as<int32_t>(), c->st_h.as<double2>(), c->stream));
+        else
+            ELOC_HIP(c, launch_pairs_to_csr(c->H, c->S, total, c->pkey.as<uint64_t>(), c->pval.as<uint32_t>(), jbits,
                                         c->st_col.as<int32_t>(), c->st_h.as<double2>(), c->stream));
     }
     ELOC_HIP(c, launch_rowptr(c->offsets.as<int64_t>(), M, P.chunks, c->st_rowptr.as<int64_t>(), c->stream));

@@ -346,6 +346,32 @@ __device__ __forceinline__ void wave_sum(AccF& a) {
     }
 }
 
+// MatrixElement of every lane's pair (called by the whole wave; an idle lane
+// passes an empty run).  Runs of up to 16 terms are summed by their lane; the
+// longer ones - the diagonal, single excitations - one after another by the
+// wave, since one lane's long run would hold up the other 63.
+template <int W, bool NW>
+__device__ __forceinline__ void wave_melem(const TermRec<W>* __restrict__ terms, int b, int m, int e,
+                                           const uint64_t* ket, double& hr, double& hi) {
+    const bool lng = e - b > 16;
+    hr = 0.0;
+    hi = 0.0;
+    if (!lng) melem<W, NW>(terms, b, m, e, 0, 1, ket, hr, hi);
+    for (uint64_t ml = __ballot(lng); ml; ml &= ml - 1) {
+        const int l = __ffsll(static_cast<unsigned long long>(ml)) - 1;
+        uint64_t k[W];
+#pragma unroll
+        for (int w = 0; w < W; ++w) k[w] = lane_shfl(ket[w], l);
+        AccD s;
+        melem<W, NW>(terms, __shfl(b, l, 64), __shfl(m, l, 64), __shfl(e, l, 64), lane_id(), 64, k, s.re, s.im);
+        wave_sum(s);
+        if (lane_id() == l) {
+            hr = s.re;
+            hi = s.im;
+        }
+    }
+}
+
 // A complex double as FP32 hi + lo pairs (re_hi, re_lo, im_hi, im_lo).
 __device__ __forceinline__ float4 split_c(double re, double im) {
     const float rh = static_cast<float>(re);

@@ -325,6 +325,7 @@ struct JoinHamDev {
     const JoinRun* runs = nullptr;     // [places]
     const int32_t* gids = nullptr;     // [places] group
     uint32_t places = 0;
+    uint32_t cross = 0;                // first place of the two-spin masks
     int nibbles = 0;                   // of one string
     uint32_t a_base = 0, a_pmin = 0, a_span = 0;   // the section (a, 0): first place, popcounts
     bool has_a_own = false;
@@ -812,6 +813,12 @@ hipError_t launch_pair_phases(const HamDev& H, const SampleDev& S, int64_t n, co
 
 hipError_t launch_pairs_to_csr(const HamDev& H, const SampleDev& S, int64_t n, const uint64_t* pkey,
                                const uint32_t* pval, int jbits, int32_t* col, double2* h, hipStream_t st);
+// The emitted pairs (row << jbits | column, group), row after row at
+// offsets[row * chunks], as (i, j, g) ordered by (i, j): for up to
+// kRowSortMax samples (a bitmap of U's columns in LDS).
+constexpr int64_t kRowSortMax = int64_t(1) << 17;
+hipError_t launch_rows_sorted(const int64_t* offsets, int64_t M, int chunks, int jbits, const uint64_t* pkey,
+                              const uint32_t* pval, int32_t* oi, int32_t* oj, int32_t* og, hipStream_t st);
 hipError_t launch_rowptr(const int64_t* offsets, int64_t M, int chunks, int64_t* rowptr, hipStream_t st);
 hipError_t launch_spmv(bool adjoint, int precision, int64_t M, const int64_t* rowptr, const int32_t* col,
                        const double2* h, const void* vec, void* partial, hipStream_t st);
@@ -868,6 +875,14 @@ hipError_t launch_join_pairs(bool adjoint, int precision, const HamDev& H, const
                              const Plan& P, const double2* vec, const float4* vecf, void* partial, hipStream_t st);
 hipError_t launch_join_count(const HamDev& H, const JoinHamDev& JH, const JoinDev& J, const Plan& P, int32_t* counts,
                              hipStream_t st);
+// Matrix elements of sample pairs by place (Hamiltonians with H.direct): of
+// (i_idx, j_idx) with the outputs of launch_pair_elements, or of emitted pairs
+// with those of launch_pairs_to_csr.
+hipError_t launch_join_elements(const HamDev& H, const JoinHamDev& JH, const SampleDev& S, int64_t n,
+                                const int32_t* i_idx, const int32_t* j_idx, double2* h_out, int32_t* cnt, int32_t* grp,
+                                uint32_t* err, hipStream_t st);
+hipError_t launch_join_to_csr(const HamDev& H, const JoinHamDev& JH, const SampleDev& S, int64_t n,
+                              const uint64_t* pkey, int jbits, int32_t* col, double2* h, hipStream_t st);
 hipError_t launch_join_fill(const HamDev& H, const JoinHamDev& JH, const JoinDev& J, const Plan& P, int jbits,
                             const int64_t* offsets, uint64_t* pkey, uint32_t* pval, hipStream_t st);
 hipError_t launch_sort_keys(int W, int n_bits, const uint64_t* keys, int64_t n, const SortScratch& S,

@@ -30,6 +30,7 @@ struct HostJoin {
     std::vector<JoinRun> runs;
     std::vector<int32_t> gids;
     int nibbles = 0;
+    uint32_t cross = 0;               // first place of the two-spin masks
     uint32_t a_base = 0;              // places of the masks (a, 0)
     uint32_t a_pmin = 0, a_span = 0;  // their smallest popcount, largest less smallest
     uint32_t cross_span = 0;          // largest popcount of a part of a two-spin mask
@@ -238,7 +239,7 @@ void build_host_join(const HostHam<W>& hh, int n_qubits, HostJoin<W>& out) {
     const int64_t places = size(out.direct);
     if (na < 1 || places > 4 * G + 4096 || places >= (int64_t(1) << 25)) return;
     out.stride = static_cast<uint32_t>(out.direct ? n_pairs : static_cast<int64_t>(bvals.size()));
-    const uint32_t cross = static_cast<uint32_t>(out.direct ? n_even : static_cast<int64_t>(bown.size()));
+    const uint32_t cross = out.cross = static_cast<uint32_t>(out.direct ? n_even : static_cast<int64_t>(bown.size()));
     out.a_base = static_cast<uint32_t>(places - (out.direct ? n_even : static_cast<int64_t>(aown.size())));
     const auto a_index = [&](ST a) {   // of a two-spin mask's spin-up part
         return static_cast<uint32_t>(std::lower_bound(out.alist.begin(), out.alist.end(), a) - out.alist.begin());

@@ -591,6 +591,93 @@ __global__ __launch_bounds__(kWave) void k_join(JoinArgs A, JoinOut O) {
 }
 
 // ---------------------------------------------------------------------------
+// Matrix elements of given pairs
+// ---------------------------------------------------------------------------
+// One pair per lane: its place by position, then a record and a T or the
+// nibble tables; the diagonal's term run by the whole wave.  CSR: pairs as
+// emitted; else given indices, checked.
+template <int W, bool CSR>
+__global__ __launch_bounds__(256) void k_join_elements(JoinHamDev H, const TermRec<W>* __restrict__ terms,
+                                                       const uint64_t* __restrict__ keys, int64_t M, int64_t n,
+                                                       const int32_t* __restrict__ pi, const int32_t* __restrict__ pj,
+                                                       const uint64_t* __restrict__ pkey, int jbits,
+                                                       double2* __restrict__ out, int32_t* __restrict__ cnt,
+                                                       int32_t* __restrict__ grp, uint32_t* __restrict__ err) {
+    using ST = JoinStr<W>;
+    const int64_t t = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+    const bool on = t < n;
+    int64_t i = 0, j = 0;
+    if (on && CSR) {
+        i = static_cast<int64_t>(pkey[t] >> jbits);
+        j = static_cast<int64_t>(pkey[t] & ((1ull << jbits) - 1ull));
+    } else if (on) {
+        i = pi[t];
+        j = pj[t];
+    }
+    const bool ok = CSR || (i >= 0 && j >= 0 && i < M && j < M);
+    if (!ok) {
+        atomicOr(err, static_cast<uint32_t>(kErrIndex));
+        i = j = 0;
+    }
+    uint64_t ket[W];
+#pragma unroll
+    for (int w = 0; w < W; ++w) ket[w] = keys[j * W + w];
+    ST ia, ib, ka, kb;
+    spin_strings<W>(keys + i * W, ia, ib);
+    spin_strings<W>(ket, ka, kb);
+    const ST a = ia ^ ka, b = ib ^ kb;
+    const uint32_t ca = pop(a), cb = pop(b), sb = static_cast<uint32_t>(H.string_bits);
+    uint32_t place = kJoinNone;
+    const bool one = a == 0 || b == 0;
+    if (one && ca + cb <= 4u && !((ca + cb) & 1u))
+        place = (a == 0 ? 0u : H.a_base) + join_even_id(static_cast<ST>(a | b), sb);
+    if (ca == 2u && cb == 2u) place = H.cross + join_pair_id(a) * H.stride + join_pair_id(b);
+    if (!on || !ok) place = kJoinNone;
+    JoinPlace<W> pl{0, 0, 0, kJoinTag};
+    if (place != kJoinNone) pl = static_cast<const JoinPlace<W>*>(H.place)[place];
+    const uint32_t kind = (pl.hi & kJoinTag) == kJoinTag ? pl.hi & 7u : static_cast<uint32_t>(kJoinSign);
+    const uint32_t pa = pop(static_cast<ST>(ka & a)) & 1u, pb = pop(static_cast<ST>(kb & b)) & 1u;
+    const bool flip = (pop(static_cast<ST>(ka & pl.za)) + pop(static_cast<ST>(kb & pl.zb))) & 1u;
+    double h = 0.0, hi = 0.0;
+    if (kind == kJoinSign) {
+        uint32_t idx = pa | (pb << 1);
+        if (one) {
+            ST p1, p3;
+            join_parity_masks(static_cast<ST>(a | b), p1, p3);
+            const ST k = a == 0 ? kb : ka;
+            idx = (pop(static_cast<ST>(k & p1)) & 1u) | ((pa ^ pb) << 1) | ((pop(static_cast<ST>(k & p3)) & 1u) << 2);
+        }
+        h = H.sign[static_cast<int64_t>(idx) * H.places + place];
+    } else if (kind == kJoinLinear) {
+        const double* F = H.linear + (static_cast<int64_t>(pl.lo) * 2 + ((pa ^ pb) & 1u)) * 2 * H.nibbles * 16;
+        for (int q = 0; q < H.nibbles; ++q) {
+            h += F[q * 16 + (static_cast<uint32_t>(ka >> (4 * q)) & 15u)];
+            h += F[(H.nibbles + q) * 16 + (static_cast<uint32_t>(kb >> (4 * q)) & 15u)];
+        }
+    }
+    if (flip) h = -h;
+    JoinRun run{0u, 0u};
+    if (kind == kJoinRunKind) run = H.runs[place];
+    const int rb = static_cast<int>(run.begin), rm = rb + static_cast<int>(run.lens & 0xFFFFu),
+              re = rm + static_cast<int>(run.lens >> 16);
+    double hr, hm;
+    wave_melem<W, false>(terms, rb, rm, re, ket, hr, hm);
+    if (kind == kJoinRunKind) {
+        h = hr;
+        hi = hm;
+    }
+    if (!on) return;
+    out[t] = make_double2(h, hi);
+    if constexpr (CSR) cnt[t] = static_cast<int32_t>(j);   // the column
+    if (!CSR && cnt) {
+        const bool hit = kind != kJoinEmpty;
+        const JoinRun r = hit ? H.runs[place] : JoinRun{0u, 0u};
+        cnt[t] = static_cast<int32_t>((r.lens & 0xFFFFu) + (r.lens >> 16));
+        grp[t] = hit ? H.gids[place] : -1;
+    }
+}
+
+// ---------------------------------------------------------------------------
 // Index of U
 // ---------------------------------------------------------------------------
 constexpr int kBlock = 256;
@@ -835,6 +922,31 @@ hipError_t launch_join_count(const HamDev& H, const JoinHamDev& JH, const JoinDe
     JoinOut O{};
     O.counts = counts;
     return launch_list<kModeCount>(H, P.rows_per_block, make_args(H.terms, JH, J, P), O, st);
+}
+
+hipError_t launch_join_elements(const HamDev& H, const JoinHamDev& JH, const SampleDev& S, int64_t n,
+                                const int32_t* i_idx, const int32_t* j_idx, double2* h_out, int32_t* cnt, int32_t* grp,
+                                uint32_t* err, hipStream_t st) {
+    const dim3 grid(div_up(n, 256)), block(256);
+    if (H.W == 2)
+        hipLaunchKernelGGL((k_join_elements<2, false>), grid, block, 0, st, JH, static_cast<const TermRec<2>*>(H.terms),
+                           S.keys, S.n, n, i_idx, j_idx, nullptr, 0, h_out, cnt, grp, err);
+    else
+        hipLaunchKernelGGL((k_join_elements<1, false>), grid, block, 0, st, JH, static_cast<const TermRec<1>*>(H.terms),
+                           S.keys, S.n, n, i_idx, j_idx, nullptr, 0, h_out, cnt, grp, err);
+    return hipGetLastError();
+}
+
+hipError_t launch_join_to_csr(const HamDev& H, const JoinHamDev& JH, const SampleDev& S, int64_t n,
+                              const uint64_t* pkey, int jbits, int32_t* col, double2* h, hipStream_t st) {
+    const dim3 grid(div_up(n, 256)), block(256);
+    if (H.W == 2)
+        hipLaunchKernelGGL((k_join_elements<2, true>), grid, block, 0, st, JH, static_cast<const TermRec<2>*>(H.terms),
+                           S.keys, S.n, n, nullptr, nullptr, pkey, jbits, h, col, nullptr, nullptr);
+    else
+        hipLaunchKernelGGL((k_join_elements<1, true>), grid, block, 0, st, JH, static_cast<const TermRec<1>*>(H.terms),
+                           S.keys, S.n, n, nullptr, nullptr, pkey, jbits, h, col, nullptr, nullptr);
+    return hipGetLastError();
 }
 
 hipError_t launch_join_fill(const HamDev& H, const JoinHamDev& JH, const JoinDev& J, const Plan& P, int jbits,

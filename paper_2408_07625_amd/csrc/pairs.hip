@@ -1470,34 +1470,28 @@ __global__ __launch_bounds__(256) void k_pair_elements(PairArgs A, int64_t n, co
                                                        int32_t* __restrict__ cnt, int32_t* __restrict__ grp,
                                                        uint32_t* __restrict__ err) {
     const int64_t t = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-    if (t >= n) return;
-    const int64_t i = pi[t], j = pj[t];
-    if (i < 0 || j < 0 || i >= A.M || j >= A.M) {
-        atomicOr(err, static_cast<uint32_t>(kErrIndex));
-        out[t] = make_double2(0.0, 0.0);
-        if (cnt) {
-            cnt[t] = 0;
-            grp[t] = -1;
-        }
-        return;
-    }
-    uint64_t xj[W], m[W];
+    const bool on = t < n;
+    const int64_t i = on ? pi[t] : 0, j = on ? pj[t] : 0;
+    const bool ok = i >= 0 && j >= 0 && i < A.M && j < A.M;
+    if (!ok) atomicOr(err, static_cast<uint32_t>(kErrIndex));
+    uint64_t xj[W] = {}, m[W];
+    int g = -1;
+    GroupRec<W> gr{};
+    if (on && ok) {
 #pragma unroll
-    for (int w = 0; w < W; ++w) {
-        xj[w] = A.keys[j * W + w];
-        m[w] = A.keys[i * W + w] ^ xj[w];
+        for (int w = 0; w < W; ++w) {
+            xj[w] = A.keys[j * W + w];
+            m[w] = A.keys[i * W + w] ^ xj[w];
+        }
+        g = table_find<table_kind(W, NW), W>(A.gtable, A.gkeys, A.khash[i] ^ A.khash[j], m);
+        if (g >= 0) gr = static_cast<const GroupRec<W>*>(A.groups)[g];
     }
-    const int g = table_find<table_kind(W, NW), W>(A.gtable, A.gkeys, A.khash[i] ^ A.khash[j], m);
-    double hr = 0.0, hi = 0.0;
-    int32_t nt = 0;
-    if (g >= 0) {
-        const GroupRec<W> gr = static_cast<const GroupRec<W>*>(A.groups)[g];
-        melem<W, NW>(static_cast<const TermRec<W>*>(A.terms), gr.begin, gr.mid, gr.end, 0, 1, xj, hr, hi);
-        nt = gr.end - gr.begin;
-    }
+    double hr, hi;
+    wave_melem<W, NW>(static_cast<const TermRec<W>*>(A.terms), gr.begin, gr.mid, gr.end, xj, hr, hi);
+    if (!on) return;
     out[t] = make_double2(hr, hi);
     if (cnt) {
-        cnt[t] = nt;
+        cnt[t] = gr.end - gr.begin;
         grp[t] = g;
     }
 }
@@ -1556,16 +1550,63 @@ __global__ __launch_bounds__(256) void k_pairs_to_csr(PairArgs A, int64_t n, con
                                                       const uint32_t* __restrict__ pval, int jbits,
                                                       int32_t* __restrict__ col, double2* __restrict__ h) {
     const int64_t t = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-    if (t >= n) return;
-    const int64_t j = static_cast<int64_t>(pkey[t] & ((1ull << jbits) - 1ull));
-    const GroupRec<W> gr = static_cast<const GroupRec<W>*>(A.groups)[pval[t]];
+    const bool on = t < n;
+    const int64_t j = on ? static_cast<int64_t>(pkey[t] & ((1ull << jbits) - 1ull)) : 0;
+    GroupRec<W> gr{};
+    if (on) gr = static_cast<const GroupRec<W>*>(A.groups)[pval[t]];
     uint64_t xj[W];
 #pragma unroll
     for (int w = 0; w < W; ++w) xj[w] = A.keys[j * W + w];
     double hr, hi;
-    melem<W, NW>(static_cast<const TermRec<W>*>(A.terms), gr.begin, gr.mid, gr.end, 0, 1, xj, hr, hi);
+    wave_melem<W, NW>(static_cast<const TermRec<W>*>(A.terms), gr.begin, gr.mid, gr.end, xj, hr, hi);
+    if (!on) return;
     col[t] = static_cast<int32_t>(j);
     h[t] = make_double2(hr, hi);
+}
+
+// The emitted pairs of one row (a wave each) in the order of their columns:
+// the columns are distinct, so a bitmap of them in LDS and its prefix counts
+// give every pair its place.  One pass over the pairs where the radix sort of
+// (row, column) takes one per eight bits.
+__global__ __launch_bounds__(kWave) void k_rows_sorted(const int64_t* __restrict__ offsets, int chunks, int jbits,
+                                                       int words, const uint64_t* __restrict__ pkey,
+                                                       const uint32_t* __restrict__ pval, int32_t* __restrict__ oi,
+                                                       int32_t* __restrict__ oj, int32_t* __restrict__ og) {
+    extern __shared__ uint32_t lds[];
+    uint32_t* bits = lds;             // [words], a multiple of 64
+    uint32_t* before = lds + words;   // set bits in the words before this one
+    const int lane = lane_id();
+    const int64_t row = blockIdx.x;
+    const int64_t p0 = offsets[row * chunks], p1 = offsets[(row + 1) * chunks];
+    if (p0 == p1) return;
+    for (int w = lane; w < words; w += kWave) bits[w] = 0u;
+    wave_sync();
+    const uint64_t mask = (1ull << jbits) - 1ull;
+    for (int64_t p = p0 + lane; p < p1; p += kWave) {
+        const uint32_t j = static_cast<uint32_t>(pkey[p] & mask);
+        atomicOr(&bits[j >> 5], 1u << (j & 31u));
+    }
+    wave_sync();
+    uint32_t base = 0;
+    for (int w0 = 0; w0 < words; w0 += kWave) {
+        const uint32_t c = static_cast<uint32_t>(__popc(bits[w0 + lane]));
+        uint32_t s = c;
+#pragma unroll
+        for (int d = 1; d < kWave; d <<= 1) {
+            const uint32_t o = __shfl_up(s, d, kWave);
+            if (lane >= d) s += o;
+        }
+        before[w0 + lane] = base + s - c;
+        base += __shfl(s, kWave - 1, kWave);
+    }
+    wave_sync();
+    for (int64_t p = p0 + lane; p < p1; p += kWave) {
+        const uint32_t j = static_cast<uint32_t>(pkey[p] & mask);
+        const int64_t o = p0 + before[j >> 5] + __popc(bits[j >> 5] & ((1u << (j & 31u)) - 1u));
+        oi[o] = static_cast<int32_t>(row);
+        oj[o] = static_cast<int32_t>(j);
+        og[o] = static_cast<int32_t>(pval[p]);
+    }
 }
 
 __global__ __launch_bounds__(256) void k_rowptr(const int64_t* __restrict__ offsets, int64_t M, int chunks,
@@ -1574,30 +1615,48 @@ __global__ __launch_bounds__(256) void k_rowptr(const int64_t* __restrict__ offs
     if (i <= M) rowptr[i] = offsets[i * chunks];
 }
 
+// Four pairs a lane are in flight per round: a row of a few hundred pairs is
+// bound by the chain column -> amplitude, not by its bytes.
+constexpr int kSpmvWaves = 4;
+
 template <int PREC, bool ADJ>
-__global__ __launch_bounds__(kWave) void k_spmv(int64_t M, const int64_t* __restrict__ rowptr,
-                                                const int32_t* __restrict__ col, const double2* __restrict__ h,
-                                                const void* __restrict__ vec, void* __restrict__ partial) {
+__global__ __launch_bounds__(kWave * kSpmvWaves) void k_spmv(int64_t M, const int64_t* __restrict__ rowptr,
+                                                             const int32_t* __restrict__ col,
+                                                             const double2* __restrict__ h,
+                                                             const void* __restrict__ vec, void* __restrict__ partial) {
     using P = Prec<PREC>;
-    const int64_t i = blockIdx.x;
+    const int64_t i = static_cast<int64_t>(blockIdx.x) * kSpmvWaves + threadIdx.x / kWave;
+    if (i >= M) return;
     const int64_t p0 = rowptr[i], p1 = rowptr[i + 1];
     typename P::Acc acc;
-    for (int64_t p = p0 + threadIdx.x; p < p1; p += kWave) {
-        double2 hv = h[p];
-        if (ADJ) hv.y = -hv.y;
-        const int32_t j = col[p];
-        if constexpr (PREC == 0) {
-            mac(acc, hv.x, hv.y, static_cast<const double2*>(vec)[j]);
-        } else {
-            const float4 s = split_c(hv.x, hv.y);
-            mac(acc, F2{s.x, s.y}, F2{s.z, s.w}, static_cast<const float4*>(vec)[j]);
+    constexpr int U = 4;
+    for (int64_t p = p0 + lane_id(); p < p1; p += U * kWave) {
+        int32_t j[U];
+        double2 hv[U];
+        typename P::Vec v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t q = min(p + u * kWave, p1 - 1);
+            j[u] = col[q];
+            hv[u] = h[q];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = static_cast<const typename P::Vec*>(vec)[j[u]];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (p + u * kWave >= p1) continue;
+            const double im = ADJ ? -hv[u].y : hv[u].y;
+            if constexpr (PREC == 0) {
+                mac(acc, hv[u].x, im, v[u]);
+            } else {
+                const float4 s = split_c(hv[u].x, im);
+                mac(acc, F2{s.x, s.y}, F2{s.z, s.w}, v[u]);
+            }
         }
     }
     wave_sum(acc);
-    if (threadIdx.x == 0) store_acc(partial, i, acc);
+    if (lane_id() == 0) store_acc(partial, i, acc);
 }
-
-
 
 template <int W, int VARIANT, int PREC, bool ADJ, bool NW>
 hipError_t launch_pairs_t(const PairArgs& A, const Plan& P, const void* vec, void* partial, hipStream_t st) {
@@ -1833,6 +1892,14 @@ hipError_t launch_pairs_to_csr(const HamDev& H, const SampleDev& S, int64_t n, c
     return hipGetLastError();
 }
 
+hipError_t launch_rows_sorted(const int64_t* offsets, int64_t M, int chunks, int jbits, const uint64_t* pkey,
+                              const uint32_t* pval, int32_t* oi, int32_t* oj, int32_t* og, hipStream_t st) {
+    const int words = static_cast<int>((M + 2047) / 2048) * 64;
+    hipLaunchKernelGGL(k_rows_sorted, dim3(static_cast<unsigned>(M)), dim3(kWave), sizeof(uint32_t) * 2 * words, st,
+                       offsets, chunks, jbits, words, pkey, pval, oi, oj, og);
+    return hipGetLastError();
+}
+
 hipError_t launch_rowptr(const int64_t* offsets, int64_t M, int chunks, int64_t* rowptr, hipStream_t st) {
     hipLaunchKernelGGL(k_rowptr, dim3(div_up(M + 1, 256)), dim3(256), 0, st, offsets, M, chunks, rowptr);
     return hipGetLastError();
@@ -1840,7 +1907,7 @@ hipError_t launch_rowptr(const int64_t* offsets, int64_t M, int chunks, int64_t*
 
 hipError_t launch_spmv(bool adjoint, int precision, int64_t M, const int64_t* rowptr, const int32_t* col,
                        const double2* h, const void* vec, void* partial, hipStream_t st) {
-    const dim3 grid(static_cast<unsigned>(M)), block(kWave);
+    const dim3 grid(div_up(M, kSpmvWaves)), block(kWave * kSpmvWaves);
     if (precision == 0) {
         if (adjoint)
             hipLaunchKernelGGL((k_spmv<0, true>), grid, block, 0, st, M, rowptr, col, h, vec, partial);

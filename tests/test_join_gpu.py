@@ -183,3 +183,46 @@ def test_noalloc_under_capture(pe, built):
         e2, _ = eng.local_energy(L)
         assert torch.equal(e2, e)
     eng.close()
+
+
+def test_pair_elements(case):
+    """H and the per-term phases of coupled and uncoupled pairs, against the
+    oracle (long and short runs, places of every kind)."""
+    eng, ham, keys, lp, variant, rows = case
+    i, j, _ = eng.find_pairs(variant)
+    rng = np.random.default_rng(9)
+    pick = dev(rng.choice(i.numel(), size=min(i.numel(), 3000), replace=False))
+    i, j = i[pick], j[pick]
+    far = dev(rng.integers(0, keys.shape[0], size=(2, 200)).astype(np.int32))
+    i, j = torch.cat([i, far[0]]), torch.cat([j, far[1]])
+    h, off, k = eng.pair_elements(i, j, phases=True)
+    ni, nj = i.cpu().numpy(), j.cpu().numpy()
+    groups = {}
+    for t, m in enumerate(map(tuple, ham.xy.tolist())):
+        groups.setdefault(m, []).append(t)
+    off, k, h = off.cpu().numpy(), k.cpu().numpy(), h.cpu().numpy()
+    bits = lambda v: sum(int(x).bit_count() if hasattr(int, "bit_count") else bin(int(x)).count("1") for x in v)  # noqa: E731
+    for t in range(0, ni.size, 7):
+        terms = groups.get(tuple((keys[ni[t]] ^ keys[nj[t]]).tolist()), [])
+        ph = [(bits(ham.xy[l] & ham.yz[l]) + 2 * bits(keys[nj[t]] & ham.yz[l])) % 4 for l in terms]
+        assert off[t + 1] - off[t] == len(terms)
+        assert k[off[t]:off[t + 1]].tolist() == ph
+        ref = sum(ham.coeff[l] * 1j ** p for l, p in zip(terms, ph))
+        scale = max(1.0, sum(abs(ham.coeff[l]) for l in terms))
+        assert abs(h[t] - ref) <= 1e-12 * scale
+
+
+@pytest.mark.parametrize("m", [1, 63, 2047, 2049, 4097])
+def test_pair_order(pe, m):
+    """The pair list is ordered by (row, column) at bitmap sizes around whole
+    and partial words, with and without the join."""
+    ham, keys, lp = molecule(20, 10, 4097, 65)
+    keys = keys[:m]
+    eng = pe.Engine(0)
+    eng.set_hamiltonian(20, ham.coeff, ham.xy, ham.yz)
+    eng.set_samples(dev(keys.view(np.int64)))
+    want = oracle.find_pairs(ham, keys)
+    for variant in ("terms", "batch", "trie"):
+        for a, b in zip(eng.find_pairs(variant), want):
+            np.testing.assert_array_equal(a.cpu().numpy(), b)
+    eng.close()
