@@ -95,7 +95,7 @@ struct eloc_ctx_s {
     DevBuf x_a, x_b, x_af, x_bf, x_shift;
     DevBuf x_part_perm, x_part_class, x_part_tile;   // U's rows by partition class of the U-and-extra table
     // stochastic reconfiguration scratch
-    DevBuf sr_w, sr_mean, sr_part, sr_T, sr_L, sr_y;
+    DevBuf sr_w, sr_mean, sr_part, sr_T, sr_y;
     // sampler: two prefix beams, the candidates of a level, the allowed count
     DevBuf ar_keys[2], ar_l[2], ar_T[2], ar_cl, ar_cT, ar_ck, ar_ci, ar_ck2, ar_ci2, ar_cnt;
     DevBuf ar_hist, ar_sel, ar_keep, ar_off;   // top-K selection scratch
@@ -884,7 +884,7 @@ void eloc_destroy(eloc_ctx c) {
                       &c->m_raw, &c->m_sorted, &c->m_perm, &c->m_flags, &c->m_pos, &c->m_count, &c->x_keys, &c->x_hash, &c->x_slots,
                       &c->x_stash, &c->x_sig, &c->x_bitcounts, &c->x_rad, &c->x_params, &c->x_err, &c->x_logpsi,
                       &c->x_a, &c->x_b, &c->x_af, &c->x_bf, &c->x_shift, &c->x_part_perm, &c->x_part_class, &c->x_part_tile, &c->st_rowptr, &c->st_col, &c->st_h,
-                      &c->sr_w, &c->sr_mean, &c->sr_part, &c->sr_T, &c->sr_L, &c->sr_y,
+                      &c->sr_w, &c->sr_mean, &c->sr_part, &c->sr_T, &c->sr_y,
                       &c->groups_b, &c->ghash_b, &c->gsplit_b, &c->gid_b, &c->gsplit, &c->gbucket, &c->part_perm, &c->part_class, &c->part_tile,
                       &c->ar_keys[0], &c->ar_keys[1], &c->ar_l[0], &c->ar_l[1], &c->ar_T[0], &c->ar_T[1],
                       &c->ar_cl, &c->ar_cT, &c->ar_ck, &c->ar_ci, &c->ar_ck2, &c->ar_ci2, &c->ar_cnt,
@@ -1400,14 +1400,17 @@ int eloc_sr_select(eloc_ctx c, int64_t n, const eloc_c64* logpsi_dev, int n_sr, 
     if (!c) return ELOC_EINVAL;
     if (n < 1 || n >= (int64_t(1) << 31) || n_sr < 1 || n_sr > n || !logpsi_dev || !idx_dev)
         return fail(c, ELOC_EINVAL, "need 1 <= n_sr <= n < 2^31 and device pointers");
-    const int64_t tiles = radix_tiles(n);
-    ELOC_HIP(c, c->s_key.ensure(sizeof(uint64_t) * n));
-    ELOC_HIP(c, c->s_key2.ensure(sizeof(uint64_t) * n));
-    ELOC_HIP(c, c->s_val.ensure(sizeof(uint32_t) * n));
-    ELOC_HIP(c, c->s_val2.ensure(sizeof(uint32_t) * n));
-    ELOC_HIP(c, c->hist.ensure(sizeof(uint32_t) * 256 * tiles));
-    ELOC_HIP(c, c->hist_off.ensure(sizeof(int64_t) * (256 * tiles + 1)));
-    ELOC_HIP(c, c->hist_scratch.ensure(sizeof(int64_t) * scan_scratch_len(256 * tiles)));
+    const int64_t len = sr_select_scratch(n);
+    ELOC_HIP(c, c->s_key.ensure(sizeof(uint64_t) * len));
+    ELOC_HIP(c, c->s_key2.ensure(sizeof(uint64_t) * len));
+    ELOC_HIP(c, c->s_val.ensure(sizeof(uint32_t) * len));
+    ELOC_HIP(c, c->s_val2.ensure(sizeof(uint32_t) * len));
+    if (!sr_select_tournament(n, n_sr)) {
+        const int64_t tiles = radix_tiles(n);
+        ELOC_HIP(c, c->hist.ensure(sizeof(uint32_t) * 256 * tiles));
+        ELOC_HIP(c, c->hist_off.ensure(sizeof(int64_t) * (256 * tiles + 1)));
+        ELOC_HIP(c, c->hist_scratch.ensure(sizeof(int64_t) * scan_scratch_len(256 * tiles)));
+    }
     c->ut_valid = false;   // the sort scratch is shared with U's sorted copy
     ELOC_HIP(c, launch_sr_select(reinterpret_cast<const double2*>(logpsi_dev), n, n_sr, c->s_key.as<uint64_t>(),
                                  c->s_val.as<uint32_t>(), c->s_key2.as<uint64_t>(), c->s_val2.as<uint32_t>(),
@@ -1422,19 +1425,15 @@ int eloc_sr_solve(eloc_ctx c, int n_sr, int64_t n_params, const double* o_re_dev
     if (n_sr < 1 || n_sr > 256 || n_params < 1 || !(lambda > 0.0) || !std::isfinite(lambda))
         return fail(c, ELOC_EINVAL, "need 1 <= n_sr <= 256, n_params >= 1, finite lambda > 0");
     if (!o_re_dev || !o_im_dev || !logpsi_set_dev || !grad_dev || !d_dev) return fail(c, ELOC_EINVAL, "null pointer");
-    const int R = 2 * n_sr + 1;
-    const int64_t R16 = (R + 15) / 16 * 16;
-    const int64_t n = 2 * n_sr;
     ELOC_HIP(c, c->sr_w.ensure(sizeof(double) * 2 * n_sr));
     ELOC_HIP(c, c->sr_mean.ensure(sizeof(double) * 2 * n_params));
-    ELOC_HIP(c, c->sr_part.ensure(sizeof(double) * sr_partial_len(n_params, static_cast<int>(R16), R)));
-    ELOC_HIP(c, c->sr_T.ensure(sizeof(double) * R * R));
-    ELOC_HIP(c, c->sr_L.ensure(sizeof(double) * n * n));
-    ELOC_HIP(c, c->sr_y.ensure(sizeof(double) * n));
+    ELOC_HIP(c, c->sr_part.ensure(sizeof(double) * sr_partial_len(n_sr, n_params)));
+    ELOC_HIP(c, c->sr_T.ensure(sizeof(double) * sr_tile_len(n_sr)));
+    ELOC_HIP(c, c->sr_y.ensure(sizeof(double) * 2 * n_sr));
     ELOC_HIP(c, hipMemsetAsync(c->err_run.p, 0, sizeof(uint32_t), c->stream));
     ELOC_HIP(c, launch_sr_solve(n_sr, n_params, o_re_dev, o_im_dev, reinterpret_cast<const double2*>(logpsi_set_dev),
                                 grad_dev, lambda, c->sr_w.as<double>(), c->sr_mean.as<double>(), c->sr_part.as<double>(),
-                                c->sr_T.as<double>(), c->sr_L.as<double>(), c->sr_y.as<double>(), d_dev,
+                                c->sr_T.as<double>(), c->sr_y.as<double>(), d_dev,
                                 c->err_run.as<uint32_t>(), c->stream));
     return ELOC_OK;
 }

@@ -938,18 +938,21 @@ hipError_t launch_unique_scatter(int W, const uint64_t* sorted, int64_t n, const
 
 // Stochastic reconfiguration over the highest-probability samples: the
 // indices of the nsr largest Re log psi (descending, ties to the lower
-// index; sorts all n with the key scratch), and the shifted solve.
+// index), and the shifted solve.  Select scratch: key, val, key2, val2 of
+// sr_select_scratch(n) elements; the histograms of a sort of n where
+// sr_select_tournament says no.
+bool sr_select_tournament(int64_t n, int nsr);
+int64_t sr_select_scratch(int64_t n);
 hipError_t launch_sr_select(const double2* logpsi, int64_t n, int nsr, uint64_t* key, uint32_t* val, uint64_t* key2,
                             uint32_t* val2, uint32_t* hist, int64_t* hist_off, int64_t* scan, int32_t* out,
                             hipStream_t st);
-// Scratch: w[2 nsr], mean[2 np], partial[sr_partial_len(np, R16, R)] (per-block
-// Gram partials [sr_partial_blocks(np)][R16][R16], then the reduction passes)
-// (R16 = 2 nsr + 1 rounded up to 16), T[R][R], L[(2 nsr)^2], y[2 nsr].
+// Scratch: w[2 nsr], mean[2 np], partial[sr_partial_len(nsr, np)] (per-block
+// Gram tiles), T[sr_tile_len(nsr)] (their sum, factored in place), y[2 nsr].
 hipError_t launch_sr_solve(int nsr, int64_t np, const double* ore, const double* oim, const double2* logpsi,
                            const double* F, double lambda, double* w, double* mean, double* partial, double* T,
-                           double* L, double* y, double* d, uint32_t* err, hipStream_t st);
-int64_t sr_partial_blocks(int64_t np);
-int64_t sr_partial_len(int64_t np, int R16, int R);   // doubles of `partial`
+                           double* y, double* d, uint32_t* err, hipStream_t st);
+int64_t sr_partial_len(int nsr, int64_t np);   // doubles of `partial`
+int64_t sr_tile_len(int nsr);                  // doubles of `T`
 
 // Autoregressive sampling without replacement: the ansatz of per-qudit
 // perceptrons (hidden width 64) and one level of the Gumbel top-K search.
