@@ -97,8 +97,8 @@ struct eloc_ctx_s {
     // stochastic reconfiguration scratch
     DevBuf sr_w, sr_mean, sr_part, sr_T, sr_y;
     // sampler: two prefix beams, the candidates of a level, the allowed count
-    DevBuf ar_keys[2], ar_l[2], ar_T[2], ar_cl, ar_cT, ar_ck, ar_ci, ar_ck2, ar_ci2, ar_cnt;
-    DevBuf ar_hist, ar_sel, ar_keep, ar_off;   // top-K selection scratch
+    DevBuf ar_keys[2], ar_l[2], ar_T[2], ar_cl, ar_ck, ar_ci, ar_ck2, ar_ci2, ar_cnt;
+    DevBuf ar_state, ar_hist, ar_count, ar_off, ar_bk, ar_bi, ar_sk;   // top-K selection
 
     // stored pair list (CSR by row of (column, H_ij)), valid until the
     // samples or the Hamiltonian change
@@ -887,8 +887,8 @@ void eloc_destroy(eloc_ctx c) {
                       &c->sr_w, &c->sr_mean, &c->sr_part, &c->sr_T, &c->sr_y,
                       &c->groups_b, &c->ghash_b, &c->gsplit_b, &c->gid_b, &c->gsplit, &c->gbucket, &c->part_perm, &c->part_class, &c->part_tile,
                       &c->ar_keys[0], &c->ar_keys[1], &c->ar_l[0], &c->ar_l[1], &c->ar_T[0], &c->ar_T[1],
-                      &c->ar_cl, &c->ar_cT, &c->ar_ck, &c->ar_ci, &c->ar_ck2, &c->ar_ci2, &c->ar_cnt,
-                      &c->ar_hist, &c->ar_sel, &c->ar_keep, &c->ar_off,
+                      &c->ar_cl, &c->ar_ck, &c->ar_ci, &c->ar_ck2, &c->ar_ci2, &c->ar_cnt,
+                      &c->ar_state, &c->ar_hist, &c->ar_count, &c->ar_off, &c->ar_bk, &c->ar_bi, &c->ar_sk,
                       &c->jh_alist, &c->jh_amask, &c->jh_blist, &c->jh_bmask, &c->jh_bc, &c->jh_bo, &c->jh_ao, &c->jh_runs, &c->jh_gids,
                       &c->jh_place, &c->jh_sign, &c->jh_linear, &c->j_cross, &c->j_heavy, &c->j_heavy_slots, &c->j_core,
                       &c->j_key, &c->j_val, &c->j_key2, &c->j_val2, &c->j_hist, &c->j_hist_off, &c->j_hist_scan,
@@ -1451,85 +1451,117 @@ int eloc_sample(eloc_ctx c, const eloc_ar_model* m, int64_t k, uint64_t seed, ui
     if (M.n_up < 0 || M.n_down < 0) M.n_up = M.n_down = -1;
     const int N = m->n_qubits, W = (N + 63) / 64, D = m->qudit;
     const int Q = (N + D - 1) / D;
-    const int64_t maxc = k * (int64_t(1) << D);
+    // candidates of the largest level
+    int64_t maxc = 0, upper = 1;
+    for (int level = 0; level < Q; ++level) {
+        const int64_t n = upper << std::min(D, N - level * D);
+        maxc = std::max(maxc, n);
+        upper = std::min(k, n);
+    }
     for (int s = 0; s < 2; ++s) {
         ELOC_HIP(c, c->ar_keys[s].ensure(sizeof(uint64_t) * W * k));
         ELOC_HIP(c, c->ar_l[s].ensure(sizeof(double) * k));
         ELOC_HIP(c, c->ar_T[s].ensure(sizeof(double) * k));
     }
     ELOC_HIP(c, c->ar_cl.ensure(sizeof(double) * maxc));
-    ELOC_HIP(c, c->ar_cT.ensure(sizeof(double) * maxc));
     ELOC_HIP(c, c->ar_ck.ensure(sizeof(uint64_t) * maxc));
-    ELOC_HIP(c, c->ar_ci.ensure(sizeof(uint32_t) * maxc));
-    ELOC_HIP(c, c->ar_ck2.ensure(sizeof(uint64_t) * maxc));
-    ELOC_HIP(c, c->ar_ci2.ensure(sizeof(uint32_t) * maxc));
-    ELOC_HIP(c, c->ar_cnt.ensure(sizeof(unsigned long long)));
-    const int64_t tiles = radix_tiles(maxc);
-    ELOC_HIP(c, c->hist.ensure(sizeof(uint32_t) * 256 * tiles));
-    ELOC_HIP(c, c->hist_off.ensure(sizeof(int64_t) * (256 * tiles + 1)));
-    ELOC_HIP(c, c->hist_scratch.ensure(sizeof(int64_t) * std::max(scan_scratch_len(256 * tiles), scan_scratch_len(maxc))));
+    ELOC_HIP(c, c->ar_state.ensure(ar_state_bytes()));
     ELOC_HIP(c, c->ar_hist.ensure(sizeof(uint32_t) * 4096));
-    ELOC_HIP(c, c->ar_sel.ensure(sizeof(int64_t) * 4));
-    ELOC_HIP(c, c->ar_keep.ensure(sizeof(int32_t) * maxc));
-    ELOC_HIP(c, c->ar_off.ensure(sizeof(int64_t) * (maxc + 1)));
-    ELOC_HIP(c, launch_ar_root(c->ar_keys[0].as<uint64_t>(), W, c->ar_l[0].as<double>(), c->ar_T[0].as<double>(),
-                               c->stream));
+    ELOC_HIP(c, c->ar_count.ensure(sizeof(uint32_t) * ar_tiles(maxc)));
+    ELOC_HIP(c, c->ar_off.ensure(sizeof(int64_t) * ar_tiles(maxc)));
+    ELOC_HIP(c, c->ar_bk.ensure(sizeof(uint64_t) * ar_bound()));
+    ELOC_HIP(c, c->ar_bi.ensure(sizeof(uint32_t) * ar_bound()));
+    auto sort_room = [&](int64_t n) -> hipError_t {
+        const int64_t tiles = radix_tiles(n);
+        hipError_t e = c->hist.ensure(sizeof(uint32_t) * 256 * tiles);
+        if (e == hipSuccess) e = c->hist_off.ensure(sizeof(int64_t) * (256 * tiles + 1));
+        if (e == hipSuccess) e = c->hist_scratch.ensure(sizeof(int64_t) * scan_scratch_len(256 * tiles));
+        if (e == hipSuccess) e = c->ar_ck2.ensure(sizeof(uint64_t) * n);
+        if (e == hipSuccess) e = c->ar_ci.ensure(sizeof(uint32_t) * n);
+        if (e == hipSuccess) e = c->ar_ci2.ensure(sizeof(uint32_t) * n);
+        return e;
+    };
+    ELOC_HIP(c, sort_room(upper));
+    ELOC_HIP(c, c->ar_sk.ensure(sizeof(uint64_t) * upper));
+    ArScratch R{};
+    R.state = c->ar_state.as<ArState>();
+    for (int s = 0; s < 2; ++s) {
+        R.keys[s] = c->ar_keys[s].as<uint64_t>();
+        R.l[s] = c->ar_l[s].as<double>();
+        R.T[s] = c->ar_T[s].as<double>();
+    }
+    R.cand_l = c->ar_cl.as<double>();
+    R.cand_key = c->ar_ck.as<uint64_t>();
+    R.hist = c->ar_hist.as<uint32_t>();
+    R.cnt = c->ar_count.as<uint32_t>();
+    R.off = c->ar_off.as<int64_t>();
+    R.bkey = c->ar_bk.as<uint64_t>();
+    R.bidx = c->ar_bi.as<uint32_t>();
+    R.sort_key = c->ar_sk.as<uint64_t>();
+    R.sort_idx = c->ar_ci.as<uint32_t>();
+    // n pairs (key, idx) by key; `by` and `idx` come back sorted
+    auto sort = [&](uint64_t*& by, uint32_t*& idx, int64_t n) -> hipError_t {
+        int alt = 0;
+        uint64_t* other = c->ar_ck2.as<uint64_t>();
+        uint32_t* other_idx = c->ar_ci2.as<uint32_t>();
+        const hipError_t e = launch_radix_sort_pairs(by, idx, other, other_idx, n, 64, c->hist.as<uint32_t>(),
+                                                     c->hist_off.as<int64_t>(), c->hist_scratch.as<int64_t>(), &alt,
+                                                     c->stream);
+        if (alt) {
+            by = other;
+            idx = other_idx;
+        }
+        return e;
+    };
+    // all levels without a wait: the device knows the number of prefixes, the
+    // launches are sized for the largest
+    ELOC_HIP(c, launch_ar_root(R, W, c->stream));
     int cur = 0;
     int64_t B = 1;
     for (int level = 0; level < Q; ++level) {
-        const int Dk = std::min(D, N - level * D);
-        const int O = 1 << Dk;
-        const int64_t n = B * O;
-        ELOC_HIP(c, hipMemsetAsync(c->ar_cnt.p, 0, sizeof(unsigned long long), c->stream));
-        ELOC_HIP(c, launch_ar_level(M, level, B, seed, c->ar_keys[cur].as<uint64_t>(), c->ar_l[cur].as<double>(),
-                                    c->ar_T[cur].as<double>(), c->ar_cl.as<double>(), c->ar_cT.as<double>(),
-                                    c->ar_ck.as<uint64_t>(), c->ar_ci.as<uint32_t>(),
-                                    c->ar_cnt.as<unsigned long long>(), c->stream));
-        unsigned long long allowed = 0;
-        ELOC_HIP(c, hipMemcpyAsync(&allowed, c->ar_cnt.p, sizeof(allowed), hipMemcpyDeviceToHost, c->stream));
-        ELOC_HIP(c, hipStreamSynchronize(c->stream));
-        const int64_t Bn = std::min<int64_t>(k, static_cast<int64_t>(allowed));
-        if (Bn == 0) return ELOC_OK;   // no allowed state
-        // the first Bn candidates in (key, index) order: large levels sort
-        // only the candidates a two-digit selection keeps, small ones all
-        uint32_t* sorted = nullptr;
-        if (n >= (int64_t(1) << 16) && n > 4 * Bn) {
-            ELOC_HIP(c, launch_ar_select(c->ar_ck.as<uint64_t>(), n, Bn, c->ar_hist.as<uint32_t>(),
-                                         c->ar_sel.as<int64_t>(), c->ar_keep.as<int32_t>(), c->ar_off.as<int64_t>(),
-                                         c->hist_scratch.as<int64_t>(), c->ar_ck2.as<uint64_t>(),
-                                         c->ar_ci2.as<uint32_t>(), c->stream));
-            int64_t m = 0;
-            ELOC_HIP(c, hipMemcpyAsync(&m, c->ar_off.as<int64_t>() + n, sizeof(m), hipMemcpyDeviceToHost, c->stream));
-            ELOC_HIP(c, hipStreamSynchronize(c->stream));
-            if (m < Bn || m > n) return fail(c, ELOC_EHIP, "top-K selection kept " + std::to_string(m) + " candidates");
-            int alt = 0;
-            ELOC_HIP(c, launch_radix_sort_pairs(c->ar_ck2.as<uint64_t>(), c->ar_ci2.as<uint32_t>(),
-                                                c->ar_ck.as<uint64_t>(), c->ar_ci.as<uint32_t>(), m, 64,
-                                                c->hist.as<uint32_t>(), c->hist_off.as<int64_t>(),
-                                                c->hist_scratch.as<int64_t>(), &alt, c->stream));
-            sorted = alt ? c->ar_ci.as<uint32_t>() : c->ar_ci2.as<uint32_t>();
-        } else {
-            int alt = 0;
-            ELOC_HIP(c, launch_radix_sort_pairs(c->ar_ck.as<uint64_t>(), c->ar_ci.as<uint32_t>(),
-                                                c->ar_ck2.as<uint64_t>(), c->ar_ci2.as<uint32_t>(), n, 64,
-                                                c->hist.as<uint32_t>(), c->hist_off.as<int64_t>(),
-                                                c->hist_scratch.as<int64_t>(), &alt, c->stream));
-            sorted = alt ? c->ar_ci2.as<uint32_t>() : c->ar_ci.as<uint32_t>();
-        }
-        const int nxt = cur ^ 1;
-        ELOC_HIP(c, launch_ar_gather(c->ar_keys[cur].as<uint64_t>(), sorted,
-                                     Bn, O, W, level * D, c->ar_cl.as<double>(), c->ar_cT.as<double>(),
-                                     c->ar_keys[nxt].as<uint64_t>(), c->ar_l[nxt].as<double>(),
-                                     c->ar_T[nxt].as<double>(), c->stream));
-        cur = nxt;
-        B = Bn;
+        ELOC_HIP(c, launch_ar_level(M, level, B, k, seed, level + 1 == Q, R, cur, c->stream));
+        B = std::min(k, B << std::min(D, N - level * D));
+        cur ^= 1;
     }
-    ELOC_HIP(c, hipMemcpyAsync(keys_dev, c->ar_keys[cur].p, sizeof(uint64_t) * W * B, hipMemcpyDeviceToDevice, c->stream));
-    ELOC_HIP(c, hipMemcpyAsync(logp_dev, c->ar_l[cur].p, sizeof(double) * B, hipMemcpyDeviceToDevice, c->stream));
-    if (pert_dev)
-        ELOC_HIP(c, hipMemcpyAsync(pert_dev, c->ar_T[cur].p, sizeof(double) * B, hipMemcpyDeviceToDevice, c->stream));
-    ELOC_HIP(c, hipStreamSynchronize(c->stream));
-    *n_out_host = B;
+    ArResult res{};
+    ELOC_HIP(c, ar_read(R, Q, &res, c->stream));
+    if (res.B == 0) return ELOC_OK;   // no allowed state
+    if (!res.redo) {
+        uint64_t* by = R.sort_key;
+        uint32_t* idx = R.sort_idx;
+        ELOC_HIP(c, sort(by, idx, res.B));
+        ELOC_HIP(c, launch_ar_out(R, cur, by, idx, res.B, W, keys_dev, logp_dev, pert_dev, c->stream));
+        ELOC_HIP(c, ar_read(R, Q, &res, c->stream));
+    }
+    if (res.redo) {
+        // equal values: sort every level, so that they come in the order of
+        // the level before
+        ELOC_HIP(c, sort_room(maxc));
+        ELOC_HIP(c, launch_ar_root(R, W, c->stream));
+        cur = 0;
+        B = 1;
+        for (int level = 0; level < Q; ++level) {
+            ELOC_HIP(c, ar_set_prefixes(R, level, &B, c->stream));
+            const int64_t n = B << std::min(D, N - level * D);
+            uint32_t* idx = c->ar_ci.as<uint32_t>();
+            uint64_t* by = R.cand_key;
+            ELOC_HIP(c, launch_ar_candidates(M, level, B, seed, R, cur, idx, c->stream));
+            ELOC_HIP(c, ar_read(R, level + 1, &res, c->stream));
+            B = std::min(k, res.allowed);
+            if (B == 0) return ELOC_OK;
+            ELOC_HIP(c, sort(by, idx, n));
+            ELOC_HIP(c, launch_ar_gather(M, level, R, cur, by, idx, B, c->stream));
+            cur ^= 1;
+        }
+        ELOC_HIP(c, hipMemcpyAsync(keys_dev, R.keys[cur], sizeof(uint64_t) * W * B, hipMemcpyDeviceToDevice,
+                                   c->stream));
+        ELOC_HIP(c, hipMemcpyAsync(logp_dev, R.l[cur], sizeof(double) * B, hipMemcpyDeviceToDevice, c->stream));
+        if (pert_dev)
+            ELOC_HIP(c, hipMemcpyAsync(pert_dev, R.T[cur], sizeof(double) * B, hipMemcpyDeviceToDevice, c->stream));
+        ELOC_HIP(c, hipStreamSynchronize(c->stream));
+        res.B = B;
+    }
+    *n_out_host = res.B;
     return ELOC_OK;
 }
 

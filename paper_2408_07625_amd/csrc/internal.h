@@ -967,24 +967,46 @@ struct ArModelDev {
     const double* W3;   // [Q][2^qudit][64]
     const double* b3;   // [Q][2^qudit]
 };
-hipError_t launch_ar_root(uint64_t* keys, int W, double* l, double* T, hipStream_t st);
-// Candidates of level `level` for the B prefixes (keys, l, T): cand_* [B O],
-// O = 2^(qudit width); *n_allowed += the unmasked ones.
-hipError_t launch_ar_level(const ArModelDev& M, int level, int64_t B, uint64_t seed, const uint64_t* keys,
-                           const double* l, const double* T, double* cand_l, double* cand_T, uint64_t* cand_key,
-                           uint32_t* cand_idx, unsigned long long* n_allowed, hipStream_t st);
-hipError_t launch_ar_gather(const uint64_t* keys, const uint32_t* sorted_idx, int64_t n, int O, int W, int q0,
-                            const double* cand_l, const double* cand_T, uint64_t* out_keys, double* out_l, double* out_T,
-                            hipStream_t st);
-// The candidates that can be among the first `need` (1 <= need <= n) in
-// (key, index) order: every candidate whose 24-bit key prefix is at most the
-// need-th's, in index order, into okey / oidx (their count in off[n]).
-// Scratch: hist[4096] (digit totals), sel[4], keep[n], off[n + 1],
-// scan as for launch_scan_i32.
-int64_t ar_select_blocks(int64_t n);
-hipError_t launch_ar_select(const uint64_t* key, int64_t n, int64_t need, uint32_t* hist, int64_t* sel,
-                            int32_t* keep, int64_t* off, int64_t* scan, uint64_t* okey, uint32_t* oidx,
-                            hipStream_t st);
+struct ArState;   // a search's counts and selection, on the device
+struct ArScratch {
+    ArState* state;
+    uint64_t* keys[2];   // prefixes [K][W]
+    double* l[2];
+    double* T[2];
+    double* cand_l;      // candidates [K 2^qudit]
+    uint64_t* cand_key;
+    uint32_t* hist;      // [4096]
+    uint32_t* cnt;       // [ar_tiles(candidates)]
+    int64_t* off;        // as cnt
+    uint64_t* bkey;      // [ar_bound()]
+    uint32_t* bidx;
+    uint64_t* sort_key;  // the last level's [K]
+    uint32_t* sort_idx;
+};
+struct ArResult {
+    int64_t B;        // prefixes out of the level before
+    int64_t allowed;  // its unmasked candidates
+    bool redo;        // the levels have to be sorted
+};
+size_t ar_state_bytes();
+int64_t ar_tiles(int64_t n);
+int64_t ar_bound();
+hipError_t launch_ar_root(const ArScratch& R, int W, hipStream_t st);
+// Level `level` for at most B prefixes in buffer `cur`, its first K candidates
+// to the other one in index order; `last`: also sort_key, sort_idx.
+hipError_t launch_ar_level(const ArModelDev& M, int level, int64_t B, int64_t K, uint64_t seed, bool last,
+                           const ArScratch& R, int cur, hipStream_t st);
+hipError_t launch_ar_out(const ArScratch& R, int cur, const uint64_t* sorted_key, const uint32_t* sorted_idx,
+                         int64_t n, int W, uint64_t* out_keys, double* out_l, double* out_T, hipStream_t st);
+// The pieces of a level that is sorted: the candidates of B prefixes (cand_key,
+// cand_l, idx = 0, 1, ...), and the first n of the sorted ones as prefixes.
+hipError_t launch_ar_candidates(const ArModelDev& M, int level, int64_t B, uint64_t seed, const ArScratch& R, int cur,
+                                uint32_t* idx, hipStream_t st);
+hipError_t launch_ar_gather(const ArModelDev& M, int level, const ArScratch& R, int cur, const uint64_t* sorted_key,
+                            const uint32_t* sorted_idx, int64_t n, hipStream_t st);
+// What came out of level - 1 (waits for the stream), and the prefixes of `level` by hand.
+hipError_t ar_read(const ArScratch& R, int level, ArResult* out, hipStream_t st);
+hipError_t ar_set_prefixes(const ArScratch& R, int level, const int64_t* B, hipStream_t st);
 
 // Fixed workspace of the allocation-free forward pass (one per device).
 constexpr size_t kNoAllocBytes = size_t(64) << 20;

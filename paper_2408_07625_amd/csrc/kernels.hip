@@ -545,6 +545,13 @@ hipError_t scan_rec(const T* in, int64_t n, int64_t* out, int64_t* scratch, hipS
 constexpr int kSortItems = 8;
 constexpr int kSortTile = kBlock * kSortItems;
 
+// Up to this many tiles the scatter adds up the digits before its tile by
+// itself, from hist[tile][256]; past them the counts hist[256][tiles] go
+// through the scan.  2^16 pairs, 32 tiles: a pass of 22 us in five launches,
+// 16 in two; past some 64 tiles the sums cost what the scan's launches did.
+constexpr int64_t kSortFewTiles = 64;
+
+template <bool FEW>
 __global__ __launch_bounds__(kBlock) void k_radix_hist(const uint64_t* __restrict__ keys, int64_t n, int shift,
                                                        uint32_t* __restrict__ hist, int64_t tiles) {
     __shared__ uint32_t cnt[256];
@@ -557,13 +564,17 @@ __global__ __launch_bounds__(kBlock) void k_radix_hist(const uint64_t* __restric
         if (idx < n) atomicAdd(&cnt[(keys[idx] >> shift) & 255u], 1u);
     }
     __syncthreads();
-    hist[static_cast<int64_t>(threadIdx.x) * tiles + blockIdx.x] = cnt[threadIdx.x];
+    if constexpr (FEW)
+        hist[static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x] = cnt[threadIdx.x];
+    else
+        hist[static_cast<int64_t>(threadIdx.x) * tiles + blockIdx.x] = cnt[threadIdx.x];
 }
 
+template <bool FEW>
 __global__ __launch_bounds__(kBlock) void k_radix_scatter(const uint64_t* __restrict__ keys,
                                                           const uint32_t* __restrict__ vals, int64_t n,
-                                                          int shift, const int64_t* __restrict__ offs,
-                                                          int64_t tiles, uint64_t* __restrict__ okeys,
+                                                          int shift, const uint32_t* __restrict__ hist,
+                                                          const int64_t* __restrict__ offs, int64_t tiles, uint64_t* __restrict__ okeys,
                                                           uint32_t* __restrict__ ovals) {
     __shared__ uint32_t run[256];
     __shared__ uint32_t wcnt[kBlock / 64][256];
@@ -571,7 +582,28 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(const uint64_t* __rest
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     run[threadIdx.x] = 0;
-    base_off[threadIdx.x] = offs[static_cast<int64_t>(threadIdx.x) * tiles + blockIdx.x];
+    if constexpr (FEW) {
+        static_assert(kBlock == 256, "a digit a thread");
+        uint32_t before = 0, total = 0;
+#pragma unroll 8
+        for (int t = 0; t < static_cast<int>(tiles); ++t) {
+            const uint32_t c = hist[t * 256 + static_cast<int>(threadIdx.x)];
+            total += c;
+            before += t < static_cast<int>(blockIdx.x) ? c : 0u;
+        }
+        uint32_t upto = total;   // over the digits of this wave
+        for (int m = 1; m < 64; m <<= 1) {
+            const uint32_t v = __shfl_up(upto, m);
+            if (lane >= m) upto += v;
+        }
+        if (lane == 63) wcnt[0][wave] = upto;
+        __syncthreads();
+        for (int w = 0; w < wave; ++w) before += wcnt[0][w];
+        base_off[threadIdx.x] = before + upto - total;
+        __syncthreads();
+    } else {
+        base_off[threadIdx.x] = offs[static_cast<int64_t>(threadIdx.x) * tiles + blockIdx.x];
+    }
     for (int w = 0; w < kBlock / 64; ++w) wcnt[w][threadIdx.x] = 0;
     __syncthreads();
     const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
@@ -883,12 +915,18 @@ hipError_t launch_radix_sort_pairs(uint64_t* keys, uint32_t* vals, uint64_t* key
     uint32_t* vb = vals_alt;
     int flips = 0;
     for (int shift = 0; shift < end_bit; shift += 8) {
-        hipLaunchKernelGGL(k_radix_hist, dim3(static_cast<unsigned>(tiles)), dim3(kBlock), 0, st, ka, n, shift, hist,
-                           tiles);
-        hipError_t e = scan_rec<uint32_t>(hist, 256 * tiles, hist_off, scan_scratch, st);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(k_radix_scatter, dim3(static_cast<unsigned>(tiles)), dim3(kBlock), 0, st, ka, va, n, shift,
-                           hist_off, tiles, kb, vb);
+        const dim3 grid(static_cast<unsigned>(tiles)), block(kBlock);
+        if (tiles <= kSortFewTiles) {
+            hipLaunchKernelGGL(k_radix_hist<true>, grid, block, 0, st, ka, n, shift, hist, tiles);
+            hipLaunchKernelGGL(k_radix_scatter<true>, grid, block, 0, st, ka, va, n, shift, hist, hist_off, tiles, kb,
+                               vb);
+        } else {
+            hipLaunchKernelGGL(k_radix_hist<false>, grid, block, 0, st, ka, n, shift, hist, tiles);
+            const hipError_t e = scan_rec<uint32_t>(hist, 256 * tiles, hist_off, scan_scratch, st);
+            if (e != hipSuccess) return e;
+            hipLaunchKernelGGL(k_radix_scatter<false>, grid, block, 0, st, ka, va, n, shift, hist, hist_off, tiles, kb,
+                               vb);
+        }
         uint64_t* tk = ka; ka = kb; kb = tk;
         uint32_t* tv = va; va = vb; vb = tv;
         ++flips;

@@ -4,28 +4,34 @@
 // into qudits", "Global activation", "Local pruning strategy").
 //
 // One level per qudit k (D_k qubits, O_k = 2^D_k outcomes), for the B kept
-// prefixes:
-//   k_ar_level   a workgroup takes 64 prefixes; four waves evaluate the
+// prefixes, B and the selection's state on the device:
+//   k_ar_net     a workgroup takes 64 prefixes; four waves evaluate the
 //                qudit's perceptron for them with FP64 MFMA (16 x 16 tiles,
 //                v_mfma_f64_16x16x4f64): the prefix bits as +-1 inputs (0
 //                past the prefix) times W1, tanh; times W2 plus the first
-//                layer's output, tanh; times W3 -> the O_k outputs z, kept in
-//                LDS.  Then one wave per prefix, one lane per outcome: the
-//                mean shift of z, the mask of outcomes that cannot reach the
-//                electron targets, the normalised log p(c | prefix), l + log p,
-//                its Gumbel perturbation, the siblings' maximum Z and the
-//                conditioned value Ltil; a sort key (descending Ltil, masked
-//                outcomes last) and the candidate index b O_k + c.
-//   select       the first min(K, allowed) candidates in (key, index) order:
-//                for large levels, two 12-bit digit histograms of the keys
-//                (k_sel_hist, k_sel_pick) find the 24-bit key prefix that
-//                holds the K-th candidate, the candidates at or below it are
-//                compacted in index order (k_sel_flags, scan, k_sel_scatter)
-//                and only those are sorted; small levels sort all candidates.
-//                The sort is a stable radix sort on 64 bits, so equal values
-//                keep the (prefix, outcome) order either way.
-//   k_ar_gather  the first min(K, allowed) candidates become the next level's
-//                prefixes (key with the outcome's bits set, l, Ltil).
+//                layer's output, tanh; times W3 -> the O_k outputs z.
+//   k_ar_cand    one lane per (prefix, outcome): the mean shift of z, the mask
+//                of outcomes that cannot reach the electron targets, the
+//                normalised log p(c | prefix), l + log p, its Gumbel
+//                perturbation, the siblings' maximum Z and the conditioned
+//                value Ltil; a sort key (descending Ltil, masked outcomes
+//                last); the histogram of the keys' top 12 bits.
+//   select       the first min(K, allowed) candidates in (key, index) order as
+//                a set: the digit of the K-th (k_ar_pick), the next 12 bits
+//                within it (k_ar_hist, k_ar_pick), the candidates of that
+//                24-bit prefix ranked in one workgroup (k_ar_count, k_ar_cut).
+//   k_ar_emit    the selected candidates become the next level's prefixes
+//                (key with the outcome's bits set, l, Ltil), in index order.
+// Levels run one after another without a wait on the host.  At 2^16 prefixes
+// of 64 outcomes a level takes 200 us (net 77, cand 86, select and emit 40); with
+// the perceptrons and the candidates in one kernel (178), the selected ones
+// sorted (180) and two waits it took 500.
+// The last level's are sorted by key (a stable radix sort).  Sorting every
+// level gives the same set in the same order as long as no two kept values of
+// a level are equal: equal values come in the order of the level before, and a
+// value that ties at one level ties again at the next, as the best child of a
+// prefix keeps its value.  So a tie shows in the last sort, or at the cut of a
+// level; then the search runs again with every level sorted.
 #include "device.h"
 
 #include <hip/hip_runtime.h>
@@ -34,13 +40,28 @@
 
 namespace eloc {
 
+// State of a search on the device.  Slot `level`: the prefixes going into it,
+// and its unmasked candidates.
+constexpr int kArLevels = 128;
+constexpr int kArBound = 4096;      // candidates of the selected 24-bit prefix at most, past which all levels are sorted
+constexpr int kArTile = 4096;       // candidates of a counting workgroup
+struct ArState {
+    int64_t B[kArLevels + 1];
+    unsigned long long allowed[kArLevels];
+    uint32_t redo;          // a tie, or more candidates than kArBound in the selected prefix
+    uint32_t bound;         // candidates in the selected prefix
+    int64_t digit, before;  // top digit of the need-th candidate, candidates before that digit
+    int64_t prefix, below;  // its 24-bit prefix (1 << 24: all are kept), candidates below that
+    uint64_t cut_key;       // the last candidate kept of that prefix
+    uint32_t cut_idx;
+};
+
 namespace {
 
 typedef double d4 __attribute__((ext_vector_type(4)));
 
 constexpr int kArH = 64;        // hidden width
-constexpr int kArRows = 64;     // prefixes per workgroup
-constexpr int kArMaxOut = 64;   // outcomes per qudit (D <= 6)
+constexpr int64_t kArWide = 256 * 128;   // prefixes from which the workgroups of 16 waves are most of a round
 
 struct ArLevel {
     int N, W, D, Dk, O, level, q0;
@@ -64,21 +85,15 @@ __device__ __forceinline__ uint64_t mix64(uint64_t z) {
 // Standard Gumbel variable of the node (level, prefix, outcome): the
 // SplitMix64 output function chained over (seed, level, prefix words,
 // outcome), u from the top 53 bits, G = -log(-log u).
-__device__ __forceinline__ double gumbel(uint64_t seed, int level, const uint64_t* prefix, int W, int outcome) {
+__device__ __forceinline__ double gumbel(uint64_t seed, int level, const uint64_t (&prefix)[kMaxWords], int W,
+                                         int outcome) {
     uint64_t h = mix64(seed + 0x9E3779B97F4A7C15ull * static_cast<uint64_t>(level + 1));
-    for (int w = 0; w < W; ++w) h = mix64(h ^ prefix[w]);
+#pragma unroll
+    for (int w = 0; w < kMaxWords; ++w)
+        if (w < W) h = mix64(h ^ prefix[w]);
     h = mix64(h ^ static_cast<uint64_t>(outcome));
     const double u = (static_cast<double>(h >> 11) + 0.5) * 0x1.0p-53;
     return -log(-log(u));
-}
-
-__device__ __forceinline__ double wave_max(double v) {
-    for (int m = 32; m >= 1; m >>= 1) v = fmax(v, shfl_xor_d(v, m));
-    return v;
-}
-__device__ __forceinline__ double wave_add(double v) {
-    for (int m = 32; m >= 1; m >>= 1) v += shfl_xor_d(v, m);
-    return v;
 }
 
 // log(1 - exp(a)) for a < 0
@@ -115,23 +130,37 @@ __device__ __forceinline__ void tiles_mma(d4 (&acc)[NT], AF a_of, const double* 
     }
 }
 
-__global__ __launch_bounds__(256) void k_ar_level(ArLevel A, int64_t B, const uint64_t* __restrict__ keys,
-                                                  const double* __restrict__ lin, const double* __restrict__ Tin,
-                                                  double* __restrict__ cand_l, double* __restrict__ cand_T,
-                                                  uint64_t* __restrict__ cand_key, uint32_t* __restrict__ cand_idx,
-                                                  unsigned long long* __restrict__ n_allowed) {
-    __shared__ uint64_t kbuf[kArRows * kMaxWords];
-    __shared__ double h[kArRows][kArH + 1];   // h1, then h2, then z (per wave's own rows)
-    __shared__ double wb[kArMaxOut][kArH + 1];   // W2, then W3 ([out][in], padded rows)
+// Bound by the FP64 rate (2 q0 64 + 2 64 64 + 2 64 O multiply-adds and 128
+// tanh a prefix) and by how many waves a CU holds to fill its gaps, which the
+// LDS for a wave's hidden layer decides: the weights are staged 32 outputs at
+// a time, so that one workgroup of NW = 16 waves fits where two of 4 did.
+// Fewer prefixes than a round of such workgroups take NW = 4: more CUs.
+constexpr int kArHalf = 32;   // outputs of a staged part of the weights
+
+template <int NW>
+__global__ __launch_bounds__(64 * NW) void k_ar_net(ArLevel A, const ArState* __restrict__ S,
+                                                    const uint64_t* __restrict__ keys, double* __restrict__ zout) {
+    constexpr int kRows = 16 * NW;
+    extern __shared__ double lds[];
+    double (*const h)[kArH + 1] = reinterpret_cast<double (*)[kArH + 1]>(lds);              // [kRows]: h1, then h2
+    double (*const wb)[kArH + 1] = reinterpret_cast<double (*)[kArH + 1]>(h[kRows]);        // [kArHalf] ([out][in])
+    uint64_t* const kbuf = reinterpret_cast<uint64_t*>(wb[kArHalf]);                        // [kRows][W]
     const int wave = static_cast<int>(threadIdx.x) / 64;
     const int lane = lane_id();
-    const int64_t b0 = static_cast<int64_t>(blockIdx.x) * kArRows;
-    for (int e = threadIdx.x; e < kArRows * A.W; e += 256) {
+    const int64_t B = S->B[A.level];
+    const int64_t b0 = static_cast<int64_t>(blockIdx.x) * kRows;
+    if (b0 >= B) return;
+    for (int e = threadIdx.x; e < kRows * A.W; e += 64 * NW) {
         const int64_t b = min(b0 + e / A.W, B - 1);
         kbuf[e] = keys[b * A.W + e % A.W];
     }
-    __syncthreads();
+    auto stage = [&](const double* w, int from, int upto) {
+        __syncthreads();
+        for (int e = threadIdx.x; e < (upto - from) * kArH; e += 64 * NW) wb[e / kArH][e % kArH] = w[from * kArH + e];
+        __syncthreads();
+    };
     const int r0 = 16 * wave;   // this wave's row tile
+    __syncthreads();
     // layer 1: inputs +-1 for the prefix qubits (q < q0), 0 after
     {
         auto a_of = [&](int r, int q) -> double {
@@ -147,243 +176,451 @@ __global__ __launch_bounds__(256) void k_ar_level(ArLevel A, int64_t B, const ui
                 h[row][col] = tanh(acc[t][c] + A.b1[col]);
             }
     }
-    for (int e = threadIdx.x; e < kArH * kArH; e += 256) wb[e / kArH][e % kArH] = A.W2[e];
-    __syncthreads();
-    // layer 2 with the residual of layer 1
+    auto a_of = [&](int r, int k) -> double { return h[r0 + r][k]; };
+    // layer 2 with the residual of layer 1 (the wave's own rows of h: no
+    // workgroup has to wait for their change)
     {
-        auto a_of = [&](int r, int k) -> double { return h[r0 + r][k]; };
-        d4 acc[kArH / 16];
-        tiles_mma(acc, a_of, &wb[0][0], kArH + 1, kArH, kArH, kArH / 16, lane);
-        __syncthreads();
+        d4 acc[2][kArHalf / 16];
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            stage(A.W2, half * kArHalf, (half + 1) * kArHalf);
+            tiles_mma(acc[half], a_of, &wb[0][0], kArH + 1, kArHalf, kArH, kArHalf / 16, lane);
+        }
 #pragma unroll
         for (int t = 0; t < kArH / 16; ++t)
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
                 const int row = r0 + 4 * c + (lane >> 4), col = 16 * t + (lane & 15);
-                h[row][col] = tanh(acc[t][c] + A.b2[col] + h[row][col]);
+                h[row][col] = tanh(acc[t / 2][t % 2][c] + A.b2[col] + h[row][col]);
             }
     }
-    for (int e = threadIdx.x; e < A.O * kArH; e += 256) wb[e / kArH][e % kArH] = A.W3[e];
-    __syncthreads();
     // output layer: z for the O outcomes
-    {
-        auto a_of = [&](int r, int k) -> double { return h[r0 + r][k]; };
-        d4 acc[kArMaxOut / 16];
-        const int nt = (A.O + 15) / 16;
-        tiles_mma(acc, a_of, &wb[0][0], kArH + 1, A.O, kArH, nt, lane);
-        __syncthreads();
+    for (int from = 0; from < A.O; from += kArHalf) {
+        const int cols = min(kArHalf, A.O - from);
+        stage(A.W3, from, from + cols);
+        d4 acc[kArHalf / 16];
+        const int nt = (cols + 15) / 16;
+        tiles_mma(acc, a_of, &wb[0][0], kArH + 1, cols, kArH, nt, lane);
 #pragma unroll
-        for (int t = 0; t < kArMaxOut / 16; ++t) {
+        for (int t = 0; t < kArHalf / 16; ++t) {
             if (t >= nt) continue;
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-                const int row = r0 + 4 * c + (lane >> 4), col = 16 * t + (lane & 15);
-                if (col < A.O) h[row][col] = acc[t][c] + A.b3[col];
+                const int64_t b = b0 + r0 + 4 * c + (lane >> 4);
+                const int col = 16 * t + (lane & 15);
+                if (col < cols && b < B) zout[b * A.O + from + col] = acc[t][c] + A.b3[from + col];
             }
         }
     }
+}
+
+template <int NW>
+void launch_net(const ArLevel& A, int64_t B, const ArState* S, const uint64_t* keys, double* z, hipStream_t st) {
+    constexpr int kRows = 16 * NW;
+    const size_t lds = sizeof(double) * (kRows + kArHalf) * (kArH + 1) + sizeof(uint64_t) * kRows * A.W;
+    hipLaunchKernelGGL(k_ar_net<NW>, dim3(static_cast<unsigned>((B + kRows - 1) / kRows)), dim3(64 * NW), lds, st, A,
+                       S, keys, z);
+}
+
+// The key's value.
+__device__ __forceinline__ uint64_t key_of(double v) {
+    const uint64_t b = static_cast<uint64_t>(__double_as_longlong(v));
+    return ~((b >> 63) ? ~b : (b | (1ull << 63)));
+}
+__device__ __forceinline__ double value_of(uint64_t key) {
+    const uint64_t b = ~key;
+    return __longlong_as_double(static_cast<int64_t>((b >> 63) ? (b & ~(1ull << 63)) : ~b));
+}
+
+constexpr int kSelBuckets = 4096;
+
+// cand_l: z in, l + log p out.  One lane per candidate, a prefix in O
+// neighbouring lanes: bound by the eight transcendental functions a candidate,
+// so it runs apart from the perceptrons, whose LDS lets in two waves a SIMD.
+// hist += the top 12 bits of the unmasked keys (they are the exponent: a few
+// values, counted by wave).
+__global__ __launch_bounds__(256) void k_ar_cand(ArLevel A, ArState* __restrict__ S, const uint64_t* __restrict__ keys,
+                                                 const double* __restrict__ lin, const double* __restrict__ Tin,
+                                                 double* __restrict__ cand_l, uint64_t* __restrict__ cand_key,
+                                                 uint32_t* __restrict__ hist) {
+    __shared__ uint32_t cnt[kSelBuckets];
+    __shared__ unsigned long long total;
+    const int lane = lane_id();
+    if (hist)
+        for (int t = threadIdx.x; t < kSelBuckets; t += 256) cnt[t] = 0u;
+    if (threadIdx.x == 0) total = 0;
     __syncthreads();
-    // per prefix: one wave, one lane per outcome
-    unsigned long long allowed_total = 0;
-    for (int r = wave; r < kArRows; r += 4) {
-        const int64_t b = b0 + r;
-        if (b >= B) break;   // wave-uniform
-        const uint64_t* key = kbuf + r * A.W;
-        const bool live = lane < A.O;
-        const double z = live ? h[r][lane] : 0.0;
-        const double mean = wave_add(z) / A.O;
-        const double a = 2.0 * (z - mean);
+    const int sh = A.Dk;
+    const int64_t n = S->B[A.level] << sh;
+    const int c = static_cast<int>(threadIdx.x) & (A.O - 1);
+    unsigned long long allowed = 0;
+    for (int64_t i0 = static_cast<int64_t>(blockIdx.x) * 256; i0 < n; i0 += static_cast<int64_t>(gridDim.x) * 256) {
+        const int64_t i = i0 + threadIdx.x;
+        const bool live = i < n;
+        const int64_t b = min(i, n - 1) >> sh;
+        const double z = live ? cand_l[i] : 0.0;
+        double sum = z;
+        for (int m = A.O / 2; m >= 1; m >>= 1) sum += shfl_xor_d(sum, m);
+        const double a = 2.0 * (z - sum / A.O);
+        uint64_t key[kMaxWords];
+#pragma unroll
+        for (int w = 0; w < kMaxWords; ++w) key[w] = w < A.W ? keys[b * A.W + w] : 0ull;
         bool ok = live;
-        if (A.n_up >= 0 && live) {
+        if (A.n_up >= 0) {
             // electrons of the prefix: even qubits spin up, odd spin down
             // (word boundaries are even, so a bit's parity is its qubit's)
             int up = 0, dn = 0;
-            for (int w = 0; w < A.W && 64 * w < A.q0; ++w) {
-                const int nb = A.q0 - 64 * w;
+#pragma unroll
+            for (int w = 0; w < kMaxWords; ++w) {
+                const int nb = min(max(A.q0 - 64 * w, 0), 64);
                 const uint64_t v = key[w] & (nb >= 64 ? ~0ull : ((1ull << nb) - 1ull));
                 up += __popcll(v & kEven);
                 dn += __popcll(v & kOdd);
             }
-            for (int t = 0; t < A.Dk; ++t)
-                if ((lane >> t) & 1) {
-                    if ((A.q0 + t) & 1)
-                        ++dn;
-                    else
-                        ++up;
-                }
-            ok = up <= A.n_up && A.n_up <= up + A.rest_up && dn <= A.n_down && A.n_down <= dn + A.rest_down;
+            const uint64_t mine = static_cast<uint64_t>(c) << (A.q0 & 1);
+            up += __popcll(mine & kEven);
+            dn += __popcll(mine & kOdd);
+            ok = ok && up <= A.n_up && A.n_up <= up + A.rest_up && dn <= A.n_down && A.n_down <= dn + A.rest_down;
         }
-        const double m = wave_max(ok ? a : -INFINITY);
-        const double s = wave_add(ok ? exp(a - m) : 0.0);
-        const double lc = lin[b] + (a - (m + log(s)));
-        const double Lp = lc + gumbel(A.seed, A.level, key, A.W, lane);
-        const double Z = wave_max(ok ? Lp : -INFINITY);
+        double mx = ok ? a : -INFINITY;
+        for (int m = A.O / 2; m >= 1; m >>= 1) mx = fmax(mx, shfl_xor_d(mx, m));
+        double s = ok ? exp(a - mx) : 0.0;
+        for (int m = A.O / 2; m >= 1; m >>= 1) s += shfl_xor_d(s, m);
+        const double lc = lin[b] + (a - (mx + log(s)));
+        const double Lp = lc + gumbel(A.seed, A.level, key, A.W, c);
+        double Z = ok ? Lp : -INFINITY;
+        for (int m = A.O / 2; m >= 1; m >>= 1) Z = fmax(Z, shfl_xor_d(Z, m));
         const double T = Tin[b];
         double Lt = T;
         if (ok && Lp < Z) {
             const double v = T - Lp + log1mexp(Lp - Z);
             Lt = T - (fmax(v, 0.0) + log1p(exp(-fabs(v))));
         }
-        const int64_t i = b * A.O + lane;
+        const uint64_t k = ok ? key_of(Lt) : ~0ull;
         if (live) {
-            uint64_t bits = static_cast<uint64_t>(__double_as_longlong(Lt));
-            bits = (bits >> 63) ? ~bits : (bits | (1ull << 63));
-            cand_key[i] = ok ? ~bits : ~0ull;
-            cand_idx[i] = static_cast<uint32_t>(i);
+            cand_key[i] = k;
             cand_l[i] = lc;
-            cand_T[i] = Lt;
         }
-        allowed_total += static_cast<unsigned long long>(__popcll(__ballot(ok)));
+        uint64_t left = __ballot(ok);
+        allowed += static_cast<unsigned long long>(__popcll(left));
+        if (hist) {
+            const int d = static_cast<int>(k >> 52);
+            while (left) {
+                const int first = __ffsll(static_cast<unsigned long long>(left)) - 1;
+                const int fd = __builtin_amdgcn_readlane(d, first);
+                const uint64_t same = __ballot(ok && d == fd) & left;
+                if (lane == first) atomicAdd(&cnt[fd], static_cast<uint32_t>(__popcll(same)));
+                left &= ~same;
+            }
+        }
     }
-    if (lane == 0 && allowed_total) atomicAdd(n_allowed, allowed_total);
+    if (lane == 0 && allowed) atomicAdd(&total, allowed);
+    __syncthreads();
+    if (threadIdx.x == 0 && total) atomicAdd(&S->allowed[A.level], total);
+    if (hist)
+        for (int t = threadIdx.x; t < kSelBuckets; t += 256)
+            if (cnt[t]) atomicAdd(hist + t, cnt[t]);
 }
 
-__global__ void k_ar_gather(const uint64_t* __restrict__ keys, const uint32_t* __restrict__ sorted_idx, int64_t n,
-                            int O, int W, int q0, const double* __restrict__ cand_l, const double* __restrict__ cand_T,
-                            uint64_t* __restrict__ out_keys, double* __restrict__ out_l, double* __restrict__ out_T) {
+__global__ void k_ar_iota(uint32_t* __restrict__ idx, int64_t n) {
     const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-    if (i >= n) return;
-    const uint32_t idx = sorted_idx[i];
+    if (i < n) idx[i] = static_cast<uint32_t>(i);
+}
+
+// The next level's prefix of candidate idx.
+__device__ __forceinline__ void child_key(const uint64_t* __restrict__ keys, int64_t idx, int O, int W, int q0,
+                                          uint64_t* __restrict__ out) {
     const int64_t b = idx / O;
-    const uint64_t c = idx % O;
+    const uint64_t c = static_cast<uint64_t>(idx % O);
     for (int w = 0; w < W; ++w) {
         uint64_t v = keys[b * W + w];
         const int lo = q0 - 64 * w;
         if (lo >= 0 && lo < 64) v |= c << lo;
         if (lo < 0 && lo > -64) v |= c >> (-lo);
-        out_keys[i * W + w] = v;
+        out[w] = v;
     }
-    out_l[i] = cand_l[idx];
-    out_T[i] = cand_T[idx];
 }
 
-__global__ void k_ar_root(uint64_t* keys, int W, double* l, double* T) {
-    if (threadIdx.x < W) keys[threadIdx.x] = 0;
-    if (threadIdx.x == 0) {
+// The first n sorted candidates as prefixes.
+__global__ void k_ar_gather(const uint64_t* __restrict__ keys, const uint64_t* __restrict__ sorted_key,
+                            const uint32_t* __restrict__ sorted_idx, int64_t n, int O, int W, int q0,
+                            const double* __restrict__ cand_l, uint64_t* __restrict__ out_keys,
+                            double* __restrict__ out_l, double* __restrict__ out_T) {
+    const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+    if (i >= n) return;
+    const uint32_t idx = sorted_idx[i];
+    child_key(keys, idx, O, W, q0, out_keys + i * W);
+    out_l[i] = cand_l[idx];
+    out_T[i] = value_of(sorted_key[i]);
+}
+
+__global__ __launch_bounds__(1024) void k_ar_root(ArState* __restrict__ S, uint32_t* __restrict__ hist, uint64_t* keys,
+                                                  int W, double* l, double* T) {
+    const int t = static_cast<int>(threadIdx.x);
+    for (int q = t; q < kSelBuckets; q += 1024) hist[q] = 0u;
+    for (int q = t; q < kArLevels; q += 1024) S->allowed[q] = 0ull;
+    if (t < W) keys[t] = 0;
+    if (t == 0) {
+        S->B[0] = 1;
+        S->redo = 0u;
+        S->bound = 0u;
         l[0] = 0.0;
         T[0] = 0.0;
     }
 }
 
-// Top-K selection.  Histogram of the 12-bit digit (key >> shift) & 4095
-// over the candidates whose key agrees above the digit with the digit chosen
-// by the previous pass (prev[0]; all candidates for the top digit, shift
-// 52): per block in LDS, then its non-zero counts added to total[4096]
-// (integer counts: the order of the additions does not matter).
-constexpr int kSelBuckets = 4096;
-constexpr int kSelPerBlock = 16384;
-
-__global__ __launch_bounds__(256) void k_sel_hist(const uint64_t* __restrict__ key, int64_t n, int shift,
-                                                  const int64_t* __restrict__ prev, uint32_t* __restrict__ total) {
-    __shared__ uint32_t h[kSelBuckets];
-    for (int t = threadIdx.x; t < kSelBuckets; t += 256) h[t] = 0u;
-    __syncthreads();
-    const bool filt = shift + 12 < 64;
-    const uint64_t prefix = filt ? static_cast<uint64_t>(prev[0]) : 0ull;
-    const int64_t i0 = static_cast<int64_t>(blockIdx.x) * kSelPerBlock;
-    const int64_t i1 = min(n, i0 + kSelPerBlock);
-    for (int64_t i = i0 + threadIdx.x; i < i1; i += 256) {
-        const uint64_t k = key[i];
-        if (!filt || (k >> (shift + 12)) == prefix) atomicAdd(&h[(k >> shift) & (kSelBuckets - 1)], 1u);
-    }
-    __syncthreads();
-    for (int t = threadIdx.x; t < kSelBuckets; t += 256)
-        if (h[t]) atomicAdd(total + t, h[t]);
-}
-
-__global__ void k_sel_clear(uint32_t* __restrict__ total) {
-    for (int t = threadIdx.x; t < kSelBuckets; t += blockDim.x) total[t] = 0u;
-}
-
-// The digit in which the running count over ascending digits reaches `need`
-// = need_total - prev[1] (the candidates before the previous pass's digit):
-// sel[0] = the digit, sel[1] = the candidates before it over both passes.
-// One workgroup, four digits per thread; need >= 1 and at most the total.
-// The totals are cleared for the next pass as they are read.
-__global__ __launch_bounds__(1024) void k_sel_pick(uint32_t* __restrict__ total, int64_t need_total,
-                                                   const int64_t* __restrict__ prev, int64_t* __restrict__ sel) {
-    __shared__ int64_t part[1024];
+// Where the need of a level, min(K, allowed), falls among the 4096 digits of
+// `total`, which is cleared for the next user.  FIRST: the top digit, and B of
+// the next level; else the 24-bit prefix.  One workgroup, four digits a thread.
+template <bool FIRST>
+__global__ __launch_bounds__(1024) void k_ar_pick(ArState* __restrict__ S, int level, int64_t K,
+                                                  uint32_t* __restrict__ total) {
+    __shared__ int64_t part[16];
     const int t = static_cast<int>(threadIdx.x);
-    int64_t c[4];
+    const int64_t allowed = static_cast<int64_t>(S->allowed[level]);
+    const int64_t all_need = min(K, allowed);
+    const bool all = all_need == allowed;
+    if (FIRST && t == 0) S->B[level + 1] = all_need;
+    if (!FIRST && t == 0) S->bound = 0u;
+    int64_t c[4], mine = 0;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         c[q] = total[4 * t + q];
         total[4 * t + q] = 0u;
+        mine += c[q];
     }
-    part[t] = c[0] + c[1] + c[2] + c[3];
+    if (all) {
+        if (t == 0) {
+            S->prefix = 1 << 24;
+            S->below = all_need;
+        }
+        return;
+    }
+    int64_t upto = mine;
+    for (int m = 1; m < 64; m <<= 1) {
+        const int64_t v = __shfl_up(static_cast<long long>(upto), m);
+        if ((t & 63) >= m) upto += v;
+    }
+    if ((t & 63) == 63) part[t / 64] = upto;
     __syncthreads();
-    for (int off = 1; off < 1024; off <<= 1) {
-        const int64_t v = t >= off ? part[t - off] : 0;
-        __syncthreads();
-        part[t] += v;
-        __syncthreads();
-    }
-    const int64_t base = prev ? prev[1] : 0;
-    const int64_t need = need_total - base;
-    const int64_t before = t ? part[t - 1] : 0;
-    if (before < need && need <= part[t]) {
-        int64_t run = before;
+    int64_t run = upto - mine;
+    for (int w = 0; w < t / 64; ++w) run += part[w];
+    const int64_t base = FIRST ? 0 : S->before;
+    const int64_t need = all_need - base;
+    if (run < need && need <= run + mine) {
         int q = 0;
         for (; q < 3; ++q) {
             if (run + c[q] >= need) break;
             run += c[q];
         }
-        sel[0] = 4 * t + q;
-        sel[1] = base + run;
+        if (FIRST) {
+            S->digit = 4 * t + q;
+            S->before = run;
+        } else {
+            S->prefix = (S->digit << 12) | (4 * t + q);
+            S->below = base + run;
+        }
     }
 }
 
-// keep[i] = 1 for the candidates whose 24-bit key prefix is at most the
-// selected one (sel1: top digit, sel2: next digit).
-__global__ void k_sel_flags(const uint64_t* __restrict__ key, int64_t n, const int64_t* __restrict__ sel1,
-                            const int64_t* __restrict__ sel2, int32_t* __restrict__ keep) {
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-    if (i >= n) return;
-    const uint64_t thr = (static_cast<uint64_t>(sel1[0]) << 12) | static_cast<uint64_t>(sel2[0]);
-    keep[i] = (key[i] >> 40) <= thr ? 1 : 0;
+// The next 12 bits of the keys with the selected top digit: per workgroup in
+// LDS, then its non-zero counts added to total (the order of integer additions
+// does not matter).
+__global__ __launch_bounds__(1024) void k_ar_hist(const ArState* __restrict__ S, int level, int sh, int64_t K,
+                                                 const uint64_t* __restrict__ key, uint32_t* __restrict__ total) {
+    __shared__ uint32_t h[kSelBuckets];
+    const int64_t n = S->B[level] << sh;
+    if (static_cast<int64_t>(S->allowed[level]) <= K) return;
+    for (int t = threadIdx.x; t < kSelBuckets; t += 1024) h[t] = 0u;
+    __syncthreads();
+    const uint64_t digit = static_cast<uint64_t>(S->digit);
+    const int64_t step = static_cast<int64_t>(gridDim.x) * 1024;
+#pragma unroll 4
+    for (int64_t i = static_cast<int64_t>(blockIdx.x) * 1024 + threadIdx.x; i < n; i += step) {
+        const uint64_t k = key[i];
+        if ((k >> 52) == digit && k != ~0ull) atomicAdd(&h[(k >> 40) & (kSelBuckets - 1)], 1u);
+    }
+    __syncthreads();
+    for (int t = threadIdx.x; t < kSelBuckets; t += 1024)
+        if (h[t]) atomicAdd(total + t, h[t]);
 }
 
-// The kept candidates, in index order, with their candidate index.
-__global__ void k_sel_scatter(const uint64_t* __restrict__ key, int64_t n, const int32_t* __restrict__ keep,
-                              const int64_t* __restrict__ off, uint64_t* __restrict__ okey,
-                              uint32_t* __restrict__ oidx) {
+// cnt[tile] = the candidates below the selected prefix; those of the prefix to
+// the list (in any order).
+__global__ __launch_bounds__(256) void k_ar_count(ArState* __restrict__ S, int level, int sh,
+                                                  const uint64_t* __restrict__ key, uint32_t* __restrict__ cnt,
+                                                  uint64_t* __restrict__ bkey, uint32_t* __restrict__ bidx) {
+    __shared__ uint32_t total;
+    if (threadIdx.x == 0) total = 0u;
+    __syncthreads();
+    const int64_t n = S->B[level] << sh;
+    const uint64_t prefix = static_cast<uint64_t>(S->prefix);
+    const int64_t base = static_cast<int64_t>(blockIdx.x) * kArTile;
+    if (base >= n) return;
+    uint32_t below = 0;
+#pragma unroll
+    for (int j = 0; j < kArTile / 256; ++j) {
+        const int64_t i = base + j * 256 + threadIdx.x;
+        const uint64_t k = i < n ? key[i] : ~0ull;
+        below += static_cast<uint32_t>(__popcll(__ballot((k >> 40) < prefix && k != ~0ull)));
+        if ((k >> 40) == prefix && k != ~0ull) {
+            const uint32_t at = atomicAdd(&S->bound, 1u);
+            if (at < kArBound) {
+                bkey[at] = k;
+                bidx[at] = static_cast<uint32_t>(i);
+            }
+        }
+    }
+    if (lane_id() == 0) atomicAdd(&total, below);
+    __syncthreads();
+    if (threadIdx.x == 0) cnt[blockIdx.x] = total;
+}
+
+// The first need - below of the list by (key, index): the last of them is the
+// cut, each counts for its tile; then cnt becomes the tiles' offsets.  One
+// workgroup.
+__global__ __launch_bounds__(1024) void k_ar_cut(ArState* __restrict__ S, int level, int sh,
+                                                 const uint64_t* __restrict__ bkey, const uint32_t* __restrict__ bidx,
+                                                 uint32_t* __restrict__ cnt, int64_t* __restrict__ off) {
+    __shared__ uint64_t k[kArBound];
+    __shared__ uint32_t v[kArBound];
+    __shared__ uint64_t last, first_out;
+    __shared__ int64_t part[16];
+    const int t = static_cast<int>(threadIdx.x);
+    const bool all = S->prefix == (1 << 24);
+    const int64_t need = S->B[level + 1];
+    const int64_t n = S->B[level] << sh;
+    const uint32_t found = all ? 0u : S->bound;
+    const int m = static_cast<int>(min(found, static_cast<uint32_t>(kArBound)));
+    const int64_t r = need - S->below;
+    if (t == 0) {
+        last = 0ull;
+        first_out = ~0ull;
+        if (found > kArBound) S->redo = 1u;
+    }
+    for (int e = t; e < m; e += 1024) {
+        k[e] = bkey[e];
+        v[e] = bidx[e];
+    }
+    __syncthreads();
+    for (int e = t; e < m; e += 1024) {
+        const uint64_t ek = k[e];
+        const uint32_t ei = v[e];
+        int64_t rank = 0;
+        for (int q = 0; q < m; ++q) rank += (k[q] < ek) | ((k[q] == ek) & (v[q] < ei));
+        if (rank < r) atomicAdd(cnt + ei / kArTile, 1u);
+        if (rank == r - 1) {
+            S->cut_key = ek;
+            S->cut_idx = ei;
+            last = ek;
+        }
+        if (rank == r) first_out = ek;
+    }
+    __threadfence();
+    __syncthreads();
+    if (t == 0 && m && last == first_out) S->redo = 1u;
+    const int64_t tiles = (n + kArTile - 1) / kArTile;
+    int64_t base = 0;
+    for (int64_t t0 = 0; t0 < tiles; t0 += 1024) {
+        const int64_t mine = t0 + t < tiles
+                                 ? static_cast<int64_t>(__hip_atomic_load(cnt + t0 + t, __ATOMIC_RELAXED,
+                                                                          __HIP_MEMORY_SCOPE_AGENT))
+                                 : 0;
+        int64_t upto = mine;
+        for (int q = 1; q < 64; q <<= 1) {
+            const int64_t u = __shfl_up(static_cast<long long>(upto), q);
+            if ((t & 63) >= q) upto += u;
+        }
+        if ((t & 63) == 63) part[t / 64] = upto;
+        __syncthreads();
+        int64_t before = base;
+        for (int w = 0; w < 16; ++w) {
+            if (w < t / 64) before += part[w];
+            base += part[w];
+        }
+        if (t0 + t < tiles) off[t0 + t] = before + upto - mine;
+        __syncthreads();
+    }
+}
+
+// The kept candidates, in index order, as the next level's prefixes; at the
+// last level also their keys and places for the sort.
+__global__ __launch_bounds__(256) void k_ar_emit(const ArState* __restrict__ S, ArLevel A,
+                                                 const uint64_t* __restrict__ key, const double* __restrict__ cand_l,
+                                                 const int64_t* __restrict__ off, const uint64_t* __restrict__ keys,
+                                                 int64_t K, uint64_t* __restrict__ out_keys, double* __restrict__ out_l,
+                                                 double* __restrict__ out_T, uint64_t* __restrict__ out_key,
+                                                 uint32_t* __restrict__ out_idx) {
+    constexpr int kPer = kArTile / 256;
+    __shared__ uint32_t part[kPer * 4];
+    const int64_t n = S->B[A.level] << A.Dk;
+    const int64_t base = static_cast<int64_t>(blockIdx.x) * kArTile;
+    if (base >= n) return;
+    const uint64_t prefix = static_cast<uint64_t>(S->prefix);
+    const uint64_t ck = S->cut_key;
+    const uint32_t ci = S->cut_idx;
+    const int wave = static_cast<int>(threadIdx.x) / 64, lane = lane_id();
+    uint64_t k[kPer];
+    uint32_t keep = 0, before[kPer];
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        const int64_t i = base + j * 256 + threadIdx.x;
+        k[j] = i < n ? key[i] : ~0ull;
+        const bool in = k[j] != ~0ull &&
+                        ((k[j] >> 40) < prefix ||
+                         ((k[j] >> 40) == prefix && (k[j] < ck || (k[j] == ck && static_cast<uint32_t>(i) <= ci))));
+        const uint64_t bal = __ballot(in);
+        before[j] = static_cast<uint32_t>(__popcll(bal & ((1ull << lane) - 1ull)));
+        keep |= (in ? 1u : 0u) << j;
+        if (lane == 0) part[4 * j + wave] = static_cast<uint32_t>(__popcll(bal));
+    }
+    __syncthreads();
+    if (wave == 0) {
+        static_assert(kPer * 4 == 64, "a part a lane");
+        const uint32_t mine = part[lane];
+        uint32_t upto = mine;
+        for (int q = 1; q < 64; q <<= 1) {
+            const uint32_t u = __shfl_up(upto, q);
+            if (lane >= q) upto += u;
+        }
+        part[lane] = upto - mine;
+    }
+    __syncthreads();
+    const int64_t at0 = off[blockIdx.x];
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        if (!((keep >> j) & 1u)) continue;
+        const int64_t i = base + j * 256 + threadIdx.x;
+        const int64_t at = at0 + part[4 * j + wave] + before[j];
+        if (at >= K) continue;   // only past a selection that is run again
+        child_key(keys, i, A.O, A.W, A.q0, out_keys + at * A.W);
+        out_l[at] = cand_l[i];
+        out_T[at] = value_of(k[j]);
+        if (out_key) {
+            out_key[at] = k[j];
+            out_idx[at] = static_cast<uint32_t>(at);
+        }
+    }
+}
+
+// The samples in sorted order to the caller; equal neighbours ask for the sorted search.
+__global__ void k_ar_out(ArState* __restrict__ S, const uint64_t* __restrict__ sorted_key,
+                         const uint32_t* __restrict__ sorted_idx, int64_t n, int W, const uint64_t* __restrict__ keys,
+                         const double* __restrict__ l, uint64_t* __restrict__ out_keys, double* __restrict__ out_l,
+                         double* __restrict__ out_T) {
     const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-    if (i >= n || !keep[i]) return;
-    okey[off[i]] = key[i];
-    oidx[off[i]] = static_cast<uint32_t>(i);
+    if (i >= n) return;
+    const uint32_t idx = sorted_idx[i];
+    const uint64_t k = sorted_key[i];
+    if (i + 1 < n && sorted_key[i + 1] == k) S->redo = 1u;
+    for (int w = 0; w < W; ++w) out_keys[i * W + w] = keys[static_cast<int64_t>(idx) * W + w];
+    out_l[i] = l[idx];
+    if (out_T) out_T[i] = value_of(k);
 }
 
 inline unsigned blocks256(int64_t n) { return static_cast<unsigned>((n + 255) / 256); }
 
-}  // namespace
-
-int64_t ar_select_blocks(int64_t n) { return (n + kSelPerBlock - 1) / kSelPerBlock; }
-
-hipError_t launch_ar_select(const uint64_t* key, int64_t n, int64_t need, uint32_t* hist, int64_t* sel,
-                            int32_t* keep, int64_t* off, int64_t* scan, uint64_t* okey, uint32_t* oidx,
-                            hipStream_t st) {
-    const int nb = static_cast<int>(ar_select_blocks(n));
-    uint32_t* total = hist;
-    hipLaunchKernelGGL(k_sel_clear, dim3(1), dim3(1024), 0, st, total);
-    hipLaunchKernelGGL(k_sel_hist, dim3(nb), dim3(256), 0, st, key, n, 52, static_cast<const int64_t*>(nullptr), total);
-    hipLaunchKernelGGL(k_sel_pick, dim3(1), dim3(1024), 0, st, total, need, static_cast<const int64_t*>(nullptr), sel);
-    hipLaunchKernelGGL(k_sel_hist, dim3(nb), dim3(256), 0, st, key, n, 40, sel, total);
-    hipLaunchKernelGGL(k_sel_pick, dim3(1), dim3(1024), 0, st, total, need, sel, sel + 2);
-    hipLaunchKernelGGL(k_sel_flags, dim3(blocks256(n)), dim3(256), 0, st, key, n, sel, sel + 2, keep);
-    const hipError_t e = launch_scan_i32(keep, n, off, scan, st);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_sel_scatter, dim3(blocks256(n)), dim3(256), 0, st, key, n, keep, off, okey, oidx);
-    return hipGetLastError();
-}
-
-hipError_t launch_ar_root(uint64_t* keys, int W, double* l, double* T, hipStream_t st) {
-    hipLaunchKernelGGL(k_ar_root, dim3(1), dim3(64), 0, st, keys, W, l, T);
-    return hipGetLastError();
-}
-
-hipError_t launch_ar_level(const ArModelDev& M, int level, int64_t B, uint64_t seed, const uint64_t* keys,
-                           const double* l, const double* T, double* cand_l, double* cand_T, uint64_t* cand_key,
-                           uint32_t* cand_idx, unsigned long long* n_allowed, hipStream_t st) {
+ArLevel level_of(const ArModelDev& M, int level, uint64_t seed) {
     ArLevel A;
     A.N = M.n_qubits;
     A.W = (M.n_qubits + 63) / 64;
@@ -410,18 +647,92 @@ hipError_t launch_ar_level(const ArModelDev& M, int level, int64_t B, uint64_t s
     A.b2 = M.b2 + static_cast<int64_t>(level) * kArH;
     A.W3 = M.W3 + static_cast<int64_t>(level) * O_full * kArH;
     A.b3 = M.b3 + static_cast<int64_t>(level) * O_full;
-    const unsigned grid = static_cast<unsigned>((B + kArRows - 1) / kArRows);
-    hipLaunchKernelGGL(k_ar_level, dim3(grid), dim3(256), 0, st, A, B, keys, l, T, cand_l, cand_T, cand_key,
-                       cand_idx, n_allowed);
+    return A;
+}
+
+// The candidates of at most B prefixes (the device has the number).
+void launch_candidates(const ArLevel& A, int64_t B, const ArScratch& R, int cur, uint32_t* hist, hipStream_t st) {
+    if (B > kArWide)
+        launch_net<16>(A, B, R.state, R.keys[cur], R.cand_l, st);
+    else
+        launch_net<4>(A, B, R.state, R.keys[cur], R.cand_l, st);
+    const int64_t blocks = std::min<int64_t>((B * A.O + 255) / 256, 2048);
+    hipLaunchKernelGGL(k_ar_cand, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st, A, R.state, R.keys[cur],
+                       R.l[cur], R.T[cur], R.cand_l, R.cand_key, hist);
+}
+
+}  // namespace
+
+size_t ar_state_bytes() { return sizeof(ArState); }
+int64_t ar_tiles(int64_t n) { return (n + kArTile - 1) / kArTile; }
+int64_t ar_bound() { return kArBound; }
+
+hipError_t launch_ar_root(const ArScratch& R, int W, hipStream_t st) {
+    hipLaunchKernelGGL(k_ar_root, dim3(1), dim3(1024), 0, st, R.state, R.hist, R.keys[0], W, R.l[0], R.T[0]);
     return hipGetLastError();
 }
 
-hipError_t launch_ar_gather(const uint64_t* keys, const uint32_t* sorted_idx, int64_t n, int O, int W, int q0,
-                            const double* cand_l, const double* cand_T, uint64_t* out_keys, double* out_l, double* out_T,
-                            hipStream_t st) {
-    hipLaunchKernelGGL(k_ar_gather, dim3(blocks256(n)), dim3(256), 0, st, keys, sorted_idx, n, O, W, q0, cand_l,
-                       cand_T, out_keys, out_l, out_T);
+// Where at most K candidates can come out nothing is selected: the digit
+// passes stay away.
+hipError_t launch_ar_level(const ArModelDev& M, int level, int64_t B, int64_t K, uint64_t seed, bool last,
+                           const ArScratch& R, int cur, hipStream_t st) {
+    const ArLevel A = level_of(M, level, seed);
+    const int64_t n = B * A.O;
+    const bool select = n > K;
+    launch_candidates(A, B, R, cur, select ? R.hist : nullptr, st);
+    hipLaunchKernelGGL(k_ar_pick<true>, dim3(1), dim3(1024), 0, st, R.state, level, K, R.hist);
+    if (select) {
+        const int64_t hb = std::min<int64_t>((n + 8191) / 8192, 256);   // few: each adds up to 4096 counts
+        hipLaunchKernelGGL(k_ar_hist, dim3(static_cast<unsigned>(hb)), dim3(1024), 0, st, R.state, level, A.Dk, K,
+                           R.cand_key, R.hist);
+        hipLaunchKernelGGL(k_ar_pick<false>, dim3(1), dim3(1024), 0, st, R.state, level, K, R.hist);
+    }
+    const unsigned tiles = static_cast<unsigned>(ar_tiles(n));
+    hipLaunchKernelGGL(k_ar_count, dim3(tiles), dim3(256), 0, st, R.state, level, A.Dk, R.cand_key, R.cnt, R.bkey,
+                       R.bidx);
+    hipLaunchKernelGGL(k_ar_cut, dim3(1), dim3(1024), 0, st, R.state, level, A.Dk, R.bkey, R.bidx, R.cnt, R.off);
+    hipLaunchKernelGGL(k_ar_emit, dim3(tiles), dim3(256), 0, st, R.state, A, R.cand_key, R.cand_l, R.off, R.keys[cur],
+                       K, R.keys[cur ^ 1], R.l[cur ^ 1], R.T[cur ^ 1], last ? R.sort_key : nullptr, R.sort_idx);
     return hipGetLastError();
+}
+
+hipError_t launch_ar_out(const ArScratch& R, int cur, const uint64_t* sorted_key, const uint32_t* sorted_idx,
+                         int64_t n, int W, uint64_t* out_keys, double* out_l, double* out_T, hipStream_t st) {
+    hipLaunchKernelGGL(k_ar_out, dim3(blocks256(n)), dim3(256), 0, st, R.state, sorted_key, sorted_idx, n, W,
+                       R.keys[cur], R.l[cur], out_keys, out_l, out_T);
+    return hipGetLastError();
+}
+
+hipError_t launch_ar_candidates(const ArModelDev& M, int level, int64_t B, uint64_t seed, const ArScratch& R, int cur,
+                                uint32_t* idx, hipStream_t st) {
+    const ArLevel A = level_of(M, level, seed);
+    launch_candidates(A, B, R, cur, nullptr, st);
+    hipLaunchKernelGGL(k_ar_iota, dim3(blocks256(B * A.O)), dim3(256), 0, st, idx, B * A.O);
+    return hipGetLastError();
+}
+
+hipError_t launch_ar_gather(const ArModelDev& M, int level, const ArScratch& R, int cur, const uint64_t* sorted_key,
+                            const uint32_t* sorted_idx, int64_t n, hipStream_t st) {
+    const ArLevel A = level_of(M, level, 0);
+    hipLaunchKernelGGL(k_ar_gather, dim3(blocks256(n)), dim3(256), 0, st, R.keys[cur], sorted_key, sorted_idx, n, A.O,
+                       A.W, A.q0, R.cand_l, R.keys[cur ^ 1], R.l[cur ^ 1], R.T[cur ^ 1]);
+    return hipGetLastError();
+}
+
+hipError_t ar_read(const ArScratch& R, int level, ArResult* out, hipStream_t st) {
+    ArState S;
+    hipError_t e = hipMemcpyAsync(&S, R.state, sizeof(S), hipMemcpyDeviceToHost, st);
+    if (e != hipSuccess) return e;
+    e = hipStreamSynchronize(st);
+    if (e != hipSuccess) return e;
+    out->B = S.B[level];
+    out->allowed = level > 0 ? static_cast<int64_t>(S.allowed[level - 1]) : 0;
+    out->redo = S.redo != 0;
+    return hipSuccess;
+}
+
+hipError_t ar_set_prefixes(const ArScratch& R, int level, const int64_t* B, hipStream_t st) {
+    return hipMemcpyAsync(&R.state->B[level], B, sizeof(*B), hipMemcpyHostToDevice, st);
 }
 
 }  // namespace eloc
