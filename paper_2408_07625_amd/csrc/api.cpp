@@ -85,7 +85,7 @@ struct eloc_ctx_s {
 
     // conventional local energy: the extra states' list (raw, sorted, run
     // flags and positions) and the set X = U followed by the extra states
-    DevBuf m_raw, m_sorted, m_perm, m_flags, m_pos, m_count;
+    DevBuf m_raw, m_sorted, m_perm, m_flags, m_pos, m_count, m_rules;
     // the last eloc_find_misses result (m_sorted / m_flags / m_pos), valid
     // for these samples, this Hamiltonian and tolerance
     bool miss_valid = false;
@@ -881,7 +881,7 @@ void eloc_destroy(eloc_ctx c) {
                       &c->counts, &c->offsets, &c->scan_scratch, &c->pkey, &c->pval, &c->pkey2, &c->pval2,
                       &c->hist, &c->hist_off, &c->hist_scratch, &c->gstash, &c->kstash, &c->xyt_keys, &c->xyt_gid, &c->xyt_nodes, &c->xyt_nkeys,
                       &c->ut_keys, &c->ut_perm, &c->ut_nodes, &c->ut_nkeys, &c->s_key, &c->s_val, &c->s_key2, &c->s_val2,
-                      &c->m_raw, &c->m_sorted, &c->m_perm, &c->m_flags, &c->m_pos, &c->m_count, &c->x_keys, &c->x_hash, &c->x_slots,
+                      &c->m_raw, &c->m_sorted, &c->m_perm, &c->m_flags, &c->m_pos, &c->m_count, &c->m_rules, &c->x_keys, &c->x_hash, &c->x_slots,
                       &c->x_stash, &c->x_sig, &c->x_bitcounts, &c->x_rad, &c->x_params, &c->x_err, &c->x_logpsi,
                       &c->x_a, &c->x_b, &c->x_af, &c->x_bf, &c->x_shift, &c->x_part_perm, &c->x_part_class, &c->x_part_tile, &c->st_rowptr, &c->st_col, &c->st_h,
                       &c->sr_w, &c->sr_mean, &c->sr_part, &c->sr_T, &c->sr_y,
@@ -1174,6 +1174,10 @@ int eloc_find_misses(eloc_ctx c, double tol, int64_t capacity, uint64_t* keys_de
     // states in ascending order (no list, no sort)
     const bool bitmap = W == 1 && c->H.n_qubits <= kMissBitmapQubits;
     const int64_t nwords = int64_t(1) << std::max(0, c->H.n_qubits - 5);
+    if (!(c->miss_valid && c->miss_tol == tol)) {
+        ELOC_HIP(c, c->m_rules.ensure(std::max<size_t>(miss_rule_bytes(c->H), 1)));
+        ELOC_HIP(c, launch_miss_rules(c->H, tol, c->m_rules.p, c->stream));
+    }
     if (bitmap && !(c->miss_valid && c->miss_tol == tol)) {
         c->miss_valid = false;
         const Plan P = make_plan(c, ELOC_TERMS);
@@ -1183,7 +1187,7 @@ int eloc_find_misses(eloc_ctx c, double tol, int64_t capacity, uint64_t* keys_de
         ELOC_HIP(c, c->scan_scratch.ensure(sizeof(int64_t) * scan_scratch_len(nwords)));
         uint32_t* bits = static_cast<uint32_t*>(c->m_raw.p);
         ELOC_HIP(c, hipMemsetAsync(bits, 0, sizeof(uint32_t) * nwords, c->stream));
-        ELOC_HIP(c, launch_misses_bitmap(c->H, c->S, P.chunks, P.per_chunk, tol, bits, c->stream));
+        ELOC_HIP(c, launch_misses_bitmap(c->H, c->S, P.chunks, P.per_chunk, tol, c->m_rules.p, bits, c->stream));
         ELOC_HIP(c, launch_bitmap_counts(bits, nwords, c->m_flags.as<int32_t>(), c->stream));
         ELOC_HIP(c, launch_scan_i32(c->m_flags.as<int32_t>(), nwords, c->m_pos.as<int64_t>(),
                                     c->scan_scratch.as<int64_t>(), c->stream));
@@ -1201,7 +1205,7 @@ int eloc_find_misses(eloc_ctx c, double tol, int64_t capacity, uint64_t* keys_de
         for (int pass = 0; pass < 2; ++pass) {
             const int64_t room = static_cast<int64_t>(c->m_raw.p ? c->m_raw.bytes / (sizeof(uint64_t) * W) : 0);
             ELOC_HIP(c, hipMemsetAsync(c->m_count.p, 0, sizeof(unsigned long long), c->stream));
-            ELOC_HIP(c, launch_misses(c->H, c->S, P.chunks, P.per_chunk, tol, c->m_count.as<unsigned long long>(),
+            ELOC_HIP(c, launch_misses(c->H, c->S, P.chunks, P.per_chunk, tol, c->m_rules.p, c->m_count.as<unsigned long long>(),
                                       room, c->m_raw.as<uint64_t>(), c->stream));
             unsigned long long cnt = 0;
             ELOC_HIP(c, hipMemcpyAsync(&cnt, c->m_count.p, sizeof(cnt), hipMemcpyDeviceToHost, c->stream));

@@ -917,14 +917,17 @@ int batch_blocks_per_cu(int W, bool narrow, int precision, int rows);
 // included) as [n][W] keys to out at positions taken from *counter (which
 // must start at 0 and ends at their number); those at positions >= capacity
 // are counted but not written.
-hipError_t launch_misses(const HamDev& H, const SampleDev& S, int chunks, int per_chunk, double tol,
+// `rules`: by launch_miss_rules for the same tol (miss_rule_bytes).
+size_t miss_rule_bytes(const HamDev& H);
+hipError_t launch_miss_rules(const HamDev& H, double tol, void* rules, hipStream_t st);
+hipError_t launch_misses(const HamDev& H, const SampleDev& S, int chunks, int per_chunk, double tol, const void* rules,
                          unsigned long long* counter, int64_t capacity, uint64_t* out, hipStream_t st);
 // One-word keys of at most kMissBitmapQubits qubits: the same states marked
 // instead in a bitmap over the whole key space (bit x' of word x' >> 5; the
 // bitmap must start cleared), which makes them unique and sorted at once.
 constexpr int kMissBitmapQubits = 30;
 hipError_t launch_misses_bitmap(const HamDev& H, const SampleDev& S, int chunks, int per_chunk, double tol,
-                                uint32_t* bitmap, hipStream_t st);
+                                const void* rules, uint32_t* bitmap, hipStream_t st);
 // counts[w] = popcount(bitmap[w]); keys of the set bits in ascending order
 // to out at the exclusive prefix sums pos of those counts
 hipError_t launch_bitmap_counts(const uint32_t* bitmap, int64_t nwords, int32_t* counts, hipStream_t st);

@@ -2,20 +2,30 @@
 // every x', the estimator that the sample-aware form replaces): the x' =
 // x ^ XY_g, x in U, that are not in U and whose matrix element is non-zero.
 //
+// Whether an element is non-zero (|H| > tol * sum |h_l| over the group's run;
+// strings that cancel exactly, e.g. hopping strings between particle-number
+// sectors, give no state) depends on few bits of the ket: the Z masks of a
+// run differ by sums of a few masks, three for a double excitation, and |H|
+// by the parities of the ket under those.  k_miss_rules finds the masks of a
+// group and the values of H for their eight parities; a candidate then is
+// three popcounts.  Groups with more masks (singles) keep the sum over the
+// run.
+//
 // k_misses walks the same (row, XY group) candidates as LoopOverTerms: a
 // wave owns kMissRows rows (keys in scalar registers), its lanes sweep 64
-// groups of the row's chunk per step.  A candidate is looked up in U's
-// table; one that is absent has its matrix element evaluated over the
-// group's run, and is a miss when |H| > tol * sum |h_l| (strings that cancel
-// exactly, e.g. hopping strings between particle-number sectors, give no
-// state).  The misses of a step (all rows) take one range of the output
-// from an atomic counter and are written there (ballot + mbcnt), those past
-// the capacity only counted; the caller reruns with a larger buffer when the
-// count exceeds it.  The list is then sorted and made unique, so the order
-// in which waves append does not show in the result.  For one-word keys of
-// at most 30 qubits the misses instead set their bit in a bitmap over the
-// key space (one atomic OR each); the set bits, read in order, are the
-// unique states already sorted.
+// groups of the row's chunk per step.  A candidate whose element is non-zero
+// is looked up in U's table, and is a miss when absent.  The misses of a step
+// (all rows) take one range of the output from an atomic counter and are
+// written there (ballot + mbcnt), those past the capacity only counted; the
+// caller reruns with a larger buffer when the count exceeds it.  The list is
+// then sorted and made unique, so the order in which waves append does not
+// show in the result.
+//
+// For one-word keys of at most 30 qubits (k_miss_bits) the states set their
+// bit in a bitmap over the key space instead, U's bits are cleared after it
+// (no lookups), and the set bits, read in order, are the unique states
+// already sorted.  20 000 rows by 10 466 groups, a third of them non-zero:
+// 3.6 ms with a lookup, the run's sum and an atomic for each, @@ this way.
 #include "device.h"
 
 #include <hip/hip_runtime.h>
@@ -27,6 +37,18 @@ namespace eloc {
 namespace {
 
 constexpr int kMissRows = 8;
+
+// The parities that decide whether a group's element is non-zero: bit idx of
+// tab, idx = sum over k of parity(ket & mask[k]) << k.  kMissRun: evaluate
+// the run.
+constexpr uint32_t kMissRun = 256u;
+
+template <int W>
+struct MissRule {
+    uint64_t mask[3][W];
+    uint32_t tab;
+    uint32_t pad;
+};
 
 struct MissArgs {
     const void* groups;      // GroupRec<W>[G]
@@ -41,6 +63,7 @@ struct MissArgs {
     int64_t M;
     const uint32_t* prep_err;
     double tol;
+    const void* rules;       // MissRule<W>[G]
 };
 
 // |H_xx'| > tol * sum |h_l| over the group's run [b, e) (real part [b, m),
@@ -67,9 +90,158 @@ __device__ __forceinline__ int lanes_below(uint64_t mask) {
                                                       __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask), 0u)));
 }
 
+template <int W>
+__global__ __launch_bounds__(64) void k_miss_rules(const GroupRec<W>* __restrict__ groups,
+                                                   const TermRec<W>* __restrict__ terms, int n_groups, double tol,
+                                                   MissRule<W>* __restrict__ rules) {
+    const int g = static_cast<int>(blockIdx.x) * 64 + static_cast<int>(threadIdx.x);
+    if (g >= n_groups) return;
+    const GroupRec<W> gr = groups[g];
+    MissRule<W> rule{};
+    int pivot[3] = {0, 0, 0};
+    int rank = 0;
+    // what `z` ^ the first mask of its part is a sum of; the remainder left in d
+    auto reduce = [&](int t, uint64_t (&d)[W]) {
+        const int first = t < gr.mid ? gr.begin : gr.mid;
+        uint32_t coef = 0;
+#pragma unroll
+        for (int w = 0; w < W; ++w) d[w] = terms[t].yz[w] ^ terms[first].yz[w];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            if (k >= rank) continue;
+            const uint64_t word = W == 2 && pivot[k] >= 64 ? d[W - 1] : d[0];
+            if ((word >> (pivot[k] & 63)) & 1ull) {
+                coef |= 1u << k;
+#pragma unroll
+                for (int w = 0; w < W; ++w) d[w] ^= rule.mask[k][w];
+            }
+        }
+        return coef;
+    };
+    bool run = false;
+    for (int t = gr.begin; t < gr.end && !run; ++t) {
+        uint64_t d[W];
+        reduce(t, d);
+        int q = -1;
+#pragma unroll
+        for (int w = 0; w < W; ++w)
+            if (q < 0 && d[w]) q = 64 * w + __ffsll(static_cast<unsigned long long>(d[w])) - 1;
+        if (q < 0) continue;
+        if (rank == 3) {
+            run = true;
+            break;
+        }
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+            if (k == rank) {
+                pivot[k] = q;
+#pragma unroll
+                for (int w = 0; w < W; ++w) rule.mask[k][w] = d[w];
+            }
+        ++rank;
+    }
+    if (run) {
+        rule.tab = kMissRun;
+    } else {
+        for (uint32_t idx = 0; idx < 8u; ++idx) {
+            double hr = 0.0, hi = 0.0, sa = 0.0;
+            for (int t = gr.begin; t < gr.end; ++t) {
+                uint64_t d[W];
+                const double h = terms[t].h;
+                const double v = (__popc(reduce(t, d) & idx) & 1) ? -h : h;
+                (t < gr.mid ? hr : hi) += v;
+                sa += fabs(h);
+            }
+            if (hypot(hr, hi) > tol * sa) rule.tab |= 1u << idx;
+        }
+    }
+    rules[g] = rule;
+}
+
+template <int W>
+__device__ __forceinline__ uint32_t rule_index(const MissRule<W>& rule, const uint64_t* ket) {
+    uint32_t idx = 0;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        int p = 0;
+#pragma unroll
+        for (int w = 0; w < W; ++w) p += __popcll(ket[w] & rule.mask[k][w]);
+        idx |= (static_cast<uint32_t>(p) & 1u) << k;
+    }
+    return idx;
+}
+
+// One-word keys of at most 30 qubits, all in 32 bits.  What bounds it is the
+// bitmap's traffic; a bit is read before it is set, as most are set many
+// times (an atomic goes past the L2s), and the reads of a step's rows are in
+// flight together.
+__global__ __launch_bounds__(64) void k_miss_bits(MissArgs A, uint32_t* __restrict__ bitmap) {
+    const int lane = lane_id();
+    const int64_t row0 = static_cast<int64_t>(blockIdx.x) * kMissRows;
+    const int chunk = static_cast<int>(blockIdx.y);
+    if (row0 >= A.M) return;
+    if (__builtin_amdgcn_readfirstlane(static_cast<int>(*A.prep_err)) != 0) return;   // U invalid: no states
+    const GroupRec<1>* __restrict__ groups = static_cast<const GroupRec<1>*>(A.groups);
+    const TermRec<1>* __restrict__ terms = static_cast<const TermRec<1>*>(A.terms);
+    const MissRule<1>* __restrict__ rules = static_cast<const MissRule<1>*>(A.rules);
+    uint32_t x[kMissRows];
+#pragma unroll
+    for (int r = 0; r < kMissRows; ++r) x[r] = static_cast<uint32_t>(A.keys[min(row0 + r, A.M - 1)]);
+    const int g0 = chunk * A.per_chunk;
+    const int g1 = min(A.n_groups, g0 + A.per_chunk);
+    for (int base = g0; base < g1; base += 64) {
+        const int g = min(base + lane, g1 - 1);   // lanes past the end set the last group's bits once more
+        const uint32_t xy = static_cast<uint32_t>(groups[g].xy[0]);
+        const MissRule<1> rule = rules[g];
+        const uint32_t m0 = static_cast<uint32_t>(rule.mask[0][0]), m1 = static_cast<uint32_t>(rule.mask[1][0]),
+                       m2 = static_cast<uint32_t>(rule.mask[2][0]);
+        const bool run = rule.tab == kMissRun;
+        uint32_t hit = 0;
+#pragma unroll
+        for (int r = 0; r < kMissRows; ++r) {
+            const uint32_t k = x[r] ^ xy;
+            const uint32_t idx = (__popc(k & m0) & 1) | ((__popc(k & m1) & 1) << 1) | ((__popc(k & m2) & 1) << 2);
+            hit |= ((rule.tab >> idx) & 1u) << r;
+        }
+        if (__ballot(run)) {
+            if (run) {
+                const GroupRec<1> gr = groups[g];
+                hit = 0;
+                for (int r = 0; r < kMissRows; ++r) {
+                    uint32_t xr = x[0];
+#pragma unroll
+                    for (int q = 1; q < kMissRows; ++q) xr = r == q ? x[q] : xr;
+                    const uint64_t ket[1] = {xr ^ xy};
+                    hit |= nonzero_element<1>(terms, gr, ket, A.tol) ? 1u << r : 0u;
+                }
+            }
+        }
+        uint32_t word[kMissRows];
+#pragma unroll
+        for (int r = 0; r < kMissRows; ++r) {
+            word[r] = ~0u;
+            if ((hit >> r) & 1u) word[r] = bitmap[(x[r] ^ xy) >> 5];
+        }
+#pragma unroll
+        for (int r = 0; r < kMissRows; ++r) {
+            const uint32_t key = x[r] ^ xy, bit = 1u << (key & 31u);
+            if (!(word[r] & bit)) atomicOr(bitmap + (key >> 5), bit);   // rows past the end: the last row once more
+        }
+    }
+}
+
+// U's own bits go.
+__global__ void k_miss_clear(const uint64_t* __restrict__ keys, int64_t n, const uint32_t* __restrict__ prep_err,
+                             uint32_t* __restrict__ bitmap) {
+    const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (i >= n || *prep_err) return;
+    const uint32_t key = static_cast<uint32_t>(keys[i]);
+    atomicAnd(bitmap + (key >> 5), ~(1u << (key & 31u)));
+}
+
 template <int W, int TK>
 __global__ __launch_bounds__(64) void k_misses(MissArgs A, unsigned long long* __restrict__ counter, int64_t capacity,
-                                               uint64_t* __restrict__ out, uint32_t* __restrict__ bitmap) {
+                                               uint64_t* __restrict__ out) {
     const int lane = lane_id();
     const int64_t row0 = static_cast<int64_t>(blockIdx.x) * kMissRows;
     const int chunk = static_cast<int>(blockIdx.y);
@@ -78,6 +250,7 @@ __global__ __launch_bounds__(64) void k_misses(MissArgs A, unsigned long long* _
     if (__builtin_amdgcn_readfirstlane(static_cast<int>(*A.prep_err)) != 0) return;   // U invalid: no states
     const GroupRec<W>* __restrict__ groups = static_cast<const GroupRec<W>*>(A.groups);
     const TermRec<W>* __restrict__ terms = static_cast<const TermRec<W>*>(A.terms);
+    const MissRule<W>* __restrict__ rules = static_cast<const MissRule<W>*>(A.rules);
     uint64_t x[kMissRows][W];
     uint64_t hx[kMissRows];
 #pragma unroll
@@ -94,6 +267,7 @@ __global__ __launch_bounds__(64) void k_misses(MissArgs A, unsigned long long* _
         const int g = base + lane;
         const bool valid = g < g1;
         const GroupRec<W> gr = groups[min(g, g1 - 1)];
+        const MissRule<W> rule = rules[min(g, g1 - 1)];
         const uint64_t gh = A.ghash[min(g, g1 - 1)];
         uint64_t m[kMissRows];
         bool miss[kMissRows];
@@ -104,26 +278,18 @@ __global__ __launch_bounds__(64) void k_misses(MissArgs A, unsigned long long* _
 #pragma unroll
             for (int w = 0; w < W; ++w) xp[w] = x[r][w] ^ gr.xy[w];
             miss[r] = false;
-            if (valid && r < nr) {
+            if (valid && r < nr &&
+                (rule.tab == kMissRun ? nonzero_element<W>(terms, gr, xp, A.tol)
+                                      : ((rule.tab >> rule_index<W>(rule, xp)) & 1u) != 0u)) {
                 const auto hs = salted<TK>(A.ktable, hx[r] ^ gh);
                 const int j = table_settle<TK, W>(A.ktable, A.keys, load_slot<TK>(A.ktable, slot1(A.ktable, hs)),
                                                   load_slot<TK>(A.ktable, slot2(A.ktable, hs)), hs, xp, nstash);
-                if (j < 0) miss[r] = nonzero_element<W>(terms, gr, xp, A.tol);
+                miss[r] = j < 0;
             }
             m[r] = __ballot(miss[r]);
             total += __popcll(m[r]);
         }
         if (total == 0) continue;   // wave-uniform
-        if (W == 1 && bitmap) {   // uniform
-#pragma unroll
-            for (int r = 0; r < kMissRows; ++r) {
-                if (miss[r]) {
-                    const uint64_t key = x[r][0] ^ gr.xy[0];
-                    atomicOr(bitmap + (key >> 5), 1u << static_cast<uint32_t>(key & 31u));
-                }
-            }
-            continue;
-        }
         unsigned long long first = 0ull;
         if (lane == 0) first = atomicAdd(counter, static_cast<unsigned long long>(total));
         const int64_t at0 = static_cast<int64_t>(
@@ -188,15 +354,18 @@ __global__ void k_bitmap_keys(const uint32_t* __restrict__ bitmap, int64_t nword
     }
 }
 
+dim3 miss_grid(const MissArgs& A) {
+    return dim3(static_cast<unsigned>((A.M + kMissRows - 1) / kMissRows), static_cast<unsigned>(A.chunks));
+}
+
 template <int W, int TK>
 hipError_t launch_misses_t(const MissArgs& A, unsigned long long* counter, int64_t capacity, uint64_t* out,
-                           uint32_t* bitmap, hipStream_t st) {
-    const dim3 grid(static_cast<unsigned>((A.M + kMissRows - 1) / kMissRows), static_cast<unsigned>(A.chunks));
-    hipLaunchKernelGGL((k_misses<W, TK>), grid, dim3(64), 0, st, A, counter, capacity, out, bitmap);
+                           hipStream_t st) {
+    hipLaunchKernelGGL((k_misses<W, TK>), miss_grid(A), dim3(64), 0, st, A, counter, capacity, out);
     return hipGetLastError();
 }
 
-MissArgs miss_args(const HamDev& H, const SampleDev& S, int chunks, int per_chunk, double tol) {
+MissArgs miss_args(const HamDev& H, const SampleDev& S, int chunks, int per_chunk, double tol, const void* rules) {
     MissArgs A;
     A.groups = H.groups;
     A.ghash = H.group_hash;
@@ -210,27 +379,45 @@ MissArgs miss_args(const HamDev& H, const SampleDev& S, int chunks, int per_chun
     A.M = S.n;
     A.prep_err = S.prep_err;
     A.tol = tol;
+    A.rules = rules;
     return A;
 }
 
 }  // namespace
 
-hipError_t launch_misses(const HamDev& H, const SampleDev& S, int chunks, int per_chunk, double tol,
+size_t miss_rule_bytes(const HamDev& H) {
+    return static_cast<size_t>(H.n_groups) * (H.W == 2 ? sizeof(MissRule<2>) : sizeof(MissRule<1>));
+}
+
+hipError_t launch_miss_rules(const HamDev& H, double tol, void* rules, hipStream_t st) {
+    const int G = static_cast<int>(H.n_groups);
+    if (G == 0) return hipSuccess;
+    const dim3 grid(static_cast<unsigned>((G + 63) / 64));
+    if (H.W == 2)
+        hipLaunchKernelGGL(k_miss_rules<2>, grid, dim3(64), 0, st, static_cast<const GroupRec<2>*>(H.groups),
+                           static_cast<const TermRec<2>*>(H.terms), G, tol, static_cast<MissRule<2>*>(rules));
+    else
+        hipLaunchKernelGGL(k_miss_rules<1>, grid, dim3(64), 0, st, static_cast<const GroupRec<1>*>(H.groups),
+                           static_cast<const TermRec<1>*>(H.terms), G, tol, static_cast<MissRule<1>*>(rules));
+    return hipGetLastError();
+}
+
+hipError_t launch_misses(const HamDev& H, const SampleDev& S, int chunks, int per_chunk, double tol, const void* rules,
                          unsigned long long* counter, int64_t capacity, uint64_t* out, hipStream_t st) {
-    const MissArgs A = miss_args(H, S, chunks, per_chunk, tol);
+    const MissArgs A = miss_args(H, S, chunks, per_chunk, tol, rules);
     const int tk = table_kind(H.W, H.narrow);
-    if (H.W == 2) return launch_misses_t<2, kTabVerify>(A, counter, capacity, out, nullptr, st);
-    if (tk == kTabNarrow) return launch_misses_t<1, kTabNarrow>(A, counter, capacity, out, nullptr, st);
-    return launch_misses_t<1, kTabWide>(A, counter, capacity, out, nullptr, st);
+    if (H.W == 2) return launch_misses_t<2, kTabVerify>(A, counter, capacity, out, st);
+    if (tk == kTabNarrow) return launch_misses_t<1, kTabNarrow>(A, counter, capacity, out, st);
+    return launch_misses_t<1, kTabWide>(A, counter, capacity, out, st);
 }
 
 hipError_t launch_misses_bitmap(const HamDev& H, const SampleDev& S, int chunks, int per_chunk, double tol,
-                                uint32_t* bitmap, hipStream_t st) {
+                                const void* rules, uint32_t* bitmap, hipStream_t st) {
     if (H.W != 1 || H.n_qubits > kMissBitmapQubits || !bitmap) return hipErrorInvalidValue;
-    const MissArgs A = miss_args(H, S, chunks, per_chunk, tol);
-    if (table_kind(H.W, H.narrow) == kTabNarrow)
-        return launch_misses_t<1, kTabNarrow>(A, nullptr, 0, nullptr, bitmap, st);
-    return launch_misses_t<1, kTabWide>(A, nullptr, 0, nullptr, bitmap, st);
+    const MissArgs A = miss_args(H, S, chunks, per_chunk, tol, rules);
+    hipLaunchKernelGGL(k_miss_bits, miss_grid(A), dim3(64), 0, st, A, bitmap);
+    hipLaunchKernelGGL(k_miss_clear, dim3(blocks256(S.n)), dim3(256), 0, st, S.keys, S.n, S.prep_err, bitmap);
+    return hipGetLastError();
 }
 
 hipError_t launch_bitmap_counts(const uint32_t* bitmap, int64_t nwords, int32_t* counts, hipStream_t st) {
