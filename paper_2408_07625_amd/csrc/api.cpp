@@ -35,6 +35,24 @@ constexpr uint64_t kPartTargetBytes = uint64_t(1) << 20;
 // caller's variants where use_join allows it
 constexpr int kJoin = 100;
 
+// The words of eloc_ctx_s::prep.
+struct PrepWords {
+    uint32_t err_prep, err_run;
+    unsigned long long rad[3];
+    Stash stash;
+    uint64_t sig[kSigWords];
+    uint32_t bitcounts[64 * kMaxWords];
+};
+
+// A part of a buffer.
+struct View {
+    void* p = nullptr;
+    template <class T>
+    T* as() const {
+        return static_cast<T*>(p);
+    }
+};
+
 }  // namespace
 
 struct eloc_ctx_s {
@@ -59,7 +77,11 @@ struct eloc_ctx_s {
 
     bool samples_set = false;
     SampleDev S;
-    DevBuf keys, khash, kslots, kstash, sig, bitcounts, rad, sparams, bloom;
+    DevBuf keys, khash, kslots, sparams, bloom;
+    // the words that preparing U starts from zero, in one piece (the two error
+    // words first, read back together), and its parts
+    DevBuf prep;
+    View err_prep, err_run, rad, kstash, sig, bitcounts;
     uint32_t bloom_words = 0;   // Bloom filter of U (0: none)
     bool bloom_built = false;   // built on first use by a kernel that reads it
     DevBuf ut_keys, ut_perm, ut_nodes, ut_nkeys;
@@ -77,7 +99,7 @@ struct eloc_ctx_s {
     bool j_room = false, j_built = false;
 
     DevBuf a, b, af, bf, v, vf, shift, amp_scratch;
-    DevBuf partial, energy_scratch, err_run, err_prep;
+    DevBuf partial, energy_scratch;
     uint32_t* err_host = nullptr;    // pinned words for synchronous read-backs
     void* ws = nullptr;              // this device's fixed workspace (eloc_local_energy_noalloc)
 
@@ -341,30 +363,39 @@ int part_bits_for(const eloc_ctx c, uint64_t bytes, uint64_t cap) {
 }
 
 // One cuckoo table of U with a fresh salt, its verification (duplicates,
-// signature bitmap) and the prefilter parameters; asynchronous.
-int build_sample_table(eloc_ctx c) {
+// signature bitmap) and the prefilter parameters; asynchronous.  clear: what
+// it starts from is not cleared yet.
+int build_sample_table(eloc_ctx c, bool clear) {
     const int64_t n = c->S.n;
     const int tk = table_kind(c->H.W, c->H.narrow);
     c->S.table = make_table(c->kslots.p, c->kstash.as<Stash>(), c->kslots_n, n, splitmix64(c->salt_state),
                             c->H.part.shift, c->part_bits);
-    ELOC_HIP(c, hipMemsetAsync(c->kslots.p, 0, slot_bytes(tk) * c->kslots_n, c->stream));
-    ELOC_HIP(c, hipMemsetAsync(c->kstash.p, 0, sizeof(Stash), c->stream));
-    ELOC_HIP(c, hipMemsetAsync(c->sig.p, 0, sizeof(uint64_t) * kSigWords, c->stream));
+    if (clear) {
+        ELOC_HIP(c, hipMemsetAsync(c->kslots.p, 0, slot_bytes(tk) * c->kslots_n, c->stream));
+        ELOC_HIP(c, hipMemsetAsync(c->kstash.p, 0, sizeof(Stash), c->stream));
+        ELOC_HIP(c, hipMemsetAsync(c->sig.p, 0, sizeof(uint64_t) * kSigWords, c->stream));
+    }
     ELOC_HIP(c, launch_table_insert(tk, c->khash.as<uint64_t>(), n, c->kslots.p, c->kstash.as<Stash>(), c->S.table,
                                     c->err_prep.as<uint32_t>(), c->stream));
-    ELOC_HIP(c, launch_sample_verify(c->H.W, c->H.narrow, c->S, c->sig.as<uint64_t>(), c->err_prep.as<uint32_t>(),
-                                     c->stream));
+    ELOC_HIP(c, launch_sample_verify(c->H.W, c->H.narrow, c->S, c->bitcounts.as<uint32_t>(),
+                                     c->rad.as<unsigned long long>(), c->sig.as<uint64_t>(),
+                                     c->err_prep.as<uint32_t>(), c->stream));
     ELOC_HIP(c, launch_sample_params(c->sig.as<uint64_t>(), c->rad.as<unsigned long long>(), c->H.n_qubits,
                                      c->sparams.as<SampleParams>(), c->stream));
     return ELOC_OK;
 }
 
-int read_err(eloc_ctx c, DevBuf& word) {
-    hipError_t e = hipMemcpyAsync(c->err_host, word.p, sizeof(uint32_t), hipMemcpyDeviceToHost, c->stream);
+int read_words(eloc_ctx c, const void* word, int n) {
+    hipError_t e = hipMemcpyAsync(c->err_host, word, sizeof(uint32_t) * n, hipMemcpyDeviceToHost, c->stream);
     if (e != hipSuccess) return hip_fail(c, e, "read error word");
     e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) return hip_fail(c, e, "hipStreamSynchronize");
     return static_cast<int>(*c->err_host);
+}
+
+template <class B>
+int read_err(eloc_ctx c, const B& word) {
+    return read_words(c, word.p, 1);
 }
 
 int map_err(eloc_ctx c, uint32_t bits) {
@@ -384,14 +415,16 @@ int map_err(eloc_ctx c, uint32_t bits) {
 // settle (which also fails the key's own lookup, so it reads as a duplicate)
 // is rebuilt here with new salts; *rebuilt tells the caller that work
 // enqueued before this call saw the broken table.
-int samples_verdict(eloc_ctx c, bool* rebuilt) {
+// *run: the run error word of the same moment.
+int samples_verdict(eloc_ctx c, bool* rebuilt, uint32_t* run = nullptr) {
     if (rebuilt) *rebuilt = false;
-    int bits = read_err(c, c->err_prep);
+    int bits = read_words(c, c->err_prep.p, 2);
     if (bits < 0) return bits;
+    if (run) *run = c->err_host[1];
     for (int attempt = 0; (bits & kErrTable) && !(bits & kErrBits); ++attempt) {
         if (attempt == 8) return fail(c, ELOC_EHIP, "membership table could not be built");
         ELOC_HIP(c, hipMemsetAsync(c->err_prep.p, 0, sizeof(uint32_t), c->stream));
-        const int rc = build_sample_table(c);
+        const int rc = build_sample_table(c, true);
         if (rc) return rc;
         bits = read_err(c, c->err_prep);
         if (bits < 0) return bits;
@@ -758,7 +791,7 @@ int prepare_variant(eloc_ctx c, int* variant) {
     return *variant == ELOC_TRIE ? ensure_utrie(c) : ELOC_OK;
 }
 
-int amp_prep(eloc_ctx c, const eloc_c64* logpsi, bool fp32) {
+int amp_prep(eloc_ctx c, const eloc_c64* logpsi, bool fp32, bool clear_err = false) {
     const int64_t M = c->S.n;
     ELOC_HIP(c, c->a.ensure(sizeof(double2) * M));
     ELOC_HIP(c, c->b.ensure(sizeof(double2) * M));
@@ -770,7 +803,7 @@ int amp_prep(eloc_ctx c, const eloc_c64* logpsi, bool fp32) {
     ELOC_HIP(c, launch_amp_prep(reinterpret_cast<const double2*>(logpsi), M, fp32, c->a.as<double2>(),
                                 c->b.as<double2>(), c->af.as<float4>(), c->bf.as<float4>(),
                                 c->shift.as<double>(), c->amp_scratch.as<double>(), c->err_run.as<uint32_t>(),
-                                c->stream));
+                                clear_err, c->stream));
     prof_end(c, pm);
     return ELOC_OK;
 }
@@ -858,14 +891,19 @@ int eloc_create(eloc_ctx* out, int device, void* hip_stream) {
     make_hash_words(c->R);
     if (c->R_dev.ensure(sizeof(c->R)) != hipSuccess ||
         hipMemcpy(c->R_dev.p, c->R, sizeof(c->R), hipMemcpyHostToDevice) != hipSuccess ||
-        c->err_run.ensure(sizeof(uint32_t)) != hipSuccess || c->err_prep.ensure(sizeof(uint32_t)) != hipSuccess ||
-        hipMemset(c->err_run.p, 0, sizeof(uint32_t)) != hipSuccess ||
-        hipMemset(c->err_prep.p, 0, sizeof(uint32_t)) != hipSuccess ||
+        c->prep.ensure(sizeof(PrepWords)) != hipSuccess || hipMemset(c->prep.p, 0, sizeof(PrepWords)) != hipSuccess ||
         hipHostMalloc(reinterpret_cast<void**>(&c->err_host), sizeof(uint32_t) * 4, hipHostMallocDefault) != hipSuccess ||
         noalloc_workspace(device, &c->ws) != hipSuccess) {
         eloc_destroy(c);
         return ELOC_EHIP;
     }
+    PrepWords* w = c->prep.as<PrepWords>();
+    c->err_prep.p = &w->err_prep;
+    c->err_run.p = &w->err_run;
+    c->rad.p = w->rad;
+    c->kstash.p = &w->stash;
+    c->sig.p = w->sig;
+    c->bitcounts.p = w->bitcounts;
     *out = c;
     return ELOC_OK;
 }
@@ -876,10 +914,10 @@ void eloc_destroy(eloc_ctx c) {
     if (c->stream) (void)hipStreamSynchronize(c->stream);
     else (void)hipDeviceSynchronize();
     DevBuf* bufs[] = {&c->R_dev, &c->groups, &c->terms, &c->terms_f, &c->term_src, &c->term_ny, &c->pe_cnt, &c->pe_grp, &c->ghash, &c->gkeys, &c->gslots,
-                      &c->keys, &c->khash, &c->kslots, &c->sig, &c->bitcounts, &c->rad, &c->sparams, &c->bloom, &c->a, &c->b, &c->af, &c->bf, &c->v, &c->vf,
-                      &c->shift, &c->amp_scratch, &c->partial, &c->energy_scratch, &c->err_run, &c->err_prep,
+                      &c->keys, &c->khash, &c->kslots, &c->prep, &c->sparams, &c->bloom, &c->a, &c->b, &c->af, &c->bf, &c->v, &c->vf,
+                      &c->shift, &c->amp_scratch, &c->partial, &c->energy_scratch,
                       &c->counts, &c->offsets, &c->scan_scratch, &c->pkey, &c->pval, &c->pkey2, &c->pval2,
-                      &c->hist, &c->hist_off, &c->hist_scratch, &c->gstash, &c->kstash, &c->xyt_keys, &c->xyt_gid, &c->xyt_nodes, &c->xyt_nkeys,
+                      &c->hist, &c->hist_off, &c->hist_scratch, &c->gstash, &c->xyt_keys, &c->xyt_gid, &c->xyt_nodes, &c->xyt_nkeys,
                       &c->ut_keys, &c->ut_perm, &c->ut_nodes, &c->ut_nkeys, &c->s_key, &c->s_val, &c->s_key2, &c->s_val2,
                       &c->m_raw, &c->m_sorted, &c->m_perm, &c->m_flags, &c->m_pos, &c->m_count, &c->m_rules, &c->x_keys, &c->x_hash, &c->x_slots,
                       &c->x_stash, &c->x_sig, &c->x_bitcounts, &c->x_rad, &c->x_params, &c->x_err, &c->x_logpsi,
@@ -974,28 +1012,20 @@ int eloc_set_samples(eloc_ctx c, int64_t n_unique, const uint64_t* keys_dev) {
     const uint64_t cap = table_capacity(n_unique);
     const int tk = table_kind(W, c->H.narrow);
     ELOC_HIP(c, c->kslots.ensure(slot_bytes(tk) * cap));
-    ELOC_HIP(c, c->kstash.ensure(sizeof(Stash)));
-    ELOC_HIP(c, c->sig.ensure(sizeof(uint64_t) * kSigWords));
-    ELOC_HIP(c, c->bitcounts.ensure(sizeof(uint32_t) * 64 * W));
-    ELOC_HIP(c, c->rad.ensure(sizeof(unsigned long long) * 3));
     ELOC_HIP(c, c->sparams.ensure(sizeof(SampleParams)));
     if (use_join(c, n_unique, ELOC_TERMS) || use_join(c, n_unique, ELOC_BATCH)) {
         const int jrc = join_room(c, n_unique);
         if (jrc) return jrc;
     }
     const int pm = prof_begin(c, ELOC_STAGE_SAMPLES);
-    ELOC_HIP(c, hipMemcpyAsync(c->keys.p, keys_dev, sizeof(uint64_t) * n_unique * W, hipMemcpyDeviceToDevice,
-                               c->stream));
-    ELOC_HIP(c, hipMemsetAsync(c->err_prep.p, 0, sizeof(uint32_t), c->stream));
-    // errors of calls on the previous samples are not carried over
-    ELOC_HIP(c, hipMemsetAsync(c->err_run.p, 0, sizeof(uint32_t), c->stream));
-    ELOC_HIP(c, hipMemsetAsync(c->bitcounts.p, 0, sizeof(uint32_t) * 64 * W, c->stream));
-    ELOC_HIP(c, hipMemsetAsync(c->rad.p, 0, sizeof(unsigned long long) * 3, c->stream));
+    // the keys' copy; the table's slots and the words of PrepWords from zero
+    // (errors of calls on the previous samples are not carried over)
+    ELOC_HIP(c, launch_sample_begin(c->prep.as<uint32_t>(), static_cast<int>(sizeof(PrepWords) / sizeof(uint32_t)),
+                                    c->kslots.p, slot_bytes(tk) * cap, keys_dev, c->keys.as<uint64_t>(),
+                                    n_unique * W, c->stream));
     ELOC_HIP(c, launch_sample_hash(W, c->keys.as<uint64_t>(), n_unique, c->R_dev.as<uint64_t>(), c->H.n_qubits,
                                    c->khash.as<uint64_t>(), c->bitcounts.as<uint32_t>(), c->err_prep.as<uint32_t>(),
                                    c->stream));
-    ELOC_HIP(c, launch_sample_radius(W, c->keys.as<uint64_t>(), n_unique, c->bitcounts.as<uint32_t>(),
-                                     c->rad.as<unsigned long long>(), c->stream));
     // Bloom filter of U: about 4 bits per key, at most 32 KB (it is staged in
     // LDS); none for batches too large for it to reject much
     c->bloom_words = n_unique <= (int64_t(1) << 17)
@@ -1016,7 +1046,7 @@ int eloc_set_samples(eloc_ctx c, int64_t n_unique, const uint64_t* keys_dev) {
     // table insert, verification and prefilter parameters, all on the
     // device: errors (duplicates, bits >= N, a table that did not settle)
     // stay latched in the preparation error word until a synchronising call
-    const int rc = build_sample_table(c);
+    const int rc = build_sample_table(c, false);
     if (rc) return rc;
     c->part_ok = false;
     c->S.part.bits = 0;
@@ -1062,8 +1092,7 @@ int eloc_local_energy(eloc_ctx c, int variant, int precision, const eloc_c64* lo
     if (rc) return rc;
     const int64_t M = c->S.n;
     const bool fp32 = precision == ELOC_FP32C;
-    ELOC_HIP(c, hipMemsetAsync(c->err_run.p, 0, sizeof(uint32_t), c->stream));
-    rc = amp_prep(c, logpsi_dev, fp32);
+    rc = amp_prep(c, logpsi_dev, fp32, true);
     if (rc) return rc;
     Plan P;
     rc = row_sums(c, false, variant, precision, c->a.as<double2>(), c->af.as<float4>(), &P);
@@ -1137,9 +1166,8 @@ int eloc_local_energy_noalloc(eloc_ctx c, int variant, int precision, const eloc
     float4* bf = fp32 ? reinterpret_cast<float4*>(ws + o_bf) : nullptr;
     double* shift = reinterpret_cast<double*>(ws + o_shift);
     void* partial = ws + o_part;
-    ELOC_HIP(c, launch_fill_u32(c->err_run.as<uint32_t>(), 1, 0u, c->stream));
     ELOC_HIP(c, launch_amp_prep(reinterpret_cast<const double2*>(logpsi_dev), M, fp32, a, b, af, bf, shift,
-                                reinterpret_cast<double*>(ws + o_amp), c->err_run.as<uint32_t>(), c->stream));
+                                reinterpret_cast<double*>(ws + o_amp), c->err_run.as<uint32_t>(), true, c->stream));
     if (variant == ELOC_STORED) {
         const void* v = fp32 ? static_cast<const void*>(af) : static_cast<const void*>(a);
         ELOC_HIP(c, launch_spmv(false, precision, M, c->st_rowptr.as<int64_t>(), c->st_col.as<int32_t>(),
@@ -1307,8 +1335,6 @@ int eloc_local_energy_full(eloc_ctx c, int precision, const eloc_c64* logpsi_dev
     ELOC_HIP(c, launch_sample_hash(W, c->x_keys.as<uint64_t>(), X, c->R_dev.as<uint64_t>(), c->H.n_qubits,
                                    c->x_hash.as<uint64_t>(), c->x_bitcounts.as<uint32_t>(), c->x_err.as<uint32_t>(),
                                    c->stream));
-    ELOC_HIP(c, launch_sample_radius(W, c->x_keys.as<uint64_t>(), X, c->x_bitcounts.as<uint32_t>(),
-                                     c->x_rad.as<unsigned long long>(), c->stream));
     SampleDev S;
     S.n = X;
     S.rows = M;
@@ -1332,8 +1358,9 @@ int eloc_local_energy_full(eloc_ctx c, int precision, const eloc_c64* logpsi_dev
         if (attempt > 0) ELOC_HIP(c, hipMemsetAsync(c->x_err.p, 0, sizeof(uint32_t), c->stream));
         ELOC_HIP(c, launch_table_insert(tk, c->x_hash.as<uint64_t>(), X, c->x_slots.p, c->x_stash.as<Stash>(), S.table,
                                         c->x_err.as<uint32_t>(), c->stream));
-        ELOC_HIP(c, launch_sample_verify(W, c->H.narrow, S, c->x_sig.as<uint64_t>(), c->x_err.as<uint32_t>(),
-                                         c->stream));
+        ELOC_HIP(c, launch_sample_verify(W, c->H.narrow, S, c->x_bitcounts.as<uint32_t>(),
+                                         c->x_rad.as<unsigned long long>(), c->x_sig.as<uint64_t>(),
+                                         c->x_err.as<uint32_t>(), c->stream));
         ELOC_HIP(c, launch_sample_params(c->x_sig.as<uint64_t>(), c->x_rad.as<unsigned long long>(), c->H.n_qubits,
                                          c->x_params.as<SampleParams>(), c->stream));
         const int b = read_err(c, c->x_err);
@@ -1344,7 +1371,6 @@ int eloc_local_energy_full(eloc_ctx c, int precision, const eloc_c64* logpsi_dev
     if (bits & kErrTable) return fail(c, ELOC_EHIP, "membership table could not be built");
     if (bits & kErrDup) return fail(c, ELOC_EDUP, "an extra state repeats or is in U");
     // amplitudes over X, LoopOverTerms over U's rows, row combination
-    ELOC_HIP(c, hipMemsetAsync(c->err_run.p, 0, sizeof(uint32_t), c->stream));
     ELOC_HIP(c, c->x_a.ensure(sizeof(double2) * X));
     ELOC_HIP(c, c->x_b.ensure(sizeof(double2) * X));
     ELOC_HIP(c, c->x_af.ensure(sizeof(float4) * (fp32 ? X : 1)));
@@ -1353,7 +1379,7 @@ int eloc_local_energy_full(eloc_ctx c, int precision, const eloc_c64* logpsi_dev
     ELOC_HIP(c, c->amp_scratch.ensure(sizeof(double) * amp_scratch_len()));
     ELOC_HIP(c, launch_amp_prep(c->x_logpsi.as<double2>(), X, fp32, c->x_a.as<double2>(), c->x_b.as<double2>(),
                                 c->x_af.as<float4>(), c->x_bf.as<float4>(), c->x_shift.as<double>(),
-                                c->amp_scratch.as<double>(), c->err_run.as<uint32_t>(), c->stream));
+                                c->amp_scratch.as<double>(), c->err_run.as<uint32_t>(), true, c->stream));
     Plan P = make_plan(c, ELOC_TERMS, M);
     P.bloom_words = 0;
     S.part.bits = 0;
@@ -1590,15 +1616,18 @@ int eloc_trie_visits(eloc_ctx c, int64_t* visits_host) {
 
 int eloc_check(eloc_ctx c) {
     if (!c) return ELOC_EINVAL;
+    uint32_t bits = 0;
     if (c->samples_set) {
         bool rebuilt = false;
-        const int rc = samples_verdict(c, &rebuilt);
+        const int rc = samples_verdict(c, &rebuilt, &bits);
         if (rc) return rc;
         if (rebuilt)
             return fail(c, ELOC_EAGAIN, "U's membership table was rebuilt with a new salt; repeat the last call");
+    } else {
+        const int b = read_err(c, c->err_run);
+        if (b < 0) return b;
+        bits = static_cast<uint32_t>(b);
     }
-    const int bits = read_err(c, c->err_run);
-    if (bits < 0) return bits;
     // a run error is reported once: the word is cleared for the calls after it
     if (bits) ELOC_HIP(c, hipMemsetAsync(c->err_run.p, 0, sizeof(uint32_t), c->stream));
     return map_err(c, static_cast<uint32_t>(bits));
@@ -1710,8 +1739,7 @@ int eloc_local_energy_adjoint(eloc_ctx c, int variant, int precision, const eloc
     if (rc) return rc;
     const int64_t M = c->S.n;
     const bool fp32 = precision == ELOC_FP32C;
-    ELOC_HIP(c, hipMemsetAsync(c->err_run.p, 0, sizeof(uint32_t), c->stream));
-    rc = amp_prep(c, logpsi_dev, fp32);
+    rc = amp_prep(c, logpsi_dev, fp32, true);
     if (rc) return rc;
     ELOC_HIP(c, c->v.ensure(sizeof(double2) * M));
     ELOC_HIP(c, c->vf.ensure(sizeof(float4) * (fp32 ? M : 1)));

@@ -756,21 +756,23 @@ struct BatchDev {
 // ---------------------------------------------------------------------------
 hipError_t launch_sample_hash(int W, const uint64_t* keys, int64_t n, const uint64_t* R,
                               int n_qubits, uint64_t* hash, uint32_t* counts, uint32_t* err, hipStream_t st);
-// rad[0..W-1] = per-qubit majority key of U (from the counts), rad[2] = max
-// distance of U's keys from it (rad[2] must start at 0).
-hipError_t launch_sample_radius(int W, const uint64_t* keys, int64_t n, const uint32_t* counts,
-                                unsigned long long* rad, hipStream_t st);
+// state[0..state_words) and the table's slots cleared, keys[0..n_words) copied.
+hipError_t launch_sample_begin(uint32_t* state, int state_words, void* slots, size_t slots_bytes,
+                               const uint64_t* from, uint64_t* keys, int64_t n_words, hipStream_t st);
 hipError_t launch_bloom_build(const uint64_t* hash, int64_t n, uint32_t* filt, uint32_t words, hipStream_t st);
 hipError_t launch_table_insert(int table_kind, const uint64_t* hash, int64_t n, void* slots, Stash* stash,
                                const Table& T, uint32_t* err, hipStream_t st);
-hipError_t launch_sample_verify(int W, bool narrow, const SampleDev& S, uint64_t* sig, uint32_t* err,
-                                hipStream_t st);
-// SampleParams from the signature bitmap and the radius words (one thread).
+// rad[0..W-1] = per-qubit majority key of U (from the counts), rad[2] = max
+// distance of U's keys from it (rad[2] must start at 0).
+hipError_t launch_sample_verify(int W, bool narrow, const SampleDev& S, const uint32_t* counts,
+                                unsigned long long* rad, uint64_t* sig, uint32_t* err, hipStream_t st);
+// SampleParams from the signature bitmap and the radius words (one wave).
 hipError_t launch_sample_params(const uint64_t* sig, const unsigned long long* rad, int n_qubits,
                                 SampleParams* out, hipStream_t st);
+// clear_err: *err = 0 first.
 hipError_t launch_amp_prep(const double2* logpsi, int64_t n, bool fp32, double2* a, double2* b,
                            float4* af, float4* bf, double* shift, double* scratch, uint32_t* err,
-                           hipStream_t st);
+                           bool clear_err, hipStream_t st);
 hipError_t launch_adj_vec(const double2* a, const double2* b, const double* weights, int64_t n,
                           bool fp32, double2* v, float4* vf, hipStream_t st);
 hipError_t launch_pairs(bool adjoint, int variant, int precision, const HamDev& H,
@@ -1016,8 +1018,6 @@ constexpr size_t kNoAllocBytes = size_t(64) << 20;
 // Device address of this device's workspace (`device` must be current on
 // the first call for it); cached per device.
 hipError_t noalloc_workspace(int device, void** out);
-// p[0..n) = v (a kernel, so that code under stream capture records no memset)
-hipError_t launch_fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t st);
 
 int64_t energy_scratch_len();
 int64_t amp_scratch_len();

@@ -28,8 +28,8 @@ __global__ __launch_bounds__(kBlock) void k_sample_hash(const uint64_t* __restri
     __shared__ uint32_t lc[64 * W];   // per-qubit counts of set bits in this block
     for (int t = threadIdx.x; t < 64 * W; t += kBlock) lc[t] = 0u;
     __syncthreads();
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
-    if (i < n) {
+    const int64_t step = static_cast<int64_t>(gridDim.x) * kBlock;
+    for (int64_t i = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; i < n; i += step) {
         uint64_t h = 0;
         bool bad = false;
 #pragma unroll
@@ -66,34 +66,6 @@ __global__ __launch_bounds__(kBlock) void k_bloom_build(const uint64_t* __restri
     atomicOr(filt + bloom_word(hf, fmask), bloom_bits(hf));
 }
 
-// Radius filter of LoopOverTerms: reference key c = per-qubit majority of U
-// (rad[0..W-1]), then rad[2] = max over U of |x ^ c|.  A candidate farther
-// than that from c is not in U.
-template <int W>
-__global__ void k_radius_ref(const uint32_t* __restrict__ counts, int64_t n, unsigned long long* __restrict__ rad) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    for (int w = 0; w < W; ++w) {
-        uint64_t c = 0;
-        for (int q = 0; q < 64; ++q)
-            if (2 * static_cast<int64_t>(counts[64 * w + q]) > n) c |= 1ull << q;
-        rad[w] = c;
-    }
-}
-
-template <int W>
-__global__ __launch_bounds__(kBlock) void k_radius_max(const uint64_t* __restrict__ keys, int64_t n,
-                                                       unsigned long long* __restrict__ rad) {
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
-    int d = 0;
-    if (i < n) {
-#pragma unroll
-        for (int w = 0; w < W; ++w) d += popc64(keys[i * W + w] ^ rad[w]);
-    }
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) d = max(d, __shfl_xor(d, m, 64));
-    if ((threadIdx.x & 63) == 0) atomicMax(rad + 2, static_cast<unsigned long long>(d));
-}
-
 template <int TK>
 __global__ __launch_bounds__(kBlock) void k_table_insert(const uint64_t* __restrict__ hash, int64_t n, void* slots,
                                                          Stash* __restrict__ stash, Table T,
@@ -103,47 +75,89 @@ __global__ __launch_bounds__(kBlock) void k_table_insert(const uint64_t* __restr
     table_insert_one<TK>(hash, i, slots, stash, T, err, static_cast<uint32_t>(kErrTable));
 }
 
-// Duplicate check (every key must find itself) and the signature bitmap of
-// (popcount on even qubits, popcount on odd qubits) over U.
+// Duplicate check (every key must find itself), the signature bitmap of
+// (popcount on even qubits, popcount on odd qubits) over U, and the radius
+// filter of LoopOverTerms: reference key c = per-qubit majority of U (from
+// the counts; rad[0..W-1]), rad[2] = max over U of |x ^ c|.  A candidate
+// farther than that from c is not in U.  What a workgroup finds goes to the
+// few words of the result once, and the workgroups are few: an atomic a wave
+// on one word took 290 us over 2^22 keys (a workgroup's keys 93).
 template <int W, int TK>
 __global__ __launch_bounds__(kBlock) void k_sample_verify(const uint64_t* __restrict__ keys,
                                                           const uint64_t* __restrict__ hash, int64_t n,
-                                                          Table T, uint64_t* __restrict__ sig,
-                                                          uint32_t* __restrict__ err) {
+                                                          Table T, const uint32_t* __restrict__ counts,
+                                                          unsigned long long* __restrict__ rad,
+                                                          uint64_t* __restrict__ sig, uint32_t* __restrict__ err) {
     __shared__ unsigned long long lsig[kSigWords];
+    __shared__ uint64_t ref[W];
+    __shared__ int far;
     for (int t = threadIdx.x; t < kSigWords; t += kBlock) lsig[t] = 0ull;
+    if (threadIdx.x < 64 * W) {
+        const uint64_t m = __ballot(2 * static_cast<int64_t>(counts[threadIdx.x]) > n);
+        if ((threadIdx.x & 63) == 0) ref[threadIdx.x / 64] = m;
+    }
+    if (threadIdx.x == 0) far = 0;
     __syncthreads();
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
-    if (i < n) {
+    int d = 0;
+    bool dup = false;
+    const int64_t step = static_cast<int64_t>(gridDim.x) * kBlock;
+    for (int64_t i = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; i < n; i += step) {
         uint64_t k[W];
-        int pa = 0, pb = 0;
+        int pa = 0, pb = 0, di = 0;
 #pragma unroll
         for (int w = 0; w < W; ++w) {
             k[w] = keys[i * W + w];
             pa += popc64(k[w] & kEven);
             pb += popc64(k[w] & kOdd);
+            di += popc64(k[w] ^ ref[w]);
         }
+        d = max(d, di);
         const int j = table_find<TK, W>(T, keys, hash[i], k);
-        if (j != static_cast<int>(i)) atomicOr(err, static_cast<uint32_t>(kErrDup));
-        atomicOr(&lsig[2 * pa + (pb >> 6)], 1ull << (pb & 63));
+        dup = dup || j != static_cast<int>(i);
+        const unsigned long long bit = 1ull << (pb & 63);
+        if (!(lsig[2 * pa + (pb >> 6)] & bit)) atomicOr(&lsig[2 * pa + (pb >> 6)], bit);
     }
+    if (dup) atomicOr(err, static_cast<uint32_t>(kErrDup));
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) d = max(d, __shfl_xor(d, m, 64));
+    if ((threadIdx.x & 63) == 0) atomicMax(&far, d);
     __syncthreads();
     for (int t = threadIdx.x; t < kSigWords; t += kBlock)
         if (lsig[t]) atomicOr(reinterpret_cast<unsigned long long*>(sig + t), lsig[t]);
+    if (threadIdx.x == 0) atomicMax(rad + 2, static_cast<unsigned long long>(far));
+    if (blockIdx.x == 0 && threadIdx.x < W) rad[threadIdx.x] = ref[threadIdx.x];
+}
+
+// The start of a set of samples: the state words and the table's slots
+// cleared, the keys copied; one launch for what were eight copies and fills.
+__global__ __launch_bounds__(kBlock) void k_sample_begin(uint32_t* __restrict__ state, int state_words,
+                                                         uint4* __restrict__ slots, int64_t n_slots16,
+                                                         const uint64_t* __restrict__ from, uint64_t* __restrict__ keys,
+                                                         int64_t n_words) {
+    const int64_t i0 = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
+    const int64_t step = static_cast<int64_t>(gridDim.x) * kBlock;
+    for (int64_t i = i0; i < state_words; i += step) state[i] = 0u;
+    for (int64_t i = i0; i < n_slots16; i += step) slots[i] = make_uint4(0u, 0u, 0u, 0u);
+    for (int64_t i = i0; i < n_words; i += step) keys[i] = from[i];
 }
 
 // Prefilter parameters of U from the signature bitmap (a single set bit:
 // U's only (even, odd) popcount signature) and the radius words (majority
 // key, largest distance from it; used when under half the qubits).
-__global__ void k_sample_params(const uint64_t* __restrict__ sig, const unsigned long long* __restrict__ rad,
-                                int n_qubits, SampleParams* __restrict__ out) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    int nsig = 0, first = -1;
-    for (int k = 0; k < kSigWords; ++k) {
+__global__ __launch_bounds__(64) void k_sample_params(const uint64_t* __restrict__ sig,
+                                                      const unsigned long long* __restrict__ rad, int n_qubits,
+                                                      SampleParams* __restrict__ out) {
+    int nsig = 0, first = kSigWords;
+    for (int k = threadIdx.x; k < kSigWords; k += 64) {
         const uint64_t v = sig[k];
-        if (v && first < 0) first = k;
+        if (v) first = min(first, k);
         nsig += popc64(v);
     }
+    for (int m = 32; m >= 1; m >>= 1) {
+        nsig += __shfl_xor(nsig, m);
+        first = min(first, __shfl_xor(first, m));
+    }
+    if (threadIdx.x != 0) return;
     SampleParams p;
     p.sig_all = nsig == 1 ? 0 : 1;
     p.sig_pa = 0;
@@ -164,8 +178,9 @@ __global__ void k_sample_params(const uint64_t* __restrict__ sig, const unsigned
 constexpr int kRedBlocks = 256;   // fixed partition of reductions over U
 
 __global__ __launch_bounds__(kBlock) void k_minmax_partial(const double2* __restrict__ L, int64_t n,
-                                                           double* __restrict__ part) {
+                                                           double* __restrict__ part, uint32_t* __restrict__ clear) {
     __shared__ double lds[2][kBlock];
+    if (clear && blockIdx.x == 0 && threadIdx.x == 0) *clear = 0u;
     double mx = -INFINITY, mn = INFINITY;
     for (int64_t i = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; i < n;
          i += static_cast<int64_t>(kRedBlocks) * kBlock) {
@@ -195,12 +210,23 @@ __global__ __launch_bounds__(kBlock) void k_amp_prep(const double2* __restrict__
                                                      double2* __restrict__ a, double2* __restrict__ b,
                                                      float4* __restrict__ af, float4* __restrict__ bf,
                                                      double* __restrict__ shift, uint32_t* __restrict__ err) {
-    __shared__ double cmax;
+    __shared__ double cmax, pmx[kBlock / 64], pmn[kBlock / 64];
+    static_assert(kBlock == kRedBlocks, "a partial a thread");
+    double mx = part[2 * threadIdx.x], mn = part[2 * threadIdx.x + 1];
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) {
+        mx = fmax(mx, shfl_xor_d(mx, m));
+        mn = fmin(mn, shfl_xor_d(mn, m));
+    }
+    if ((threadIdx.x & 63) == 0) {
+        pmx[threadIdx.x / 64] = mx;
+        pmn[threadIdx.x / 64] = mn;
+    }
+    __syncthreads();
     if (threadIdx.x == 0) {
-        double mx = -INFINITY, mn = INFINITY;
-        for (int k = 0; k < kRedBlocks; ++k) {
-            mx = fmax(mx, part[2 * k]);
-            mn = fmin(mn, part[2 * k + 1]);
+        for (int w = 1; w < kBlock / 64; ++w) {
+            mx = fmax(mx, pmx[w]);
+            mn = fmin(mn, pmn[w]);
         }
         cmax = mx;
         if (blockIdx.x == 0) {
@@ -391,40 +417,39 @@ __global__ __launch_bounds__(kBlock) void k_energy_p1(const double2* __restrict_
     }
 }
 
-__global__ __launch_bounds__(kBlock) void k_energy_mid(const double* __restrict__ part,
-                                                       const double* __restrict__ weights,
-                                                       const double* __restrict__ shift,
-                                                       double* __restrict__ stats, double* __restrict__ scal,
-                                                       uint32_t* __restrict__ err) {
-    __shared__ double lds[3][kBlock];
-    double v[3] = {0.0, 0.0, 0.0};
-    for (int k = threadIdx.x; k < kRedBlocks; k += kBlock) {
-        v[0] += part[3 * k];
-        v[1] += part[3 * k + 1];
-        v[2] += part[3 * k + 2];
-    }
-    block_sum<3, kBlock>(v, lds);
-    if (threadIdx.x == 0) {
-        const double tot = v[0];
-        if (!(tot > 0.0) || !isfinite(tot)) atomicOr(err, static_cast<uint32_t>(kErrWeights));
-        const double er = v[1] / tot, ei = v[2] / tot;
-        stats[0] = er;
-        stats[1] = ei;
-        stats[3] = weights ? tot : tot * exp(2.0 * shift[0]);
-        scal[0] = er;
-        scal[1] = ei;
-        scal[2] = tot;
-    }
-}
-
+// Every workgroup adds up the partials of p1 by itself; the first one writes
+// the statistics.  part2: the variance's partials.
 __global__ __launch_bounds__(kBlock) void k_energy_p2(const double2* __restrict__ eloc,
                                                       const double2* __restrict__ L,
                                                       const double* __restrict__ weights,
                                                       const double* __restrict__ shift, int64_t n,
-                                                      const double* __restrict__ scal, double* __restrict__ part) {
-    __shared__ double lds[1][kBlock];
+                                                      const double* __restrict__ part, double* __restrict__ stats,
+                                                      double* __restrict__ scal, double* __restrict__ part2,
+                                                      uint32_t* __restrict__ err) {
+    __shared__ double lds[3][kBlock];
+    __shared__ double tot3[3];
     const double c = shift[0];
-    const double er = scal[0], ei = scal[1];
+    double s3[3] = {0.0, 0.0, 0.0};
+    for (int k = threadIdx.x; k < kRedBlocks; k += kBlock) {
+        s3[0] += part[3 * k];
+        s3[1] += part[3 * k + 1];
+        s3[2] += part[3 * k + 2];
+    }
+    block_sum<3, kBlock>(s3, lds);
+    if (threadIdx.x == 0) {
+        const double tot = s3[0];
+        tot3[0] = s3[1] / tot;
+        tot3[1] = s3[2] / tot;
+        if (blockIdx.x == 0) {
+            if (!(tot > 0.0) || !isfinite(tot)) atomicOr(err, static_cast<uint32_t>(kErrWeights));
+            stats[0] = tot3[0];
+            stats[1] = tot3[1];
+            stats[3] = weights ? tot : tot * exp(2.0 * c);
+            scal[0] = tot;
+        }
+    }
+    __syncthreads();
+    const double er = tot3[0], ei = tot3[1];
     double v[1] = {0.0};
     bool bad = false;
     for (int64_t i = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; i < n;
@@ -435,7 +460,7 @@ __global__ __launch_bounds__(kBlock) void k_energy_p2(const double2* __restrict_
         v[0] += w * (dr * dr + di * di);
     }
     block_sum<1, kBlock>(v, lds);
-    if (threadIdx.x == 0) part[blockIdx.x] = v[0];
+    if (threadIdx.x == 0) part2[blockIdx.x] = v[0];
 }
 
 __global__ __launch_bounds__(kBlock) void k_energy_p3(const double* __restrict__ part,
@@ -445,7 +470,7 @@ __global__ __launch_bounds__(kBlock) void k_energy_p3(const double* __restrict__
     double v[1] = {0.0};
     for (int k = threadIdx.x; k < kRedBlocks; k += kBlock) v[0] += part[k];
     block_sum<1, kBlock>(v, lds);
-    if (threadIdx.x == 0) stats[2] = v[0] / scal[2];
+    if (threadIdx.x == 0) stats[2] = v[0] / scal[0];
 }
 
 __global__ __launch_bounds__(kBlock) void k_asum_partial(const double2* __restrict__ a, int64_t n,
@@ -709,11 +734,8 @@ __global__ __launch_bounds__(kBlock) void k_trie_build(const uint64_t* __restric
 }
 
 inline unsigned blocks_for(int64_t n) { return static_cast<unsigned>((n + kBlock - 1) / kBlock); }
-
-__global__ void k_fill_u32(uint32_t* __restrict__ p, int64_t n, uint32_t v) {
-    const int64_t t = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (t < n) p[t] = v;
-}
+// Workgroups of the kernels that end in atomics on a few words.
+inline unsigned few_blocks(int64_t n) { return std::min<unsigned>(blocks_for(n), 1024u); }
 
 // Partition classes of U's rows (hash_part of the unsalted hash).
 __global__ void k_class_keys(const uint64_t* __restrict__ hash, int64_t n, int shift, int bits,
@@ -761,10 +783,10 @@ __global__ void k_class_bounds(const uint64_t* __restrict__ key, const uint32_t*
 hipError_t launch_sample_hash(int W, const uint64_t* keys, int64_t n, const uint64_t* R, int n_qubits,
                               uint64_t* hash, uint32_t* counts, uint32_t* err, hipStream_t st) {
     if (W == 1)
-        hipLaunchKernelGGL(k_sample_hash<1>, dim3(blocks_for(n)), dim3(kBlock), 0, st, keys, n, R, n_qubits, hash,
+        hipLaunchKernelGGL(k_sample_hash<1>, dim3(few_blocks(n)), dim3(kBlock), 0, st, keys, n, R, n_qubits, hash,
                            counts, err);
     else
-        hipLaunchKernelGGL(k_sample_hash<2>, dim3(blocks_for(n)), dim3(kBlock), 0, st, keys, n, R, n_qubits, hash,
+        hipLaunchKernelGGL(k_sample_hash<2>, dim3(few_blocks(n)), dim3(kBlock), 0, st, keys, n, R, n_qubits, hash,
                            counts, err);
     return hipGetLastError();
 }
@@ -774,15 +796,11 @@ hipError_t launch_bloom_build(const uint64_t* hash, int64_t n, uint32_t* filt, u
     return hipGetLastError();
 }
 
-hipError_t launch_sample_radius(int W, const uint64_t* keys, int64_t n, const uint32_t* counts,
-                                unsigned long long* rad, hipStream_t st) {
-    if (W == 1) {
-        hipLaunchKernelGGL(k_radius_ref<1>, dim3(1), dim3(64), 0, st, counts, n, rad);
-        hipLaunchKernelGGL(k_radius_max<1>, dim3(blocks_for(n)), dim3(kBlock), 0, st, keys, n, rad);
-    } else {
-        hipLaunchKernelGGL(k_radius_ref<2>, dim3(1), dim3(64), 0, st, counts, n, rad);
-        hipLaunchKernelGGL(k_radius_max<2>, dim3(blocks_for(n)), dim3(kBlock), 0, st, keys, n, rad);
-    }
+hipError_t launch_sample_begin(uint32_t* state, int state_words, void* slots, size_t slots_bytes,
+                               const uint64_t* from, uint64_t* keys, int64_t n_words, hipStream_t st) {
+    const int64_t n16 = static_cast<int64_t>(slots_bytes / sizeof(uint4));   // tables are powers of two from 1 KB
+    hipLaunchKernelGGL(k_sample_begin, dim3(few_blocks(std::max(n16, n_words))), dim3(kBlock), 0, st, state,
+                       state_words, static_cast<uint4*>(slots), n16, from, keys, n_words);
     return hipGetLastError();
 }
 
@@ -798,14 +816,18 @@ hipError_t launch_table_insert(int table_kind, const uint64_t* hash, int64_t n, 
     return hipGetLastError();
 }
 
-hipError_t launch_sample_verify(int W, bool narrow, const SampleDev& S, uint64_t* sig, uint32_t* err, hipStream_t st) {
-    const dim3 grid(blocks_for(S.n)), block(kBlock);
+hipError_t launch_sample_verify(int W, bool narrow, const SampleDev& S, const uint32_t* counts,
+                                unsigned long long* rad, uint64_t* sig, uint32_t* err, hipStream_t st) {
+    const dim3 grid(few_blocks(S.n)), block(kBlock);
     if (W == 2)
-        hipLaunchKernelGGL((k_sample_verify<2, kTabVerify>), grid, block, 0, st, S.keys, S.hash, S.n, S.table, sig, err);
+        hipLaunchKernelGGL((k_sample_verify<2, kTabVerify>), grid, block, 0, st, S.keys, S.hash, S.n, S.table, counts, rad,
+                           sig, err);
     else if (narrow)
-        hipLaunchKernelGGL((k_sample_verify<1, kTabNarrow>), grid, block, 0, st, S.keys, S.hash, S.n, S.table, sig, err);
+        hipLaunchKernelGGL((k_sample_verify<1, kTabNarrow>), grid, block, 0, st, S.keys, S.hash, S.n, S.table, counts, rad,
+                           sig, err);
     else
-        hipLaunchKernelGGL((k_sample_verify<1, kTabWide>), grid, block, 0, st, S.keys, S.hash, S.n, S.table, sig, err);
+        hipLaunchKernelGGL((k_sample_verify<1, kTabWide>), grid, block, 0, st, S.keys, S.hash, S.n, S.table, counts, rad,
+                           sig, err);
     return hipGetLastError();
 }
 
@@ -829,8 +851,10 @@ hipError_t launch_row_classes(const uint64_t* hash, int64_t n, int shift, int bi
 }
 
 hipError_t launch_amp_prep(const double2* logpsi, int64_t n, bool fp32, double2* a, double2* b, float4* af,
-                           float4* bf, double* shift, double* scratch, uint32_t* err, hipStream_t st) {
-    hipLaunchKernelGGL(k_minmax_partial, dim3(kRedBlocks), dim3(kBlock), 0, st, logpsi, n, scratch);
+                           float4* bf, double* shift, double* scratch, uint32_t* err, bool clear_err,
+                           hipStream_t st) {
+    hipLaunchKernelGGL(k_minmax_partial, dim3(kRedBlocks), dim3(kBlock), 0, st, logpsi, n, scratch,
+                       clear_err ? err : nullptr);
     hipLaunchKernelGGL(k_amp_prep, dim3(blocks_for(n)), dim3(kBlock), 0, st, logpsi, n, scratch, fp32 ? 1 : 0, a,
                        b, af, bf, shift, err);
     return hipGetLastError();
@@ -873,17 +897,17 @@ hipError_t launch_adj_finish(int precision, int64_t n, const Plan& P, const void
 
 hipError_t launch_energy(const double2* eloc, const double2* logpsi, const double* weights, const double* shift,
                          int64_t n, double* stats, double* scratch, uint32_t* err, hipStream_t st) {
-    double* part = scratch;                 // 3 * kRedBlocks
-    double* scal = scratch + 3 * kRedBlocks;  // 3
+    double* part = scratch;                    // 3 * kRedBlocks
+    double* part2 = part + 3 * kRedBlocks;     // kRedBlocks
+    double* scal = part2 + kRedBlocks;         // 1
     hipLaunchKernelGGL(k_energy_p1, dim3(kRedBlocks), dim3(kBlock), 0, st, eloc, logpsi, weights, shift, n, part, err);
-    hipLaunchKernelGGL(k_energy_mid, dim3(1), dim3(kBlock), 0, st, part, weights, shift, stats, scal, err);
-    hipLaunchKernelGGL(k_energy_p2, dim3(kRedBlocks), dim3(kBlock), 0, st, eloc, logpsi, weights, shift, n, scal,
-                       part);
-    hipLaunchKernelGGL(k_energy_p3, dim3(1), dim3(kBlock), 0, st, part, scal, stats);
+    hipLaunchKernelGGL(k_energy_p2, dim3(kRedBlocks), dim3(kBlock), 0, st, eloc, logpsi, weights, shift, n, part,
+                       stats, scal, part2, err);
+    hipLaunchKernelGGL(k_energy_p3, dim3(1), dim3(kBlock), 0, st, part2, scal, stats);
     return hipGetLastError();
 }
 
-int64_t energy_scratch_len() { return 3 * kRedBlocks + 4; }
+int64_t energy_scratch_len() { return 4 * kRedBlocks + 4; }
 int64_t amp_scratch_len() { return 2 * kRedBlocks; }
 
 int64_t scan_scratch_len(int64_t n) {
@@ -1013,11 +1037,6 @@ hipError_t noalloc_workspace(int device, void** out) {
     }
     *out = g_ws_ptr[device];
     return hipSuccess;
-}
-
-hipError_t launch_fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t st) {
-    hipLaunchKernelGGL(k_fill_u32, dim3(blocks_for(n)), dim3(kBlock), 0, st, p, n, v);
-    return hipGetLastError();
 }
 
 }  // namespace eloc

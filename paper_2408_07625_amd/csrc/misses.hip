@@ -25,7 +25,7 @@
 // bit in a bitmap over the key space instead, U's bits are cleared after it
 // (no lookups), and the set bits, read in order, are the unique states
 // already sorted.  20 000 rows by 10 466 groups, a third of them non-zero:
-// 3.6 ms with a lookup, the run's sum and an atomic for each, @@ this way.
+// 3.6 ms with a lookup, the run's sum and an atomic for each, 0.97 this way.
 #include "device.h"
 
 #include <hip/hip_runtime.h>
