@@ -71,9 +71,7 @@ struct eloc_ctx_s {
     DevBuf pe_cnt, pe_grp;   // pair_elements: term counts and groups of the pairs
     DevBuf xyt_keys, xyt_gid, xyt_nodes, xyt_nkeys;
     // spin-string join: the masks by spin part
-    JoinHamDev JH;
-    DevBuf jh_alist, jh_amask, jh_blist, jh_bmask, jh_bc, jh_bo, jh_ao, jh_runs, jh_gids, jh_place, jh_sign, jh_linear;
-    bool jh_split = false;   // its pairs allow the heavy / light split
+    JoinMasks JH;
 
     bool samples_set = false;
     SampleDev S;
@@ -90,12 +88,9 @@ struct eloc_ctx_s {
     bool part_ok = false;                      // U's table is partitioned and its rows classed
     int part_bits = 0;                         // 2^part_bits partitions of U's table (0: none)
     DevBuf s_key, s_val, s_key2, s_val2;   // sort scratch
-    // spin-string join: U in two sorted orders.  The buffers (with their own
-    // sort scratch) are sized by eloc_set_samples alone, the index is built by
-    // the first call that reads it
-    JoinDev J;
-    DevBuf j_key, j_val, j_key2, j_val2, j_hist, j_hist_off, j_hist_scan;
-    DevBuf j_perm, j_group, j_scan, j_cross, j_vec, j_slots, j_heavy, j_heavy_slots, j_core;
+    // spin-string join: U in two sorted orders.  The buffers are sized by
+    // eloc_set_samples alone, the index is built by the first call that reads it
+    JoinIndex J;
     bool j_room = false, j_built = false;
 
     DevBuf a, b, af, bf, v, vf, shift, amp_scratch;
@@ -180,43 +175,25 @@ int resolve_variant(const eloc_ctx c, int v) {
 
 // The spin-string join replaces the search of a variant where the
 // Hamiltonian's masks factor by spin, the caller has not tuned the loops'
-// launch shape, and the loop's candidates outweigh the join: the loops take
-// about 6.5e8 candidates a millisecond (|U| |XY| for LoopOverTerms, |U|^2 for
-// LoopOverBatch; LoopOverTrie costs about eight of them per |U| |XY|), the join
-// about 0.2 ms for U's two orders and 6 to 15 ns a sample.  Measured, loop /
-// join: LoopOverTerms, 28 qubits, 65 536 samples (6.9e8) 1.09 / 0.53 ms;
-// 52 qubits, 2^20 (1.4e11) 97 / 18 ms; LoopOverBatch, 40 qubits, 9999 samples
-// (1.0e8) 0.16 / 0.24 ms.
+// launch shape, and the loop's candidates outweigh the join.
 bool use_join(const eloc_ctx c, int64_t M, int variant) {
-    if (!c->JH.ok || c->tune_chunks || !c->tune_sig || c->tune_rows || c->tune_bloom || c->tune_waves ||
+    if (!c->JH.dev.ok || c->tune_chunks || !c->tune_sig || c->tune_rows || c->tune_bloom || c->tune_waves ||
         c->tune_part || c->tune_part_count || c->tune_trie_chunk)
         return false;
-    const int64_t loop = variant == ELOC_BATCH ? M * M : M * c->H.n_groups * (variant == ELOC_TRIE ? 8 : 1);
-    return loop >= (int64_t(1) << 27) + (M << 12);
+    return join_pays(M, variant == ELOC_BATCH ? M * M : M * c->H.n_groups * (variant == ELOC_TRIE ? 8 : 1));
 }
 
-// Room for the index of n samples (nothing is allocated when it is built;
-// eloc_set_samples makes it for the variants that may not allocate later).
+// Room for the index of n samples (eloc_set_samples makes it for the variants
+// that may not allocate later).  Without the memory for it the loops serve.
 int join_room(eloc_ctx c, int64_t n) {
-    const size_t st = c->H.W == 1 ? sizeof(uint32_t) : sizeof(uint64_t);
-    const int64_t tiles = radix_tiles(2 * n);
-    ELOC_HIP(c, c->j_key.ensure(sizeof(uint64_t) * 2 * n));
-    ELOC_HIP(c, c->j_key2.ensure(sizeof(uint64_t) * 2 * n));
-    ELOC_HIP(c, c->j_val.ensure(sizeof(uint32_t) * 2 * n));
-    ELOC_HIP(c, c->j_val2.ensure(sizeof(uint32_t) * 2 * n));
-    ELOC_HIP(c, c->j_hist.ensure(sizeof(uint32_t) * 256 * tiles));
-    ELOC_HIP(c, c->j_hist_off.ensure(sizeof(int64_t) * (256 * tiles + 1)));
-    ELOC_HIP(c, c->j_hist_scan.ensure(sizeof(int64_t) * scan_scratch_len(256 * tiles)));
-    ELOC_HIP(c, c->j_perm.ensure(sizeof(int32_t) * 2 * n));
-    ELOC_HIP(c, c->j_group.ensure(st * 2 * n));
-    ELOC_HIP(c, c->j_scan.ensure(st * 2 * n));
-    ELOC_HIP(c, c->j_vec.ensure(sizeof(double2) * 2 * n));
-    ELOC_HIP(c, c->j_slots.ensure(sizeof(JoinBucket) * (size_t(2) << join_bucket_bits(n))));
-    ELOC_HIP(c, c->j_cross.ensure(st * n));
-    ELOC_HIP(c, c->j_heavy.ensure(sizeof(JoinHeavy)));
-    ELOC_HIP(c, c->j_heavy_slots.ensure(2 * st * 2 * kJoinHeavySlots));
-    ELOC_HIP(c, c->j_core.ensure(sizeof(uint32_t) * kJoinCore));
-    c->j_room = true;
+    const hipError_t e = c->J.room(c->H.W, n);
+    c->j_room = e == hipSuccess;
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();
+        c->J.release();
+        return ELOC_OK;
+    }
+    ELOC_HIP(c, e);
     return ELOC_OK;
 }
 
@@ -225,44 +202,8 @@ int join_room(eloc_ctx c, int64_t n) {
 // taken for the calls after it.
 int ensure_join(eloc_ctx c) {
     if (c->j_built) return ELOC_OK;
-    const int64_t n = c->S.n;
-    JoinBuild B;
-    B.keys = c->keys.as<uint64_t>();
-    B.M = n;
-    B.n_qubits = c->H.n_qubits;
-    B.split = c->jh_split;
-    B.key = c->j_key.as<uint64_t>();
-    B.key2 = c->j_key2.as<uint64_t>();
-    B.val = c->j_val.as<uint32_t>();
-    B.val2 = c->j_val2.as<uint32_t>();
-    B.hist = c->j_hist.as<uint32_t>();
-    B.hist_off = c->j_hist_off.as<int64_t>();
-    B.hist_scan = c->j_hist_scan.as<int64_t>();
-    B.perm = c->j_perm.as<int32_t>();
-    B.group = c->j_group.p;
-    B.scan = c->j_scan.p;
-    B.cross = c->j_cross.p;
-    B.slots = c->j_slots.as<JoinBucket>();
-    B.bits = join_bucket_bits(n);
-    B.heavy = c->j_heavy.as<JoinHeavy>();
-    B.heavy_slots = c->j_heavy_slots.p;
-    B.core = c->j_core.as<uint32_t>();
-    ELOC_HIP(c, launch_join_index(c->H.W, B, c->stream));
-    JoinDev J;
-    J.M = n;
-    J.perm = B.perm;
-    J.group = B.group;
-    J.scan = B.scan;
-    J.cross = B.cross;
-    J.vec = c->j_vec.as<double2>();
-    J.keys = B.keys;
-    J.slots = B.slots;
-    J.bits = B.bits;
-    J.heavy = B.heavy;
-    J.heavy_slots = B.heavy_slots;
-    J.core = B.core;
-    J.prep_err = c->err_prep.as<uint32_t>();
-    c->J = J;
+    ELOC_HIP(c, c->J.build(c->H.W, c->keys.as<uint64_t>(), c->S.n, c->H.n_qubits, c->JH.split,
+                           c->err_prep.as<uint32_t>(), c->stream));
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess) (void)hipGetLastError();
     c->j_built = cap == hipStreamCaptureStatusNone;
@@ -292,21 +233,7 @@ void set_part_plan(Plan& P, int64_t M, int bits) {
 Plan make_plan(const eloc_ctx c, int variant, int64_t n_rows = -1, bool allow_part = false) {
     Plan P;
     const int64_t M = n_rows >= 0 ? n_rows : c->S.n;
-    if (variant == kJoin) {
-        // chunk 0: the spin-down order; chunk 1: the heavy-heavy table; then
-        // alist in chunks of at least 16 masks
-        // 16 rows a wave share a scanned column and a bucket lookup, but a
-        // heavy string's wave then runs long: 52 qubits, 2^20 samples, 18.8 ms
-        // with 16 rows, 19.3 with 8; 28 qubits, 65 536, 0.63 with 8, 0.66 with 16
-        P.rows_per_block = M >= (int64_t(1) << 17) ? 16 : 8;
-        const int64_t target = 32768;   // waves
-        const int64_t tiles = (M + P.rows_per_block - 1) / P.rows_per_block;
-        const int64_t chunks = std::max<int64_t>(1, std::min<int64_t>((c->JH.n_a + 15) / 16, (target + tiles - 1) / tiles - 2));
-        P.per_chunk = static_cast<int>((c->JH.n_a + chunks - 1) / chunks);
-        if (P.per_chunk > 64) P.per_chunk = (P.per_chunk + 63) / 64 * 64;
-        P.chunks = 2 + (c->JH.n_a + P.per_chunk - 1) / P.per_chunk;
-        return P;
-    }
+    if (variant == kJoin) return join_plan(c->JH.dev.n_a, M);
     // LoopOverTerms with the prefilters reads U's Bloom filter from LDS when
     // U has one: 4 waves of 4 rows share it; else one wave of 8 rows
     // (the shared filter needs 4-row waves to keep the workgroup's LDS under 64 KB)
@@ -454,27 +381,6 @@ int build_table(eloc_ctx c, int tk, const uint64_t* hash, int64_t n, void* slots
     return fail(c, ELOC_EHIP, "membership table could not be built");
 }
 
-// A function on a thread of its own, joined at the end of the scope at the
-// latest; run in place where no thread can be had.
-class BesideThread {
-public:
-    template <class F>
-    explicit BesideThread(F f) {
-        try {
-            t_ = std::thread(f);
-        } catch (const std::system_error&) {
-            f();
-        }
-    }
-    ~BesideThread() { wait(); }
-    void wait() {
-        if (t_.joinable()) t_.join();
-    }
-
-private:
-    std::thread t_;
-};
-
 template <int W>
 int ingest(eloc_ctx c, int n_qubits, int64_t n_terms, const double* coeff, const uint64_t* xy,
            const uint64_t* yz) {
@@ -485,14 +391,7 @@ int ingest(eloc_ctx c, int n_qubits, int64_t n_terms, const double* coeff, const
     // uploads below (the 74-qubit Hamiltonian of 2.8 million terms: 0.09 s).
     // Without memory for them the loops serve.
     HostJoin<W> hj;
-    BesideThread beside([&hh, &hj, n_qubits] {
-        if (n_qubits > kJoinMaxQubits) return;
-        try {
-            build_host_join<W>(hh, n_qubits, hj);
-        } catch (const std::bad_alloc&) {
-            hj.ok = false;
-        }
-    });
+    BesideThread beside([&hh, &hj, n_qubits] { build_host_join_if<W>(hh, n_qubits, hj); });
     const int64_t G = hh.G;
     const std::vector<GroupRec<W>>& groups = hh.groups;
     const std::vector<TermRec<W>>& terms = hh.terms;
@@ -607,57 +506,7 @@ int ingest(eloc_ctx c, int n_qubits, int64_t n_terms, const double* coeff, const
     H.xyt.chunk = 0;
     H.xyt.chunks = 0;
     beside.wait();
-    JoinHamDev JH;
-    c->jh_split = false;
-    if (hj.ok) {
-        const auto put = [](DevBuf& b, const auto& v) -> hipError_t {
-            const size_t bytes = v.size() * sizeof(v[0]);
-            const hipError_t e = b.ensure(bytes);
-            return e != hipSuccess || bytes == 0 ? e : hipMemcpy(b.p, v.data(), bytes, hipMemcpyHostToDevice);
-        };
-        ELOC_HIP(c, put(c->jh_alist, hj.alist));
-        ELOC_HIP(c, put(c->jh_amask, hj.amask));
-        ELOC_HIP(c, put(c->jh_blist, hj.blist));
-        ELOC_HIP(c, put(c->jh_bmask, hj.bmask));
-        ELOC_HIP(c, put(c->jh_bc, hj.b_cross));
-        ELOC_HIP(c, put(c->jh_bo, hj.b_own));
-        ELOC_HIP(c, put(c->jh_ao, hj.a_own));
-        ELOC_HIP(c, put(c->jh_place, hj.place));
-        ELOC_HIP(c, put(c->jh_sign, hj.sign));
-        ELOC_HIP(c, put(c->jh_linear, hj.linear));
-        ELOC_HIP(c, put(c->jh_runs, hj.runs));
-        ELOC_HIP(c, put(c->jh_gids, hj.gids));
-        JH.ok = true;
-        JH.n_a = static_cast<int>(hj.alist.size());
-        JH.alist = c->jh_alist.p;
-        JH.amask = c->jh_amask.as<JoinMask>();
-        JH.n_b = static_cast<int>(hj.blist.size());
-        JH.blist = c->jh_blist.p;
-        JH.bmask = c->jh_bmask.as<JoinMask>();
-        JH.direct = hj.direct;
-        JH.stride = hj.stride;
-        JH.b_cross = c->jh_bc.p;
-        JH.b_own = c->jh_bo.p;
-        JH.a_own = c->jh_ao.p;
-        JH.b_cross_bits = bits_for(hj.b_cross.size() - 1);
-        JH.b_own_bits = bits_for(hj.b_own.size() - 1);
-        JH.a_own_bits = bits_for(hj.a_own.size() - 1);
-        JH.place = c->jh_place.p;
-        JH.string_bits = join_string_bits(n_qubits);
-        JH.sign = c->jh_sign.as<double>();
-        JH.linear = c->jh_linear.as<double>();
-        JH.runs = c->jh_runs.as<JoinRun>();
-        JH.gids = c->jh_gids.as<int32_t>();
-        JH.places = static_cast<uint32_t>(hj.place.size());
-        JH.cross = hj.cross;
-        JH.nibbles = hj.nibbles;
-        JH.a_base = hj.a_base;
-        JH.a_pmin = hj.a_pmin;
-        JH.a_span = hj.a_span;
-        JH.has_a_own = hj.a_base < hj.place.size();
-        c->jh_split = join_splits(n_qubits, JH, hj.cross_span);
-    }
-    c->JH = JH;
+    ELOC_HIP(c, c->JH.upload(hj, n_qubits));
     c->H = H;
     c->ham_set = true;
     return ELOC_OK;
@@ -781,12 +630,14 @@ int ensure_utrie(eloc_ctx c) {
 int prepare_variant(eloc_ctx c, int* variant) {
     *variant = resolve_variant(c, *variant);
     if (use_join(c, c->S.n, *variant)) {
-        *variant = kJoin;
         if (!c->j_room) {
             const int rc = join_room(c, c->S.n);
             if (rc) return rc;
         }
-        return ensure_join(c);
+        if (c->j_room) {
+            *variant = kJoin;
+            return ensure_join(c);
+        }
     }
     return *variant == ELOC_TRIE ? ensure_utrie(c) : ELOC_OK;
 }
@@ -822,7 +673,7 @@ int row_sums(eloc_ctx c, bool adjoint, int variant, int precision, const double2
         ELOC_HIP(c, launch_spmv(adjoint, precision, M, c->st_rowptr.as<int64_t>(), c->st_col.as<int32_t>(),
                                 c->st_h.as<double2>(), v, c->partial.p, c->stream));
     } else if (variant == kJoin) {
-        ELOC_HIP(c, launch_join_pairs(adjoint, precision, c->H, c->JH, c->J, P, vec, vecf, c->partial.p, c->stream));
+        ELOC_HIP(c, launch_join_pairs(adjoint, precision, c->H, c->JH.dev, c->J.dev, P, vec, vecf, c->partial.p, c->stream));
     } else {
         ELOC_HIP(c, launch_pairs(adjoint, variant, precision, c->H, c->S, P, vec, vecf, c->partial.p, c->stream));
     }
@@ -851,7 +702,7 @@ int count_into_offsets(eloc_ctx c, int variant, const Plan& P, int64_t* total) {
     // the partitioned count skips its writes while U is invalid
     if (P.part) ELOC_HIP(c, hipMemsetAsync(c->counts.p, 0, sizeof(int32_t) * n, c->stream));
     if (variant == kJoin)
-        ELOC_HIP(c, launch_join_count(c->H, c->JH, c->J, P, c->counts.as<int32_t>(), c->stream));
+        ELOC_HIP(c, launch_join_count(c->H, c->JH.dev, c->J.dev, P, c->counts.as<int32_t>(), c->stream));
     else
         ELOC_HIP(c, launch_pairs_count(variant, c->H, c->S, P, c->counts.as<int32_t>(), c->stream));
     ELOC_HIP(c, launch_scan_i32(c->counts.as<int32_t>(), n, c->offsets.as<int64_t>(),
@@ -866,7 +717,7 @@ int count_into_offsets(eloc_ctx c, int variant, const Plan& P, int64_t* total) {
 // The pairs as (row << jbits | column, group) at the offsets counted before.
 hipError_t fill_pairs(eloc_ctx c, int variant, const Plan& P, int jbits) {
     if (variant == kJoin)
-        return launch_join_fill(c->H, c->JH, c->J, P, jbits, c->offsets.as<int64_t>(), c->pkey.as<uint64_t>(),
+        return launch_join_fill(c->H, c->JH.dev, c->J.dev, P, jbits, c->offsets.as<int64_t>(), c->pkey.as<uint64_t>(),
                                 c->pval.as<uint32_t>(), c->stream);
     return launch_pairs_fill(variant, c->H, c->S, P, jbits, c->offsets.as<int64_t>(), c->pkey.as<uint64_t>(),
                              c->pval.as<uint32_t>(), c->stream);
@@ -926,12 +777,10 @@ void eloc_destroy(eloc_ctx c) {
                       &c->groups_b, &c->ghash_b, &c->gsplit_b, &c->gid_b, &c->gsplit, &c->gbucket, &c->part_perm, &c->part_class, &c->part_tile,
                       &c->ar_keys[0], &c->ar_keys[1], &c->ar_l[0], &c->ar_l[1], &c->ar_T[0], &c->ar_T[1],
                       &c->ar_cl, &c->ar_ck, &c->ar_ci, &c->ar_ck2, &c->ar_ci2, &c->ar_cnt,
-                      &c->ar_state, &c->ar_hist, &c->ar_count, &c->ar_off, &c->ar_bk, &c->ar_bi, &c->ar_sk,
-                      &c->jh_alist, &c->jh_amask, &c->jh_blist, &c->jh_bmask, &c->jh_bc, &c->jh_bo, &c->jh_ao, &c->jh_runs, &c->jh_gids,
-                      &c->jh_place, &c->jh_sign, &c->jh_linear, &c->j_cross, &c->j_heavy, &c->j_heavy_slots, &c->j_core,
-                      &c->j_key, &c->j_val, &c->j_key2, &c->j_val2, &c->j_hist, &c->j_hist_off, &c->j_hist_scan,
-                      &c->j_perm, &c->j_group, &c->j_scan, &c->j_vec, &c->j_slots};
+                      &c->ar_state, &c->ar_hist, &c->ar_count, &c->ar_off, &c->ar_bk, &c->ar_bi, &c->ar_sk};
     for (DevBuf* b : bufs) b->release();
+    c->JH.release();
+    c->J.release();
     for (auto& m : c->marks) {
         c->ev_pool.push_back(m.a);
         c->ev_pool.push_back(m.b);
@@ -1176,7 +1025,7 @@ int eloc_local_energy_noalloc(eloc_ctx c, int variant, int precision, const eloc
         const int rc = ensure_join(c);
         if (rc) return rc;
         P = J;
-        ELOC_HIP(c, launch_join_pairs(false, precision, c->H, c->JH, c->J, P, a, af, partial, c->stream));
+        ELOC_HIP(c, launch_join_pairs(false, precision, c->H, c->JH.dev, c->J.dev, P, a, af, partial, c->stream));
     } else {
         ELOC_HIP(c, launch_pairs(false, variant, precision, c->H, c->S, P, a, af, partial, c->stream));
     }
@@ -1712,8 +1561,8 @@ int eloc_pair_elements(eloc_ctx c, int64_t n, const int32_t* i_dev, const int32_
     }
     int32_t* cnt = phases ? c->pe_cnt.as<int32_t>() : nullptr;
     int32_t* grp = phases ? c->pe_grp.as<int32_t>() : nullptr;
-    if (c->JH.ok && c->JH.direct)
-        ELOC_HIP(c, launch_join_elements(c->H, c->JH, c->S, n, i_dev, j_dev, reinterpret_cast<double2*>(h_dev), cnt, grp,
+    if (c->JH.dev.ok && c->JH.dev.direct)
+        ELOC_HIP(c, launch_join_elements(c->H, c->JH.dev, c->S, n, i_dev, j_dev, reinterpret_cast<double2*>(h_dev), cnt, grp,
                                          c->err_run.as<uint32_t>(), c->stream));
     else
         ELOC_HIP(c, launch_pair_elements(c->H, c->S, n, i_dev, j_dev, reinterpret_cast<double2*>(h_dev), cnt, grp,
@@ -1787,8 +1636,8 @@ int eloc_store_pairs(eloc_ctx c, int variant, size_t budget_bytes, int64_t* n_pa
     ELOC_HIP(c, c->st_rowptr.ensure(sizeof(int64_t) * (M + 1)));
     if (total > 0) {
         ELOC_HIP(c, fill_pairs(c, variant, P, jbits));
-        if (c->JH.ok && c->JH.direct)
-            ELOC_HIP(c, launch_join_to_csr(c->H, c->JH, c->S, total, c->pkey.as<uint64_t>(), jbits,
+        if (c->JH.dev.ok && c->JH.dev.direct)
+            ELOC_HIP(c, launch_join_to_csr(c->H, c->JH.dev, c->S, total, c->pkey.as<uint64_t>(), jbits,
                                            c->st_col.as<int32_t>(), c->st_h.as<double2>(), c->stream));
         else
             ELOC_HIP(c, launch_pairs_to_csr(c->H, c->S, total, c->pkey.as<uint64_t>(), c->pval.as<uint32_t>(), jbits,

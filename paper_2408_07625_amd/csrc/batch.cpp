@@ -9,6 +9,7 @@
 #include "ham.h"
 #include "host.h"
 #include "internal.h"
+#include "join.h"
 
 #include <hip/hip_runtime.h>
 
@@ -17,6 +18,7 @@
 #include <cstdio>
 #include <cstring>
 #include <fstream>
+#include <memory>
 #include <numeric>
 #include <sstream>
 #include <string>
@@ -32,6 +34,22 @@ struct ProbInfo {
     int64_t G;
     int64_t M;
     int maxpop;
+};
+
+// A problem that the spin-string join can serve in place of work items.
+struct BatchJoin {
+    HamDev H;
+    JoinMasks masks;
+    JoinIndex index;
+    Plan plan;
+    bool on = false;    // with the schedule as it is
+    bool ran = false;   // in the last run
+    DevBuf counts;
+    ~BatchJoin() {
+        masks.release();
+        index.release();
+        counts.release();
+    }
 };
 
 }  // namespace
@@ -52,6 +70,9 @@ struct eloc_batch_s {
     std::vector<BatchProb> desc;     // host copy of the descriptors
     std::vector<RTile> tiles;
     std::vector<uint64_t> kcap;      // key-table capacity per problem
+    std::vector<std::unique_ptr<BatchJoin>> join;   // per problem, or none
+    hipStream_t side = nullptr;      // the joins' stream beside the pair kernels
+    hipEvent_t fork = nullptr, joined = nullptr;
 
     DevBuf R_dev, groups, terms, terms_f, ghash, gkeys, gsplit, gslots, gstash;
     DevBuf probs, pid, tiles_dev, sched, keys, khash, kslots, kstash;
@@ -155,6 +176,15 @@ int apply_schedule(eloc_batch b, const eloc_batch_schedule& s) {
         D.chunks = static_cast<int32_t>((span + per - 1) / per);
         const int64_t row_tiles = (I.M + s.rows_per_wave - 1) / s.rows_per_wave;
         D.items = row_tiles * D.chunks;
+        // the join in place of the items, under the schedules that leave the
+        // pair loops as they are by default
+        if (BatchJoin* J = b->join[static_cast<size_t>(k)].get()) {
+            J->on = s.rows_per_wave == 8 && s.batch_ratio == 1.0;
+            if (J->on) {
+                D.chunks = J->plan.chunks;
+                D.items = 0;
+            }
+        }
         cost[static_cast<size_t>(k)] = I.M * span;
     }
     std::vector<int32_t> order(static_cast<size_t>(n));
@@ -225,8 +255,29 @@ int enqueue(eloc_batch b, int precision, hipStream_t st, bool timed = false) {
     BATCH_HIP(b, mark(0));
     BATCH_HIP(b, launch_batch_prepare(B, precision == ELOC_FP32C, st));
     BATCH_HIP(b, mark(1));
+    // the joins on a stream of their own, beside the items of the others:
+    // their indexes are a dozen small launches each
+    bool joins = false;
+    for (int k = 0; k < b->n; ++k) {
+        BatchJoin* J = b->join[static_cast<size_t>(k)].get();
+        if (J) J->ran = J->on;
+        if (!J || !J->on) continue;
+        if (!joins) {
+            BATCH_HIP(b, hipEventRecord(b->fork, st));
+            BATCH_HIP(b, hipStreamWaitEvent(b->side, b->fork, 0));
+            joins = true;
+        }
+        const BatchProb& D = b->desc[static_cast<size_t>(k)];
+        BATCH_HIP(b, J->index.build(b->W, B.keys + D.s0 * b->W, D.M, J->H.n_qubits, J->masks.split, B.err + k, b->side));
+        BATCH_HIP(b, launch_join_pairs(false, precision, J->H, J->masks.dev, J->index.dev, J->plan, B.a + D.s0,
+                                       B.af + D.s0, static_cast<double2*>(B.partial) + D.pbase, b->side));
+    }
     BATCH_HIP(b, launch_batch_pairs(B, precision, b->schedule.rows_per_wave, launch_blocks(b, precision, true),
                                     launch_blocks(b, precision, false), st));
+    if (joins) {
+        BATCH_HIP(b, hipEventRecord(b->joined, b->side));
+        BATCH_HIP(b, hipStreamWaitEvent(st, b->joined, 0));
+    }
     BATCH_HIP(b, mark(2));
     BATCH_HIP(b, launch_batch_finish(B, precision, st));
     BATCH_HIP(b, mark(3));
@@ -299,6 +350,18 @@ int ingest_all(eloc_batch b, const eloc_problem* probs) {
         const std::string why = build_host_ham<W>(b->R, p.n_terms, p.coeff, xy.data(), yz.data(), hh[static_cast<size_t>(k)]);
         if (!why.empty()) return bfail(b, ELOC_EINVAL, "problem " + std::to_string(k) + ": " + why);
     }
+    // the masks by spin part of the problems whose samples pay for the join
+    // under the default schedule (its loop is over the fewer of samples and
+    // masks), built beside the uploads below
+    std::vector<HostJoin<W>> hj(static_cast<size_t>(n));
+    BesideThread beside([&] {
+        for (int k = 0; k < n; ++k) {
+            const HostHam<W>& h = hh[static_cast<size_t>(k)];
+            const int64_t M = probs[k].n_unique;
+            if (join_pays(M, M * std::min<int64_t>(M, h.G), true))
+                build_host_join_if<W>(h, probs[k].n_qubits, hj[static_cast<size_t>(k)]);
+        }
+    });
     // each problem's table format: narrow for one-word batches of problems of
     // at most 32 qubits whose group parts fit the narrow hit queue's 16 bits
     std::vector<int> tk(static_cast<size_t>(n));
@@ -377,6 +440,32 @@ int ingest_all(eloc_batch b, const eloc_problem* probs) {
         D.kslots = b->kslots.as<char>() + static_cast<size_t>(kcoff[static_cast<size_t>(k)]);
         D.kstash = b->kstash.as<Stash>() + k;
         D.ktable = make_table(D.kslots, D.kstash, b->kcap[static_cast<size_t>(k)], I.M, splitmix64(b->salt_state));
+    }
+    beside.wait();
+    for (int k = 0; k < n; ++k) {
+        const HostJoin<W>& h = hj[static_cast<size_t>(k)];
+        if (!h.ok) continue;
+        const ProbInfo& I = b->info[static_cast<size_t>(k)];
+        const BatchProb& D = b->desc[static_cast<size_t>(k)];
+        auto J = std::make_unique<BatchJoin>();
+        BATCH_HIP(b, J->masks.upload(h, I.n_qubits));
+        if (!J->masks.dev.ok) continue;
+        const hipError_t e = J->index.room(W, I.M);
+        if (e == hipErrorOutOfMemory) {   // the loops serve
+            (void)hipGetLastError();
+            continue;
+        }
+        BATCH_HIP(b, e);
+        J->plan = join_plan(J->masks.dev.n_a, I.M);
+        J->H.W = W;
+        J->H.n_qubits = I.n_qubits;
+        J->H.n_groups = I.G;
+        J->H.terms = D.terms;
+        J->H.terms_f = D.terms_f;
+        b->join[static_cast<size_t>(k)] = std::move(J);
+        if (!b->side) BATCH_HIP(b, hipStreamCreateWithFlags(&b->side, hipStreamNonBlocking));
+        if (!b->fork) BATCH_HIP(b, hipEventCreateWithFlags(&b->fork, hipEventDisableTiming));
+        if (!b->joined) BATCH_HIP(b, hipEventCreateWithFlags(&b->joined, hipEventDisableTiming));
     }
     return ELOC_OK;
 }
@@ -503,6 +592,7 @@ int eloc_batch_create(eloc_batch* out, int device, void* hip_stream, int n, cons
     int W = 1;
     b->info.resize(static_cast<size_t>(n));
     b->desc.assign(static_cast<size_t>(n), BatchProb{});
+    b->join.resize(static_cast<size_t>(n));
     int64_t S = 0;
     for (int k = 0; k < n; ++k) {
         const eloc_problem& p = probs[k];
@@ -592,6 +682,12 @@ void eloc_batch_destroy(eloc_batch b) {
     else (void)hipDeviceSynchronize();
     drop_graphs(b);
     if (b->cap_stream) (void)hipStreamDestroy(b->cap_stream);
+    if (b->side) {
+        (void)hipStreamSynchronize(b->side);
+        (void)hipStreamDestroy(b->side);
+    }
+    if (b->fork) (void)hipEventDestroy(b->fork);
+    if (b->joined) (void)hipEventDestroy(b->joined);
     DevBuf* bufs[] = {&b->R_dev, &b->groups, &b->terms, &b->terms_f, &b->ghash, &b->gkeys, &b->gsplit, &b->gslots, &b->gstash,
                       &b->probs, &b->pid, &b->tiles_dev, &b->sched, &b->keys, &b->khash, &b->kslots, &b->kstash,
                       &b->err_dev, &b->sigmin, &b->sigmax, &b->bitcounts, &b->rad, &b->shift, &b->scal, &b->part, &b->pairs,
@@ -666,6 +762,24 @@ int eloc_batch_pair_counts(eloc_batch b, int64_t* counts_host) {
     if (!b || !counts_host) return ELOC_EINVAL;
     BATCH_HIP(b, hipStreamSynchronize(b->stream));
     BATCH_HIP(b, hipMemcpy(counts_host, b->pairs.p, sizeof(int64_t) * b->n, hipMemcpyDeviceToHost));
+    // the joins of the last run, counted now from their indexes
+    for (int k = 0; k < b->n; ++k) {
+        BatchJoin* J = b->join[static_cast<size_t>(k)].get();
+        if (!J || !J->ran) continue;
+        const size_t cells = static_cast<size_t>(J->plan.chunks) * static_cast<size_t>(J->index.dev.M);
+        BATCH_HIP(b, J->counts.ensure(sizeof(int32_t) * cells));
+        BATCH_HIP(b, hipMemsetAsync(J->counts.p, 0, sizeof(int32_t) * cells, b->stream));
+        BATCH_HIP(b, launch_join_count(J->H, J->masks.dev, J->index.dev, J->plan, J->counts.as<int32_t>(), b->stream));
+        std::vector<int32_t> host;
+        try {
+            host.resize(cells);
+        } catch (const std::bad_alloc&) {
+            return bfail(b, ELOC_ENOMEM, "host memory for the pair counts");
+        }
+        BATCH_HIP(b, hipStreamSynchronize(b->stream));
+        BATCH_HIP(b, hipMemcpy(host.data(), J->counts.p, sizeof(int32_t) * cells, hipMemcpyDeviceToHost));
+        counts_host[k] = std::accumulate(host.begin(), host.end(), int64_t(0));
+    }
     return ELOC_OK;
 }
 

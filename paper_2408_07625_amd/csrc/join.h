@@ -10,6 +10,9 @@
 #include <cmath>
 #include <cstdint>
 #include <cstring>
+#include <new>
+#include <system_error>
+#include <thread>
 #include <vector>
 
 namespace eloc {
@@ -304,5 +307,236 @@ void build_host_join(const HostHam<W>& hh, int n_qubits, HostJoin<W>& out) {
     table(out.a_own, aown);
     out.ok = true;
 }
+
+// The masks by spin part, where the strings are short enough and there is the
+// memory for them; else hj.ok stays false.
+template <int W>
+inline void build_host_join_if(const HostHam<W>& hh, int n_qubits, HostJoin<W>& hj) {
+    if (n_qubits > kJoinMaxQubits) return;
+    try {
+        build_host_join<W>(hh, n_qubits, hj);
+    } catch (const std::bad_alloc&) {
+        hj = HostJoin<W>{};
+    }
+}
+
+// A function on a thread of its own, joined at the end of the scope at the
+// latest; run in place where no thread can be had.
+class BesideThread {
+public:
+    template <class F>
+    explicit BesideThread(F f) {
+        try {
+            t_ = std::thread(f);
+        } catch (const std::system_error&) {
+            f();
+        }
+    }
+    ~BesideThread() { wait(); }
+    void wait() {
+        if (t_.joinable()) t_.join();
+    }
+
+private:
+    std::thread t_;
+};
+
+// Whether the join is taken for M samples where the loop would meet `loop`
+// candidates.  The loops take about 6.5e8 candidates a millisecond (|U| |XY|
+// for LoopOverTerms, |U|^2 for LoopOverBatch; LoopOverTrie costs about eight of
+// them per |U| |XY|), the join about 0.2 ms for U's two orders and 6 to 15 ns a
+// sample.  Measured, loop / join: LoopOverTerms, 28 qubits, 65 536 samples
+// (6.9e8) 1.09 / 0.53 ms; 52 qubits, 2^20 (1.4e11) 97 / 18 ms; LoopOverBatch,
+// 40 qubits, 9999 samples (1.0e8) 0.16 / 0.24 ms.
+// `beside`: in a batch the join's many small launches run beside the others'
+// items, which is worth about half of the fixed part: 26 qubits, 29 882 samples
+// (2.3e8) in a batch of 16, 1.29 ms for the batch with its loop, 1.06 with the join.
+inline bool join_pays(int64_t M, int64_t loop, bool beside = false) {
+    return loop >= (int64_t(1) << (beside ? 26 : 27)) + (M << 12);
+}
+
+// Launch geometry for M rows.  Chunk 0: the spin-down order; chunk 1: the
+// heavy-heavy table; then alist in chunks of at least 16 masks.  16 rows a wave
+// share a scanned column and a bucket lookup, but a heavy string's wave then
+// runs long: 52 qubits, 2^20 samples, 18.8 ms with 16 rows, 19.3 with 8; 28
+// qubits, 65 536, 0.63 with 8, 0.66 with 16.
+inline Plan join_plan(int n_a, int64_t M) {
+    Plan P;
+    P.rows_per_block = M >= (int64_t(1) << 17) ? 16 : 8;
+    const int64_t target = 32768;   // waves
+    const int64_t tiles = (M + P.rows_per_block - 1) / P.rows_per_block;
+    const int64_t chunks = std::max<int64_t>(1, std::min<int64_t>((n_a + 15) / 16, (target + tiles - 1) / tiles - 2));
+    P.per_chunk = static_cast<int>((n_a + chunks - 1) / chunks);
+    if (P.per_chunk > 64) P.per_chunk = (P.per_chunk + 63) / 64 * 64;
+    P.chunks = 2 + (n_a + P.per_chunk - 1) / P.per_chunk;
+    return P;
+}
+
+// The masks on the device.
+struct JoinMasks {
+    JoinHamDev dev;
+    bool split = false;   // the pairs allow the heavy / light split
+    DevBuf all;           // its arrays in one allocation and one copy
+
+    template <int W>
+    hipError_t upload(const HostJoin<W>& hj, int n_qubits) {
+        dev = JoinHamDev{};
+        split = false;
+        if (!hj.ok) return hipSuccess;
+        std::vector<unsigned char> host;
+        const auto put = [&](const auto& v) {
+            const size_t at = (host.size() + 255) / 256 * 256, bytes = v.size() * sizeof(v[0]);
+            host.resize(at + bytes);
+            if (bytes) std::memcpy(host.data() + at, v.data(), bytes);
+            return at;
+        };
+        const auto size = [](const auto& v) { return v.size() * sizeof(v[0]) + 256; };
+        hipError_t e = hipSuccess;
+        size_t at[12];
+        try {
+            host.reserve(size(hj.alist) + size(hj.amask) + size(hj.blist) + size(hj.bmask) + size(hj.b_cross) +
+                         size(hj.b_own) + size(hj.a_own) + size(hj.place) + size(hj.sign) + size(hj.linear) +
+                         size(hj.runs) + size(hj.gids));
+            at[0] = put(hj.alist);
+            at[1] = put(hj.amask);
+            at[2] = put(hj.blist);
+            at[3] = put(hj.bmask);
+            at[4] = put(hj.b_cross);
+            at[5] = put(hj.b_own);
+            at[6] = put(hj.a_own);
+            at[7] = put(hj.place);
+            at[8] = put(hj.sign);
+            at[9] = put(hj.linear);
+            at[10] = put(hj.runs);
+            at[11] = put(hj.gids);
+            e = all.ensure(host.size());
+        } catch (const std::bad_alloc&) {
+            return hipSuccess;   // the loops serve
+        }
+        if (e == hipErrorOutOfMemory) {   // the loops serve
+            (void)hipGetLastError();
+            return hipSuccess;
+        }
+        if (e == hipSuccess) e = hipMemcpy(all.p, host.data(), host.size(), hipMemcpyHostToDevice);
+        if (e != hipSuccess) return e;
+        const auto part = [&](int k) -> void* { return all.as<unsigned char>() + at[k]; };
+        JoinHamDev H;
+        H.ok = true;
+        H.n_a = static_cast<int>(hj.alist.size());
+        H.alist = part(0);
+        H.amask = static_cast<const JoinMask*>(part(1));
+        H.n_b = static_cast<int>(hj.blist.size());
+        H.blist = part(2);
+        H.bmask = static_cast<const JoinMask*>(part(3));
+        H.direct = hj.direct;
+        H.stride = hj.stride;
+        H.b_cross = part(4);
+        H.b_own = part(5);
+        H.a_own = part(6);
+        H.b_cross_bits = bits_for(hj.b_cross.size() - 1);
+        H.b_own_bits = bits_for(hj.b_own.size() - 1);
+        H.a_own_bits = bits_for(hj.a_own.size() - 1);
+        H.place = part(7);
+        H.string_bits = join_string_bits(n_qubits);
+        H.sign = static_cast<const double*>(part(8));
+        H.linear = static_cast<const double*>(part(9));
+        H.runs = static_cast<const JoinRun*>(part(10));
+        H.gids = static_cast<const int32_t*>(part(11));
+        H.places = static_cast<uint32_t>(hj.place.size());
+        H.cross = hj.cross;
+        H.nibbles = hj.nibbles;
+        H.a_base = hj.a_base;
+        H.a_pmin = hj.a_pmin;
+        H.a_span = hj.a_span;
+        H.has_a_own = hj.a_base < hj.place.size();
+        split = join_splits(n_qubits, H, hj.cross_span);
+        dev = H;
+        return hipSuccess;
+    }
+    void release() { all.release(); }
+};
+
+// U in two sorted orders: the buffers (with their own sort scratch) and the
+// index built in them.
+struct JoinIndex {
+    JoinDev dev;
+    DevBuf key, val, key2, val2, hist, hist_off, hist_scan;
+    DevBuf perm, group, scan, cross, vec, slots, heavy, heavy_slots, core;
+
+    // Room for n samples; nothing is allocated when the index is built.
+    hipError_t room(int W, int64_t n) {
+        const size_t st = W == 1 ? sizeof(uint32_t) : sizeof(uint64_t);
+        const int64_t tiles = radix_tiles(2 * n);
+        hipError_t e = hipSuccess;
+        const auto need = [&](DevBuf& b, size_t bytes) {
+            if (e == hipSuccess) e = b.ensure(bytes);
+        };
+        need(key, sizeof(uint64_t) * 2 * n);
+        need(key2, sizeof(uint64_t) * 2 * n);
+        need(val, sizeof(uint32_t) * 2 * n);
+        need(val2, sizeof(uint32_t) * 2 * n);
+        need(hist, sizeof(uint32_t) * 256 * tiles);
+        need(hist_off, sizeof(int64_t) * (256 * tiles + 1));
+        need(hist_scan, sizeof(int64_t) * scan_scratch_len(256 * tiles));
+        need(perm, sizeof(int32_t) * 2 * n);
+        need(group, st * 2 * n);
+        need(scan, st * 2 * n);
+        need(vec, sizeof(double2) * 2 * n);
+        need(slots, sizeof(JoinBucket) * (size_t(2) << join_bucket_bits(n)));
+        need(cross, st * n);
+        need(heavy, sizeof(JoinHeavy));
+        need(heavy_slots, 2 * st * 2 * kJoinHeavySlots);
+        need(core, sizeof(uint32_t) * kJoinCore);
+        return e;
+    }
+    // The index of keys[n][W]; enqueued.
+    hipError_t build(int W, const uint64_t* keys, int64_t n, int n_qubits, bool split, const uint32_t* prep_err,
+                     hipStream_t st) {
+        JoinBuild B;
+        B.keys = keys;
+        B.M = n;
+        B.n_qubits = n_qubits;
+        B.split = split;
+        B.key = key.as<uint64_t>();
+        B.key2 = key2.as<uint64_t>();
+        B.val = val.as<uint32_t>();
+        B.val2 = val2.as<uint32_t>();
+        B.hist = hist.as<uint32_t>();
+        B.hist_off = hist_off.as<int64_t>();
+        B.hist_scan = hist_scan.as<int64_t>();
+        B.perm = perm.as<int32_t>();
+        B.group = group.p;
+        B.scan = scan.p;
+        B.cross = cross.p;
+        B.slots = slots.as<JoinBucket>();
+        B.bits = join_bucket_bits(n);
+        B.heavy = heavy.as<JoinHeavy>();
+        B.heavy_slots = heavy_slots.p;
+        B.core = core.as<uint32_t>();
+        const hipError_t e = launch_join_index(W, B, st);
+        if (e != hipSuccess) return e;
+        JoinDev J;
+        J.M = n;
+        J.perm = B.perm;
+        J.group = B.group;
+        J.scan = B.scan;
+        J.cross = B.cross;
+        J.vec = vec.as<double2>();
+        J.keys = B.keys;
+        J.slots = B.slots;
+        J.bits = B.bits;
+        J.heavy = B.heavy;
+        J.heavy_slots = B.heavy_slots;
+        J.core = B.core;
+        J.prep_err = prep_err;
+        dev = J;
+        return hipSuccess;
+    }
+    void release() {
+        for (DevBuf* b : {&key, &val, &key2, &val2, &hist, &hist_off, &hist_scan, &perm, &group, &scan, &cross, &vec, &slots,
+                          &heavy, &heavy_slots, &core})
+            b->release();
+    }
+};
 
 }  // namespace eloc
