@@ -10,12 +10,34 @@
 #include <cmath>
 #include <cstdint>
 #include <cstring>
+#include <memory>
 #include <new>
 #include <system_error>
 #include <thread>
 #include <vector>
 
 namespace eloc {
+
+// A function on a thread of its own, joined at the end of the scope at the
+// latest; run in place where no thread can be had.
+class BesideThread {
+public:
+    template <class F>
+    explicit BesideThread(F f) {
+        try {
+            t_ = std::thread(f);
+        } catch (const std::system_error&) {
+            f();
+        }
+    }
+    ~BesideThread() { wait(); }
+    void wait() {
+        if (t_.joinable()) t_.join();
+    }
+
+private:
+    std::thread t_;
+};
 
 template <int W>
 struct HostJoin {
@@ -111,41 +133,49 @@ inline JoinKind join_kind_of(uint32_t hi) {
     return (hi & kJoinTag) == kJoinTag ? static_cast<JoinKind>(hi & 7u) : kJoinSign;
 }
 
-// One place's evaluation; appends a linear table where it needs one.
+// One place's evaluation where its terms share the bits outside the mask; false
+// where they do not.  Writes that place alone.
 template <int W>
-void join_place(const HostHam<W>& hh, const GroupRec<W>& gr, size_t place, bool mixed, HostJoin<W>& out) {
+bool join_place_one(const HostHam<W>& hh, const GroupRec<W>& gr, size_t place, bool mixed, HostJoin<W>& out) {
     using ST = JoinStr<W>;
     const size_t P = out.place.size();
     JoinPlace<W>& pl = out.place[place];
     pl = join_tag<W>(kJoinRunKind);
-    if (gr.end != gr.mid) return;
+    if (gr.end != gr.mid) return true;
     ST a, b;
     spin_strings<W>(gr.xy, a, b);
-    // the bits outside the mask: one z for all terms, or a majority z and
-    // one further bit
     uint64_t z[W];
-    const int n = gr.end - gr.begin;
     bool one = true;
     for (int w = 0; w < W; ++w) {
         z[w] = hh.terms[static_cast<size_t>(gr.begin)].yz[w] & ~gr.xy[w];
         for (int t = gr.begin + 1; t < gr.end; ++t)
             one = one && ((hh.terms[static_cast<size_t>(t)].yz[w] & ~gr.xy[w]) == z[w]);
     }
-    if (one) {
-        double T[kJoinIdx];
-        if (!join_signs<W>(hh, gr, a, b, mixed, T)) return;
-        pl = join_tag<W>(kJoinSign);
-        spin_strings<W>(z, pl.za, pl.zb);
-        for (size_t i = 0; i < kJoinIdx; ++i) out.sign[i * P + place] = T[i];
-        if (mixed) {
-            uint64_t bits;
-            std::memcpy(&bits, &T[kJoinMain], sizeof(bits));
-            pl.lo = static_cast<uint32_t>(bits);
-            pl.hi = static_cast<uint32_t>(bits >> 32);
-        }
-        return;
+    if (!one) return false;
+    double T[kJoinIdx];
+    if (!join_signs<W>(hh, gr, a, b, mixed, T)) return true;
+    pl = join_tag<W>(kJoinSign);
+    spin_strings<W>(z, pl.za, pl.zb);
+    for (size_t i = 0; i < kJoinIdx; ++i) out.sign[i * P + place] = T[i];
+    if (mixed) {
+        uint64_t bits;
+        std::memcpy(&bits, &T[kJoinMain], sizeof(bits));
+        pl.lo = static_cast<uint32_t>(bits);
+        pl.hi = static_cast<uint32_t>(bits >> 32);
     }
-    if (n < 8 || (a == 0 && b == 0)) return;
+    return true;
+}
+
+// The others: a majority z and one further bit, by the linear table `number`
+// (zeros so far; left so where the place keeps its run).
+template <int W>
+void join_place_linear(const HostHam<W>& hh, const GroupRec<W>& gr, size_t place, size_t number, HostJoin<W>& out) {
+    JoinPlace<W>& pl = out.place[place];
+    uint64_t z[W];
+    const int n = gr.end - gr.begin;
+    bool any = false;
+    for (int w = 0; w < W; ++w) any = any || gr.xy[w] != 0;
+    if (n < 8 || !any || number >= (size_t(1) << 16)) return;
     {   // a bit of the majority z is the majority of the bits
         int c[64 * W] = {};
         for (int t = gr.begin; t < gr.end; ++t)
@@ -159,7 +189,7 @@ void join_place(const HostHam<W>& hh, const GroupRec<W>& gr, size_t place, bool 
         }
     }
     const size_t half = static_cast<size_t>(out.nibbles) * 16, per = 2 * half;
-    std::vector<double> tab(2 * per, 0.0);
+    double* const tab = out.linear.data() + number * 2 * per;
     for (int t = gr.begin; t < gr.end; ++t) {
         const TermRec<W>& tr = hh.terms[static_cast<size_t>(t)];
         int bit = -1, extra = 0;
@@ -171,18 +201,18 @@ void join_place(const HostHam<W>& hh, const GroupRec<W>& gr, size_t place, bool 
             none = none && y == 0;
             all = all && y == gr.xy[w];
         }
-        if (extra > 1 || !(none || all)) return;
+        if (extra > 1 || !(none || all)) {
+            std::fill(tab, tab + 2 * per, 0.0);
+            return;
+        }
         const int q = bit < 0 ? 0 : bit / 2;   // bit of the string
         for (int par = 0; par < 2; ++par) {
             const double h = (all && par) ? -tr.h : tr.h;
-            double* F = tab.data() + static_cast<size_t>(par) * per + (bit >= 0 && (bit & 1) ? half : 0) +
+            double* F = tab + static_cast<size_t>(par) * per + (bit >= 0 && (bit & 1) ? half : 0) +
                         static_cast<size_t>(q / 4) * 16;
             for (int v = 0; v < 16; ++v) F[v] += (bit >= 0 && ((v >> (q % 4)) & 1)) ? -h : h;
         }
     }
-    const size_t number = out.linear.size() / (2 * per);
-    if (number >= (size_t(1) << 16)) return;
-    out.linear.insert(out.linear.end(), tab.begin(), tab.end());
     pl = join_tag<W>(kJoinLinear, static_cast<uint32_t>(number));
     spin_strings<W>(z, pl.za, pl.zb);
 }
@@ -206,6 +236,15 @@ void build_host_join(const HostHam<W>& hh, int n_qubits, HostJoin<W>& out) {
     std::vector<ST> avals, bvals, aown, bown;
     std::vector<int32_t> bid(static_cast<size_t>(G));
     bool zero = false, pairs = true;   // pairs: every mask has ids by position
+    // what `number` gave the parts of two bits, by position
+    const size_t by_two = static_cast<size_t>(32 * W) * (32 * W - 1) / 2;
+    std::vector<int64_t> atwo(by_two, -1), btwo(by_two, -1);
+    const auto number_part = [&](XYMap& map, std::vector<ST>& vals, std::vector<int64_t>& two, ST v, uint32_t count) {
+        if (count != 2u) return number(map, vals, v);
+        int64_t& id = two[join_pair_id(v)];
+        if (id < 0) id = number(map, vals, v);
+        return id;
+    };
     for (int64_t g = 0; g < G; ++g) {
         ST a, b;
         spin_strings<W>(&hh.gkeys[static_cast<size_t>(g * W)], a, b);
@@ -218,8 +257,8 @@ void build_host_join(const HostHam<W>& hh, int n_qubits, HostJoin<W>& out) {
             id = a == 0 ? number(bomap, bown, b) : number(aomap, aown, a);
             pairs = pairs && (pa + pb) % 2 == 0 && pa + pb <= 4;
         } else {
-            (void)number(amap, avals, a);
-            id = number(bmap, bvals, b);
+            (void)number_part(amap, avals, atwo, a, pa);
+            id = number_part(bmap, bvals, btwo, b, pb);
             pairs = pairs && pa == 2 && pb == 2;
             out.cross_span = std::max(out.cross_span, std::max(pa, pb));
         }
@@ -264,7 +303,7 @@ void build_host_join(const HostHam<W>& hh, int n_qubits, HostJoin<W>& out) {
     out.gids.assign(static_cast<size_t>(places), -1);
     out.place.assign(static_cast<size_t>(places), join_tag<W>(kJoinEmpty));
     out.sign.assign(static_cast<size_t>(places) * kJoinIdx, 0.0);
-    int64_t by_run = 0;
+    std::vector<uint32_t> at(static_cast<size_t>(G));
     uint32_t pmin = ~0u, pmax = 0;
     for (int64_t g = 0; g < G; ++g) {
         const ST a = as[static_cast<size_t>(g)], b = bs[static_cast<size_t>(g)];
@@ -288,9 +327,37 @@ void build_host_join(const HostHam<W>& hh, int n_qubits, HostJoin<W>& out) {
                                   static_cast<uint32_t>(gr.mid - gr.begin) |
                                       (static_cast<uint32_t>(gr.end - gr.mid) << 16)};
         out.gids[place] = static_cast<int32_t>(g);
-        join_place<W>(hh, gr, place, a != 0 && b != 0, out);
-        by_run += join_kind_of(out.place[place].hi) == kJoinRunKind;
+        at[static_cast<size_t>(g)] = static_cast<uint32_t>(place);
     }
+    // the evaluations, a part of the groups a thread (each writes its own
+    // places and tables)
+    const auto in_parts = [](int64_t n, int64_t least, const auto& part) {
+        const int64_t per = std::max<int64_t>(least, (n + 3) / 4);
+        std::vector<std::unique_ptr<BesideThread>> others;
+        for (int64_t i0 = per; i0 < n; i0 += per)
+            others.push_back(std::make_unique<BesideThread>([&part, i0, i1 = std::min(n, i0 + per)] { part(i0, i1); }));
+        part(0, std::min(n, per));
+    };
+    std::vector<uint8_t> more(static_cast<size_t>(G), 0);
+    in_parts(G, 4096, [&](int64_t g0, int64_t g1) {
+        for (int64_t g = g0; g < g1; ++g) {
+            const size_t i = static_cast<size_t>(g);
+            more[i] = join_place_one<W>(hh, hh.groups[i], at[i], as[i] != 0 && bs[i] != 0, out) ? 0 : 1;
+        }
+    });
+    std::vector<int64_t> rest;
+    for (int64_t g = 0; g < G; ++g)
+        if (more[static_cast<size_t>(g)]) rest.push_back(g);
+    out.linear.assign(std::min<size_t>(rest.size(), size_t(1) << 16) * 4 * static_cast<size_t>(out.nibbles) * 16, 0.0);
+    in_parts(static_cast<int64_t>(rest.size()), 64, [&](int64_t k0, int64_t k1) {
+        for (int64_t k = k0; k < k1; ++k) {
+            const size_t i = static_cast<size_t>(rest[static_cast<size_t>(k)]);
+            join_place_linear<W>(hh, hh.groups[i], at[i], static_cast<size_t>(k), out);
+        }
+    });
+    int64_t by_run = 0;
+    for (int64_t g = 0; g < G; ++g)
+        by_run += join_kind_of(out.place[at[static_cast<size_t>(g)]].hi) == kJoinRunKind;
     if (8 * by_run > G) return;
     if (out.direct)
         for (int64_t k = zero ? 1 : 0; k < na; ++k) out.amask[static_cast<size_t>(k)].span = 1u;
@@ -319,27 +386,6 @@ inline void build_host_join_if(const HostHam<W>& hh, int n_qubits, HostJoin<W>& 
         hj = HostJoin<W>{};
     }
 }
-
-// A function on a thread of its own, joined at the end of the scope at the
-// latest; run in place where no thread can be had.
-class BesideThread {
-public:
-    template <class F>
-    explicit BesideThread(F f) {
-        try {
-            t_ = std::thread(f);
-        } catch (const std::system_error&) {
-            f();
-        }
-    }
-    ~BesideThread() { wait(); }
-    void wait() {
-        if (t_.joinable()) t_.join();
-    }
-
-private:
-    std::thread t_;
-};
 
 // Whether the join is taken for M samples where the loop would meet `loop`
 // candidates.  The loops take about 6.5e8 candidates a millisecond (|U| |XY|
