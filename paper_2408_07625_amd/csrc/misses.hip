@@ -25,7 +25,7 @@
 // bit in a bitmap over the key space instead, U's bits are cleared after it
 // (no lookups), and the set bits, read in order, are the unique states
 // already sorted.  20 000 rows by 10 466 groups, a third of them non-zero:
-// 3.6 ms with a lookup, the run's sum and an atomic for each, 0.97 this way.
+// 3.6 ms with a lookup, the run's sum and an atomic for each, 0.5 this way.
 #include "device.h"
 
 #include <hip/hip_runtime.h>
@@ -171,6 +171,31 @@ __device__ __forceinline__ uint32_t rule_index(const MissRule<W>& rule, const ui
     return idx;
 }
 
+// Bit r: row r's element of the group is non-zero, by its run; a term is read
+// once for all rows.
+__device__ __forceinline__ uint32_t run_hits(const TermRec<1>* __restrict__ terms, const GroupRec<1>& gr,
+                                             const uint32_t (&x)[kMissRows], uint32_t xy, double tol) {
+    double hr[kMissRows] = {}, hi[kMissRows] = {}, sa = 0.0;
+    for (int t = gr.begin; t < gr.mid; ++t) {
+        const double h = terms[t].h;
+        const uint32_t yz = static_cast<uint32_t>(terms[t].yz[0]);
+#pragma unroll
+        for (int r = 0; r < kMissRows; ++r) hr[r] += (__popc(yz & (x[r] ^ xy)) & 1) ? -h : h;
+        sa += fabs(h);
+    }
+    for (int t = gr.mid; t < gr.end; ++t) {
+        const double h = terms[t].h;
+        const uint32_t yz = static_cast<uint32_t>(terms[t].yz[0]);
+#pragma unroll
+        for (int r = 0; r < kMissRows; ++r) hi[r] += (__popc(yz & (x[r] ^ xy)) & 1) ? -h : h;
+        sa += fabs(h);
+    }
+    uint32_t hit = 0;
+#pragma unroll
+    for (int r = 0; r < kMissRows; ++r) hit |= hypot(hr[r], hi[r]) > tol * sa ? 1u << r : 0u;
+    return hit;
+}
+
 // One-word keys of at most 30 qubits, all in 32 bits.  What bounds it is the
 // bitmap's traffic; a bit is read before it is set, as most are set many
 // times (an atomic goes past the L2s), and the reads of a step's rows are in
@@ -195,7 +220,7 @@ __global__ __launch_bounds__(64) void k_miss_bits(MissArgs A, uint32_t* __restri
         const MissRule<1> rule = rules[g];
         const uint32_t m0 = static_cast<uint32_t>(rule.mask[0][0]), m1 = static_cast<uint32_t>(rule.mask[1][0]),
                        m2 = static_cast<uint32_t>(rule.mask[2][0]);
-        const bool run = rule.tab == kMissRun;
+        const bool run = rule.tab == kMissRun && xy != 0u;   // x itself is no miss
         uint32_t hit = 0;
 #pragma unroll
         for (int r = 0; r < kMissRows; ++r) {
@@ -204,17 +229,7 @@ __global__ __launch_bounds__(64) void k_miss_bits(MissArgs A, uint32_t* __restri
             hit |= ((rule.tab >> idx) & 1u) << r;
         }
         if (__ballot(run)) {
-            if (run) {
-                const GroupRec<1> gr = groups[g];
-                hit = 0;
-                for (int r = 0; r < kMissRows; ++r) {
-                    uint32_t xr = x[0];
-#pragma unroll
-                    for (int q = 1; q < kMissRows; ++q) xr = r == q ? x[q] : xr;
-                    const uint64_t ket[1] = {xr ^ xy};
-                    hit |= nonzero_element<1>(terms, gr, ket, A.tol) ? 1u << r : 0u;
-                }
-            }
+            if (run) hit = run_hits(terms, groups[g], x, xy, A.tol);
         }
         uint32_t word[kMissRows];
 #pragma unroll
@@ -268,6 +283,10 @@ __global__ __launch_bounds__(64) void k_misses(MissArgs A, unsigned long long* _
         const bool valid = g < g1;
         const GroupRec<W> gr = groups[min(g, g1 - 1)];
         const MissRule<W> rule = rules[min(g, g1 - 1)];
+        const bool by_run = rule.tab == kMissRun;
+        bool self = true;   // x itself is no miss
+#pragma unroll
+        for (int w = 0; w < W; ++w) self = self && gr.xy[w] == 0ull;
         const uint64_t gh = A.ghash[min(g, g1 - 1)];
         uint64_t m[kMissRows];
         bool miss[kMissRows];
@@ -278,13 +297,11 @@ __global__ __launch_bounds__(64) void k_misses(MissArgs A, unsigned long long* _
 #pragma unroll
             for (int w = 0; w < W; ++w) xp[w] = x[r][w] ^ gr.xy[w];
             miss[r] = false;
-            if (valid && r < nr &&
-                (rule.tab == kMissRun ? nonzero_element<W>(terms, gr, xp, A.tol)
-                                      : ((rule.tab >> rule_index<W>(rule, xp)) & 1u) != 0u)) {
+            if (valid && r < nr && !self && (by_run || ((rule.tab >> rule_index<W>(rule, xp)) & 1u) != 0u)) {
                 const auto hs = salted<TK>(A.ktable, hx[r] ^ gh);
                 const int j = table_settle<TK, W>(A.ktable, A.keys, load_slot<TK>(A.ktable, slot1(A.ktable, hs)),
                                                   load_slot<TK>(A.ktable, slot2(A.ktable, hs)), hs, xp, nstash);
-                miss[r] = j < 0;
+                miss[r] = j < 0 && (!by_run || nonzero_element<W>(terms, gr, xp, A.tol));
             }
             m[r] = __ballot(miss[r]);
             total += __popcll(m[r]);
