@@ -239,7 +239,18 @@ Plan make_plan(const eloc_ctx c, int variant, int64_t n_rows = -1, bool allow_pa
     // (the shared filter needs 4-row waves to keep the workgroup's LDS under 64 KB)
     const bool bloom = variant == ELOC_TERMS && c->tune_bloom != 0 && c->bloom_words > 0 && c->tune_rows != 8 &&
                        c->tune_waves != 1;
-    const int rows = c->tune_rows ? c->tune_rows : (bloom ? 4 : 8);
+    // few candidates: 4 rows a wave.  What a wave does one row after another
+    // (a long run, the queue's hits) then bounds the launch: LoopOverTerms, 12
+    // qubits, 300 samples 31 us with 4, 49 with 8; 20 qubits, 6000 66 / 84; from
+    // about 2^26 candidates on the scan's share of a wave counts for more (40
+    // qubits, 9999 551 / 527) but for two-word keys (66 qubits, 3000 1620 / 1880).
+    // LoopOverBatch up to 2^14 samples, with a quarter of the waves: 20 qubits,
+    // 6000 61 / 70; 28 qubits, 8000 81 / 100; 40 qubits, 9999 146 / 148.  A
+    // partitioned table has tiles of its own.
+    const bool small = n_rows < 0 && c->tune_chunks <= 0 && !bloom && c->part_bits == 0 && M <= (int64_t(1) << 14) &&
+                       (variant == ELOC_BATCH ||
+                        (variant == ELOC_TERMS && (c->H.W == 2 || M * c->H.n_groups < (int64_t(1) << 26))));
+    const int rows = c->tune_rows ? c->tune_rows : (bloom || small ? 4 : 8);
     P.rows_per_block = rows_per_block(variant, rows);
     P.waves_per_block = bloom ? 4 : 1;
     // the exact prefilters of LoopOverTerms (U's single popcount signature,
@@ -256,7 +267,7 @@ Plan make_plan(const eloc_ctx c, int variant, int64_t n_rows = -1, bool allow_pa
     const int64_t waves = (M + P.rows_per_block - 1) / P.rows_per_block;   // row tiles
     // about 65 536 (row tile, chunk) waves: at the medium workload 8 chunks of
     // LoopOverTerms run 1.17 ms against 1.25 ms with 2 (a shorter tail)
-    const int64_t target = 65536;
+    const int64_t target = small && variant == ELOC_BATCH && c->tune_rows == 0 ? 16384 : 65536;
     const int64_t span = (variant == ELOC_TERMS) ? c->H.n_groups : M;
     const int64_t steps = (span + 63) / 64;
     int64_t chunks = c->tune_chunks > 0 ? c->tune_chunks : (target + waves - 1) / waves;
@@ -1057,7 +1068,7 @@ int eloc_find_misses(eloc_ctx c, double tol, int64_t capacity, uint64_t* keys_de
     }
     if (bitmap && !(c->miss_valid && c->miss_tol == tol)) {
         c->miss_valid = false;
-        const Plan P = make_plan(c, ELOC_TERMS);
+        const Plan P = make_plan(c, ELOC_TERMS, c->S.n);
         ELOC_HIP(c, c->m_raw.ensure(sizeof(uint32_t) * nwords));
         ELOC_HIP(c, c->m_flags.ensure(sizeof(int32_t) * nwords));
         ELOC_HIP(c, c->m_pos.ensure(sizeof(int64_t) * (nwords + 1)));
@@ -1074,7 +1085,7 @@ int eloc_find_misses(eloc_ctx c, double tol, int64_t capacity, uint64_t* keys_de
         total = uniq;
     } else if (!(c->miss_valid && c->miss_tol == tol)) {
         c->miss_valid = false;
-        const Plan P = make_plan(c, ELOC_TERMS);
+        const Plan P = make_plan(c, ELOC_TERMS, c->S.n);
         // one append pass into the buffer as it stands; when the states
         // outnumber it, a second pass into one of the counted size
         ELOC_HIP(c, c->m_count.ensure(sizeof(unsigned long long)));
