@@ -74,12 +74,15 @@ inline void join_insert(std::vector<JoinSlot<W>>& t, JoinStr<W> key, uint32_t id
 }
 
 // T[idx] of a group whose terms share z; false where the dependence on ket & m
-// does not go through idx.  mixed: y is a union of the spin-up and the
-// spin-down part, whose parities idx holds; else y is an even subset of at most
-// four bits, and idx holds the parities of join_parity_masks and of all.
+// does not go through idx.  mixed: y is y0 (ya0, yb0) with the spin-up part,
+// the spin-down part, both or neither flipped, idx holds the parities of the
+// parts, and the sign of y0 is left to the caller (where a Jordan-Wigner string
+// of one spin passes over a flipped orbital of the other, y0 is not empty); else
+// y is an even subset of at most four bits, and idx holds the parities of
+// join_parity_masks and of all.
 template <int W>
 inline bool join_signs(const HostHam<W>& hh, const GroupRec<W>& gr, JoinStr<W> a, JoinStr<W> b, bool mixed,
-                       double (&T)[kJoinIdx]) {
+                       JoinStr<W> ya0, JoinStr<W> yb0, double (&T)[kJoinIdx]) {
     using ST = JoinStr<W>;
     const ST w = a | b;
     if (!mixed && join_count(w) > 4) return false;
@@ -107,6 +110,8 @@ inline bool join_signs(const HostHam<W>& hh, const GroupRec<W>& gr, JoinStr<W> a
         ST ya, yb;
         spin_strings<W>(y, ya, yb);
         if (mixed) {
+            ya ^= ya0;
+            yb ^= yb0;
             if ((ya != 0 && ya != a) || (yb != 0 && yb != b)) return false;
             c[(ya != 0 ? 1 : 0) + (yb != 0 ? 2 : 0)] += tr.h;
         } else {
@@ -153,9 +158,19 @@ bool join_place_one(const HostHam<W>& hh, const GroupRec<W>& gr, size_t place, b
     }
     if (!one) return false;
     double T[kJoinIdx];
-    if (!join_signs<W>(hh, gr, a, b, mixed, T)) return true;
+    uint64_t y0[W];
+    for (int w = 0; w < W; ++w) y0[w] = hh.terms[static_cast<size_t>(gr.begin)].yz[w] & gr.xy[w];
+    ST ya0 = 0, yb0 = 0;
+    if (mixed) {   // with each part's fewer bits
+        spin_strings<W>(y0, ya0, yb0);
+        if (2 * join_count(ya0) > join_count(a)) ya0 ^= a;
+        if (2 * join_count(yb0) > join_count(b)) yb0 ^= b;
+    }
+    if (!join_signs<W>(hh, gr, a, b, mixed, ya0, yb0, T)) return true;
     pl = join_tag<W>(kJoinSign);
     spin_strings<W>(z, pl.za, pl.zb);
+    pl.za ^= ya0;
+    pl.zb ^= yb0;
     for (size_t i = 0; i < kJoinIdx; ++i) out.sign[i * P + place] = T[i];
     if (mixed) {
         uint64_t bits;

@@ -116,6 +116,17 @@ def test_energy_and_adjoint(case, precision):
     assert (g - g2).abs().max().item() <= TOL[precision] * max(1.0, g2.abs().max().item())
 
 
+def test_join_is_taken(case):
+    """The two routes add a row's pairs in different orders: the same bits in
+    every row of thousands would mean that the loops served both."""
+    eng, ham, keys, lp, variant, rows = case
+    L = dev(lp)
+    joined = eng.local_energy(L, None, variant)[0].clone()
+    plain = eng.local_energy(L, None, loops(eng))[0].clone()
+    eng.set_tuning()
+    assert (joined != plain).any()
+
+
 def test_pair_list(case):
     eng, ham, keys, lp, variant, rows = case
     got = [t.clone() for t in eng.find_pairs(variant)]
