@@ -32,21 +32,23 @@ sys.path.insert(0, str(ROOT))
 
 PROFILES = ROOT / "profiles"
 GOLDEN = ROOT / "tests" / "golden"
-PAIR_SOURCES = [ROOT / "paper_2408_07625_amd" / "csrc" / f for f in ("pairs.hip", "device.h", "internal.h")]
+CSRC = ROOT / "paper_2408_07625_amd" / "csrc"
+PAIR_SOURCES = [CSRC / f for f in ("pairs.hip", "device.h", "internal.h")]
+JOIN_SOURCES = [CSRC / f for f in ("join.hip", "join.h", "device.h", "internal.h")]
 
 PEAK_LANE_OPS = 256 * 64 * 2.4e9   # CUs x lanes x clock: one wave instruction per CU per clock
 PEAK_HBM = 8.0e12                  # bytes/s
 
 
-def pair_source_hash() -> str:
+def source_hash(sources) -> str:
     import hashlib
     h = hashlib.sha256()
-    for p in PAIR_SOURCES:
+    for p in sources:
         h.update(p.read_bytes())
     return h.hexdigest()[:16]
 
 
-def measured_traffic(name: str):
+def measured_traffic(name: str, sources):
     """HBM bytes per launch of the pair kernel from a committed counter
     summary, if it was taken on the current kernel source; else None."""
     path = PROFILES / name
@@ -57,7 +59,7 @@ def measured_traffic(name: str):
         if ":" in line and line.startswith("- "):
             k, v = line[2:].split(":", 1)
             fields[k.strip()] = v.strip().strip("`")
-    if fields.get("source_hash") != pair_source_hash():
+    if fields.get("source_hash") != source_hash(sources):
         return None
     try:
         return float(fields["hbm_bytes_per_launch"])
@@ -81,7 +83,11 @@ def ops_per_candidate(variant: str, W: int) -> int:
     return 4 * W + 2
 
 
+#  spin-string join, a coupled pair: its place by position (XORs, bit
+#  positions, about 15) and the element's sign from two masks (about 15); the
+#  columns it scans to find the pairs are not counted.
 OPS_PER_TERM = 12
+OPS_PER_JOIN_PAIR = 30
 OPS_PER_PAIR = {"fp64": 4, "fp32c": 30}
 
 
@@ -167,15 +173,21 @@ def time_steps(eng, step, steps, warmup):
     return e0.elapsed_time(e1) / steps, prof
 
 
-def roofline(variant, prec, W, M, n_terms, n_groups, cand, term_evals, n_pairs, kernel_s, traffic):
-    ops = cand * ops_per_candidate(variant, W) + term_evals * OPS_PER_TERM + n_pairs * OPS_PER_PAIR[prec]
+def roofline(variant, prec, W, M, n_terms, n_groups, cand, term_evals, n_pairs, kernel_s, traffic, joined=False):
+    """joined: the spin-string join ran in place of the variant's loop; it meets
+    no candidates and evaluates no terms, so only the pairs' own work counts."""
+    if joined:
+        ops = n_pairs * (OPS_PER_JOIN_PAIR + OPS_PER_PAIR[prec])
+    else:
+        ops = cand * ops_per_candidate(variant, W) + term_evals * OPS_PER_TERM + n_pairs * OPS_PER_PAIR[prec]
     # compulsory bytes of one launch: keys, amplitudes in, row sums out,
     # the term and group records of the Hamiltonian
     compulsory = M * (8 * W + 16 + 16) + n_terms * (8 * W + 8) + n_groups * (8 * W + 8)
     achieved = ops / kernel_s
     r = {"bound": "alu", "achieved": achieved / 1e12, "peak": PEAK_LANE_OPS / 1e12, "unit": "Tlane-op/s",
          "frac": achieved / PEAK_LANE_OPS, "traffic": traffic,
-         "kernel": f"k_pairs {variant} {prec} (fused FindCoupledPairs + MatrixElement + accumulation)",
+         "kernel": (f"k_join {prec} (spin-string join in place of {variant}; the pairs' own operations)" if joined else
+                    f"k_pairs {variant} {prec} (fused FindCoupledPairs + MatrixElement + accumulation)"),
          "kernel_ms": kernel_s * 1e3, "ops_per_launch": ops,
          "hbm": {"compulsory_bytes": compulsory, "compulsory_frac": compulsory / kernel_s / PEAK_HBM,
                  "counter_bytes": traffic,
@@ -220,20 +232,24 @@ def main():
             eng.local_energy(L, Wt, variant, prec, out=out, stats=stats, check=False)
         return step
 
+    def measure(var, prec, steps, warm, label):
+        ms, prof = time_steps(eng, make_step(var, prec), steps, warm)
+        print(f"# {label} {prec}: {ms:.3f} ms/step  stages(ms/launch): " +
+              ", ".join(f"{k}={v[0] / v[1]:.3f}" for k, v in prof.items() if v[1]), file=sys.stderr, flush=True)
+        return {"ms_per_step": ms, "steps": steps, "stage_ms": {k: v[0] / v[1] for k, v in prof.items() if v[1]},
+                "eloc": out.cpu().numpy().copy(), "stats": stats.cpu().numpy().copy()}
+
+    # the headline: the variant as a caller asks for it, which the spin-string
+    # join may serve; then the variants' own loops (a set launch shape keeps
+    # them), which give the same sums in another order
+    head_res = {prec: measure(args.variant, prec, args.steps, args.warmup, args.variant) for prec in ("fp64", "fp32c")}
     order = [args.variant] + [v for v in ("terms", "batch", "trie") if v != args.variant and not args.only]
     res = {}
+    eng.set_tuning(rows_per_wave=8, partition=args.partition, partition_count=args.partition_count)
     for var in order:
-        steps = args.steps if var == args.variant else min(args.steps, args.other_steps)
-        warm = args.warmup if var == args.variant else min(args.warmup, 2)
-        for prec in ("fp64", "fp32c"):
-            ms, prof = time_steps(eng, make_step(var, prec), steps, warm)
-            res.setdefault(var, {})[prec] = {
-                "ms_per_step": ms, "steps": steps,
-                "stage_ms": {k: v[0] / v[1] for k, v in prof.items() if v[1]},
-                "eloc": out.cpu().numpy().copy(), "stats": stats.cpu().numpy().copy()}
-            print(f"# {var} {prec}: {ms:.3f} ms/step  stages(ms/launch): " +
-                  ", ".join(f"{k}={v[0] / v[1]:.3f}" for k, v in prof.items() if v[1]),
-                  file=sys.stderr, flush=True)
+        res[var] = {prec: measure(var, prec, min(args.steps, args.other_steps), min(args.warmup, 2), f"{var} loop")
+                    for prec in ("fp64", "fp32c")}
+    joined = not np.array_equal(head_res["fp64"]["eloc"], res[args.variant]["fp64"]["eloc"])
 
     # work counts (outside the timed regions)
     sizes = group_sizes_by_id(w.ham)
@@ -246,11 +262,11 @@ def main():
         assert counts[var]["coupled_pairs"] == n_pairs, (var, counts[var], n_pairs)
     print(f"# {n_pairs} coupled pairs, {term_evals} term evaluations", file=sys.stderr, flush=True)
 
-    head = res[args.variant]["fp32c"]
-    fp64 = res[args.variant]["fp64"]
+    head = head_res["fp32c"]
+    fp64 = head_res["fp64"]
     pairs_s = n_pairs / (head["ms_per_step"] * 1e-3)
 
-    traffic = measured_traffic(f"k_pairs_{w.name}_{args.variant}_fp32c_traffic.md")
+    traffic = measured_traffic(f"k_pairs_{w.name}_{args.variant}_fp32c_traffic.md", PAIR_SOURCES)
     rooflines = {}
     for var in order:
         if counts[var]["candidates"] is None:
@@ -261,6 +277,10 @@ def main():
                                                   n_pairs, k_ms * 1e-3,
                                                   traffic if (var, prec) == (args.variant, "fp32c") else None)
     roof = rooflines[f"{args.variant}_fp32c"]
+    if joined:
+        roof = roofline(args.variant, "fp32c", W, M, NT, G, counts[args.variant]["candidates"], term_evals, n_pairs,
+                        head["stage_ms"]["pairs"] * 1e-3,
+                        measured_traffic(f"k_join_{w.name}_fp32c_traffic.md", JOIN_SOURCES), joined=True)
 
     rec = {
         "metric": "coupled pairs/sec + E_loc^var samples/sec vs plain FP64 at |dE|<=1e-6 Ha",
@@ -270,13 +290,15 @@ def main():
         "vs_baseline": None, "dtype": "f32c", "data": "synthetic",
         "config": {"workload": f"{w.name}: {N} qubits, {w.n_electrons} electrons, {M} unique determinants, "
                                f"{NT} Pauli terms in {G} XY groups",
-                   "variant": args.variant, "global_batch": M},
+                   "variant": args.variant, "route": "spin-string join" if joined else "loop", "global_batch": M},
         "samples_per_s": M / (head["ms_per_step"] * 1e-3),
         "coupled_pairs": n_pairs, "candidates": counts[args.variant]["candidates"], "term_evaluations": term_evals,
         "fp64": {"pairs_per_s": n_pairs / (fp64["ms_per_step"] * 1e-3),
                  "samples_per_s": M / (fp64["ms_per_step"] * 1e-3), "ms_per_step": fp64["ms_per_step"]},
         "fp32c_over_fp64": fp64["ms_per_step"] / head["ms_per_step"],
         "roofline": roof,
+        "headline": {prec: {"ms_per_step": head_res[prec]["ms_per_step"], "stage_ms": head_res[prec]["stage_ms"]}
+                     for prec in ("fp64", "fp32c")},
         "variants": {var: {prec: {"ms_per_step": res[var][prec]["ms_per_step"], "steps": res[var][prec]["steps"],
                                   "pairs_per_s": n_pairs / (res[var][prec]["ms_per_step"] * 1e-3),
                                   "stage_ms": res[var][prec]["stage_ms"],
@@ -293,9 +315,9 @@ def main():
         E_ref = gold["stats"][0] + 1j * gold["stats"][1]
         rec["accuracy"] = {"reference": f"oracle results stored in tests/golden/{gold_path.name} "
                                         f"({rows.size} sampled rows; E and Var over all rows)"}
-        for var in order:
+        for var, by_prec in [("headline", head_res)] + [(v, res[v]) for v in order]:
             for prec in ("fp64", "fp32c"):
-                r = res[var][prec]
+                r = by_prec[prec]
                 rec["accuracy"][f"{var}_{prec}"] = {
                     "max_abs_dE_loc": float(np.abs(r["eloc"][rows] - gold["eloc"]).max()),
                     "abs_dE": float(abs(r["stats"][0] + 1j * r["stats"][1] - E_ref)),
@@ -303,7 +325,7 @@ def main():
         rec["energy"] = {"E": float(gold["stats"][0]), "Var": float(gold["stats"][2])}
 
     if not args.no_cpu_baseline:
-        rec["cpu_baseline"] = cpu_baseline(w, res[args.variant])
+        rec["cpu_baseline"] = cpu_baseline(w, head_res)
     if not args.no_medium and w.name != "medium":
         eng.close()
         eng = None
@@ -374,7 +396,8 @@ def cpu_baseline(w, res_head):
 
 
 def bench_medium(args):
-    """28 qubits, 65 536 samples: LoopOverTerms, both precisions."""
+    """28 qubits, 65 536 samples: LoopOverTerms, both precisions, as a caller
+    asks for it (which the spin-string join serves) and its own loop."""
     import numpy as np
     import torch
 
@@ -392,20 +415,30 @@ def bench_medium(args):
     stats = torch.empty(4, dtype=torch.float64, device="cuda")
     r = {"workload": f"medium: {N} qubits, {w.n_electrons} electrons, {M} unique determinants, "
                      f"{info['n_terms']} Pauli terms in {info['n_groups']} XY groups", "variant": "terms"}
-    for prec in ("fp64", "fp32c"):
-        def step():
-            eng.set_samples(keys, check=False)
-            eng.local_energy(L, None, "terms", prec, out=out, stats=stats, check=False)
-        ms, prof = time_steps(eng, step, args.steps, args.warmup)
-        r[prec] = {"ms_per_step": ms, "stage_ms": {k: v[0] / v[1] for k, v in prof.items() if v[1]}}
+    eloc = {}
+    for route in ("default", "loop"):
+        eng.set_tuning(rows_per_wave=8 if route == "loop" else 0)
+        for prec in ("fp64", "fp32c"):
+            def step():
+                eng.set_samples(keys, check=False)
+                eng.local_energy(L, None, "terms", prec, out=out, stats=stats, check=False)
+            ms, prof = time_steps(eng, step, args.steps, args.warmup)
+            d = {"ms_per_step": ms, "stage_ms": {k: v[0] / v[1] for k, v in prof.items() if v[1]}}
+            if route == "default":
+                r[prec] = d
+            else:
+                r[prec]["loop"] = d
+        eloc[route] = out.cpu().numpy().copy()
+    joined = not np.array_equal(eloc["default"], eloc["loop"])
+    r["route"] = "spin-string join" if joined else "loop"
     n_pairs = eng.count_pairs("terms")
     te = term_evaluations(eng, "terms", group_sizes_by_id(w.ham))
     r["coupled_pairs"] = n_pairs
     for prec in ("fp64", "fp32c"):
         r[prec]["pairs_per_s"] = n_pairs / (r[prec]["ms_per_step"] * 1e-3)
-        rf = roofline("terms", prec, W, M, info["n_terms"], info["n_groups"], M * info["n_groups"], te, n_pairs,
-                      r[prec]["stage_ms"]["pairs"] * 1e-3, None)
-        r[prec]["roofline_frac"] = rf["frac"]
+        for d, jn in ((r[prec], joined), (r[prec]["loop"], False)):
+            d["roofline_frac"] = roofline("terms", prec, W, M, info["n_terms"], info["n_groups"], M * info["n_groups"],
+                                          te, n_pairs, d["stage_ms"]["pairs"] * 1e-3, None, joined=jn)["frac"]
     print(f"# medium: fp64 {r['fp64']['ms_per_step']:.3f} ms, fp32c {r['fp32c']['ms_per_step']:.3f} ms",
           file=sys.stderr, flush=True)
     eng.close()
@@ -646,6 +679,21 @@ def bench_batched(args):
         out["coupled_pairs"] = pairs
         print(f"# batched {prec}: graph {ms:.3f} ms, eager {ms_eager:.3f} ms, {pairs} pairs, stages "
               + ", ".join(f"{k}={v[0] / max(v[1], 1):.3f}" for k, v in prof.items()), file=sys.stderr, flush=True)
+    # the work items alone: any other ratio than the default 1 keeps the joins
+    # out, and no problem has as many samples as masks within a millionth
+    loops = dict(schedule, batch_ratio=min(schedule["batch_ratio"], 1 - 1e-6) if schedule["batch_ratio"] == 1 else
+                 schedule["batch_ratio"])
+    b.set_schedule(**loops)
+    b.set_graph(False)
+    for prec in ("fp32c", "fp64"):
+        b.profile(True)
+        b.profile_read()
+        ms = timed(lambda: b.run(prec, check=False), max(1, args.steps // 4))
+        b.check()
+        prof = b.profile_read()
+        b.profile(False)
+        out[prec]["loops"] = {"eager_ms_per_step": ms,
+                              "eager_stage_ms": {k: v[0] / v[1] for k, v in prof.items() if v[1]}}
     # the same problems one by one: one context each (Hamiltonian ingested
     # once), each step sets the samples and runs the forward pass
     engines = []
@@ -677,10 +725,10 @@ def bench_batched(args):
         out[prec]["speedup_vs_sequential"] = ms / out[prec]["ms_per_step"]
         print(f"# sequential {prec}: {ms:.3f} ms", file=sys.stderr, flush=True)
         ops = cand + te * OPS_PER_TERM + pairs_k * OPS_PER_PAIR[prec]
-        k_s = out[prec]["eager_stage_ms"]["pairs"] * 1e-3
+        k_s = out[prec]["loops"]["eager_stage_ms"]["pairs"] * 1e-3
         out[prec]["roofline"] = {"bound": "alu", "achieved": ops / k_s / 1e12, "peak": PEAK_LANE_OPS / 1e12,
                                  "unit": "Tlane-op/s", "frac": ops / k_s / PEAK_LANE_OPS,
-                                 "kernel": "k_pairs_batched (both key formats), eager launch",
+                                 "kernel": "k_pairs_batched (both key formats), eager launch without joins",
                                  "kernel_ms": k_s * 1e3, "ops_per_launch": ops}
     out["term_evaluations"] = te
     out["fp32c_over_fp64"] = out["fp64"]["ms_per_step"] / out["fp32c"]["ms_per_step"]
