@@ -67,7 +67,10 @@ enum eloc_status {
     ELOC_EAGAIN = -8     /* a hash table overflowed and was rebuilt; repeat the call  */
 };
 
-/* FindCoupledPairs variants (Sec. "FindCoupledPairs implementations"). */
+/* FindCoupledPairs variants (Sec. "FindCoupledPairs implementations").  The
+ * first four give the same pairs; where it is the shorter way a join of the
+ * samples' spin-up and spin-down strings serves them in place of the loop
+ * named, unless eloc_set_tuning names rows per wave or the like. */
 enum eloc_variant {
     ELOC_TERMS = 0, /* loop over the unique XY set, look x ^ XY up in U (Alg. 2A)   */
     ELOC_BATCH = 1, /* loop over U, look x ^ x' up in the XY set (Alg. 2B)           */
