@@ -14,10 +14,12 @@ PKG = Path(__file__).resolve().parent
 ROOT = PKG.parent
 CSRC = PKG / "csrc"
 LIB = PKG / "libeloc.so"
-SOURCES = [CSRC / "kernels.hip", CSRC / "pairs.hip", CSRC / "join.hip", CSRC / "batch.hip", CSRC / "misses.hip", CSRC / "sr.hip", CSRC / "sampler.hip",
+SOURCES = [CSRC / "kernels.hip", CSRC / "pairs.hip", CSRC / "join.hip", CSRC / "batch.hip", CSRC / "misses.hip",
+           CSRC / "full.hip", CSRC / "sr.hip", CSRC / "sampler.hip",
            CSRC / "api.cpp",
            CSRC / "batch.cpp"]
 HEADERS = [CSRC / "internal.h", CSRC / "device.h", CSRC / "trie.h", CSRC / "ham.h", CSRC / "host.h", CSRC / "join.h",
+           CSRC / "full.h",
            ROOT / "include" / "eloc.h"]
 
 # Packed-FP32 instructions are disabled for all HIP code (the compiler would

@@ -5,6 +5,7 @@
 #include "ham.h"
 #include "host.h"
 #include "internal.h"
+#include "full.h"
 #include "join.h"
 #include "trie.h"
 
@@ -110,6 +111,7 @@ struct eloc_ctx_s {
     int64_t miss_total = 0, miss_uniq = 0;
     DevBuf x_keys, x_hash, x_slots, x_stash, x_sig, x_bitcounts, x_rad, x_params, x_err, x_logpsi;
     DevBuf x_a, x_b, x_af, x_bf, x_shift;
+    DevBuf x_perm;                                   // the U-and-extra states by partition class
     DevBuf x_part_perm, x_part_class, x_part_tile;   // U's rows by partition class of the U-and-extra table
     // stochastic reconfiguration scratch
     DevBuf sr_w, sr_mean, sr_part, sr_T, sr_y;
@@ -181,6 +183,18 @@ bool use_join(const eloc_ctx c, int64_t M, int variant) {
         c->tune_part || c->tune_part_count || c->tune_trie_chunk)
         return false;
     return join_pays(M, variant == ELOC_BATCH ? M * M : M * c->H.n_groups * (variant == ELOC_TRIE ? 8 : 1));
+}
+
+// Whether U's rows over U and n_extra states more are summed with lanes over
+// rows (full.hip): one-word keys, launch shape not tuned, and the larger set
+// mostly coupled states, so that most candidates are pairs.  A whole call, loop
+// / lanes over rows: 12 qubits, 100 rows, 300 states more 347 / 285 us; 14
+// qubits, 500 and 725 392 / 324; 16 qubits, 1677 and 3223 488 / 401; 28 qubits,
+// 20 000 and 3.8e6 3820 / 2745, the search for the states in all of them.
+// Fewer states than rows were not measured.
+bool full_by_rows(const eloc_ctx c, int64_t M, int64_t n_extra) {
+    return c->H.W == 1 && n_extra >= M && !c->tune_chunks && c->tune_sig && !c->tune_rows && !c->tune_bloom &&
+           !c->tune_waves && !c->tune_part && !c->tune_part_count;
 }
 
 // Room for the index of n samples (eloc_set_samples makes it for the variants
@@ -783,7 +797,7 @@ void eloc_destroy(eloc_ctx c) {
                       &c->ut_keys, &c->ut_perm, &c->ut_nodes, &c->ut_nkeys, &c->s_key, &c->s_val, &c->s_key2, &c->s_val2,
                       &c->m_raw, &c->m_sorted, &c->m_perm, &c->m_flags, &c->m_pos, &c->m_count, &c->m_rules, &c->x_keys, &c->x_hash, &c->x_slots,
                       &c->x_stash, &c->x_sig, &c->x_bitcounts, &c->x_rad, &c->x_params, &c->x_err, &c->x_logpsi,
-                      &c->x_a, &c->x_b, &c->x_af, &c->x_bf, &c->x_shift, &c->x_part_perm, &c->x_part_class, &c->x_part_tile, &c->st_rowptr, &c->st_col, &c->st_h,
+                      &c->x_a, &c->x_b, &c->x_af, &c->x_bf, &c->x_shift, &c->x_perm, &c->x_part_perm, &c->x_part_class, &c->x_part_tile, &c->st_rowptr, &c->st_col, &c->st_h,
                       &c->sr_w, &c->sr_mean, &c->sr_part, &c->sr_T, &c->sr_y,
                       &c->groups_b, &c->ghash_b, &c->gsplit_b, &c->gid_b, &c->gsplit, &c->gbucket, &c->part_perm, &c->part_class, &c->part_tile,
                       &c->ar_keys[0], &c->ar_keys[1], &c->ar_l[0], &c->ar_l[1], &c->ar_T[0], &c->ar_T[1],
@@ -1153,6 +1167,38 @@ int eloc_find_misses(eloc_ctx c, double tol, int64_t capacity, uint64_t* keys_de
     return ELOC_OK;
 }
 
+// X's keys and hashes (c->x_keys, c->x_hash: X states) in the order of their
+// partition class, into the sort scratch; x_perm is that order.  Without the
+// memory for it *done stays false.
+static int order_by_class(eloc_ctx c, int64_t X, int bits, bool* done) {
+    const int64_t tiles = radix_tiles(X);
+    hipError_t e = c->s_key.ensure(sizeof(uint64_t) * X);
+    if (e == hipSuccess) e = c->s_key2.ensure(sizeof(uint64_t) * X);
+    if (e == hipSuccess) e = c->s_val.ensure(sizeof(uint32_t) * X);
+    if (e == hipSuccess) e = c->s_val2.ensure(sizeof(uint32_t) * X);
+    if (e == hipSuccess) e = c->x_perm.ensure(sizeof(int32_t) * X);
+    if (e == hipSuccess) e = c->hist.ensure(sizeof(uint32_t) * 256 * tiles);
+    if (e == hipSuccess) e = c->hist_off.ensure(sizeof(int64_t) * (256 * tiles + 1));
+    if (e == hipSuccess) e = c->hist_scratch.ensure(sizeof(int64_t) * scan_scratch_len(256 * tiles));
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();
+        for (DevBuf* b : {&c->s_key, &c->s_key2, &c->s_val, &c->s_val2, &c->x_perm}) b->release();
+        return ELOC_OK;
+    }
+    ELOC_HIP(c, e);
+    ELOC_HIP(c, c->x_part_class.ensure(sizeof(int64_t) * (kMaxParts + 1)));
+    ELOC_HIP(c, c->x_part_tile.ensure(sizeof(int64_t) * (kMaxParts + 1)));
+    ELOC_HIP(c, launch_row_classes(c->x_hash.as<uint64_t>(), X, c->H.part.shift, bits, c->s_key.as<uint64_t>(),
+                                   c->s_val.as<uint32_t>(), c->s_key2.as<uint64_t>(), c->s_val2.as<uint32_t>(),
+                                   c->hist.as<uint32_t>(), c->hist_off.as<int64_t>(), c->hist_scratch.as<int64_t>(),
+                                   c->x_perm.as<int32_t>(), c->x_part_class.as<int64_t>(),
+                                   c->x_part_tile.as<int64_t>(), c->stream));
+    ELOC_HIP(c, launch_full_order(X, c->x_perm.as<int32_t>(), c->x_keys.as<uint64_t>(), c->x_hash.as<uint64_t>(),
+                                  c->s_key.as<uint64_t>(), c->s_key2.as<uint64_t>(), c->stream));
+    *done = true;
+    return ELOC_OK;
+}
+
 int eloc_local_energy_full(eloc_ctx c, int precision, const eloc_c64* logpsi_dev, const double* weights_dev,
                            int64_t n_extra, const uint64_t* extra_keys_dev, const eloc_c64* extra_logpsi_dev,
                            eloc_c64* eloc_dev, double* stats_dev) {
@@ -1208,6 +1254,20 @@ int eloc_local_energy_full(eloc_ctx c, int precision, const eloc_c64* logpsi_dev
     // a large table is split into partitions as U's is (the group records are
     // bucketed for the same partition shift at ingest)
     const int xbits = part_bits_for(c, slot_bytes(tk) * cap, cap);
+    // with lanes over rows a partition's states are neighbours, so that their
+    // amplitudes stay in the L2 that probes the partition
+    const bool by_rows = full_by_rows(c, M, n_extra);
+    Plan P = by_rows ? full_plan(c->H, M, xbits) : make_plan(c, ELOC_TERMS, M);
+    P.bloom_words = 0;
+    bool ordered = false;
+    if (by_rows && P.part) {
+        rc = order_by_class(c, X, xbits, &ordered);
+        if (rc) return rc;
+        if (ordered) {
+            S.keys = c->s_key.as<uint64_t>();
+            S.hash = c->s_key2.as<uint64_t>();
+        }
+    }
     uint32_t bits = kErrTable;
     for (int attempt = 0; attempt < 8 && (bits & kErrTable) && !(bits & kErrBits); ++attempt) {
         S.table = make_table(c->x_slots.p, c->x_stash.as<Stash>(), cap, X, splitmix64(c->salt_state),
@@ -1216,7 +1276,7 @@ int eloc_local_energy_full(eloc_ctx c, int precision, const eloc_c64* logpsi_dev
         ELOC_HIP(c, hipMemsetAsync(c->x_stash.p, 0, sizeof(Stash), c->stream));
         ELOC_HIP(c, hipMemsetAsync(c->x_sig.p, 0, sizeof(uint64_t) * kSigWords, c->stream));
         if (attempt > 0) ELOC_HIP(c, hipMemsetAsync(c->x_err.p, 0, sizeof(uint32_t), c->stream));
-        ELOC_HIP(c, launch_table_insert(tk, c->x_hash.as<uint64_t>(), X, c->x_slots.p, c->x_stash.as<Stash>(), S.table,
+        ELOC_HIP(c, launch_table_insert(tk, S.hash, X, c->x_slots.p, c->x_stash.as<Stash>(), S.table,
                                         c->x_err.as<uint32_t>(), c->stream));
         ELOC_HIP(c, launch_sample_verify(W, c->H.narrow, S, c->x_bitcounts.as<uint32_t>(),
                                          c->x_rad.as<unsigned long long>(), c->x_sig.as<uint64_t>(),
@@ -1240,10 +1300,20 @@ int eloc_local_energy_full(eloc_ctx c, int precision, const eloc_c64* logpsi_dev
     ELOC_HIP(c, launch_amp_prep(c->x_logpsi.as<double2>(), X, fp32, c->x_a.as<double2>(), c->x_b.as<double2>(),
                                 c->x_af.as<float4>(), c->x_bf.as<float4>(), c->x_shift.as<double>(),
                                 c->amp_scratch.as<double>(), c->err_run.as<uint32_t>(), true, c->stream));
-    Plan P = make_plan(c, ELOC_TERMS, M);
-    P.bloom_words = 0;
+    S.keys = c->x_keys.as<uint64_t>();
+    S.hash = c->x_hash.as<uint64_t>();
+    const double2* vec = c->x_a.as<double2>();
+    const float4* vecf = c->x_af.as<float4>();
+    if (ordered) {
+        // the log-amplitudes are used up
+        double2* to = c->x_logpsi.as<double2>();
+        ELOC_HIP(c, launch_full_vec(X, c->x_perm.as<int32_t>(),
+                                    fp32 ? reinterpret_cast<const double2*>(vecf) : vec, to, c->stream));
+        vec = to;
+        vecf = reinterpret_cast<const float4*>(to);
+    }
     S.part.bits = 0;
-    if (xbits > 0) {
+    if (xbits > 0 && (P.part || !by_rows)) {
         // U's rows (the first M of X) in classes by their hashes' partition
         // field, as eloc_set_samples orders them for U's own table
         const int64_t tiles = radix_tiles(M);
@@ -1266,11 +1336,14 @@ int eloc_local_energy_full(eloc_ctx c, int precision, const eloc_c64* logpsi_dev
         S.part.class_off = c->x_part_class.as<int64_t>();
         S.part.tile_off = c->x_part_tile.as<int64_t>();
         S.part.bits = xbits;
-        set_part_plan(P, M, xbits);
+        if (!by_rows) set_part_plan(P, M, xbits);
     }
     ELOC_HIP(c, c->partial.ensure((fp32 ? sizeof(float4) : sizeof(double2)) * P.chunks * M));
-    ELOC_HIP(c, launch_pairs(false, ELOC_TERMS, precision, c->H, S, P, c->x_a.as<double2>(), c->x_af.as<float4>(),
-                             c->partial.p, c->stream));
+    if (by_rows)
+        ELOC_HIP(c, launch_full_rows(precision, c->H, S, P, vec, vecf, c->partial.p, c->stream));
+    else
+        ELOC_HIP(c, launch_pairs(false, ELOC_TERMS, precision, c->H, S, P, c->x_a.as<double2>(), c->x_af.as<float4>(),
+                                 c->partial.p, c->stream));
     ELOC_HIP(c, launch_finish(precision, M, P, c->partial.p, c->x_b.as<double2>(), c->x_bf.as<float4>(),
                               reinterpret_cast<double2*>(eloc_dev), c->stream));
     // weighted energy over U (its own amplitude shift for the |psi|^2 weights)
