@@ -20,6 +20,7 @@ constexpr int kBlock = 256;
 // ---------------------------------------------------------------------------
 // Sample preparation.
 // ---------------------------------------------------------------------------
+// Linear hashes and per-qubit counts of set bits.
 template <int W>
 __global__ __launch_bounds__(kBlock) void k_sample_hash(const uint64_t* __restrict__ keys, int64_t n,
                                                         const uint64_t* __restrict__ R, int n_qubits,
@@ -51,6 +52,67 @@ __global__ __launch_bounds__(kBlock) void k_sample_hash(const uint64_t* __restri
         hash[i] = h;
         if (bad) atomicOr(err, static_cast<uint32_t>(kErrBits));
     }
+    __syncthreads();
+    for (int t = threadIdx.x; t < 64 * W; t += kBlock)
+        if (lc[t]) atomicAdd(counts + t, lc[t]);
+}
+
+// The same for many keys.  A wave takes its keys one qubit after another: lane q
+// holds R's word and the count, the popcount of the lanes' mask.  The loop over
+// a key's set bits gathers R and meets in one LDS counter: 3.8e6 keys of 28
+// qubits 141 us, this 62.  Few keys wait for the longer chain: 65 536 of 28
+// qubits 5.9 and 7.1 us, of 74 qubits 13.0 and 14.4.  The line is where a
+// workgroup begins to take more than 256 keys.
+constexpr int64_t kHashMany = int64_t(1) << 18;
+template <int W>
+__global__ __launch_bounds__(kBlock) void k_sample_hash_many(const uint64_t* __restrict__ keys, int64_t n,
+                                                        const uint64_t* __restrict__ R, int n_qubits,
+                                                        uint64_t* __restrict__ hash, uint32_t* __restrict__ counts,
+                                                        uint32_t* __restrict__ err) {
+    __shared__ uint32_t lc[64 * W];   // per-qubit counts of set bits in this block
+    for (int t = threadIdx.x; t < 64 * W; t += kBlock) lc[t] = 0u;
+    __syncthreads();
+    const int lane = lane_id();
+    const int64_t step = static_cast<int64_t>(gridDim.x) * kBlock;
+    uint32_t mine[W] = {};            // of qubits 64 w + lane, in this wave
+    uint64_t r[W];
+#pragma unroll
+    for (int w = 0; w < W; ++w) r[w] = R[64 * w + lane];
+    bool bad = false;
+    const int64_t first = static_cast<int64_t>(blockIdx.x) * kBlock +
+                          __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x)) / 64 * 64;
+    for (int64_t i0 = first; i0 < n; i0 += step) {
+        const int64_t i = i0 + lane;
+        uint64_t h = 0;
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            uint64_t v = i < n ? keys[i * W + w] : 0ull;
+            const int valid = min(64, max(0, n_qubits - 64 * w));
+            if (valid < 64) {
+                const uint64_t allowed = (1ull << valid) - 1ull;
+                bad = bad || (v & ~allowed) != 0ull;
+            }
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+                const uint32_t bits = static_cast<uint32_t>(v >> (32 * half));
+                const int top = min(32, valid - 32 * half);
+#pragma unroll 4
+                for (int q = 0; q < top; ++q) {
+                    const bool set = (bits & (1u << q)) != 0u;
+                    const uint32_t lo = __builtin_amdgcn_readlane(static_cast<uint32_t>(r[w]), 32 * half + q),
+                                   hi = __builtin_amdgcn_readlane(static_cast<uint32_t>(r[w] >> 32), 32 * half + q);
+                    h ^= set ? (static_cast<uint64_t>(hi) << 32) | lo : 0ull;
+                    const uint32_t c = static_cast<uint32_t>(__popcll(__builtin_amdgcn_ballot_w64(set)));
+                    mine[w] += lane == 32 * half + q ? c : 0u;
+                }
+            }
+        }
+        if (i < n) hash[i] = h;
+    }
+    if (bad) atomicOr(err, static_cast<uint32_t>(kErrBits));
+#pragma unroll
+    for (int w = 0; w < W; ++w)
+        if (mine[w]) atomicAdd(&lc[64 * w + lane], mine[w]);
     __syncthreads();
     for (int t = threadIdx.x; t < 64 * W; t += kBlock)
         if (lc[t]) atomicAdd(counts + t, lc[t]);
@@ -790,12 +852,9 @@ __global__ void k_class_bounds(const uint64_t* __restrict__ key, const uint32_t*
 // ---------------------------------------------------------------------------
 hipError_t launch_sample_hash(int W, const uint64_t* keys, int64_t n, const uint64_t* R, int n_qubits,
                               uint64_t* hash, uint32_t* counts, uint32_t* err, hipStream_t st) {
-    if (W == 1)
-        hipLaunchKernelGGL(k_sample_hash<1>, dim3(few_blocks(n)), dim3(kBlock), 0, st, keys, n, R, n_qubits, hash,
-                           counts, err);
-    else
-        hipLaunchKernelGGL(k_sample_hash<2>, dim3(few_blocks(n)), dim3(kBlock), 0, st, keys, n, R, n_qubits, hash,
-                           counts, err);
+    const auto kernel = n > kHashMany ? (W == 1 ? &k_sample_hash_many<1> : &k_sample_hash_many<2>)
+                                      : (W == 1 ? &k_sample_hash<1> : &k_sample_hash<2>);
+    hipLaunchKernelGGL(kernel, dim3(few_blocks(n)), dim3(kBlock), 0, st, keys, n, R, n_qubits, hash, counts, err);
     return hipGetLastError();
 }
 
