@@ -1084,16 +1084,17 @@ int eloc_find_misses(eloc_ctx c, double tol, int64_t capacity, uint64_t* keys_de
         c->miss_valid = false;
         const Plan P = make_plan(c, ELOC_TERMS, c->S.n);
         ELOC_HIP(c, c->m_raw.ensure(sizeof(uint32_t) * nwords));
-        ELOC_HIP(c, c->m_flags.ensure(sizeof(int32_t) * nwords));
-        ELOC_HIP(c, c->m_pos.ensure(sizeof(int64_t) * (nwords + 1)));
-        ELOC_HIP(c, c->scan_scratch.ensure(sizeof(int64_t) * scan_scratch_len(nwords)));
+        const int64_t tiles = bitmap_tiles(nwords);
+        ELOC_HIP(c, c->m_flags.ensure(sizeof(int32_t) * tiles));
+        ELOC_HIP(c, c->m_pos.ensure(sizeof(int64_t) * (tiles + 1)));
+        ELOC_HIP(c, c->scan_scratch.ensure(sizeof(int64_t) * scan_scratch_len(tiles)));
         uint32_t* bits = static_cast<uint32_t*>(c->m_raw.p);
         ELOC_HIP(c, hipMemsetAsync(bits, 0, sizeof(uint32_t) * nwords, c->stream));
         ELOC_HIP(c, launch_misses_bitmap(c->H, c->S, P.chunks, P.per_chunk, tol, c->m_rules.p, bits, c->stream));
         ELOC_HIP(c, launch_bitmap_counts(bits, nwords, c->m_flags.as<int32_t>(), c->stream));
-        ELOC_HIP(c, launch_scan_i32(c->m_flags.as<int32_t>(), nwords, c->m_pos.as<int64_t>(),
+        ELOC_HIP(c, launch_scan_i32(c->m_flags.as<int32_t>(), tiles, c->m_pos.as<int64_t>(),
                                     c->scan_scratch.as<int64_t>(), c->stream));
-        ELOC_HIP(c, hipMemcpyAsync(&uniq, c->m_pos.as<int64_t>() + nwords, sizeof(int64_t), hipMemcpyDeviceToHost,
+        ELOC_HIP(c, hipMemcpyAsync(&uniq, c->m_pos.as<int64_t>() + tiles, sizeof(int64_t), hipMemcpyDeviceToHost,
                                    c->stream));
         ELOC_HIP(c, hipStreamSynchronize(c->stream));
         total = uniq;

@@ -930,8 +930,11 @@ hipError_t launch_misses(const HamDev& H, const SampleDev& S, int chunks, int pe
 constexpr int kMissBitmapQubits = 30;
 hipError_t launch_misses_bitmap(const HamDev& H, const SampleDev& S, int chunks, int per_chunk, double tol,
                                 const void* rules, uint32_t* bitmap, hipStream_t st);
-// counts[w] = popcount(bitmap[w]); keys of the set bits in ascending order
-// to out at the exclusive prefix sums pos of those counts
+// counts[t] = set bits of the t-th kBitmapTile words; keys of the set bits in
+// ascending order to out at the exclusive prefix sums pos of those counts.
+// bitmap: aligned to 16 bytes
+constexpr int kBitmapTile = 1024;
+inline int64_t bitmap_tiles(int64_t nwords) { return (nwords + kBitmapTile - 1) / kBitmapTile; }
 hipError_t launch_bitmap_counts(const uint32_t* bitmap, int64_t nwords, int32_t* counts, hipStream_t st);
 hipError_t launch_bitmap_keys(const uint32_t* bitmap, int64_t nwords, const int64_t* pos, uint64_t* out,
                               hipStream_t st);

@@ -353,22 +353,52 @@ __global__ void k_scatter_unique(const uint64_t* __restrict__ sorted, int64_t n,
 
 inline unsigned blocks256(int64_t n) { return static_cast<unsigned>((n + 255) / 256); }
 
-__global__ void k_bitmap_counts(const uint32_t* __restrict__ bitmap, int64_t nwords, int32_t* __restrict__ counts) {
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i < nwords) counts[i] = __popc(bitmap[i]);
+// Four words a thread: a workgroup counts a tile, so that the scan is over
+// tiles (2^23 words: counts, scan and keys 140 us by words, 52 by tiles).
+static_assert(kBitmapTile == 4 * 256, "a workgroup's words");
+__device__ __forceinline__ uint4 tile_words(const uint32_t* __restrict__ bitmap, int64_t nwords, int64_t i) {
+    if (i + 4 <= nwords) return *reinterpret_cast<const uint4*>(bitmap + i);
+    uint4 b = make_uint4(0u, 0u, 0u, 0u);
+    if (i < nwords) b.x = bitmap[i];
+    if (i + 1 < nwords) b.y = bitmap[i + 1];
+    if (i + 2 < nwords) b.z = bitmap[i + 2];
+    return b;
 }
 
-__global__ void k_bitmap_keys(const uint32_t* __restrict__ bitmap, int64_t nwords, const int64_t* __restrict__ pos,
-                              uint64_t* __restrict__ out) {
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i >= nwords) return;
-    uint32_t b = bitmap[i];
-    int64_t o = pos[i];
-    while (b) {
-        const int k = __builtin_ctz(b);
-        out[o++] = (static_cast<uint64_t>(i) << 5) | static_cast<uint64_t>(k);
-        b &= b - 1u;
+__device__ __forceinline__ int popc4(const uint4& b) { return __popc(b.x) + __popc(b.y) + __popc(b.z) + __popc(b.w); }
+
+__global__ __launch_bounds__(256) void k_bitmap_counts(const uint32_t* __restrict__ bitmap, int64_t nwords,
+                                                       int32_t* __restrict__ counts) {
+    __shared__ int part[4];
+    int c = popc4(tile_words(bitmap, nwords, static_cast<int64_t>(blockIdx.x) * kBitmapTile + threadIdx.x * 4));
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) c += __shfl_xor(c, m, 64);
+    if ((threadIdx.x & 63u) == 0) part[threadIdx.x / 64] = c;
+    __syncthreads();
+    if (threadIdx.x == 0) counts[blockIdx.x] = part[0] + part[1] + part[2] + part[3];
+}
+
+__global__ __launch_bounds__(256) void k_bitmap_keys(const uint32_t* __restrict__ bitmap, int64_t nwords,
+                                                     const int64_t* __restrict__ pos, uint64_t* __restrict__ out) {
+    __shared__ int part[4];
+    const int64_t i = static_cast<int64_t>(blockIdx.x) * kBitmapTile + threadIdx.x * 4;
+    const uint4 b4 = tile_words(bitmap, nwords, i);
+    const int mine = popc4(b4), wave = static_cast<int>(threadIdx.x) / 64;
+    int upto = mine;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int o = __shfl_up(upto, d, 64);
+        if (lane_id() >= d) upto += o;
     }
+    if (lane_id() == 63) part[wave] = upto;
+    __syncthreads();
+    int64_t o = pos[blockIdx.x] + upto - mine;
+    for (int w = 0; w < wave; ++w) o += part[w];
+    const uint32_t words[4] = {b4.x, b4.y, b4.z, b4.w};
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+        for (uint32_t b = words[u]; b; b &= b - 1u)
+            out[o++] = (static_cast<uint64_t>(i + u) << 5) | static_cast<uint64_t>(__builtin_ctz(b));
 }
 
 dim3 miss_grid(const MissArgs& A) {
@@ -438,13 +468,15 @@ hipError_t launch_misses_bitmap(const HamDev& H, const SampleDev& S, int chunks,
 }
 
 hipError_t launch_bitmap_counts(const uint32_t* bitmap, int64_t nwords, int32_t* counts, hipStream_t st) {
-    hipLaunchKernelGGL(k_bitmap_counts, dim3(blocks256(nwords)), dim3(256), 0, st, bitmap, nwords, counts);
+    hipLaunchKernelGGL(k_bitmap_counts, dim3(static_cast<unsigned>(bitmap_tiles(nwords))), dim3(256), 0, st, bitmap, nwords,
+                       counts);
     return hipGetLastError();
 }
 
 hipError_t launch_bitmap_keys(const uint32_t* bitmap, int64_t nwords, const int64_t* pos, uint64_t* out,
                               hipStream_t st) {
-    hipLaunchKernelGGL(k_bitmap_keys, dim3(blocks256(nwords)), dim3(256), 0, st, bitmap, nwords, pos, out);
+    hipLaunchKernelGGL(k_bitmap_keys, dim3(static_cast<unsigned>(bitmap_tiles(nwords))), dim3(256), 0, st, bitmap, nwords,
+                       pos, out);
     return hipGetLastError();
 }
 
