@@ -205,6 +205,12 @@ __host__ __device__ __forceinline__ uint32_t join_high(uint64_t d) { return 63u 
 __host__ __device__ __forceinline__ uint32_t join_count(uint32_t d) { return static_cast<uint32_t>(__builtin_popcount(d)); }
 __host__ __device__ __forceinline__ uint32_t join_count(uint64_t d) { return static_cast<uint32_t>(__builtin_popcountll(d)); }
 
+// The bits of a string of n qubits.
+template <class ST>
+__host__ __device__ __forceinline__ ST join_string_mask(uint32_t n) {
+    return n >= 8u * sizeof(ST) ? ~ST(0) : static_cast<ST>((ST(1) << n) - 1u);
+}
+
 // Number of a string with two bits set: its rank among them.
 template <class ST>
 __host__ __device__ __forceinline__ uint32_t join_pair_id(ST d) {
