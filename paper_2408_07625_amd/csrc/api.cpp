@@ -93,6 +93,7 @@ struct eloc_ctx_s {
     // eloc_set_samples alone, the index is built by the first call that reads it
     JoinIndex J;
     bool j_room = false, j_built = false;
+    bool samples_captured = false;   // set under stream capture: every replay sets others
 
     DevBuf a, b, af, bf, v, vf, shift, amp_scratch;
     DevBuf partial, energy_scratch;
@@ -211,16 +212,21 @@ int join_room(eloc_ctx c, int64_t n) {
     return ELOC_OK;
 }
 
+bool capturing(hipStream_t st) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cap) != hipSuccess) (void)hipGetLastError();
+    return cap != hipStreamCaptureStatusNone;
+}
+
 // The join's index of the current samples; enqueued, allocates nothing.  A
 // build under stream capture has not run when this returns, so it is not
-// taken for the calls after it.
+// taken for the calls after it; nor is any build of samples that a graph sets,
+// which a replay changes without a call that would tell.
 int ensure_join(eloc_ctx c) {
     if (c->j_built) return ELOC_OK;
     ELOC_HIP(c, c->J.build(c->H.W, c->keys.as<uint64_t>(), c->S.n, c->H.n_qubits, c->JH.split,
                            c->err_prep.as<uint32_t>(), c->stream));
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess) (void)hipGetLastError();
-    c->j_built = cap == hipStreamCaptureStatusNone;
+    c->j_built = !c->samples_captured && !capturing(c->stream);
     return ELOC_OK;
 }
 
@@ -881,6 +887,7 @@ int eloc_set_samples(eloc_ctx c, int64_t n_unique, const uint64_t* keys_dev) {
     c->miss_valid = false;
     c->j_built = false;
     c->j_room = false;
+    c->samples_captured = capturing(c->stream);
     ELOC_HIP(c, c->keys.ensure(sizeof(uint64_t) * n_unique * W));
     ELOC_HIP(c, c->khash.ensure(sizeof(uint64_t) * n_unique));
     const uint64_t cap = table_capacity(n_unique);
