@@ -256,28 +256,40 @@ int enqueue(eloc_batch b, int precision, hipStream_t st, bool timed = false) {
     BATCH_HIP(b, launch_batch_prepare(B, precision == ELOC_FP32C, st));
     BATCH_HIP(b, mark(1));
     // the joins on a stream of their own, beside the items of the others:
-    // their indexes are a dozen small launches each
-    bool joins = false;
-    for (int k = 0; k < b->n; ++k) {
-        BatchJoin* J = b->join[static_cast<size_t>(k)].get();
-        if (J) J->ran = J->on;
-        if (!J || !J->on) continue;
-        if (!joins) {
-            BATCH_HIP(b, hipEventRecord(b->fork, st));
-            BATCH_HIP(b, hipStreamWaitEvent(b->side, b->fork, 0));
-            joins = true;
+    // their indexes are a dozen small launches each.  Once forked the stream is
+    // joined again whatever fails between: what it has been given would else
+    // run past this call, or leave a capture open
+    bool forked = false;
+    const auto pairs = [&]() -> hipError_t {
+        for (int k = 0; k < b->n; ++k) {
+            BatchJoin* J = b->join[static_cast<size_t>(k)].get();
+            if (J) J->ran = J->on;
+            if (!J || !J->on) continue;
+            hipError_t e = hipSuccess;
+            if (!forked) {
+                e = hipEventRecord(b->fork, st);
+                if (e == hipSuccess) e = hipStreamWaitEvent(b->side, b->fork, 0);
+                if (e != hipSuccess) return e;
+                forked = true;
+            }
+            const BatchProb& D = b->desc[static_cast<size_t>(k)];
+            e = J->index.build(b->W, B.keys + D.s0 * b->W, D.M, J->H.n_qubits, J->masks.split, B.err + k, b->side);
+            if (e == hipSuccess)
+                e = launch_join_pairs(false, precision, J->H, J->masks.dev, J->index.dev, J->plan, B.a + D.s0,
+                                      B.af + D.s0, static_cast<double2*>(B.partial) + D.pbase, b->side);
+            if (e != hipSuccess) return e;
         }
-        const BatchProb& D = b->desc[static_cast<size_t>(k)];
-        BATCH_HIP(b, J->index.build(b->W, B.keys + D.s0 * b->W, D.M, J->H.n_qubits, J->masks.split, B.err + k, b->side));
-        BATCH_HIP(b, launch_join_pairs(false, precision, J->H, J->masks.dev, J->index.dev, J->plan, B.a + D.s0,
-                                       B.af + D.s0, static_cast<double2*>(B.partial) + D.pbase, b->side));
+        return launch_batch_pairs(B, precision, b->schedule.rows_per_wave, launch_blocks(b, precision, true),
+                                  launch_blocks(b, precision, false), st);
+    };
+    const hipError_t ran = pairs();
+    if (forked) {
+        const hipError_t back = hipEventRecord(b->joined, b->side);
+        const hipError_t waits = back == hipSuccess ? hipStreamWaitEvent(st, b->joined, 0) : back;
+        BATCH_HIP(b, ran);
+        BATCH_HIP(b, waits);
     }
-    BATCH_HIP(b, launch_batch_pairs(B, precision, b->schedule.rows_per_wave, launch_blocks(b, precision, true),
-                                    launch_blocks(b, precision, false), st));
-    if (joins) {
-        BATCH_HIP(b, hipEventRecord(b->joined, b->side));
-        BATCH_HIP(b, hipStreamWaitEvent(st, b->joined, 0));
-    }
+    BATCH_HIP(b, ran);
     BATCH_HIP(b, mark(2));
     BATCH_HIP(b, launch_batch_finish(B, precision, st));
     BATCH_HIP(b, mark(3));
