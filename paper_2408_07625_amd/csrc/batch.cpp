@@ -43,12 +43,9 @@ struct BatchJoin {
     JoinIndex index;
     Plan plan;
     bool on = false;    // with the schedule as it is
-    bool ran = false;   // in the last run
-    DevBuf counts;
     ~BatchJoin() {
         masks.release();
         index.release();
-        counts.release();
     }
 };
 
@@ -76,7 +73,7 @@ struct eloc_batch_s {
 
     DevBuf R_dev, groups, terms, terms_f, ghash, gkeys, gsplit, gslots, gstash;
     DevBuf probs, pid, tiles_dev, sched, keys, khash, kslots, kstash;
-    DevBuf err_dev, sigmin, sigmax, bitcounts, rad, shift, scal, part, pairs, a, b, af, bf, partial;
+    DevBuf err_dev, sigmin, sigmax, bitcounts, rad, shift, scal, part, pairs, join_pairs, a, b, af, bf, partial;
     uint32_t* err_host = nullptr;
 
     eloc_batch_schedule schedule{};
@@ -142,6 +139,7 @@ BatchDev dev_view(const eloc_batch b) {
     B.scal = b->scal.as<double>();
     B.part = b->part.as<double>();
     B.pairs = b->pairs.as<unsigned long long>();
+    B.join_pairs = b->join_pairs.as<unsigned long long>();
     B.a = b->a.as<double2>();
     B.b = b->b.as<double2>();
     B.af = b->af.as<float4>();
@@ -263,7 +261,6 @@ int enqueue(eloc_batch b, int precision, hipStream_t st, bool timed = false) {
     const auto pairs = [&]() -> hipError_t {
         for (int k = 0; k < b->n; ++k) {
             BatchJoin* J = b->join[static_cast<size_t>(k)].get();
-            if (J) J->ran = J->on;
             if (!J || !J->on) continue;
             hipError_t e = hipSuccess;
             if (!forked) {
@@ -276,7 +273,8 @@ int enqueue(eloc_batch b, int precision, hipStream_t st, bool timed = false) {
             e = J->index.build(b->W, B.keys + D.s0 * b->W, D.M, J->H.n_qubits, J->masks.split, B.err + k, b->side);
             if (e == hipSuccess)
                 e = launch_join_pairs(false, precision, J->H, J->masks.dev, J->index.dev, J->plan, B.a + D.s0,
-                                      B.af + D.s0, static_cast<double2*>(B.partial) + D.pbase, b->side);
+                                      B.af + D.s0, static_cast<double2*>(B.partial) + D.pbase, b->side,
+                                      B.join_pairs + static_cast<int64_t>(k) * kJoinPairSlots * kJoinPairStride);
             if (e != hipSuccess) return e;
         }
         return launch_batch_pairs(B, precision, b->schedule.rows_per_wave, launch_blocks(b, precision, true),
@@ -674,6 +672,7 @@ int eloc_batch_create(eloc_batch* out, int device, void* hip_stream, int n, cons
     BATCH_HIP(b, b->scal.ensure(sizeof(double) * 3 * n));
     BATCH_HIP(b, b->part.ensure(sizeof(double) * 3 * nt));
     BATCH_HIP(b, b->pairs.ensure(sizeof(unsigned long long) * n));
+    BATCH_HIP(b, b->join_pairs.ensure(sizeof(unsigned long long) * n * kJoinPairSlots * kJoinPairStride));
     BATCH_HIP(b, b->a.ensure(sizeof(double2) * S));
     BATCH_HIP(b, b->b.ensure(sizeof(double2) * S));
     BATCH_HIP(b, b->af.ensure(sizeof(float4) * S));
@@ -702,7 +701,7 @@ void eloc_batch_destroy(eloc_batch b) {
     if (b->joined) (void)hipEventDestroy(b->joined);
     DevBuf* bufs[] = {&b->R_dev, &b->groups, &b->terms, &b->terms_f, &b->ghash, &b->gkeys, &b->gsplit, &b->gslots, &b->gstash,
                       &b->probs, &b->pid, &b->tiles_dev, &b->sched, &b->keys, &b->khash, &b->kslots, &b->kstash,
-                      &b->err_dev, &b->sigmin, &b->sigmax, &b->bitcounts, &b->rad, &b->shift, &b->scal, &b->part, &b->pairs,
+                      &b->err_dev, &b->sigmin, &b->sigmax, &b->bitcounts, &b->rad, &b->shift, &b->scal, &b->part, &b->pairs, &b->join_pairs,
                       &b->a, &b->b, &b->af, &b->bf, &b->partial};
     for (DevBuf* d : bufs) d->release();
     for (hipEvent_t e : b->prof_ev) (void)hipEventDestroy(e);
@@ -774,24 +773,6 @@ int eloc_batch_pair_counts(eloc_batch b, int64_t* counts_host) {
     if (!b || !counts_host) return ELOC_EINVAL;
     BATCH_HIP(b, hipStreamSynchronize(b->stream));
     BATCH_HIP(b, hipMemcpy(counts_host, b->pairs.p, sizeof(int64_t) * b->n, hipMemcpyDeviceToHost));
-    // the joins of the last run, counted now from their indexes
-    for (int k = 0; k < b->n; ++k) {
-        BatchJoin* J = b->join[static_cast<size_t>(k)].get();
-        if (!J || !J->ran) continue;
-        const size_t cells = static_cast<size_t>(J->plan.chunks) * static_cast<size_t>(J->index.dev.M);
-        BATCH_HIP(b, J->counts.ensure(sizeof(int32_t) * cells));
-        BATCH_HIP(b, hipMemsetAsync(J->counts.p, 0, sizeof(int32_t) * cells, b->stream));
-        BATCH_HIP(b, launch_join_count(J->H, J->masks.dev, J->index.dev, J->plan, J->counts.as<int32_t>(), b->stream));
-        std::vector<int32_t> host;
-        try {
-            host.resize(cells);
-        } catch (const std::bad_alloc&) {
-            return bfail(b, ELOC_ENOMEM, "host memory for the pair counts");
-        }
-        BATCH_HIP(b, hipStreamSynchronize(b->stream));
-        BATCH_HIP(b, hipMemcpy(host.data(), J->counts.p, sizeof(int32_t) * cells, hipMemcpyDeviceToHost));
-        counts_host[k] = std::accumulate(host.begin(), host.end(), int64_t(0));
-    }
     return ELOC_OK;
 }
 

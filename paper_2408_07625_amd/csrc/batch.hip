@@ -35,6 +35,7 @@ __global__ __launch_bounds__(kBlock) void k_bt_clear(BatchDev B) {
         B.sigmin[t0] = 0xFFFFFFFFu;
         B.sigmax[t0] = 0u;
         B.pairs[t0] = 0ull;
+        for (int q = 0; q < kJoinPairSlots; ++q) B.join_pairs[(t0 * kJoinPairSlots + q) * kJoinPairStride] = 0ull;
     }
 }
 
@@ -327,7 +328,7 @@ __global__ __launch_bounds__(kBlock) void k_bt_energy1(BatchDev B) {
     }
 }
 
-// one thread per problem: E = sum w E_loc / sum w
+// one thread per problem: E = sum w E_loc / sum w, and the pairs of its join
 __global__ __launch_bounds__(kBlock) void k_bt_energy2(BatchDev B) {
     const int k = static_cast<int>(blockIdx.x) * kBlock + threadIdx.x;
     if (k >= B.n) return;
@@ -338,6 +339,11 @@ __global__ __launch_bounds__(kBlock) void k_bt_energy2(BatchDev B) {
         sr += B.part[3 * t + 1];
         si += B.part[3 * t + 2];
     }
+    unsigned long long joined = 0;
+#pragma unroll
+    for (int q = 0; q < kJoinPairSlots; ++q)
+        joined += B.join_pairs[(static_cast<int64_t>(k) * kJoinPairSlots + q) * kJoinPairStride];
+    B.pairs[k] += joined;
     if (!(tot > 0.0) || !isfinite(tot)) atomicOr(B.err + k, static_cast<uint32_t>(kErrWeights));
     const double er = sr / tot, ei = si / tot;
     P.stats[0] = er;

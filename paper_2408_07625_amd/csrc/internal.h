@@ -749,6 +749,7 @@ struct BatchDev {
     double* scal;              // [n][3] E re, E im, sum w
     double* part;              // [n_tiles][3] reduction partials
     unsigned long long* pairs; // [n] coupled pairs found
+    unsigned long long* join_pairs; // [n][kJoinPairSlots][kJoinPairStride] parts of them, by the joins
     int64_t narrow_items;      // items [0, narrow_items) belong to narrow problems
     double2* a;
     double2* b;
@@ -876,11 +877,17 @@ struct JoinBuild {
     uint32_t* core;            // [kJoinCore]
 };
 hipError_t launch_join_index(int W, const JoinBuild& B, hipStream_t st);
+// Words that the waves of a join count their pairs in, each in a cache line of
+// its own: tens of thousands of waves, at 4 ns an atomic on one word.
+constexpr int kJoinPairSlots = 16;
+constexpr int kJoinPairStride = 16;
 // Row sums into partial[chunk][M]: chunk 0 the spin-down order (own buckets,
 // then the light buckets of blist), chunk 1 the heavy-heavy table, chunks 2 ..
-// P.chunks - 1 the masks of alist, P.per_chunk each.
+// P.chunks - 1 the masks of alist, P.per_chunk each.  pairs: words that the
+// number of pairs is added to, or none.
 hipError_t launch_join_pairs(bool adjoint, int precision, const HamDev& H, const JoinHamDev& JH, const JoinDev& J,
-                             const Plan& P, const double2* vec, const float4* vecf, void* partial, hipStream_t st);
+                             const Plan& P, const double2* vec, const float4* vecf, void* partial, hipStream_t st,
+                             unsigned long long* pairs = nullptr);
 hipError_t launch_join_count(const HamDev& H, const JoinHamDev& JH, const JoinDev& J, const Plan& P, int32_t* counts,
                              hipStream_t st);
 // Matrix elements of sample pairs by place (Hamiltonians with H.direct): of

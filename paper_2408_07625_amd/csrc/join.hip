@@ -101,10 +101,13 @@ __device__ __forceinline__ uint32_t find_part(const JoinSlot<W>* __restrict__ sl
     return kJoinNone;
 }
 
-enum { kModeSum = 0, kModeCount = 1, kModeFill = 2 };
+// kModeSumPairs: the sums, and the number of pairs (1.2% of 52 qubits, 2^20
+// samples, so only where a caller wants it)
+enum { kModeSum = 0, kModeCount = 1, kModeFill = 2, kModeSumPairs = 3 };
 
 struct JoinOut {
     void* partial;             // kModeSum
+    unsigned long long* pairs; // kModeSumPairs: += the pairs, over kJoinPairSlots words
     int32_t* counts;           // kModeCount
     const int64_t* offsets;    // kModeFill
     uint64_t* pkey;
@@ -124,15 +127,16 @@ __global__ __launch_bounds__(kWave) void k_join(JoinArgs A, JoinOut O) {
         uint32_t at;
         ST s;
     };
+    constexpr bool kSums = MODE == kModeSum || MODE == kModeSumPairs;
     constexpr int kList = kWave * kSmall;                                   // gathered columns
     constexpr int kNear = kList * 4 / static_cast<int>(sizeof(Near));
     // queued columns: position | row << 24, place base, the two strings
     __shared__ uint2 q[kQueue];
     __shared__ ST qs[kQueue][2];
-    __shared__ uint2 lq[MODE == kModeSum ? kQueue : 1];   // pairs of linear places: position | row << 24, place
+    __shared__ uint2 lq[kSums ? kQueue : 1];   // pairs of linear places: position | row << 24, place
     __shared__ uint64_t buf[kList / 2];             // list, or near
     __shared__ ST rowstr[kRows][2];   // the rows' scanned string, their order's string
-    __shared__ double2 acc_raw[MODE == kModeSum ? kRows * kAccCols : 1];
+    __shared__ double2 acc_raw[kSums ? kRows * kAccCols : 1];
     static_assert(sizeof(Acc) == sizeof(double2), "accumulators are 16 bytes");
     uint32_t* list = reinterpret_cast<uint32_t*>(buf);   // position | mask lane << 24
     Near* near = reinterpret_cast<Near*>(buf);
@@ -165,7 +169,7 @@ __global__ __launch_bounds__(kWave) void k_join(JoinArgs A, JoinOut O) {
     if (bad || (core && heavy_min == kJoinNone)) {   // invalid samples: no pairs
         if constexpr (MODE == kModeCount)
             if (lane < n) O.counts[static_cast<int64_t>(row) * A.chunks + chunk] = 0;
-        if constexpr (MODE == kModeSum)
+        if constexpr (kSums)
             if (lane < n) store_acc(O.partial, static_cast<int64_t>(chunk) * M + row, Acc{});
         return;
     }
@@ -175,7 +179,7 @@ __global__ __launch_bounds__(kWave) void k_join(JoinArgs A, JoinOut O) {
         rowstr[lane][0] = sl;
         rowstr[lane][1] = gl;
     }
-    if constexpr (MODE == kModeSum)
+    if constexpr (kSums)
         for (int i = lane; i < kRows * kAccCols; i += kWave) acc[i] = Acc{};
     ST srow[kRows];
 #pragma unroll
@@ -218,6 +222,7 @@ __global__ __launch_bounds__(kWave) void k_join(JoinArgs A, JoinOut O) {
     };
     int qn = 0;   // queued columns (wave-uniform)
     int ln = 0;   // queued pairs of linear places
+    int found = 0;   // pairs (kModeSumPairs)
     // the last m of them: a table entry per nibble of the ket's strings
     auto drain_linear = [&](int m) __attribute__((always_inline)) {
         wave_sync();
@@ -294,7 +299,7 @@ __global__ __launch_bounds__(kWave) void k_join(JoinArgs A, JoinOut O) {
         pend.at = e.x;
         pend.place = id == kJoinNone ? kJoinNone : place;
         pend.pl = ld<JoinPlace<W>>(A.H.place, place * static_cast<uint32_t>(sizeof(JoinPlace<W>)));
-        if constexpr (MODE == kModeSum) {
+        if constexpr (kSums) {
             pend.v = ld<Vec>(vec, (e.x & 0xFFFFFFu) * 16u);
             const ST ks = ADJ ? rs : cs, kt = ADJ ? rt : ct;
             pend.ka = down ? ks : kt;
@@ -349,6 +354,7 @@ __global__ __launch_bounds__(kWave) void k_join(JoinArgs A, JoinOut O) {
             __builtin_memcpy(&h, &hb, sizeof(h));
             h = (zp & 1u) ? -h : h;
             const bool sign = kind == kJoinSign;
+            if constexpr (MODE == kModeSumPairs) found += __popcll(__ballot(kind != kJoinEmpty));
             Acc sum{};
             if (sign) product(sum, h, v);
             add(r, sum, sign);
@@ -564,7 +570,7 @@ __global__ __launch_bounds__(kWave) void k_join(JoinArgs A, JoinOut O) {
     }
     if (qn > 0) drain(qn);
     if (pending) consume();
-    if constexpr (MODE == kModeSum)
+    if constexpr (kSums)
         if (ln > 0) drain_linear(ln);
     wave_sync();
     if constexpr (MODE == kModeCount) {
@@ -572,7 +578,7 @@ __global__ __launch_bounds__(kWave) void k_join(JoinArgs A, JoinOut O) {
         for (int r = 0; r < kRows; ++r)
             if (lane == r && r < n) O.counts[static_cast<int64_t>(row) * A.chunks + chunk] = cnt[r];
     }
-    if constexpr (MODE == kModeSum) {
+    if constexpr (kSums) {
         // kPer lanes a row: some columns each, then pairwise
         constexpr int kPer = kWave / kRows;
         const int mine = lane / kPer, sub = lane % kPer;
@@ -587,6 +593,8 @@ __global__ __launch_bounds__(kWave) void k_join(JoinArgs A, JoinOut O) {
         }
         const int32_t id = __shfl(row, mine, kWave);
         if (sub == 0 && mine < n) store_acc(O.partial, static_cast<int64_t>(chunk) * M + id, t);
+        if (MODE == kModeSumPairs && lane == 0 && found)
+            atomicAdd(O.pairs + (blockIdx.x % kJoinPairSlots) * kJoinPairStride, static_cast<unsigned long long>(found));
     }
 }
 
@@ -868,6 +876,10 @@ hipError_t launch_rows(int rows, const JoinArgs& A, const JoinOut& O, hipStream_
 
 template <int W, bool ADJ, bool NW>
 hipError_t launch_sum(int precision, int rows, const JoinArgs& A, const JoinOut& O, hipStream_t st) {
+    if constexpr (!ADJ)
+        if (O.pairs)
+            return precision == 0 ? launch_rows<W, 0, ADJ, NW, kModeSumPairs>(rows, A, O, st)
+                                  : launch_rows<W, 1, ADJ, NW, kModeSumPairs>(rows, A, O, st);
     return precision == 0 ? launch_rows<W, 0, ADJ, NW, kModeSum>(rows, A, O, st)
                           : launch_rows<W, 1, ADJ, NW, kModeSum>(rows, A, O, st);
 }
@@ -903,10 +915,13 @@ hipError_t launch_join_index(int W, const JoinBuild& B, hipStream_t st) {
 }
 
 hipError_t launch_join_pairs(bool adjoint, int precision, const HamDev& H, const JoinHamDev& JH, const JoinDev& J,
-                             const Plan& P, const double2* vec, const float4* vecf, void* partial, hipStream_t st) {
+                             const Plan& P, const double2* vec, const float4* vecf, void* partial, hipStream_t st,
+                             unsigned long long* pairs) {
+    if (adjoint && pairs) return hipErrorInvalidValue;   // the forward sums count
     const JoinArgs A = make_args(precision == 0 ? H.terms : H.terms_f, JH, J, P);
     JoinOut O{};
     O.partial = partial;
+    O.pairs = pairs;
     static_assert(sizeof(double2) == sizeof(float4), "one copy serves both precisions");
     hipLaunchKernelGGL(k_join_vec, dim3(div_up(2 * J.M, kBlock)), dim3(kBlock), 0, st, 2 * J.M, J.perm,
                        precision == 0 ? vec : reinterpret_cast<const double2*>(vecf), J.vec);
