@@ -1423,10 +1423,11 @@ int eloc_sample(eloc_ctx c, const eloc_ar_model* m, int64_t k, uint64_t seed, ui
     const int N = m->n_qubits, W = (N + 63) / 64, D = m->qudit;
     const int Q = (N + D - 1) / D;
     // candidates of the largest level
-    int64_t maxc = 0, upper = 1;
+    int64_t maxc = 0, maxsel = 1, upper = 1;   // of all levels, of those with more than k
     for (int level = 0; level < Q; ++level) {
         const int64_t n = upper << std::min(D, N - level * D);
         maxc = std::max(maxc, n);
+        if (n > k) maxsel = std::max(maxsel, n);
         upper = std::min(k, n);
     }
     for (int s = 0; s < 2; ++s) {
@@ -1440,20 +1441,20 @@ int eloc_sample(eloc_ctx c, const eloc_ar_model* m, int64_t k, uint64_t seed, ui
     ELOC_HIP(c, c->ar_hist.ensure(sizeof(uint32_t) * 4096));
     ELOC_HIP(c, c->ar_count.ensure(sizeof(uint32_t) * ar_tiles(maxc)));
     ELOC_HIP(c, c->ar_off.ensure(sizeof(int64_t) * ar_tiles(maxc)));
-    ELOC_HIP(c, c->ar_bk.ensure(sizeof(uint64_t) * ar_bound()));
-    ELOC_HIP(c, c->ar_bi.ensure(sizeof(uint32_t) * ar_bound()));
+    ELOC_HIP(c, c->ar_bk.ensure(sizeof(uint64_t) * maxsel));
+    ELOC_HIP(c, c->ar_bi.ensure(sizeof(uint32_t) * maxsel));
     auto sort_room = [&](int64_t n) -> hipError_t {
         const int64_t tiles = radix_tiles(n);
         hipError_t e = c->hist.ensure(sizeof(uint32_t) * 256 * tiles);
         if (e == hipSuccess) e = c->hist_off.ensure(sizeof(int64_t) * (256 * tiles + 1));
         if (e == hipSuccess) e = c->hist_scratch.ensure(sizeof(int64_t) * scan_scratch_len(256 * tiles));
         if (e == hipSuccess) e = c->ar_ck2.ensure(sizeof(uint64_t) * n);
-        if (e == hipSuccess) e = c->ar_ci.ensure(sizeof(uint32_t) * n);
         if (e == hipSuccess) e = c->ar_ci2.ensure(sizeof(uint32_t) * n);
         return e;
     };
     ELOC_HIP(c, sort_room(upper));
     ELOC_HIP(c, c->ar_sk.ensure(sizeof(uint64_t) * upper));
+    ELOC_HIP(c, c->ar_ci.ensure(sizeof(uint32_t) * upper));
     ArScratch R{};
     R.state = c->ar_state.as<ArState>();
     for (int s = 0; s < 2; ++s) {
@@ -1496,8 +1497,8 @@ int eloc_sample(eloc_ctx c, const eloc_ar_model* m, int64_t k, uint64_t seed, ui
     }
     ArResult res{};
     ELOC_HIP(c, ar_read(R, Q, &res, c->stream));
-    if (res.B == 0) return ELOC_OK;   // no allowed state
     if (!res.redo) {
+        if (res.B == 0) return ELOC_OK;   // no allowed state
         uint64_t* by = R.sort_key;
         uint32_t* idx = R.sort_idx;
         ELOC_HIP(c, sort(by, idx, res.B));
@@ -1505,32 +1506,34 @@ int eloc_sample(eloc_ctx c, const eloc_ar_model* m, int64_t k, uint64_t seed, ui
         ELOC_HIP(c, ar_read(R, Q, &res, c->stream));
     }
     if (res.redo) {
-        // equal values: sort every level, so that they come in the order of
-        // the level before
+        // equal values: sort what can be kept of every level, so that they come
+        // in the order of the level before
         ELOC_HIP(c, sort_room(maxc));
+        ELOC_HIP(c, c->ar_bk.ensure(sizeof(uint64_t) * maxc));
+        ELOC_HIP(c, c->ar_bi.ensure(sizeof(uint32_t) * maxc));
+        R.bkey = c->ar_bk.as<uint64_t>();
+        R.bidx = c->ar_bi.as<uint32_t>();
         ELOC_HIP(c, launch_ar_root(R, W, c->stream));
         cur = 0;
         B = 1;
         for (int level = 0; level < Q; ++level) {
-            ELOC_HIP(c, ar_set_prefixes(R, level, &B, c->stream));
-            const int64_t n = B << std::min(D, N - level * D);
-            uint32_t* idx = c->ar_ci.as<uint32_t>();
-            uint64_t* by = R.cand_key;
-            ELOC_HIP(c, launch_ar_candidates(M, level, B, seed, R, cur, idx, c->stream));
+            ELOC_HIP(c, launch_ar_survivors(M, level, B, k, seed, R, cur, c->stream));
             ELOC_HIP(c, ar_read(R, level + 1, &res, c->stream));
-            B = std::min(k, res.allowed);
+            B = res.B;
             if (B == 0) return ELOC_OK;
-            ELOC_HIP(c, sort(by, idx, n));
+            if (res.listed < B || res.listed > maxc)
+                return fail(c, ELOC_EHIP, "top-K selection kept " + std::to_string(res.listed) + " candidates");
+            uint64_t* by = R.bkey;
+            uint32_t* idx = R.bidx;
+            ELOC_HIP(c, sort(by, idx, res.listed));
             ELOC_HIP(c, launch_ar_gather(M, level, R, cur, by, idx, B, c->stream));
             cur ^= 1;
         }
-        ELOC_HIP(c, hipMemcpyAsync(keys_dev, R.keys[cur], sizeof(uint64_t) * W * B, hipMemcpyDeviceToDevice,
-                                   c->stream));
+        ELOC_HIP(c, hipMemcpyAsync(keys_dev, R.keys[cur], sizeof(uint64_t) * W * B, hipMemcpyDeviceToDevice, c->stream));
         ELOC_HIP(c, hipMemcpyAsync(logp_dev, R.l[cur], sizeof(double) * B, hipMemcpyDeviceToDevice, c->stream));
         if (pert_dev)
             ELOC_HIP(c, hipMemcpyAsync(pert_dev, R.T[cur], sizeof(double) * B, hipMemcpyDeviceToDevice, c->stream));
         ELOC_HIP(c, hipStreamSynchronize(c->stream));
-        res.B = B;
     }
     *n_out_host = res.B;
     return ELOC_OK;

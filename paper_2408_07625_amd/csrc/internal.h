@@ -999,19 +999,18 @@ struct ArScratch {
     uint32_t* hist;      // [4096]
     uint32_t* cnt;       // [ar_tiles(candidates)]
     int64_t* off;        // as cnt
-    uint64_t* bkey;      // [ar_bound()]
+    uint64_t* bkey;      // listed candidates [those of the largest level with more than K; sorted levels: of the largest]
     uint32_t* bidx;
     uint64_t* sort_key;  // the last level's [K]
     uint32_t* sort_idx;
 };
 struct ArResult {
     int64_t B;        // prefixes out of the level before
-    int64_t allowed;  // its unmasked candidates
+    int64_t listed;   // candidates in its list of survivors
     bool redo;        // the levels have to be sorted
 };
 size_t ar_state_bytes();
 int64_t ar_tiles(int64_t n);
-int64_t ar_bound();
 hipError_t launch_ar_root(const ArScratch& R, int W, hipStream_t st);
 // Level `level` for at most B prefixes in buffer `cur`, its first K candidates
 // to the other one in index order; `last`: also sort_key, sort_idx.
@@ -1019,15 +1018,15 @@ hipError_t launch_ar_level(const ArModelDev& M, int level, int64_t B, int64_t K,
                            const ArScratch& R, int cur, hipStream_t st);
 hipError_t launch_ar_out(const ArScratch& R, int cur, const uint64_t* sorted_key, const uint32_t* sorted_idx,
                          int64_t n, int W, uint64_t* out_keys, double* out_l, double* out_T, hipStream_t st);
-// The pieces of a level that is sorted: the candidates of B prefixes (cand_key,
-// cand_l, idx = 0, 1, ...), and the first n of the sorted ones as prefixes.
-hipError_t launch_ar_candidates(const ArModelDev& M, int level, int64_t B, uint64_t seed, const ArScratch& R, int cur,
-                                uint32_t* idx, hipStream_t st);
+// The pieces of a level that is sorted: the candidates that can be among its
+// first K to bkey, bidx in index order, and the first n of them sorted as
+// prefixes.
+hipError_t launch_ar_survivors(const ArModelDev& M, int level, int64_t B, int64_t K, uint64_t seed, const ArScratch& R,
+                               int cur, hipStream_t st);
 hipError_t launch_ar_gather(const ArModelDev& M, int level, const ArScratch& R, int cur, const uint64_t* sorted_key,
                             const uint32_t* sorted_idx, int64_t n, hipStream_t st);
-// What came out of level - 1 (waits for the stream), and the prefixes of `level` by hand.
+// What came out of level - 1 (waits for the stream).
 hipError_t ar_read(const ArScratch& R, int level, ArResult* out, hipStream_t st);
-hipError_t ar_set_prefixes(const ArScratch& R, int level, const int64_t* B, hipStream_t st);
 
 // Fixed workspace of the allocation-free forward pass (one per device).
 constexpr size_t kNoAllocBytes = size_t(64) << 20;

@@ -18,8 +18,9 @@
 //                last); the histogram of the keys' top 12 bits.
 //   select       the first min(K, allowed) candidates in (key, index) order as
 //                a set: the digit of the K-th (k_ar_pick), the next 12 bits
-//                within it (k_ar_hist, k_ar_pick), the candidates of that
-//                24-bit prefix ranked in one workgroup (k_ar_count, k_ar_cut).
+//                within it (k_ar_hist, k_ar_pick; for large K twice at need), the
+//                candidates of that prefix listed (k_ar_count) and ranked in
+//                one workgroup (k_ar_cut).
 //   k_ar_emit    the selected candidates become the next level's prefixes
 //                (key with the outcome's bits set, l, Ltil), in index order.
 // Levels run one after another without a wait on the host.  At 2^16 prefixes
@@ -31,7 +32,9 @@
 // a level are equal: equal values come in the order of the level before, and a
 // value that ties at one level ties again at the next, as the best child of a
 // prefix keeps its value.  So a tie shows in the last sort, or at the cut of a
-// level; then the search runs again with every level sorted.
+// level; then the search runs again with every level sorted (those that can be
+// among its first K).  A tie at a cut, or a list past what one workgroup should
+// cut down, ends the first search there: what is left of it returns at once.
 #include "device.h"
 
 #include <hip/hip_runtime.h>
@@ -43,17 +46,20 @@ namespace eloc {
 // State of a search on the device.  Slot `level`: the prefixes going into it,
 // and its unmasked candidates.
 constexpr int kArLevels = 128;
-constexpr int kArBound = 4096;      // candidates of the selected 24-bit prefix at most, past which all levels are sorted
+constexpr int kArBound = 4096;      // candidates that k_ar_cut ranks in LDS
+constexpr uint32_t kArList = 1u << 17;   // and cuts down to that many
 constexpr int kArTile = 4096;       // candidates of a counting workgroup
 struct ArState {
     int64_t B[kArLevels + 1];
     unsigned long long allowed[kArLevels];
-    uint32_t redo;          // a tie, or more candidates than kArBound in the selected prefix
+    uint32_t redo;          // this search gives way to the one with sorted levels
     uint32_t bound;         // candidates in the selected prefix
-    int64_t digit, before;  // top digit of the need-th candidate, candidates before that digit
-    int64_t prefix, below;  // its 24-bit prefix (1 << 24: all are kept), candidates below that
+    int shift;              // the prefix is key >> shift
+    uint32_t deep;          // it holds more than kArBound
+    int64_t prefix, below;  // digits of the need-th candidate (one past them: all are kept), candidates below those
     uint64_t cut_key;       // the last candidate kept of that prefix
     uint32_t cut_idx;
+    int64_t listed;         // candidates counted in the tiles
 };
 
 namespace {
@@ -149,7 +155,7 @@ __global__ __launch_bounds__(64 * NW) void k_ar_net(ArLevel A, const ArState* __
     const int lane = lane_id();
     const int64_t B = S->B[A.level];
     const int64_t b0 = static_cast<int64_t>(blockIdx.x) * kRows;
-    if (b0 >= B) return;
+    if (b0 >= B || S->redo) return;
     for (int e = threadIdx.x; e < kRows * A.W; e += 64 * NW) {
         const int64_t b = min(b0 + e / A.W, B - 1);
         kbuf[e] = keys[b * A.W + e % A.W];
@@ -246,6 +252,7 @@ __global__ __launch_bounds__(256) void k_ar_cand(ArLevel A, ArState* __restrict_
     __shared__ uint32_t cnt[kSelBuckets];
     __shared__ unsigned long long total;
     const int lane = lane_id();
+    if (S->redo) return;
     if (hist)
         for (int t = threadIdx.x; t < kSelBuckets; t += 256) cnt[t] = 0u;
     if (threadIdx.x == 0) total = 0;
@@ -296,7 +303,10 @@ __global__ __launch_bounds__(256) void k_ar_cand(ArLevel A, ArState* __restrict_
             const double v = T - Lp + log1mexp(Lp - Z);
             Lt = T - (fmax(v, 0.0) + log1p(exp(-fabs(v))));
         }
-        const uint64_t k = ok ? key_of(Lt) : ~0ull;
+        // masked outcomes alone have the last key (a NaN of all ones would share it)
+        uint64_t k = key_of(Lt);
+        if (k == ~0ull) k = ~1ull;
+        if (!ok) k = ~0ull;
         if (live) {
             cand_key[i] = k;
             cand_l[i] = lc;
@@ -322,11 +332,6 @@ __global__ __launch_bounds__(256) void k_ar_cand(ArLevel A, ArState* __restrict_
             if (cnt[t]) atomicAdd(hist + t, cnt[t]);
 }
 
-__global__ void k_ar_iota(uint32_t* __restrict__ idx, int64_t n) {
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-    if (i < n) idx[i] = static_cast<uint32_t>(i);
-}
-
 // The next level's prefix of candidate idx.
 __device__ __forceinline__ void child_key(const uint64_t* __restrict__ keys, int64_t idx, int O, int W, int q0,
                                           uint64_t* __restrict__ out) {
@@ -339,19 +344,6 @@ __device__ __forceinline__ void child_key(const uint64_t* __restrict__ keys, int
         if (lo < 0 && lo > -64) v |= c >> (-lo);
         out[w] = v;
     }
-}
-
-// The first n sorted candidates as prefixes.
-__global__ void k_ar_gather(const uint64_t* __restrict__ keys, const uint64_t* __restrict__ sorted_key,
-                            const uint32_t* __restrict__ sorted_idx, int64_t n, int O, int W, int q0,
-                            const double* __restrict__ cand_l, uint64_t* __restrict__ out_keys,
-                            double* __restrict__ out_l, double* __restrict__ out_T) {
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-    if (i >= n) return;
-    const uint32_t idx = sorted_idx[i];
-    child_key(keys, idx, O, W, q0, out_keys + i * W);
-    out_l[i] = cand_l[idx];
-    out_T[i] = value_of(sorted_key[i]);
 }
 
 __global__ __launch_bounds__(1024) void k_ar_root(ArState* __restrict__ S, uint32_t* __restrict__ hist, uint64_t* keys,
@@ -370,18 +362,18 @@ __global__ __launch_bounds__(1024) void k_ar_root(ArState* __restrict__ S, uint3
 }
 
 // Where the need of a level, min(K, allowed), falls among the 4096 digits of
-// `total`, which is cleared for the next user.  FIRST: the top digit, and B of
-// the next level; else the 24-bit prefix.  One workgroup, four digits a thread.
-template <bool FIRST>
+// `total`, which is cleared for the next user: the PASS-th 12 bits of the prefix;
+// the first time also B of the next level.  One workgroup, four digits a thread.
+template <int PASS>
 __global__ __launch_bounds__(1024) void k_ar_pick(ArState* __restrict__ S, int level, int64_t K,
                                                   uint32_t* __restrict__ total) {
     __shared__ int64_t part[16];
     const int t = static_cast<int>(threadIdx.x);
+    if (PASS == 2 && !S->deep) return;
     const int64_t allowed = static_cast<int64_t>(S->allowed[level]);
     const int64_t all_need = min(K, allowed);
     const bool all = all_need == allowed;
-    if (FIRST && t == 0) S->B[level + 1] = all_need;
-    if (!FIRST && t == 0) S->bound = 0u;
+    const int64_t above = PASS == 0 ? 0 : S->prefix, base = PASS == 0 ? 0 : S->below;
     int64_t c[4], mine = 0;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -389,23 +381,26 @@ __global__ __launch_bounds__(1024) void k_ar_pick(ArState* __restrict__ S, int l
         total[4 * t + q] = 0u;
         mine += c[q];
     }
-    if (all) {
-        if (t == 0) {
-            S->prefix = 1 << 24;
-            S->below = all_need;
-        }
-        return;
-    }
     int64_t upto = mine;
     for (int m = 1; m < 64; m <<= 1) {
         const int64_t v = __shfl_up(static_cast<long long>(upto), m);
         if ((t & 63) >= m) upto += v;
     }
     if ((t & 63) == 63) part[t / 64] = upto;
-    __syncthreads();
+    __syncthreads();   // also: every thread has the state of the pass before
+    if (t == 0) {
+        if (PASS == 0) S->B[level + 1] = all_need;
+        S->bound = 0u;
+        S->shift = 52 - 12 * PASS;
+        if (all) {
+            S->prefix = int64_t(1) << (12 * (PASS + 1));
+            S->below = all_need;
+            S->deep = 0u;
+        }
+    }
+    if (all) return;
     int64_t run = upto - mine;
     for (int w = 0; w < t / 64; ++w) run += part[w];
-    const int64_t base = FIRST ? 0 : S->before;
     const int64_t need = all_need - base;
     if (run < need && need <= run + mine) {
         int q = 0;
@@ -413,100 +408,205 @@ __global__ __launch_bounds__(1024) void k_ar_pick(ArState* __restrict__ S, int l
             if (run + c[q] >= need) break;
             run += c[q];
         }
-        if (FIRST) {
-            S->digit = 4 * t + q;
-            S->before = run;
-        } else {
-            S->prefix = (S->digit << 12) | (4 * t + q);
-            S->below = base + run;
-        }
+        S->prefix = (above << 12) | (4 * t + q);
+        S->below = base + run;
+        S->deep = c[q] > kArBound ? 1u : 0u;
     }
 }
 
-// The next 12 bits of the keys with the selected top digit: per workgroup in
-// LDS, then its non-zero counts added to total (the order of integer additions
-// does not matter).
+// The PASS-th 12 bits of the keys with the selected bits before: per workgroup
+// in LDS, then its non-zero counts added to total (the order of integer
+// additions does not matter).
+template <int PASS>
 __global__ __launch_bounds__(1024) void k_ar_hist(const ArState* __restrict__ S, int level, int sh, int64_t K,
                                                  const uint64_t* __restrict__ key, uint32_t* __restrict__ total) {
     __shared__ uint32_t h[kSelBuckets];
     const int64_t n = S->B[level] << sh;
-    if (static_cast<int64_t>(S->allowed[level]) <= K) return;
+    if (static_cast<int64_t>(S->allowed[level]) <= K || S->redo || (PASS == 2 && !S->deep)) return;
     for (int t = threadIdx.x; t < kSelBuckets; t += 1024) h[t] = 0u;
     __syncthreads();
-    const uint64_t digit = static_cast<uint64_t>(S->digit);
+    const uint64_t above = static_cast<uint64_t>(S->prefix);
     const int64_t step = static_cast<int64_t>(gridDim.x) * 1024;
 #pragma unroll 4
     for (int64_t i = static_cast<int64_t>(blockIdx.x) * 1024 + threadIdx.x; i < n; i += step) {
         const uint64_t k = key[i];
-        if ((k >> 52) == digit && k != ~0ull) atomicAdd(&h[(k >> 40) & (kSelBuckets - 1)], 1u);
+        if ((k >> (64 - 12 * PASS)) == above && k != ~0ull)
+            atomicAdd(&h[(k >> (52 - 12 * PASS)) & (kSelBuckets - 1)], 1u);
     }
     __syncthreads();
     for (int t = threadIdx.x; t < kSelBuckets; t += 1024)
         if (h[t]) atomicAdd(total + t, h[t]);
 }
 
-// cnt[tile] = the candidates below the selected prefix; those of the prefix to
-// the list (in any order).
+// cnt[tile] = the candidates below the selected prefix.  LIST:
+// those of the prefix to the list (the tiles in any order), a tile's place in it
+// taken at once: with an atomic a candidate the one word is what a prefix of
+// thousands waits for.  Else cnt has them too.
+template <bool LIST>
 __global__ __launch_bounds__(256) void k_ar_count(ArState* __restrict__ S, int level, int sh,
                                                   const uint64_t* __restrict__ key, uint32_t* __restrict__ cnt,
                                                   uint64_t* __restrict__ bkey, uint32_t* __restrict__ bidx) {
-    __shared__ uint32_t total;
+    constexpr int kPer = kArTile / 256;
+    __shared__ uint32_t total, listed[4], at0;
+    if (S->redo) return;
     if (threadIdx.x == 0) total = 0u;
     __syncthreads();
     const int64_t n = S->B[level] << sh;
     const uint64_t prefix = static_cast<uint64_t>(S->prefix);
+    const int shift = S->shift;
     const int64_t base = static_cast<int64_t>(blockIdx.x) * kArTile;
     if (base >= n) return;
-    uint32_t below = 0;
+    const int wave = static_cast<int>(threadIdx.x) / 64, lane = lane_id();
+    uint64_t k[kPer];
+    uint32_t below = 0, mine = 0;
 #pragma unroll
-    for (int j = 0; j < kArTile / 256; ++j) {
+    for (int j = 0; j < kPer; ++j) {
         const int64_t i = base + j * 256 + threadIdx.x;
-        const uint64_t k = i < n ? key[i] : ~0ull;
-        below += static_cast<uint32_t>(__popcll(__ballot((k >> 40) < prefix && k != ~0ull)));
-        if ((k >> 40) == prefix && k != ~0ull) {
-            const uint32_t at = atomicAdd(&S->bound, 1u);
-            if (at < kArBound) {
-                bkey[at] = k;
-                bidx[at] = static_cast<uint32_t>(i);
-            }
-        }
+        k[j] = i < n ? key[i] : ~0ull;
+        below += static_cast<uint32_t>(__popcll(__ballot((k[j] >> shift) < prefix && k[j] != ~0ull)));
+        mine += static_cast<uint32_t>(__popcll(__ballot((k[j] >> shift) == prefix && k[j] != ~0ull)));
     }
-    if (lane_id() == 0) atomicAdd(&total, below);
+    if (lane == 0) {
+        atomicAdd(&total, below);
+        listed[wave] = mine;
+    }
     __syncthreads();
-    if (threadIdx.x == 0) cnt[blockIdx.x] = total;
+    const uint32_t all = listed[0] + listed[1] + listed[2] + listed[3];
+    if (threadIdx.x == 0) {
+        cnt[blockIdx.x] = LIST ? total : total + all;
+        if (LIST && all) at0 = atomicAdd(&S->bound, all);
+    }
+    if (!LIST || all == 0u) return;
+    __syncthreads();
+    uint32_t at = at0;
+    for (int w = 0; w < wave; ++w) at += listed[w];
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        const bool in = (k[j] >> shift) == prefix && k[j] != ~0ull;
+        const uint64_t bal = __ballot(in);
+        if (in) {
+            const uint32_t to = at + static_cast<uint32_t>(__popcll(bal & ((1ull << lane) - 1ull)));
+            bkey[to] = k[j];
+            bidx[to] = static_cast<uint32_t>(base + j * 256 + threadIdx.x);
+        }
+        at += static_cast<uint32_t>(__popcll(bal));
+    }
 }
 
 // The first need - below of the list by (key, index): the last of them is the
 // cut, each counts for its tile; then cnt becomes the tiles' offsets.  One
-// workgroup.
+// workgroup.  The candidates of a 24-bit prefix grow with K (a flat tail of 52
+// qubits: 130 at K = 2^16, 8000 at 2^22) and with the values' distance from
+// zero (most of a peaked distribution's second shell); past what is ranked in
+// LDS they are cut down first, by 8 bits a pass of the key bits left and then
+// the index.
 __global__ __launch_bounds__(1024) void k_ar_cut(ArState* __restrict__ S, int level, int sh,
                                                  const uint64_t* __restrict__ bkey, const uint32_t* __restrict__ bidx,
                                                  uint32_t* __restrict__ cnt, int64_t* __restrict__ off) {
     __shared__ uint64_t k[kArBound];
     __shared__ uint32_t v[kArBound];
+    __shared__ uint32_t hist[256];
+    __shared__ uint32_t pick[3];   // digit, listed before it, listed with it
+    __shared__ uint32_t put;
     __shared__ uint64_t last, first_out;
     __shared__ int64_t part[16];
+    if (S->redo) return;
     const int t = static_cast<int>(threadIdx.x);
-    const bool all = S->prefix == (1 << 24);
     const int64_t need = S->B[level + 1];
     const int64_t n = S->B[level] << sh;
-    const uint32_t found = all ? 0u : S->bound;
-    const int m = static_cast<int>(min(found, static_cast<uint32_t>(kArBound)));
-    const int64_t r = need - S->below;
+    const uint32_t found = S->bound;
+    if (found > kArList) {
+        if (t == 0) S->redo = 1u;
+        return;
+    }
+    const int shift = S->shift, key_passes = (shift + 7) / 8;
+    const uint32_t r = static_cast<uint32_t>(need - S->below);   // 1 <= r <= found where there is a list
     if (t == 0) {
         last = 0ull;
         first_out = ~0ull;
-        if (found > kArBound) S->redo = 1u;
+        put = 0u;
     }
-    for (int e = t; e < m; e += 1024) {
-        k[e] = bkey[e];
-        v[e] = bidx[e];
+    uint64_t pk = 0, maskk = 0;
+    uint32_t pi = 0, maski = 0;
+    uint32_t before = 0, upto = found;   // before the chosen digits, and with them
+    for (int d = 0; upto - before > kArBound && d < key_passes + 4; ++d) {
+        if (t < 256) hist[t] = 0u;
+        __syncthreads();
+        const bool of_key = d < key_passes;
+        const int s = of_key ? max(shift - 8 * (d + 1), 0) : 24 - 8 * (d - key_passes);
+#pragma unroll 4
+        for (uint32_t e = t; e < found; e += 1024) {
+            const uint64_t ek = bkey[e];
+            const uint32_t ei = bidx[e];
+            if (((ek ^ pk) & maskk) == 0 && ((ei ^ pi) & maski) == 0)
+                atomicAdd(&hist[(of_key ? ek >> s : static_cast<uint64_t>(ei) >> s) & 255], 1u);
+        }
+        __syncthreads();
+        if (t < 64) {
+            uint32_t c[4], own = 0;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                c[q] = hist[4 * t + q];
+                own += c[q];
+            }
+            uint32_t run = own;
+            for (int m = 1; m < 64; m <<= 1) {
+                const uint32_t u = __shfl_up(run, m);
+                if (t >= m) run += u;
+            }
+            run += before - own;
+            if (run < r && r <= run + own) {   // one lane
+                int q = 0;
+                for (; q < 3; ++q) {
+                    if (run + c[q] >= r) break;
+                    run += c[q];
+                }
+                pick[0] = static_cast<uint32_t>(4 * t + q);
+                pick[1] = run;
+                pick[2] = c[q];
+            }
+        }
+        __syncthreads();
+        before = pick[1];
+        upto = before + pick[2];
+        if (of_key) {
+            pk |= static_cast<uint64_t>(pick[0]) << s;
+            maskk |= 255ull << s;
+        } else {
+            pi |= pick[0] << s;
+            maski |= 255u << s;
+        }
+        __syncthreads();
+    }
+    const int m = static_cast<int>(min(upto - before, static_cast<uint32_t>(kArBound)));
+    if (maskk == 0) {
+        for (int e = t; e < m; e += 1024) {
+            k[e] = bkey[e];
+            v[e] = bidx[e];
+        }
+    } else {
+        __syncthreads();
+        for (uint32_t e = t; e < found; e += 1024) {
+            const uint64_t ek = bkey[e];
+            const uint32_t ei = bidx[e];
+            const uint64_t mk = ek & maskk;
+            const uint32_t mi = ei & maski;
+            if (mk == pk && mi == pi) {
+                const uint32_t at = atomicAdd(&put, 1u);
+                if (at < kArBound) {
+                    k[at] = ek;
+                    v[at] = ei;
+                }
+            } else if (mk < pk || (mk == pk && mi < pi)) {
+                atomicAdd(cnt + ei / kArTile, 1u);
+            }
+        }
     }
     __syncthreads();
     for (int e = t; e < m; e += 1024) {
         const uint64_t ek = k[e];
         const uint32_t ei = v[e];
-        int64_t rank = 0;
+        uint32_t rank = before;
         for (int q = 0; q < m; ++q) rank += (k[q] < ek) | ((k[q] == ek) & (v[q] < ei));
         if (rank < r) atomicAdd(cnt + ei / kArTile, 1u);
         if (rank == r - 1) {
@@ -526,37 +626,42 @@ __global__ __launch_bounds__(1024) void k_ar_cut(ArState* __restrict__ S, int le
                                  ? static_cast<int64_t>(__hip_atomic_load(cnt + t0 + t, __ATOMIC_RELAXED,
                                                                           __HIP_MEMORY_SCOPE_AGENT))
                                  : 0;
-        int64_t upto = mine;
+        int64_t run = mine;
         for (int q = 1; q < 64; q <<= 1) {
-            const int64_t u = __shfl_up(static_cast<long long>(upto), q);
-            if ((t & 63) >= q) upto += u;
+            const int64_t u = __shfl_up(static_cast<long long>(run), q);
+            if ((t & 63) >= q) run += u;
         }
-        if ((t & 63) == 63) part[t / 64] = upto;
+        if ((t & 63) == 63) part[t / 64] = run;
         __syncthreads();
-        int64_t before = base;
+        int64_t first = base;
         for (int w = 0; w < 16; ++w) {
-            if (w < t / 64) before += part[w];
+            if (w < t / 64) first += part[w];
             base += part[w];
         }
-        if (t0 + t < tiles) off[t0 + t] = before + upto - mine;
+        if (t0 + t < tiles) off[t0 + t] = first + run - mine;
         __syncthreads();
     }
+    if (t == 0) S->listed = base;
 }
 
 // The kept candidates, in index order, as the next level's prefixes; at the
-// last level also their keys and places for the sort.
-__global__ __launch_bounds__(256) void k_ar_emit(const ArState* __restrict__ S, ArLevel A,
+// last level also their keys and places for the sort.  PAIRS: the candidates up
+// to the prefix, as keys and indices alone.
+template <bool PAIRS>
+__global__ __launch_bounds__(256) void k_ar_emit(const ArState* __restrict__ S, ArLevel A, int64_t room,
                                                  const uint64_t* __restrict__ key, const double* __restrict__ cand_l,
                                                  const int64_t* __restrict__ off, const uint64_t* __restrict__ keys,
-                                                 int64_t K, uint64_t* __restrict__ out_keys, double* __restrict__ out_l,
+                                                 uint64_t* __restrict__ out_keys, double* __restrict__ out_l,
                                                  double* __restrict__ out_T, uint64_t* __restrict__ out_key,
                                                  uint32_t* __restrict__ out_idx) {
     constexpr int kPer = kArTile / 256;
     __shared__ uint32_t part[kPer * 4];
+    if (S->redo) return;
     const int64_t n = S->B[A.level] << A.Dk;
     const int64_t base = static_cast<int64_t>(blockIdx.x) * kArTile;
     if (base >= n) return;
     const uint64_t prefix = static_cast<uint64_t>(S->prefix);
+    const int shift = S->shift;
     const uint64_t ck = S->cut_key;
     const uint32_t ci = S->cut_idx;
     const int wave = static_cast<int>(threadIdx.x) / 64, lane = lane_id();
@@ -567,8 +672,9 @@ __global__ __launch_bounds__(256) void k_ar_emit(const ArState* __restrict__ S, 
         const int64_t i = base + j * 256 + threadIdx.x;
         k[j] = i < n ? key[i] : ~0ull;
         const bool in = k[j] != ~0ull &&
-                        ((k[j] >> 40) < prefix ||
-                         ((k[j] >> 40) == prefix && (k[j] < ck || (k[j] == ck && static_cast<uint32_t>(i) <= ci))));
+                        ((k[j] >> shift) < prefix ||
+                         ((k[j] >> shift) == prefix &&
+                          (PAIRS || k[j] < ck || (k[j] == ck && static_cast<uint32_t>(i) <= ci))));
         const uint64_t bal = __ballot(in);
         before[j] = static_cast<uint32_t>(__popcll(bal & ((1ull << lane) - 1ull)));
         keep |= (in ? 1u : 0u) << j;
@@ -592,7 +698,12 @@ __global__ __launch_bounds__(256) void k_ar_emit(const ArState* __restrict__ S, 
         if (!((keep >> j) & 1u)) continue;
         const int64_t i = base + j * 256 + threadIdx.x;
         const int64_t at = at0 + part[4 * j + wave] + before[j];
-        if (at >= K) continue;   // only past a selection that is run again
+        if (at >= room) continue;
+        if constexpr (PAIRS) {
+            out_key[at] = k[j];
+            out_idx[at] = static_cast<uint32_t>(i);
+            continue;
+        }
         child_key(keys, i, A.O, A.W, A.q0, out_keys + at * A.W);
         out_l[at] = cand_l[i];
         out_T[at] = value_of(k[j]);
@@ -603,7 +714,21 @@ __global__ __launch_bounds__(256) void k_ar_emit(const ArState* __restrict__ S, 
     }
 }
 
-// The samples in sorted order to the caller; equal neighbours ask for the sorted search.
+// The first n sorted candidates as prefixes.
+__global__ void k_ar_gather(const uint64_t* __restrict__ keys, const uint64_t* __restrict__ sorted_key,
+                            const uint32_t* __restrict__ sorted_idx, int64_t n, int O, int W, int q0,
+                            const double* __restrict__ cand_l, uint64_t* __restrict__ out_keys,
+                            double* __restrict__ out_l, double* __restrict__ out_T) {
+    const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+    if (i >= n) return;
+    const uint32_t idx = sorted_idx[i];
+    child_key(keys, idx, O, W, q0, out_keys + i * W);
+    out_l[i] = cand_l[idx];
+    out_T[i] = value_of(sorted_key[i]);
+}
+
+// The samples in sorted order to the caller; equal neighbours ask for the search
+// with sorted levels.
 __global__ void k_ar_out(ArState* __restrict__ S, const uint64_t* __restrict__ sorted_key,
                          const uint32_t* __restrict__ sorted_idx, int64_t n, int W, const uint64_t* __restrict__ keys,
                          const double* __restrict__ l, uint64_t* __restrict__ out_keys, double* __restrict__ out_l,
@@ -665,49 +790,62 @@ void launch_candidates(const ArLevel& A, int64_t B, const ArScratch& R, int cur,
 
 size_t ar_state_bytes() { return sizeof(ArState); }
 int64_t ar_tiles(int64_t n) { return (n + kArTile - 1) / kArTile; }
-int64_t ar_bound() { return kArBound; }
 
 hipError_t launch_ar_root(const ArScratch& R, int W, hipStream_t st) {
     hipLaunchKernelGGL(k_ar_root, dim3(1), dim3(1024), 0, st, R.state, R.hist, R.keys[0], W, R.l[0], R.T[0]);
     return hipGetLastError();
 }
 
-// Where at most K candidates can come out nothing is selected: the digit
-// passes stay away.
+// Sets up to this size take two digits: the prefix then mostly holds some 130
+// candidates, and a third digit's two launches a level, even where they return
+// at once, would be 2% of it (2^16: 35 of 2190 us).
+constexpr int64_t kArTwoDigits = int64_t(1) << 16;
+
+namespace {
+
+// The level's candidates, and the prefix of the need-th of them.  Where at most
+// K can come out nothing is selected: the digit passes stay away.
+void launch_select(const ArLevel& A, int64_t B, int64_t K, const ArScratch& R, int cur, hipStream_t st) {
+    const int64_t n = B * A.O;
+    const bool select = n > K;
+    const dim3 one(1), block(1024);
+    launch_candidates(A, B, R, cur, select ? R.hist : nullptr, st);
+    hipLaunchKernelGGL(k_ar_pick<0>, one, block, 0, st, R.state, A.level, K, R.hist);
+    if (!select) return;
+    const dim3 few(static_cast<unsigned>(std::min<int64_t>((n + 8191) / 8192, 256)));   // each adds up to 4096 counts
+    hipLaunchKernelGGL(k_ar_hist<1>, few, block, 0, st, R.state, A.level, A.Dk, K, R.cand_key, R.hist);
+    hipLaunchKernelGGL(k_ar_pick<1>, one, block, 0, st, R.state, A.level, K, R.hist);
+    if (K <= kArTwoDigits) return;
+    hipLaunchKernelGGL(k_ar_hist<2>, few, block, 0, st, R.state, A.level, A.Dk, K, R.cand_key, R.hist);
+    hipLaunchKernelGGL(k_ar_pick<2>, one, block, 0, st, R.state, A.level, K, R.hist);
+}
+
+}  // namespace
+
 hipError_t launch_ar_level(const ArModelDev& M, int level, int64_t B, int64_t K, uint64_t seed, bool last,
                            const ArScratch& R, int cur, hipStream_t st) {
     const ArLevel A = level_of(M, level, seed);
-    const int64_t n = B * A.O;
-    const bool select = n > K;
-    launch_candidates(A, B, R, cur, select ? R.hist : nullptr, st);
-    hipLaunchKernelGGL(k_ar_pick<true>, dim3(1), dim3(1024), 0, st, R.state, level, K, R.hist);
-    if (select) {
-        const int64_t hb = std::min<int64_t>((n + 8191) / 8192, 256);   // few: each adds up to 4096 counts
-        hipLaunchKernelGGL(k_ar_hist, dim3(static_cast<unsigned>(hb)), dim3(1024), 0, st, R.state, level, A.Dk, K,
-                           R.cand_key, R.hist);
-        hipLaunchKernelGGL(k_ar_pick<false>, dim3(1), dim3(1024), 0, st, R.state, level, K, R.hist);
-    }
-    const unsigned tiles = static_cast<unsigned>(ar_tiles(n));
-    hipLaunchKernelGGL(k_ar_count, dim3(tiles), dim3(256), 0, st, R.state, level, A.Dk, R.cand_key, R.cnt, R.bkey,
-                       R.bidx);
+    launch_select(A, B, K, R, cur, st);
+    const unsigned tiles = static_cast<unsigned>(ar_tiles(B * A.O));
+    hipLaunchKernelGGL(k_ar_count<true>, dim3(tiles), dim3(256), 0, st, R.state, level, A.Dk, R.cand_key, R.cnt,
+                       R.bkey, R.bidx);
     hipLaunchKernelGGL(k_ar_cut, dim3(1), dim3(1024), 0, st, R.state, level, A.Dk, R.bkey, R.bidx, R.cnt, R.off);
-    hipLaunchKernelGGL(k_ar_emit, dim3(tiles), dim3(256), 0, st, R.state, A, R.cand_key, R.cand_l, R.off, R.keys[cur],
-                       K, R.keys[cur ^ 1], R.l[cur ^ 1], R.T[cur ^ 1], last ? R.sort_key : nullptr, R.sort_idx);
+    hipLaunchKernelGGL(k_ar_emit<false>, dim3(tiles), dim3(256), 0, st, R.state, A, K, R.cand_key, R.cand_l,
+                       R.off, R.keys[cur], R.keys[cur ^ 1], R.l[cur ^ 1], R.T[cur ^ 1], last ? R.sort_key : nullptr,
+                       R.sort_idx);
     return hipGetLastError();
 }
 
-hipError_t launch_ar_out(const ArScratch& R, int cur, const uint64_t* sorted_key, const uint32_t* sorted_idx,
-                         int64_t n, int W, uint64_t* out_keys, double* out_l, double* out_T, hipStream_t st) {
-    hipLaunchKernelGGL(k_ar_out, dim3(blocks256(n)), dim3(256), 0, st, R.state, sorted_key, sorted_idx, n, W,
-                       R.keys[cur], R.l[cur], out_keys, out_l, out_T);
-    return hipGetLastError();
-}
-
-hipError_t launch_ar_candidates(const ArModelDev& M, int level, int64_t B, uint64_t seed, const ArScratch& R, int cur,
-                                uint32_t* idx, hipStream_t st) {
+hipError_t launch_ar_survivors(const ArModelDev& M, int level, int64_t B, int64_t K, uint64_t seed, const ArScratch& R,
+                               int cur, hipStream_t st) {
     const ArLevel A = level_of(M, level, seed);
-    launch_candidates(A, B, R, cur, nullptr, st);
-    hipLaunchKernelGGL(k_ar_iota, dim3(blocks256(B * A.O)), dim3(256), 0, st, idx, B * A.O);
+    launch_select(A, B, K, R, cur, st);
+    const unsigned tiles = static_cast<unsigned>(ar_tiles(B * A.O));
+    hipLaunchKernelGGL(k_ar_count<false>, dim3(tiles), dim3(256), 0, st, R.state, level, A.Dk, R.cand_key, R.cnt,
+                       nullptr, nullptr);
+    hipLaunchKernelGGL(k_ar_cut, dim3(1), dim3(1024), 0, st, R.state, level, A.Dk, nullptr, nullptr, R.cnt, R.off);
+    hipLaunchKernelGGL(k_ar_emit<true>, dim3(tiles), dim3(256), 0, st, R.state, A, B * A.O, R.cand_key, nullptr,
+                       R.off, nullptr, nullptr, nullptr, nullptr, R.bkey, R.bidx);
     return hipGetLastError();
 }
 
@@ -719,6 +857,13 @@ hipError_t launch_ar_gather(const ArModelDev& M, int level, const ArScratch& R, 
     return hipGetLastError();
 }
 
+hipError_t launch_ar_out(const ArScratch& R, int cur, const uint64_t* sorted_key, const uint32_t* sorted_idx,
+                         int64_t n, int W, uint64_t* out_keys, double* out_l, double* out_T, hipStream_t st) {
+    hipLaunchKernelGGL(k_ar_out, dim3(blocks256(n)), dim3(256), 0, st, R.state, sorted_key, sorted_idx, n, W,
+                       R.keys[cur], R.l[cur], out_keys, out_l, out_T);
+    return hipGetLastError();
+}
+
 hipError_t ar_read(const ArScratch& R, int level, ArResult* out, hipStream_t st) {
     ArState S;
     hipError_t e = hipMemcpyAsync(&S, R.state, sizeof(S), hipMemcpyDeviceToHost, st);
@@ -726,13 +871,9 @@ hipError_t ar_read(const ArScratch& R, int level, ArResult* out, hipStream_t st)
     e = hipStreamSynchronize(st);
     if (e != hipSuccess) return e;
     out->B = S.B[level];
-    out->allowed = level > 0 ? static_cast<int64_t>(S.allowed[level - 1]) : 0;
+    out->listed = S.listed;
     out->redo = S.redo != 0;
     return hipSuccess;
-}
-
-hipError_t ar_set_prefixes(const ArScratch& R, int level, const int64_t* B, hipStream_t st) {
-    return hipMemcpyAsync(&R.state->B[level], B, sizeof(*B), hipMemcpyHostToDevice, st);
 }
 
 }  // namespace eloc
