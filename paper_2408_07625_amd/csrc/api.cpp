@@ -1609,7 +1609,7 @@ int eloc_find_pairs(eloc_ctx c, int variant, int64_t capacity, int32_t* i_dev, i
     const int end_bit = 2 * jbits;
     ELOC_HIP(c, c->pkey.ensure(sizeof(uint64_t) * total));
     ELOC_HIP(c, c->pval.ensure(sizeof(uint32_t) * total));
-    if (M <= kRowSortMax) {
+    if (rows_sorted_pays(M, total)) {
         ELOC_HIP(c, fill_pairs(c, variant, P, jbits));
         ELOC_HIP(c, launch_rows_sorted(c->offsets.as<int64_t>(), M, P.chunks, jbits, c->pkey.as<uint64_t>(),
                                        c->pval.as<uint32_t>(), i_dev, j_dev, g_dev, c->stream));

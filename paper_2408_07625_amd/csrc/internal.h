@@ -823,9 +823,17 @@ hipError_t launch_pair_phases(const HamDev& H, const SampleDev& S, int64_t n, co
 hipError_t launch_pairs_to_csr(const HamDev& H, const SampleDev& S, int64_t n, const uint64_t* pkey,
                                const uint32_t* pval, int jbits, int32_t* col, double2* h, hipStream_t st);
 // The emitted pairs (row << jbits | column, group), row after row at
-// offsets[row * chunks], as (i, j, g) ordered by (i, j): for up to
-// kRowSortMax samples (a bitmap of U's columns in LDS).
+// offsets[row * chunks], as (i, j, g) ordered by (i, j): a wave a row, with a
+// bitmap of U's columns in LDS, for up to kRowSortMax samples.  A row costs the
+// bitmap's words, and the fewer rows a CU then holds the more so: 1.0e-18 s M^3
+// in all, where the radix sort of the pairs costs 0.1 ms and 0.1 ns a pair.
+// find_pairs, sort / rows: 14 819 samples of 1 and 256 pairs 202 / 137 and
+// 524 / 259 us; 59 265 of 16 and 64 300 / 389 and 602 / 459; 118 451 of 4 and
+// 64 296 / 1763 and 1044 / 1935.
 constexpr int64_t kRowSortMax = int64_t(1) << 17;
+inline bool rows_sorted_pays(int64_t M, int64_t pairs) {
+    return M <= kRowSortMax && M * M * M <= 100000000 * (pairs + 1000000);
+}
 hipError_t launch_rows_sorted(const int64_t* offsets, int64_t M, int chunks, int jbits, const uint64_t* pkey,
                               const uint32_t* pval, int32_t* oi, int32_t* oj, int32_t* og, hipStream_t st);
 hipError_t launch_rowptr(const int64_t* offsets, int64_t M, int chunks, int64_t* rowptr, hipStream_t st);
