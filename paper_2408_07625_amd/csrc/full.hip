@@ -161,7 +161,9 @@ __global__ __launch_bounds__(kWave) void k_full_rows(FullArgs A, const typename 
     const int nstash = __builtin_amdgcn_readfirstlane(static_cast<int>(T.stash->count));
     const bool any = __builtin_amdgcn_readfirstlane(A.sp->sig_all) != 0;
     const uint32_t sig_pa = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(A.sp->sig_pa)),
-                   sig_n = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(A.sp->sig_n));
+                   sig_n = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(A.sp->sig_n)),
+                   rad_max = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(A.sp->rad_max));
+    const uint64_t ref = A.sp->rad_ref[0];
     const auto* __restrict__ terms = static_cast<const typename P::template Term<1>*>(A.terms);
     const uint64_t x = A.keys[row];
     const uint64_t hx = A.hash[row] ^ T.salt;
@@ -180,19 +182,27 @@ __global__ __launch_bounds__(kWave) void k_full_rows(FullArgs A, const typename 
             gr[u] = A.groups[gg];
             hs[u] = static_cast<HT>(hx ^ A.ghash[gg]);
         }
-        // X's signature, where it has a single one
+        // X's signature, where it has a single one, else its radius
 #pragma unroll
         for (int u = 0; u < kStep; ++u) {
             xp[u] = x ^ gr[u].xy[0];
-            uint32_t pa, pn;
-            if constexpr (NW) {
-                pa = __popc(static_cast<uint32_t>(xp[u]) & static_cast<uint32_t>(kEvenBits));
-                pn = __popc(static_cast<uint32_t>(xp[u]));
+            bool pass;
+            if (any) {
+                const uint32_t d = NW ? __popc(static_cast<uint32_t>(xp[u]) ^ static_cast<uint32_t>(ref))
+                                      : popc64(xp[u] ^ ref);
+                pass = d <= rad_max;
             } else {
-                pa = popc64(xp[u] & kEvenBits);
-                pn = popc64(xp[u]);
+                uint32_t pa, pn;
+                if constexpr (NW) {
+                    pa = __popc(static_cast<uint32_t>(xp[u]) & static_cast<uint32_t>(kEvenBits));
+                    pn = __popc(static_cast<uint32_t>(xp[u]));
+                } else {
+                    pa = popc64(xp[u] & kEvenBits);
+                    pn = popc64(xp[u]);
+                }
+                pass = pa == sig_pa && pn == sig_n;
             }
-            ok[u] = on && g + u * stride < g1 && (any || (pa == sig_pa && pn == sig_n));
+            ok[u] = on && g + u * stride < g1 && pass;
             v1[u] = slots.load(slot1(T, hs[u]), ok[u]);
         }
 #pragma unroll
