@@ -188,14 +188,18 @@ bool use_join(const eloc_ctx c, int64_t M, int variant) {
 
 // Whether U's rows over U and n_extra states more are summed with lanes over
 // rows (full.hip): one-word keys, launch shape not tuned, and the larger set
-// mostly coupled states, so that most candidates are pairs.  A whole call, loop
-// / lanes over rows: 12 qubits, 100 rows, 300 states more 347 / 285 us; 14
-// qubits, 500 and 725 392 / 324; 16 qubits, 1677 and 3223 488 / 401; 28 qubits,
-// 20 000 and 3.8e6 3820 / 2745, the search for the states in all of them.
-// Fewer states than rows were not measured.
+// mostly coupled states, so that many candidates are pairs - a pair costs there
+// what any candidate does.  Few candidates are a matter of latency, where it is
+// the shorter way with as many states more as rows already.  A whole call, loop
+// / lanes over rows: up to 4.7e7 candidates 12 qubits, 100 rows, 300 states more
+// 347 / 285 us; 28 qubits, 2000 and 2010 265 / 214; 34 qubits, 2000 and 2010
+// 330 / 284; from 7.3e7 on 28 qubits, 20 000 rows of 1, 10, 40 and 188 states
+// more each 595 / 708, 839 / 887, 1132 / 976 and 3880 / 1850; 32 qubits, 4000
+// of 10 and 40 350 / 369 and 445 / 434; 30 qubits, 8000 of 10 and 25 (all there
+// are) 430 / 481 and 674 / 569.
 bool full_by_rows(const eloc_ctx c, int64_t M, int64_t n_extra) {
-    return c->H.W == 1 && n_extra >= M && !c->tune_chunks && c->tune_sig && !c->tune_rows && !c->tune_bloom &&
-           !c->tune_waves && !c->tune_part && !c->tune_part_count;
+    return c->H.W == 1 && n_extra >= (M * c->H.n_groups <= (int64_t(1) << 26) ? M : 24 * M) && !c->tune_chunks &&
+           c->tune_sig && !c->tune_rows && !c->tune_bloom && !c->tune_waves && !c->tune_part && !c->tune_part_count;
 }
 
 // Room for the index of n samples (eloc_set_samples makes it for the variants
