@@ -267,13 +267,16 @@ Plan make_plan(const eloc_ctx c, int variant, int64_t n_rows = -1, bool allow_pa
     // (a long run, the queue's hits) then bounds the launch: LoopOverTerms, 12
     // qubits, 300 samples 31 us with 4, 49 with 8; 20 qubits, 6000 66 / 84; from
     // about 2^26 candidates on the scan's share of a wave counts for more (40
-    // qubits, 9999 551 / 527) but for two-word keys (66 qubits, 3000 1620 / 1880).
+    // qubits, 9999 551 / 527), with two-word keys from 2048 samples on (energies
+    // in a spin-blocked order, 66 qubits, 2000 1272 / 1354, 3000 2363 / 2172; 100
+    // qubits, 2000 6223 / 6831, 3000 12 481 / 11 347).
     // LoopOverBatch up to 2^14 samples, with a quarter of the waves: 20 qubits,
     // 6000 61 / 70; 28 qubits, 8000 81 / 100; 40 qubits, 9999 146 / 148.  A
     // partitioned table has tiles of its own.
     const bool small = n_rows < 0 && c->tune_chunks <= 0 && !bloom && c->part_bits == 0 && M <= (int64_t(1) << 14) &&
                        (variant == ELOC_BATCH ||
-                        (variant == ELOC_TERMS && (c->H.W == 2 || M * c->H.n_groups < (int64_t(1) << 26))));
+                        (variant == ELOC_TERMS && ((c->H.W == 2 && M <= 2048) ||
+                                                   M * c->H.n_groups < (int64_t(1) << 26))));
     const int rows = c->tune_rows ? c->tune_rows : (bloom || small ? 4 : 8);
     P.rows_per_block = rows_per_block(variant, rows);
     P.waves_per_block = bloom ? 4 : 1;
