@@ -93,6 +93,7 @@ struct eloc_ctx_s {
     // eloc_set_samples alone, the index is built by the first call that reads it
     JoinIndex J;
     bool j_room = false, j_built = false;
+    bool j_huge = false;             // a bucket is too long for the join to list
     bool samples_captured = false;   // set under stream capture: every replay sets others
 
     DevBuf a, b, af, bf, v, vf, shift, amp_scratch;
@@ -205,7 +206,7 @@ bool full_by_rows(const eloc_ctx c, int64_t M, int64_t n_extra) {
 // Room for the index of n samples (eloc_set_samples makes it for the variants
 // that may not allocate later).  Without the memory for it the loops serve.
 int join_room(eloc_ctx c, int64_t n) {
-    const hipError_t e = c->J.room(c->H.W, n);
+    const hipError_t e = c->J.room(c->H.W, n, c->JH);
     c->j_room = e == hipSuccess;
     if (e == hipErrorOutOfMemory) {
         (void)hipGetLastError();
@@ -228,8 +229,8 @@ bool capturing(hipStream_t st) {
 // which a replay changes without a call that would tell.
 int ensure_join(eloc_ctx c) {
     if (c->j_built) return ELOC_OK;
-    ELOC_HIP(c, c->J.build(c->H.W, c->keys.as<uint64_t>(), c->S.n, c->H.n_qubits, c->JH.split,
-                           c->err_prep.as<uint32_t>(), c->stream));
+    ELOC_HIP(c, c->J.build(c->H.W, c->keys.as<uint64_t>(), c->S.n, c->H.n_qubits, c->JH, c->err_prep.as<uint32_t>(),
+                           c->stream));
     c->j_built = !c->samples_captured && !capturing(c->stream);
     return ELOC_OK;
 }
@@ -664,10 +665,11 @@ int ensure_utrie(eloc_ctx c) {
     return ELOC_OK;
 }
 
-// The variant that serves the caller's, with what it needs of U built.
-int prepare_variant(eloc_ctx c, int* variant) {
+// The variant that serves the caller's, with what it needs of U built.  join:
+// the join among them.
+int prepare_variant(eloc_ctx c, int* variant, bool join = true) {
     *variant = resolve_variant(c, *variant);
-    if (use_join(c, c->S.n, *variant)) {
+    if (join && use_join(c, c->S.n, *variant)) {
         if (!c->j_room) {
             const int rc = join_room(c, c->S.n);
             if (rc) return rc;
@@ -697,6 +699,10 @@ int amp_prep(eloc_ctx c, const eloc_c64* logpsi, bool fp32, bool clear_err = fal
     return ELOC_OK;
 }
 
+JoinOwn join_own(const eloc_ctx c) {
+    return JoinOwn{c->H.terms, c->S.hash, c->S.table, c->H.narrow, c->S.params};
+}
+
 // The row sums of the forward (vec = a) or adjoint (vec = v) pass into
 // c->partial: the fused pair kernel for a variant, or one pass over the
 // stored pair list (one partial per row).
@@ -711,7 +717,8 @@ int row_sums(eloc_ctx c, bool adjoint, int variant, int precision, const double2
         ELOC_HIP(c, launch_spmv(adjoint, precision, M, c->st_rowptr.as<int64_t>(), c->st_col.as<int32_t>(),
                                 c->st_h.as<double2>(), v, c->partial.p, c->stream));
     } else if (variant == kJoin) {
-        ELOC_HIP(c, launch_join_pairs(adjoint, precision, c->H, c->JH.dev, c->J.dev, P, vec, vecf, c->partial.p, c->stream));
+        ELOC_HIP(c, launch_join_pairs(adjoint, precision, c->H, c->JH.dev, c->J.dev, P, join_own(c), vec, vecf,
+                                      c->partial.p, c->stream));
     } else {
         ELOC_HIP(c, launch_pairs(adjoint, variant, precision, c->H, c->S, P, vec, vecf, c->partial.p, c->stream));
     }
@@ -749,6 +756,25 @@ int count_into_offsets(eloc_ctx c, int variant, const Plan& P, int64_t* total) {
     ELOC_HIP(c, hipMemcpyAsync(&t, c->offsets.as<int64_t>() + n, sizeof(int64_t), hipMemcpyDeviceToHost, c->stream));
     ELOC_HIP(c, hipStreamSynchronize(c->stream));
     *total = t;
+    return ELOC_OK;
+}
+
+// A listing call's variant and plan, with the pairs counted.  The join lists no
+// huge buckets: the count tells, and the loops take its place for these samples.
+int count_variant(eloc_ctx c, int* variant, Plan* P, int64_t* total) {
+    const int asked = *variant;
+    bool join = !c->j_huge;
+    for (int pass = 0; pass < 2; ++pass) {
+        *variant = asked;
+        int rc = prepare_variant(c, variant, join);
+        if (rc) return rc;
+        *P = make_plan(c, *variant, -1, true);
+        rc = count_into_offsets(c, *variant, *P, total);
+        if (rc) return rc;
+        if (*variant != kJoin || *total >= 0) break;
+        join = false;
+        c->j_huge = !c->samples_captured;
+    }
     return ELOC_OK;
 }
 
@@ -894,6 +920,7 @@ int eloc_set_samples(eloc_ctx c, int64_t n_unique, const uint64_t* keys_dev) {
     c->miss_valid = false;
     c->j_built = false;
     c->j_room = false;
+    c->j_huge = false;
     c->samples_captured = capturing(c->stream);
     ELOC_HIP(c, c->keys.ensure(sizeof(uint64_t) * n_unique * W));
     ELOC_HIP(c, c->khash.ensure(sizeof(uint64_t) * n_unique));
@@ -1064,7 +1091,8 @@ int eloc_local_energy_noalloc(eloc_ctx c, int variant, int precision, const eloc
         const int rc = ensure_join(c);
         if (rc) return rc;
         P = J;
-        ELOC_HIP(c, launch_join_pairs(false, precision, c->H, c->JH.dev, c->J.dev, P, a, af, partial, c->stream));
+        ELOC_HIP(c, launch_join_pairs(false, precision, c->H, c->JH.dev, c->J.dev, P, join_own(c), a, af, partial,
+                                      c->stream));
     } else {
         ELOC_HIP(c, launch_pairs(false, variant, precision, c->H, c->S, P, a, af, partial, c->stream));
     }
@@ -1589,10 +1617,12 @@ int eloc_count_pairs(eloc_ctx c, int variant, int64_t* n_pairs_host) {
     if (rc) return rc;
     if (!valid_variant(variant)) return fail(c, ELOC_EINVAL, "unknown or unavailable variant");
     if (!n_pairs_host) return fail(c, ELOC_EINVAL, "null pointer");
-    rc = prepare_variant(c, &variant);
+    Plan P;
+    int64_t total = 0;
+    rc = count_variant(c, &variant, &P, &total);
     if (rc) return rc;
-    const Plan P = make_plan(c, variant, -1, true);
-    return count_into_offsets(c, variant, P, n_pairs_host);
+    *n_pairs_host = total;
+    return ELOC_OK;
 }
 
 int eloc_find_pairs(eloc_ctx c, int variant, int64_t capacity, int32_t* i_dev, int32_t* j_dev, int32_t* g_dev,
@@ -1601,11 +1631,9 @@ int eloc_find_pairs(eloc_ctx c, int variant, int64_t capacity, int32_t* i_dev, i
     if (rc) return rc;
     if (!valid_variant(variant)) return fail(c, ELOC_EINVAL, "unknown or unavailable variant");
     if (!n_pairs_host) return fail(c, ELOC_EINVAL, "null pointer");
-    rc = prepare_variant(c, &variant);
-    if (rc) return rc;
-    const Plan P = make_plan(c, variant, -1, true);
+    Plan P;
     int64_t total = 0;
-    rc = count_into_offsets(c, variant, P, &total);
+    rc = count_variant(c, &variant, &P, &total);
     if (rc) return rc;
     *n_pairs_host = total;
     if (total > capacity) return fail(c, ELOC_ECAPACITY, "pair capacity too small");
@@ -1714,12 +1742,10 @@ int eloc_store_pairs(eloc_ctx c, int variant, size_t budget_bytes, int64_t* n_pa
     if (rc) return rc;
     if (!n_pairs_host) return fail(c, ELOC_EINVAL, "null pointer");
     if (!valid_variant(variant)) return fail(c, ELOC_EINVAL, "unknown or unavailable variant");
-    rc = prepare_variant(c, &variant);
-    if (rc) return rc;
     c->st_valid = false;
-    const Plan P = make_plan(c, variant, -1, true);
+    Plan P;
     int64_t total = 0;
-    rc = count_into_offsets(c, variant, P, &total);
+    rc = count_variant(c, &variant, &P, &total);
     if (rc) return rc;
     *n_pairs_host = total;
     const int64_t M = c->S.n;

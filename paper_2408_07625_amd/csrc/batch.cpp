@@ -270,10 +270,11 @@ int enqueue(eloc_batch b, int precision, hipStream_t st, bool timed = false) {
                 forked = true;
             }
             const BatchProb& D = b->desc[static_cast<size_t>(k)];
-            e = J->index.build(b->W, B.keys + D.s0 * b->W, D.M, J->H.n_qubits, J->masks.split, B.err + k, b->side);
+            e = J->index.build(b->W, B.keys + D.s0 * b->W, D.M, J->H.n_qubits, J->masks, B.err + k, b->side);
             if (e == hipSuccess)
-                e = launch_join_pairs(false, precision, J->H, J->masks.dev, J->index.dev, J->plan, B.a + D.s0,
-                                      B.af + D.s0, static_cast<double2*>(B.partial) + D.pbase, b->side,
+                e = launch_join_pairs(false, precision, J->H, J->masks.dev, J->index.dev, J->plan,
+                                      JoinOwn{D.terms, B.khash + D.s0, D.ktable, D.narrow != 0, nullptr},
+                                      B.a + D.s0, B.af + D.s0, static_cast<double2*>(B.partial) + D.pbase, b->side,
                                       B.join_pairs + static_cast<int64_t>(k) * kJoinPairSlots * kJoinPairStride);
             if (e != hipSuccess) return e;
         }
@@ -460,7 +461,7 @@ int ingest_all(eloc_batch b, const eloc_problem* probs) {
         auto J = std::make_unique<BatchJoin>();
         BATCH_HIP(b, J->masks.upload(h, I.n_qubits));
         if (!J->masks.dev.ok) continue;
-        const hipError_t e = J->index.room(W, I.M);
+        const hipError_t e = J->index.room(W, I.M, J->masks);
         if (e == hipErrorOutOfMemory) {   // the loops serve
             (void)hipGetLastError();
             continue;

@@ -375,6 +375,26 @@ __device__ __forceinline__ void wave_melem(const TermRec<W>* __restrict__ terms,
     }
 }
 
+// table_settle for the lookups of a whole wave in an exact table.  A stashed key
+// has been in its first slot and found it taken since, so the stash is read only
+// where some lane's first slot is another key's and its second slot not its own.
+// Where most candidates are in the table that is rare, and the stash of a few
+// million states is close to full.
+template <int TK>
+__device__ __forceinline__ int wave_settle(const Table& T, typename TabT<TK>::slot v1, typename TabT<TK>::slot v2,
+                                           typename TabT<TK>::hash hs, int nstash) {
+    using ST = typename TabT<TK>::slot;
+    const ST t = static_cast<ST>((hs >> T.capbits) << 1);
+    int j = -1;
+    if ((v1 >> T.ibits) == t) j = static_cast<int>(v1 & T.imask) - 1;
+    if ((v2 >> T.ibits) == (t | 1u)) j = static_cast<int>(v2 & T.imask) - 1;
+    const bool open = v1 != 0 && j < 0;
+    if (nstash && __ballot(open))
+        for (int k = 0; k < nstash && k < kStash; ++k)
+            if (open && T.stash->hs[k] == static_cast<uint64_t>(hs)) j = static_cast<int>(T.stash->idx[k]);
+    return j;
+}
+
 // A complex double as FP32 hi + lo pairs (re_hi, re_lo, im_hi, im_lo).
 __device__ __forceinline__ float4 split_c(double re, double im) {
     const float rh = static_cast<float>(re);

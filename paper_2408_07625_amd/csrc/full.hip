@@ -83,26 +83,6 @@ __device__ __forceinline__ F2 run_all(const TermRecF<1>* __restrict__ terms, int
     return h;
 }
 
-// A lookup's outcome from its two slot values, as table_settle's.  A stashed
-// key has been in its first slot and found it taken since, so the stash is
-// read only where some lane's first slot is another key's and its second slot
-// not its own.  Here that is rare, as most candidates are in the table, and
-// the stash of a few million states is close to full.
-template <int TK>
-__device__ __forceinline__ int settle(const Table& T, typename TabT<TK>::slot v1, typename TabT<TK>::slot v2,
-                                      typename TabT<TK>::hash hs, int nstash) {
-    using ST = typename TabT<TK>::slot;
-    const ST t = static_cast<ST>((hs >> T.capbits) << 1);
-    int j = -1;
-    if ((v1 >> T.ibits) == t) j = static_cast<int>(v1 & T.imask) - 1;
-    if ((v2 >> T.ibits) == (t | 1u)) j = static_cast<int>(v2 & T.imask) - 1;
-    const bool open = v1 != 0 && j < 0;
-    if (nstash && __ballot(open))
-        for (int k = 0; k < nstash && k < kStash; ++k)
-            if (open && T.stash->hs[k] == static_cast<uint64_t>(hs)) j = static_cast<int>(T.stash->idx[k]);
-    return j;
-}
-
 // One wave: 64 rows, a chunk of the groups.
 template <int PREC, bool NW>
 __global__ __launch_bounds__(kWave) void k_full_rows(FullArgs A, const typename Prec<PREC>::Vec* __restrict__ vec,
@@ -209,7 +189,7 @@ __global__ __launch_bounds__(kWave) void k_full_rows(FullArgs A, const typename 
         for (int u = 0; u < kStep; ++u) v2[u] = slots.load(slot2(T, hs[u]), need_slot2<TK>(T, v1[u], hs[u]));
 #pragma unroll
         for (int u = 0; u < kStep; ++u) {
-            j[u] = settle<TK>(T, v1[u], v2[u], hs[u], nstash);
+            j[u] = wave_settle<TK>(T, v1[u], v2[u], hs[u], nstash);
             v[u] = typename P::Vec{};
             if (j[u] >= 0) v[u] = vec[j[u]];
         }

@@ -301,10 +301,24 @@ struct JoinHeavy {
     uint32_t taken[2];  // ids given out
     uint32_t bits[2];   // their tables' sizes
     uint32_t hist[2][26];   // buckets of at least 16 by floor(log2(size))
+    uint32_t huge;      // some bucket is past its order's limit (join_own_limit)
 };
 constexpr uint32_t kJoinCore = 1u << 16;       // cells of the heavy-heavy table
 constexpr int kJoinHeavyBits = 14;             // a quarter of these slots may be taken
 constexpr uint32_t kJoinHeavySlots = 1u << kJoinHeavyBits;
+// A mask of one spin: its part, and the hash of the mask.
+template <int W>
+struct JoinOwnMask {
+    JoinStr<W> part;
+    uint64_t hash;
+};
+struct JoinOwnDev {
+    int n = 0;
+    const void* masks = nullptr;    // JoinOwnMask<W>[n]
+    const void* groups = nullptr;   // GroupRec<W>[n]
+    const void* place = nullptr;    // their JoinPlace<W>[n]
+    const double* sign = nullptr;   // and T [kJoinIdx][n]
+};
 // The masks (a, b) of H, spin-up part a and spin-down part b, in three
 // sections of places: (0, b) by the table b_own; (a, b) with both parts, at
 // base(a) + id(b); (a, 0) with a != 0 by the table a_own.
@@ -335,6 +349,9 @@ struct JoinHamDev {
     int nibbles = 0;                   // of one string
     uint32_t a_base = 0, a_pmin = 0, a_span = 0;   // the section (a, 0): first place, popcounts
     bool has_a_own = false;
+    // the masks that stay in a bucket of the spin-up order, (0, b), and of the
+    // spin-down order, (a, 0) without the diagonal, long runs first
+    JoinOwnDev own[2];
 };
 // U in its two sorted orders (positions [0, M): by spin-up string; [M, 2M):
 // by spin-down string), each stable in the caller's order.
@@ -356,6 +373,9 @@ struct JoinDev {
     const uint32_t* core = nullptr;       // [heavy spin-up][heavy spin-down] position + 1 (0: none)
     const void* cross = nullptr;          // JoinStr<W>[M] scan strings of the spin-down order, no
                                           // column with a light spin-up string passing any test
+    // Bloom filter of U, filled where a bucket is huge (none: no huge buckets are possible)
+    uint32_t* filter = nullptr;
+    uint32_t filter_mask = 0;             // its words less one
     const uint32_t* prep_err = nullptr;
 };
 
@@ -871,6 +891,9 @@ struct JoinBuild {
     int64_t M;
     int n_qubits;
     bool split;                // heavy / light split on
+    uint32_t own_limit[2];     // by order
+    uint32_t* filter;          // words to clear, or none
+    int64_t filter_words;
     uint64_t *key, *key2;      // [2M] sort scratch
     uint32_t *val, *val2;
     uint32_t* hist;            // radix scratch for 2M
@@ -885,6 +908,39 @@ struct JoinBuild {
     uint32_t* core;            // [kJoinCore]
 };
 hipError_t launch_join_index(int W, const JoinBuild& B, hipStream_t st);
+// An own bucket is scanned whole by each of its rows, which is the square of the
+// bucket where many samples share a spin string (all electrons of one spin, a
+// frozen spin).  Past this many samples its rows look the masks up instead, in
+// U's table (k_join_own): a lookup costs about 13 scanned columns.
+inline uint32_t join_own_limit(int n_own) {
+    return n_own > 0 && n_own < (1 << 24) ? 13u * static_cast<uint32_t>(n_own) : kJoinNone;
+}
+// Whether M samples can have such a bucket.
+inline bool join_own_possible(const JoinHamDev& H, int64_t M) {
+    const int64_t most = H.string_bits < 24 ? std::min<int64_t>(M, int64_t(1) << H.string_bits) : M;
+    return most > static_cast<int64_t>(std::min(join_own_limit(H.own[0].n), join_own_limit(H.own[1].n)));
+}
+// The row sums allow for it past this size: the kernel costs 3 us where no
+// bucket is that long, and a bucket of up to 2^16 scanned by all of its rows
+// costs no more than the loop.
+constexpr int64_t kJoinOwnLeast = int64_t(1) << 16;
+// Words of the Bloom filter for M samples (0: no huge buckets are possible): 16
+// bits a sample up to 1 MB, then 8: past that the L2s hold it beside the rest.
+inline int64_t join_filter_words(const JoinHamDev& H, int64_t M) {
+    if (M <= kJoinOwnLeast || !join_own_possible(H, M)) return 0;
+    int64_t w = 1;
+    while (2 * w < M && w < (int64_t(1) << 18)) w *= 2;
+    while (4 * w < M) w *= 2;
+    return w;
+}
+// What the lookups read.  params: U's signature, or none.
+struct JoinOwn {
+    const void* terms = nullptr;       // TermRec<W>
+    const uint64_t* khash = nullptr;
+    Table table{};
+    bool narrow = false;
+    const SampleParams* params = nullptr;
+};
 // Words that the waves of a join count their pairs in, each in a cache line of
 // its own: tens of thousands of waves, at 4 ns an atomic on one word.
 constexpr int kJoinPairSlots = 16;
@@ -892,10 +948,12 @@ constexpr int kJoinPairStride = 16;
 // Row sums into partial[chunk][M]: chunk 0 the spin-down order (own buckets,
 // then the light buckets of blist), chunk 1 the heavy-heavy table, chunks 2 ..
 // P.chunks - 1 the masks of alist, P.per_chunk each.  pairs: words that the
-// number of pairs is added to, or none.
+// number of pairs is added to, or none.  Where huge own buckets are possible
+// their pairs come from U's table.
 hipError_t launch_join_pairs(bool adjoint, int precision, const HamDev& H, const JoinHamDev& JH, const JoinDev& J,
-                             const Plan& P, const double2* vec, const float4* vecf, void* partial, hipStream_t st,
-                             unsigned long long* pairs = nullptr);
+                             const Plan& P, const JoinOwn& own, const double2* vec, const float4* vecf, void* partial,
+                             hipStream_t st, unsigned long long* pairs = nullptr);
+// counts[row][chunk]; with a bucket past the limit -1 throughout: the loops list then.
 hipError_t launch_join_count(const HamDev& H, const JoinHamDev& JH, const JoinDev& J, const Plan& P, int32_t* counts,
                              hipStream_t st);
 // Matrix elements of sample pairs by place (Hamiltonians with H.direct): of

@@ -54,6 +54,12 @@ struct HostJoin {
     std::vector<double> linear;       // [tables][2][2 nibbles][16]
     std::vector<JoinRun> runs;
     std::vector<int32_t> gids;
+    struct Own {
+        std::vector<JoinOwnMask<W>> masks;
+        std::vector<GroupRec<W>> groups;
+        std::vector<JoinPlace<W>> place;
+        std::vector<double> sign;
+    } own[2];                         // the masks (0, b); (a, 0) with a != 0
     int nibbles = 0;
     uint32_t cross = 0;               // first place of the two-spin masks
     uint32_t a_base = 0;              // places of the masks (a, 0)
@@ -374,6 +380,24 @@ void build_host_join(const HostHam<W>& hh, int n_qubits, HostJoin<W>& out) {
     for (int64_t g = 0; g < G; ++g)
         by_run += join_kind_of(out.place[at[static_cast<size_t>(g)]].hi) == kJoinRunKind;
     if (8 * by_run > G) return;
+    for (int o = 0; o < 2; ++o) {
+        std::vector<size_t> list;
+        for (size_t i = 0; i < static_cast<size_t>(G); ++i)
+            if (o == 0 ? as[i] == 0 : as[i] != 0 && bs[i] == 0) list.push_back(i);
+        std::stable_sort(list.begin(), list.end(), [&](size_t x, size_t y) {
+            return hh.groups[x].end - hh.groups[x].begin > hh.groups[y].end - hh.groups[y].begin;
+        });
+        typename HostJoin<W>::Own& own = out.own[o];
+        own.sign.resize(kJoinIdx * list.size());
+        for (size_t k = 0; k < list.size(); ++k) {
+            const size_t i = list[k];
+            own.masks.push_back(JoinOwnMask<W>{o == 0 ? bs[i] : as[i], hh.ghash[i]});
+            own.groups.push_back(hh.groups[i]);
+            own.place.push_back(out.place[at[i]]);
+            for (size_t q = 0; q < kJoinIdx; ++q)
+                own.sign[q * list.size() + k] = out.sign[q * static_cast<size_t>(places) + at[i]];
+        }
+    }
     if (out.direct)
         for (int64_t k = zero ? 1 : 0; k < na; ++k) out.amask[static_cast<size_t>(k)].span = 1u;
     if (!aown.empty()) {
@@ -405,8 +429,10 @@ inline void build_host_join_if(const HostHam<W>& hh, int n_qubits, HostJoin<W>& 
 // Whether the join is taken for M samples where the loop would meet `loop`
 // candidates.  The loops take about 6.5e8 candidates a millisecond (|U| |XY|
 // for LoopOverTerms, |U|^2 for LoopOverBatch; LoopOverTrie costs about eight of
-// them per |U| |XY|), the join about 0.2 ms for U's two orders and 6 to 15 ns a
-// sample.  Measured, loop / join: LoopOverTerms, 28 qubits, 65 536 samples
+// them per |U| |XY|), the join about 0.2 ms for U's two orders and 6 ns a sample
+// at 28 qubits, 17 at 52, 26 at 74, 60 at 100, where the masks are many more.
+// Samples that share a spin string make it longer (join_own_limit).  Measured,
+// loop / join: LoopOverTerms, 28 qubits, 65 536 samples
 // (6.9e8) 1.09 / 0.53 ms; 52 qubits, 2^20 (1.4e11) 97 / 18 ms; LoopOverBatch,
 // 40 qubits, 9999 samples (1.0e8) 0.16 / 0.24 ms.
 // `beside`: in a batch the join's many small launches run beside the others'
@@ -453,11 +479,14 @@ struct JoinMasks {
         };
         const auto size = [](const auto& v) { return v.size() * sizeof(v[0]) + 256; };
         hipError_t e = hipSuccess;
-        size_t at[12];
+        size_t at[20];
         try {
+            size_t own_bytes = 0;
+            for (const auto& own : hj.own)
+                own_bytes += size(own.masks) + size(own.groups) + size(own.place) + size(own.sign);
             host.reserve(size(hj.alist) + size(hj.amask) + size(hj.blist) + size(hj.bmask) + size(hj.b_cross) +
                          size(hj.b_own) + size(hj.a_own) + size(hj.place) + size(hj.sign) + size(hj.linear) +
-                         size(hj.runs) + size(hj.gids));
+                         size(hj.runs) + size(hj.gids) + own_bytes);
             at[0] = put(hj.alist);
             at[1] = put(hj.amask);
             at[2] = put(hj.blist);
@@ -470,6 +499,12 @@ struct JoinMasks {
             at[9] = put(hj.linear);
             at[10] = put(hj.runs);
             at[11] = put(hj.gids);
+            for (int o = 0; o < 2; ++o) {
+                at[12 + 4 * o] = put(hj.own[o].masks);
+                at[13 + 4 * o] = put(hj.own[o].groups);
+                at[14 + 4 * o] = put(hj.own[o].place);
+                at[15 + 4 * o] = put(hj.own[o].sign);
+            }
             e = all.ensure(host.size());
         } catch (const std::bad_alloc&) {
             return hipSuccess;   // the loops serve
@@ -510,6 +545,13 @@ struct JoinMasks {
         H.a_pmin = hj.a_pmin;
         H.a_span = hj.a_span;
         H.has_a_own = hj.a_base < hj.place.size();
+        for (int o = 0; o < 2; ++o) {
+            H.own[o].n = static_cast<int>(hj.own[o].masks.size());
+            H.own[o].masks = part(12 + 4 * o);
+            H.own[o].groups = part(13 + 4 * o);
+            H.own[o].place = part(14 + 4 * o);
+            H.own[o].sign = static_cast<const double*>(part(15 + 4 * o));
+        }
         split = join_splits(n_qubits, H, hj.cross_span);
         dev = H;
         return hipSuccess;
@@ -522,10 +564,11 @@ struct JoinMasks {
 struct JoinIndex {
     JoinDev dev;
     DevBuf key, val, key2, val2, hist, hist_off, hist_scan;
-    DevBuf perm, group, scan, cross, vec, slots, heavy, heavy_slots, core;
+    DevBuf perm, group, scan, cross, vec, slots, heavy, heavy_slots, core, filter;
+    int64_t filter_words = 0;
 
     // Room for n samples; nothing is allocated when the index is built.
-    hipError_t room(int W, int64_t n) {
+    hipError_t room(int W, int64_t n, const JoinMasks& masks) {
         const size_t st = W == 1 ? sizeof(uint32_t) : sizeof(uint64_t);
         const int64_t tiles = radix_tiles(2 * n);
         hipError_t e = hipSuccess;
@@ -548,16 +591,21 @@ struct JoinIndex {
         need(heavy, sizeof(JoinHeavy));
         need(heavy_slots, 2 * st * 2 * kJoinHeavySlots);
         need(core, sizeof(uint32_t) * kJoinCore);
+        filter_words = join_filter_words(masks.dev, n);
+        if (filter_words) need(filter, sizeof(uint32_t) * filter_words);
         return e;
     }
     // The index of keys[n][W]; enqueued.
-    hipError_t build(int W, const uint64_t* keys, int64_t n, int n_qubits, bool split, const uint32_t* prep_err,
-                     hipStream_t st) {
+    hipError_t build(int W, const uint64_t* keys, int64_t n, int n_qubits, const JoinMasks& masks,
+                     const uint32_t* prep_err, hipStream_t st) {
         JoinBuild B;
         B.keys = keys;
         B.M = n;
         B.n_qubits = n_qubits;
-        B.split = split;
+        B.split = masks.split;
+        for (int o = 0; o < 2; ++o) B.own_limit[o] = join_own_limit(masks.dev.own[o].n);
+        B.filter = filter_words ? filter.as<uint32_t>() : nullptr;
+        B.filter_words = filter_words;
         B.key = key.as<uint64_t>();
         B.key2 = key2.as<uint64_t>();
         B.val = val.as<uint32_t>();
@@ -589,13 +637,15 @@ struct JoinIndex {
         J.heavy = B.heavy;
         J.heavy_slots = B.heavy_slots;
         J.core = B.core;
+        J.filter = B.filter;
+        J.filter_mask = static_cast<uint32_t>(filter_words - 1);
         J.prep_err = prep_err;
         dev = J;
         return hipSuccess;
     }
     void release() {
         for (DevBuf* b : {&key, &val, &key2, &val2, &hist, &hist_off, &hist_scan, &perm, &group, &scan, &cross, &vec, &slots,
-                          &heavy, &heavy_slots, &core})
+                          &heavy, &heavy_slots, &core, &filter})
             b->release();
     }
 };

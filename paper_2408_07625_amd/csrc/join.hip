@@ -39,6 +39,7 @@ struct JoinArgs {
     int chunks;      // 0: spin-down order; 1: heavy-heavy table; the rest: alist
     int per_chunk;   // masks of alist per chunk
     int64_t tiles;
+    uint32_t own_up, own_down;   // longest own bucket scanned, by order (sums)
 };
 
 __device__ __forceinline__ int lanes_below(uint64_t mask) {
@@ -166,9 +167,10 @@ __global__ __launch_bounds__(kWave) void k_join(JoinArgs A, JoinOut O) {
     for (int r = 0; r < kRows; ++r) cnt[r] = 0;
     int64_t fill_at = 0;
     if constexpr (MODE == kModeFill) fill_at = O.offsets[static_cast<int64_t>(row) * A.chunks + chunk];
-    if (bad || (core && heavy_min == kJoinNone)) {   // invalid samples: no pairs
+    const bool huge = !kSums && rdlane(A.U.heavy->huge, 0) != 0u;   // not listed here
+    if (bad || huge || (core && heavy_min == kJoinNone)) {   // invalid samples: no pairs
         if constexpr (MODE == kModeCount)
-            if (lane < n) O.counts[static_cast<int64_t>(row) * A.chunks + chunk] = 0;
+            if (lane < n) O.counts[static_cast<int64_t>(row) * A.chunks + chunk] = huge && !bad ? -1 : 0;
         if constexpr (kSums)
             if (lane < n) store_acc(O.partial, static_cast<int64_t>(chunk) * M + row, Acc{});
         return;
@@ -460,9 +462,10 @@ __global__ __launch_bounds__(kWave) void k_join(JoinArgs A, JoinOut O) {
                                                    : kJoinNone;
                     if (id != kJoinNone) b = make_uint2(id * core_row, 1u);
                 } else {
-                    // heavy buckets are left to the spin-down order and the table
+                    // heavy buckets are left to the spin-down order and the
+                    // table, own ones past the limit to k_join_own
                     if (on) b = find_bucket<ST>(slots, A.U.bits, t);
-                    if (!own && b.y >= heavy_min) b.y = 0u;
+                    if (own ? kSums && b.y > (down ? A.own_down : A.own_up) : b.y >= heavy_min) b.y = 0u;
                 }
                 if (!core) {
                     // the small buckets' columns are gathered side by side
@@ -704,6 +707,8 @@ __global__ __launch_bounds__(kBlock) void k_join_keys(JoinBuild B, int sbits) {
     uint4* core = reinterpret_cast<uint4*>(B.core);
     if (B.split)
         for (int64_t s = t; s < kJoinCore / 4; s += step) core[s] = make_uint4(0u, 0u, 0u, 0u);
+    if (B.filter)
+        for (int64_t s = t; s < B.filter_words; s += step) B.filter[s] = 0u;
     JoinSlot<W>* hs = static_cast<JoinSlot<W>*>(B.heavy_slots);
     if (B.split)
         for (int64_t s = t; s < 2 * static_cast<int64_t>(kJoinHeavySlots); s += step) hs[s] = JoinSlot<W>{0, kJoinNone};
@@ -757,6 +762,7 @@ __global__ __launch_bounds__(kBlock) void k_join_index(JoinBuild B, int sbits, c
             hi = mid;
     }
     const uint32_t len = static_cast<uint32_t>(hi - p);
+    if (len > (down ? B.own_limit[1] : B.own_limit[0])) B.heavy->huge = 1u;
     if (B.split && len >= kHeavyLeast) atomicAdd(&B.heavy->hist[down ? 1 : 0][31 - __clz(static_cast<int>(len))], 1u);
     const uint64_t word = static_cast<uint64_t>(p - o0) | (static_cast<uint64_t>(len) << 32);
     JoinBucket* tab = B.slots + (down ? (int64_t(1) << B.bits) : 0);
@@ -844,11 +850,196 @@ __global__ __launch_bounds__(kBlock) void k_join_core(JoinBuild B, int sbits) {
     if (b != kJoinNone) B.core[a * B.heavy->n[1] + b] = static_cast<uint32_t>(p) + 1u;
 }
 
-// The amplitudes in both orders.
-__global__ __launch_bounds__(kBlock) void k_join_vec(int64_t n, const int32_t* __restrict__ perm,
-                                                     const double2* __restrict__ in, double2* __restrict__ out) {
+// The pairs inside own buckets past the limit, for the row sums: a row looks its
+// masks of that order up in U's table, as the loop over masks does but over a
+// ninth of them.  A wave takes 64 positions and of their rows those that have
+// such a bucket, four at a time (a step's 64 masks are read once for them); with
+// none in U every wave ends at once.  A candidate passes U's signature and a
+// Bloom filter that stays in the L2s, and those that pass are queued and looked
+// up 64 at a time.  What bounds it are the L2s' requests and misses, of the
+// slots and amplitudes (2^20 samples: 1.3e10 and 3.2e9 in 70 ms; looked up
+// unfiltered and evaluated from their terms where they were found 150).
+// Energies, all electrons of one spin, by scans / here / by the loop: 52 qubits,
+// 2^18 samples 17.0 / 12.2 / 15.0 ms, 2^20 225 / 81 / 70; 56 qubits, 2^20 and
+// 2^21 here 73 and 218, by the loop 83 and 192.
+constexpr int kOwnRows = 4;
+
+template <int W, int PREC, bool ADJ, bool NW>
+__global__ __launch_bounds__(kBlock) void k_join_own(JoinArgs A, JoinOwn T, const typename Prec<PREC>::Vec* __restrict__ vec,
+                                                     void* __restrict__ partial, unsigned long long* __restrict__ pairs) {
+    using P = Prec<PREC>;
+    using ST = JoinStr<W>;
+    using Acc = typename P::Acc;
+    constexpr int TK = table_kind(W, NW);
+    using HT = typename TabT<TK>::hash;
+    struct Cand {   // of a row: the mask's number and part, the candidate's salted hash
+        uint32_t at;
+        ST part;
+        HT hs;
+    };
+    __shared__ Cand queue[kBlock / kWave][kOwnRows][kQueue];
+    if (*A.U.prep_err != 0u || A.U.heavy->huge == 0u) return;
+    const int lane = lane_id();
+    Cand (*const q)[kQueue] = queue[threadIdx.x / kWave];
+    const int64_t M = A.U.M, tiles = (M + kWave - 1) / kWave;
+    const int64_t waves = static_cast<int64_t>(gridDim.x) * (kBlock / kWave);
+    const TermRec<W>* __restrict__ terms = static_cast<const TermRec<W>*>(T.terms);
+    const uint32_t* __restrict__ filter = A.U.filter;
+    const uint32_t fmask = A.U.filter_mask;
+    const int nstash = __builtin_amdgcn_readfirstlane(static_cast<int>(T.table.stash->count));
+    const bool sig = T.params && __builtin_amdgcn_readfirstlane(T.params->sig_all) == 0;
+    unsigned long long found = 0;
+    for (int64_t t = static_cast<int64_t>(blockIdx.x) * (kBlock / kWave) +
+                     __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave);
+         t < 2 * tiles; t += waves) {
+        // the rows of an order's buckets in the other order, that of the strings
+        // that differ
+        const int o = t >= tiles ? 1 : 0;
+        const int64_t p0 = (t - (o ? tiles : 0)) * kWave;
+        const bool in = p0 + lane < M;
+        const int64_t p = (o ? 0 : M) + min(p0 + lane, M - 1);
+        const ST g = static_cast<const ST*>(A.U.scan)[p];
+        const uint2 b = find_bucket<ST>(A.U.slots + (o ? (int64_t(1) << A.U.bits) : 0), A.U.bits, g);
+        const int32_t sample = A.U.perm[p];
+        const JoinOwnDev own = o ? A.H.own[1] : A.H.own[0];
+        const JoinOwnMask<W>* __restrict__ masks = static_cast<const JoinOwnMask<W>*>(own.masks);
+        const GroupRec<W>* __restrict__ groups = static_cast<const GroupRec<W>*>(own.groups);
+        const JoinPlace<W>* __restrict__ places = static_cast<const JoinPlace<W>*>(own.place);
+        const int n = own.n;
+        const ST scanned = static_cast<const ST*>(A.U.group)[p];
+        uint64_t rows = __ballot(in && b.y > (o ? A.own_down : A.own_up));
+        while (rows) {
+            int64_t x[kOwnRows];
+            uint64_t hx[kOwnRows];
+            ST str[kOwnRows], grp[kOwnRows];   // the row's scanned string, its order's
+            uint32_t ones[kOwnRows];
+            Acc acc[kOwnRows];
+            int qn[kOwnRows], nr = 0;
+#pragma unroll
+            for (int r = 0; r < kOwnRows; ++r) {   // past the last: the tile's first, without candidates
+                const int l = rows ? __ffsll(static_cast<unsigned long long>(rows)) - 1 : 0;
+                nr += rows ? 1 : 0;
+                rows &= rows - 1;
+                x[r] = __shfl(sample, l, kWave);
+                str[r] = rdlane(scanned, l);
+                grp[r] = rdlane(g, l);
+                ones[r] = pop(str[r]);
+                hx[r] = T.khash[x[r]];
+                acc[r] = Acc{};
+                qn[r] = 0;
+            }
+            // the last m of row r's candidates
+            auto drain = [&](int r, int m) __attribute__((always_inline)) {
+                wave_sync();
+                const bool on = lane < m;
+                const Cand e = q[r][qn[r] - m + (on ? lane : 0)];
+                qn[r] -= m;
+                const int c = static_cast<int>(e.at);
+                const HT hs = e.hs;
+                typename TabT<TK>::slot v1 = 0, v2 = 0;
+                if (on) v1 = load_slot<TK>(T.table, slot1(T.table, hs));
+                const JoinPlace<W> pl = places[c];
+                const ST ks = ADJ ? str[r] : static_cast<ST>(str[r] ^ e.part);
+                ST p1, p3;
+                join_parity_masks(e.part, p1, p3);
+                const uint32_t idx = (pop(static_cast<ST>(ks & p1)) & 1u) | ((pop(static_cast<ST>(ks & e.part)) & 1u) << 1) |
+                                     ((pop(static_cast<ST>(ks & p3)) & 1u) << 2);
+                double hr = own.sign[static_cast<int64_t>(idx) * n + c], hi = 0.0;
+                if (need_slot2<TK>(T.table, v1, hs)) v2 = load_slot<TK>(T.table, slot2(T.table, hs));
+                const uint32_t zp = pop(static_cast<ST>(ks & (o ? pl.za : pl.zb))) + pop(static_cast<ST>(grp[r] & (o ? pl.zb : pl.za)));
+                hr = (zp & 1u) ? -hr : hr;
+                const bool by_run = (pl.hi & kJoinTag) == kJoinTag && (pl.hi & 7u) != static_cast<uint32_t>(kJoinSign);
+                uint64_t row[W], xp[W];
+                GroupRec<W> gr{};
+                if (TK == kTabVerify || __ballot(by_run)) {
+                    gr = groups[c];
+#pragma unroll
+                    for (int w = 0; w < W; ++w) {
+                        row[w] = A.U.keys[x[r] * W + w];
+                        xp[w] = row[w] ^ gr.xy[w];
+                    }
+                }
+                int j;
+                if constexpr (TK == kTabVerify)
+                    j = table_settle<TK, W>(T.table, A.U.keys, v1, v2, hs, xp, nstash, on);
+                else
+                    j = wave_settle<TK>(T.table, v1, v2, hs, nstash);
+                const bool hit = on && j >= 0;
+                found += static_cast<unsigned long long>(__popcll(__ballot(hit)));
+                const typename P::Vec v = vec[hit ? j : 0];
+                if (__ballot(hit && by_run)) {   // runs not told by signs: single excitations, the diagonal
+                    const bool run = hit && by_run;
+                    double rr, ri;
+                    wave_melem<W, NW>(terms, run ? gr.begin : 0, run ? gr.mid : 0, run ? gr.end : 0, ADJ ? row : xp, rr, ri);
+                    if (by_run) {
+                        hr = rr;
+                        hi = ri;
+                    }
+                }
+                if (hit) {
+                    if constexpr (PREC == 0) {
+                        mac(acc[r], hr, hi, v);
+                    } else {
+                        const float4 h = split_c(hr, hi);
+                        mac(acc[r], F2{h.x, h.y}, F2{h.z, h.w}, v);
+                    }
+                }
+                wave_sync();
+            };
+            for (int j0 = 0; j0 < n; j0 += kWave) {
+                const JoinOwnMask<W> mask = masks[min(j0 + lane, n - 1)];
+                bool ok[kOwnRows];
+                uint32_t word[kOwnRows], bits[kOwnRows];
+#pragma unroll
+                for (int r = 0; r < kOwnRows; ++r) {
+                    ok[r] = j0 + lane < n && r < nr && (!sig || pop(static_cast<ST>(str[r] ^ mask.part)) == ones[r]);
+                    const uint32_t hf = static_cast<uint32_t>((hx[r] ^ mask.hash) >> 32);
+                    bits[r] = bloom_bits(hf);
+                    word[r] = 0u;
+                    if (ok[r]) word[r] = filter[bloom_word(hf, fmask)];
+                }
+#pragma unroll
+                for (int r = 0; r < kOwnRows; ++r) {
+                    const bool pass = ok[r] && (word[r] & bits[r]) == bits[r];
+                    const uint64_t mk = __ballot(pass);
+                    if (pass)
+                        q[r][qn[r] + lanes_below(mk)] = Cand{static_cast<uint32_t>(j0 + lane), mask.part,
+                                                             static_cast<HT>(hx[r] ^ mask.hash ^ T.table.salt)};
+                    qn[r] += __popcll(mk);
+                    if (qn[r] >= kWave) drain(r, kWave);
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < kOwnRows; ++r) {
+                if (r >= nr) continue;
+                if (qn[r] > 0) drain(r, qn[r]);
+                wave_sum(acc[r]);
+                // the row's sum of the chunk that has its own bucket
+                if (lane == 0) {
+                    const int64_t to = (o ? 0 : 2) * M + x[r];
+                    Acc sum;
+                    __builtin_memcpy(&sum, static_cast<const double2*>(partial) + to, sizeof(sum));
+                    acc_plus(sum, acc[r]);
+                    store_acc(partial, to, sum);
+                }
+            }
+        }
+    }
+    if (pairs && lane == 0 && found)
+        atomicAdd(pairs + (blockIdx.x % kJoinPairSlots) * kJoinPairStride, found);
+}
+
+// The amplitudes in both orders; with huge buckets in U also its filter.
+__global__ __launch_bounds__(kBlock) void k_join_vec(JoinDev U, const uint64_t* __restrict__ khash,
+                                                     const double2* __restrict__ in) {
     const int64_t p = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
-    if (p < n) out[p] = in[perm[p]];
+    if (p >= 2 * U.M) return;
+    const int32_t i = U.perm[p];
+    U.vec[p] = in[i];
+    if (U.filter && p < U.M && U.heavy->huge) {
+        const uint32_t hf = static_cast<uint32_t>(khash[i] >> 32);
+        atomicOr(U.filter + bloom_word(hf, U.filter_mask), bloom_bits(hf));
+    }
 }
 
 inline unsigned div_up(int64_t n, int64_t d) { return static_cast<unsigned>((n + d - 1) / d); }
@@ -861,7 +1052,24 @@ JoinArgs make_args(const void* terms, const JoinHamDev& JH, const JoinDev& J, co
     A.chunks = P.chunks;
     A.per_chunk = P.per_chunk;
     A.tiles = (J.M + P.rows_per_block - 1) / P.rows_per_block;
+    A.own_up = A.own_down = kJoinNone;
     return A;
+}
+
+template <int W, bool NW>
+void launch_own(bool adjoint, int precision, const JoinArgs& A, const JoinOwn& T, const double2* vec, const float4* vecf,
+                void* partial, unsigned long long* pairs, hipStream_t st) {
+    // one round of the chip at most, four waves a SIMD
+    const int64_t tiles = 2 * ((A.U.M + kWave - 1) / kWave);
+    const dim3 grid(static_cast<unsigned>(std::min<int64_t>((tiles + 3) / 4, 1024))), block(kBlock);
+    if (precision == 0 && adjoint)
+        hipLaunchKernelGGL((k_join_own<W, 0, true, NW>), grid, block, 0, st, A, T, vec, partial, pairs);
+    else if (precision == 0)
+        hipLaunchKernelGGL((k_join_own<W, 0, false, NW>), grid, block, 0, st, A, T, vec, partial, pairs);
+    else if (adjoint)
+        hipLaunchKernelGGL((k_join_own<W, 1, true, NW>), grid, block, 0, st, A, T, vecf, partial, pairs);
+    else
+        hipLaunchKernelGGL((k_join_own<W, 1, false, NW>), grid, block, 0, st, A, T, vecf, partial, pairs);
 }
 
 template <int W, int PREC, bool ADJ, bool NW, int MODE>
@@ -914,25 +1122,43 @@ hipError_t launch_join_index(int W, const JoinBuild& B, hipStream_t st) {
     return W == 1 ? join_index<1>(B, st) : join_index<2>(B, st);
 }
 
+static hipError_t join_sums(bool adjoint, int precision, const HamDev& H, const JoinArgs& A, const JoinOut& O, int rows,
+                            hipStream_t st) {
+    if (H.W == 2)
+        return adjoint ? launch_sum<2, true, false>(precision, rows, A, O, st)
+                       : launch_sum<2, false, false>(precision, rows, A, O, st);
+    if (H.n_qubits <= 32)
+        return adjoint ? launch_sum<1, true, true>(precision, rows, A, O, st)
+                       : launch_sum<1, false, true>(precision, rows, A, O, st);
+    return adjoint ? launch_sum<1, true, false>(precision, rows, A, O, st)
+                   : launch_sum<1, false, false>(precision, rows, A, O, st);
+}
+
 hipError_t launch_join_pairs(bool adjoint, int precision, const HamDev& H, const JoinHamDev& JH, const JoinDev& J,
-                             const Plan& P, const double2* vec, const float4* vecf, void* partial, hipStream_t st,
-                             unsigned long long* pairs) {
+                             const Plan& P, const JoinOwn& own, const double2* vec, const float4* vecf, void* partial,
+                             hipStream_t st, unsigned long long* pairs) {
     if (adjoint && pairs) return hipErrorInvalidValue;   // the forward sums count
-    const JoinArgs A = make_args(precision == 0 ? H.terms : H.terms_f, JH, J, P);
+    JoinArgs A = make_args(precision == 0 ? H.terms : H.terms_f, JH, J, P);
+    const bool huge = J.filter != nullptr;
+    if (huge) {
+        A.own_up = join_own_limit(JH.own[0].n);
+        A.own_down = join_own_limit(JH.own[1].n);
+    }
     JoinOut O{};
     O.partial = partial;
     O.pairs = pairs;
     static_assert(sizeof(double2) == sizeof(float4), "one copy serves both precisions");
-    hipLaunchKernelGGL(k_join_vec, dim3(div_up(2 * J.M, kBlock)), dim3(kBlock), 0, st, 2 * J.M, J.perm,
-                       precision == 0 ? vec : reinterpret_cast<const double2*>(vecf), J.vec);
+    hipLaunchKernelGGL(k_join_vec, dim3(div_up(2 * J.M, kBlock)), dim3(kBlock), 0, st, J, own.khash,
+                       precision == 0 ? vec : reinterpret_cast<const double2*>(vecf));
+    const hipError_t e = join_sums(adjoint, precision, H, A, O, P.rows_per_block, st);
+    if (e != hipSuccess || !huge) return e;
     if (H.W == 2)
-        return adjoint ? launch_sum<2, true, false>(precision, P.rows_per_block, A, O, st)
-                       : launch_sum<2, false, false>(precision, P.rows_per_block, A, O, st);
-    if (H.n_qubits <= 32)
-        return adjoint ? launch_sum<1, true, true>(precision, P.rows_per_block, A, O, st)
-                       : launch_sum<1, false, true>(precision, P.rows_per_block, A, O, st);
-    return adjoint ? launch_sum<1, true, false>(precision, P.rows_per_block, A, O, st)
-                   : launch_sum<1, false, false>(precision, P.rows_per_block, A, O, st);
+        launch_own<2, false>(adjoint, precision, A, own, vec, vecf, partial, pairs, st);
+    else if (own.narrow)
+        launch_own<1, true>(adjoint, precision, A, own, vec, vecf, partial, pairs, st);
+    else
+        launch_own<1, false>(adjoint, precision, A, own, vec, vecf, partial, pairs, st);
+    return hipGetLastError();
 }
 
 hipError_t launch_join_count(const HamDev& H, const JoinHamDev& JH, const JoinDev& J, const Plan& P, int32_t* counts,
