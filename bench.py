@@ -234,9 +234,10 @@ def main():
 
     def measure(var, prec, steps, warm, label):
         ms, prof = time_steps(eng, make_step(var, prec), steps, warm)
-        print(f"# {label} {prec}: {ms:.3f} ms/step  stages(ms/launch): " +
-              ", ".join(f"{k}={v[0] / v[1]:.3f}" for k, v in prof.items() if v[1]), file=sys.stderr, flush=True)
-        return {"ms_per_step": ms, "steps": steps, "stage_ms": {k: v[0] / v[1] for k, v in prof.items() if v[1]},
+        stage_ms = {k: v[0] / steps for k, v in prof.items() if v[1]}   # a stage may have several parts a step
+        print(f"# {label} {prec}: {ms:.3f} ms/step  stages(ms/step): " +
+              ", ".join(f"{k}={v:.3f}" for k, v in stage_ms.items()), file=sys.stderr, flush=True)
+        return {"ms_per_step": ms, "steps": steps, "stage_ms": stage_ms,
                 "eloc": out.cpu().numpy().copy(), "stats": stats.cpu().numpy().copy()}
 
     # the headline: the variant as a caller asks for it, which the spin-string
@@ -423,7 +424,7 @@ def bench_medium(args):
                 eng.set_samples(keys, check=False)
                 eng.local_energy(L, None, "terms", prec, out=out, stats=stats, check=False)
             ms, prof = time_steps(eng, step, args.steps, args.warmup)
-            d = {"ms_per_step": ms, "stage_ms": {k: v[0] / v[1] for k, v in prof.items() if v[1]}}
+            d = {"ms_per_step": ms, "stage_ms": {k: v[0] / args.steps for k, v in prof.items() if v[1]}}
             if route == "default":
                 r[prec] = d
             else:

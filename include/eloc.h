@@ -391,7 +391,8 @@ int eloc_get_tuning(eloc_ctx ctx, eloc_tuning* tuning);
  * MatrixElement + accumulation, reductions).  While enabled, every call
  * records a start/end event pair around each of its stages. */
 enum eloc_stage {
-    ELOC_STAGE_SAMPLES = 0,        /* eloc_set_samples: copy, hash table, checks  */
+    ELOC_STAGE_SAMPLES = 0,        /* eloc_set_samples: copy, hash table, checks; what
+                                    * a call builds of U on first use (orders, trees) */
     ELOC_STAGE_AMPLITUDES = 1,     /* exp(L - max Re L) and its inverse           */
     ELOC_STAGE_PAIRS = 2,          /* fused pair kernel (forward)                  */
     ELOC_STAGE_FINISH = 3,         /* chunk sums times 1/psi(x)                    */

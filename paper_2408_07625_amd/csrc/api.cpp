@@ -217,6 +217,9 @@ int join_room(eloc_ctx c, int64_t n) {
     return ELOC_OK;
 }
 
+int prof_begin(eloc_ctx c, int stage);
+void prof_end(eloc_ctx c, int mark);
+
 bool capturing(hipStream_t st) {
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &cap) != hipSuccess) (void)hipGetLastError();
@@ -229,9 +232,12 @@ bool capturing(hipStream_t st) {
 // which a replay changes without a call that would tell.
 int ensure_join(eloc_ctx c) {
     if (c->j_built) return ELOC_OK;
+    const bool cap = capturing(c->stream);
+    const int pm = cap ? -1 : prof_begin(c, ELOC_STAGE_SAMPLES);
     ELOC_HIP(c, c->J.build(c->H.W, c->keys.as<uint64_t>(), c->S.n, c->H.n_qubits, c->JH, c->err_prep.as<uint32_t>(),
                            c->stream));
-    c->j_built = !c->samples_captured && !capturing(c->stream);
+    prof_end(c, pm);
+    c->j_built = !c->samples_captured && !cap;
     return ELOC_OK;
 }
 
