@@ -35,8 +35,9 @@ __global__ __launch_bounds__(kBlock) void k_bt_clear(BatchDev B) {
         B.sigmin[t0] = 0xFFFFFFFFu;
         B.sigmax[t0] = 0u;
         B.pairs[t0] = 0ull;
-        for (int q = 0; q < kJoinPairSlots; ++q) B.join_pairs[(t0 * kJoinPairSlots + q) * kJoinPairStride] = 0ull;
     }
+    for (int64_t i = t0; i < static_cast<int64_t>(B.n) * kJoinPairSlots; i += stride)
+        if (B.probs[i / kJoinPairSlots].items == 0) B.join_pairs[i * kJoinPairStride] = 0ull;   // joined
 }
 
 // Copy of the caller keys (words beyond the problem's own are zero), linear
@@ -339,11 +340,13 @@ __global__ __launch_bounds__(kBlock) void k_bt_energy2(BatchDev B) {
         sr += B.part[3 * t + 1];
         si += B.part[3 * t + 2];
     }
-    unsigned long long joined = 0;
+    if (P.items == 0) {   // joined
+        unsigned long long joined = 0;
 #pragma unroll
-    for (int q = 0; q < kJoinPairSlots; ++q)
-        joined += B.join_pairs[(static_cast<int64_t>(k) * kJoinPairSlots + q) * kJoinPairStride];
-    B.pairs[k] += joined;
+        for (int q = 0; q < kJoinPairSlots; ++q)
+            joined += B.join_pairs[(static_cast<int64_t>(k) * kJoinPairSlots + q) * kJoinPairStride];
+        B.pairs[k] = joined;
+    }
     if (!(tot > 0.0) || !isfinite(tot)) atomicOr(B.err + k, static_cast<uint32_t>(kErrWeights));
     const double er = sr / tot, ei = si / tot;
     P.stats[0] = er;
