@@ -272,7 +272,7 @@ Plan make_plan(const eloc_ctx c, int variant, int64_t n_rows = -1, bool allow_pa
                        c->tune_waves != 1;
     // few candidates: 4 rows a wave.  What a wave does one row after another
     // (a long run, the queue's hits) then bounds the launch: LoopOverTerms, 12
-    // qubits, 300 samples 31 us with 4, 49 with 8; 20 qubits, 6000 66 / 84; from
+    // qubits, 300 samples 23 us with 4, 40 with 8; 20 qubits, 6000 66 / 84; from
     // about 2^26 candidates on the scan's share of a wave counts for more (40
     // qubits, 9999 551 / 527), with two-word keys from 2048 samples on (energies
     // in a spin-blocked order, 66 qubits, 2000 1272 / 1354, 3000 2363 / 2172; 100

@@ -385,7 +385,7 @@ __global__ __launch_bounds__(kBlock) void k_adj_finish(const void* __restrict__ 
         sr = 0.0;
         si = 0.0;
 #pragma unroll 8
-    for (int c = 0; c < chunks; ++c) {
+        for (int c = 0; c < chunks; ++c) {
             const double2 p = static_cast<const double2*>(partial)[c * n + i];
             sr += p.x;
             si += p.y;
@@ -397,7 +397,7 @@ __global__ __launch_bounds__(kBlock) void k_adj_finish(const void* __restrict__ 
     } else {
         F2 re{0.f, 0.f}, im{0.f, 0.f};
 #pragma unroll 8
-    for (int c = 0; c < chunks; ++c) {
+        for (int c = 0; c < chunks; ++c) {
             const float4 p = static_cast<const float4*>(partial)[c * n + i];
             acc_add(re, p.x, p.y);
             acc_add(im, p.z, p.w);

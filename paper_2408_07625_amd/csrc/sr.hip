@@ -309,8 +309,9 @@ constexpr int chol_tile_waves(int nt) { return kCholWaves - chol_factor_waves(nt
 static_assert(chol_tile_waves(kCholMaxTiles) > 0, "waves left for the tiles of the largest set");
 
 // sqrt(d) and 1 / sqrt(d) together, for normal d > 0: the hardware's reciprocal
-// root, two coupled Newton steps (g -> sqrt, h -> 1 / (2 sqrt)) and the
-// residual of the root.  Half the chain of a root and a division.
+// root, two steps of Goldschmidt's coupled iteration (g -> sqrt, h -> 1 / (2
+// sqrt), both corrected by the one residual 1/2 - g h) and the residual of the
+// root.  Half the chain of a root and a division.
 __device__ __forceinline__ void root_and_inverse(double d, double& root, double& inv) {
     const double r = __builtin_amdgcn_rsq(d);
     double g = d * r, h = 0.5 * r;
@@ -783,7 +784,10 @@ int64_t sr_select_scratch(int64_t n) { return std::max<int64_t>(n, kTopChunks + 
 
 // The tournament: up to the set sizes of the solve and 2^22 samples, where
 // its worst case (a kept list of nsr n / 2048 elements cut down by one
-// workgroup) still costs less than the eight passes of the sort.
+// workgroup) still costs less than the eight passes of the sort.  256 of 2^22,
+// sort / tournament: every value the same 456 / 153 us, a few values 721 / 108,
+// descending 625 / 91, in no order 795 / 64; of 2^20 every value the same 245 /
+// 131, in no order 301 / 44.
 hipError_t launch_sr_select(const double2* logpsi, int64_t n, int nsr, uint64_t* key, uint32_t* val, uint64_t* key2,
                             uint32_t* val2, uint32_t* hist, int64_t* hist_off, int64_t* scan, int32_t* out,
                             hipStream_t st) {
